@@ -99,8 +99,10 @@ __device__ __forceinline__ float group_sum(float v)
 
 // ----- factor rows ------------------------------------------------------------
 // Factor storage: float32, or bfloat16 kept as its raw 16 bits (the upper
-// half of a float32).  VW elements per lane: 16-byte vector loads when the
-// row length allows it, one element otherwise.
+// half of a float32).  VW elements per lane, one load each.  A row starts at
+// any multiple of its element's size (R is not rounded up to VW), so the
+// vector types are declared with the element's alignment: global loads and
+// stores take it as it is, in one instruction.
 
 struct bf16raw { uint16_t x; };
 
@@ -110,10 +112,17 @@ template <> struct Elem<bf16raw> { static constexpr int VEC = 8; };
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
+typedef float float4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef float float2e __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t uint4e __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t uint2e __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t uint1e __attribute__((aligned(2)));
+
 // A row chunk as loaded (raw registers), converted to float32 when used.
 template <typename FT, int VW> struct Raw;
 template <> struct Raw<float, 4> { float4 v; };
 template <> struct Raw<bf16raw, 8> { uint4 v; };
+template <> struct Raw<float, 2> { float2 v; };
 template <> struct Raw<float, 1> { float v; };
 template <> struct Raw<bf16raw, 1> { uint32_t v; };
 template <> struct Raw<bf16raw, 2> { uint32_t v; };   // two consecutive bfloat16
@@ -122,12 +131,25 @@ template <> struct Raw<bf16raw, 4> { uint2 v; };      // four consecutive bfloat
 template <typename FT, int VW>
 __device__ __forceinline__ void load_raw(const FT *__restrict__ p, Raw<FT, VW> &r)
 {
-    if constexpr (sizeof(FT) == 4 && VW == 4) r.v = *reinterpret_cast<const float4 *>(p);
-    else if constexpr (sizeof(FT) == 2 && VW == 8) r.v = *reinterpret_cast<const uint4 *>(p);
-    else if constexpr (sizeof(FT) == 4 && VW == 1) r.v = *reinterpret_cast<const float *>(p);
-    else if constexpr (sizeof(FT) == 2 && VW == 2) r.v = *reinterpret_cast<const uint32_t *>(p);
-    else if constexpr (sizeof(FT) == 2 && VW == 4) r.v = *reinterpret_cast<const uint2 *>(p);
-    else r.v = (uint32_t)(*reinterpret_cast<const uint16_t *>(p));
+    if constexpr (sizeof(FT) == 4 && VW == 4) {
+        const float4e x = *reinterpret_cast<const float4e *>(p);
+        r.v = make_float4(x.x, x.y, x.z, x.w);
+    } else if constexpr (sizeof(FT) == 4 && VW == 2) {
+        const float2e x = *reinterpret_cast<const float2e *>(p);
+        r.v = make_float2(x.x, x.y);
+    } else if constexpr (sizeof(FT) == 2 && VW == 8) {
+        const uint4e x = *reinterpret_cast<const uint4e *>(p);
+        r.v = make_uint4(x.x, x.y, x.z, x.w);
+    } else if constexpr (sizeof(FT) == 2 && VW == 4) {
+        const uint2e x = *reinterpret_cast<const uint2e *>(p);
+        r.v = make_uint2(x.x, x.y);
+    } else if constexpr (sizeof(FT) == 2 && VW == 2) {
+        r.v = *reinterpret_cast<const uint1e *>(p);
+    } else if constexpr (sizeof(FT) == 4 && VW == 1) {
+        r.v = *reinterpret_cast<const float *>(p);
+    } else {
+        r.v = (uint32_t)(*reinterpret_cast<const uint16_t *>(p));
+    }
 }
 
 template <typename FT, int VW>
@@ -135,6 +157,7 @@ __device__ __forceinline__ void set_one(Raw<FT, VW> &r)
 {
     if constexpr (sizeof(FT) == 4 && VW == 4) r.v = make_float4(1.f, 1.f, 1.f, 1.f);
     else if constexpr (sizeof(FT) == 2 && VW == 8) r.v = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
+    else if constexpr (sizeof(FT) == 4 && VW == 2) r.v = make_float2(1.f, 1.f);
     else if constexpr (sizeof(FT) == 4 && VW == 1) r.v = 1.f;
     else if constexpr (sizeof(FT) == 2 && VW == 2) r.v = 0x3F803F80u;
     else if constexpr (sizeof(FT) == 2 && VW == 4) r.v = make_uint2(0x3F803F80u, 0x3F803F80u);
@@ -151,6 +174,8 @@ __device__ __forceinline__ void to_float(const Raw<FT, VW> &r, float (&out)[VW])
         out[2] = bf16_to_f32(r.v.y & 0xFFFFu); out[3] = bf16_to_f32(r.v.y >> 16);
         out[4] = bf16_to_f32(r.v.z & 0xFFFFu); out[5] = bf16_to_f32(r.v.z >> 16);
         out[6] = bf16_to_f32(r.v.w & 0xFFFFu); out[7] = bf16_to_f32(r.v.w >> 16);
+    } else if constexpr (sizeof(FT) == 4 && VW == 2) {
+        out[0] = r.v.x; out[1] = r.v.y;
     } else if constexpr (sizeof(FT) == 4 && VW == 1) {
         out[0] = r.v;
     } else if constexpr (sizeof(FT) == 2 && VW == 2) {
@@ -178,7 +203,9 @@ __device__ __forceinline__ void store_row(float *__restrict__ p, const float (&v
     if constexpr (VW % 4 == 0) {
 #pragma unroll
         for (int k = 0; k < VW; k += 4)
-            *reinterpret_cast<float4 *>(p + k) = make_float4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+            *reinterpret_cast<float4e *>(p + k) = float4e{v[k], v[k + 1], v[k + 2], v[k + 3]};
+    } else if constexpr (VW == 2) {
+        *reinterpret_cast<float2e *>(p) = float2e{v[0], v[1]};
     } else {
 #pragma unroll
         for (int k = 0; k < VW; ++k) p[k] = v[k];
@@ -190,31 +217,18 @@ __device__ __forceinline__ void store_row(float *__restrict__ p, const float (&v
 template <int VW>
 __device__ __forceinline__ void store_row_stream(float *__restrict__ p, const float (&v)[VW])
 {
-    typedef float f4 __attribute__((ext_vector_type(4)));
     if constexpr (VW % 4 == 0) {
 #pragma unroll
         for (int k = 0; k < VW; k += 4) {
-            const f4 x = {v[k], v[k + 1], v[k + 2], v[k + 3]};
-            __builtin_nontemporal_store(x, reinterpret_cast<f4 *>(p + k));
+            const float4e x = {v[k], v[k + 1], v[k + 2], v[k + 3]};
+            __builtin_nontemporal_store(x, reinterpret_cast<float4e *>(p + k));
         }
+    } else if constexpr (VW == 2) {
+        const float2e x = {v[0], v[1]};
+        __builtin_nontemporal_store(x, reinterpret_cast<float2e *>(p));
     } else {
 #pragma unroll
         for (int k = 0; k < VW; ++k) __builtin_nontemporal_store(v[k], p + k);
-    }
-}
-
-template <int VW>
-__device__ __forceinline__ void load_out(const float *__restrict__ p, float (&v)[VW])
-{
-    if constexpr (VW % 4 == 0) {
-#pragma unroll
-        for (int k = 0; k < VW; k += 4) {
-            const float4 x = *reinterpret_cast<const float4 *>(p + k);
-            v[k] = x.x; v[k + 1] = x.y; v[k + 2] = x.z; v[k + 3] = x.w;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < VW; ++k) v[k] = p[k];
     }
 }
 

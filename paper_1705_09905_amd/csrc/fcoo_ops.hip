@@ -211,31 +211,38 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         // build's lane_cols picks (fcoo_autotune times both); by default 4
         // columns with exactly two product modes (with three, the batch per mode
         // gets short and 8-column chunks won on the order-4 Zipf tensor)
-        const bool half_ok = p.dtype == FCOO_BF16 && !resid && !p.kron && np <= 3 && R % 4 == 0 && R <= 64;
-        L.half = half_ok && (b.lane_cols == 4 || (b.lane_cols == 0 && np == 2 && b.op == FCOO_OP_MTTKRP));
-        const int V = (p.dtype == FCOO_F32 || L.half) ? 4 : 8;
-        // a lane's VW columns must lie in one row piece of the (last) factor
-        L.vec = ((p.kron ? p.kr[np - 1] : R) % V) == 0;
-        const int VW = L.vec ? V : 1;
+        const bool half_ok = p.dtype == FCOO_BF16 && !resid && !p.kron && np <= 3 && R >= 4 && R <= 64;
+        L.half = half_ok && (b.lane_cols == 4 || R < 8 || (b.lane_cols == 0 && np == 2 && b.op == FCOO_OP_MTTKRP));
+        // columns per lane: the type's vector, or the widest piece a shorter row
+        // holds.  A row need not be a multiple of it: its last piece ends at
+        // column R and overlaps the one before.  (Such rows once ran one column
+        // per lane, 64 lanes a nonzero: SpMTTKRP of 4M nonzeros, order 4, R = 25
+        // took 323 us and takes 100; SpTTM of 300k, bfloat16 R = 10, 321 and 16)
+        int V = (p.dtype == FCOO_F32 || L.half) ? 4 : 8;
+        if (p.kron) {
+            if (p.kr[np - 1] % V) V = 1;              // a lane's columns lie in one row piece of the last factor
+        } else {
+            while (V > R) V >>= 1;
+        }
+        L.vw = V;
         // SpTTMc: KB columns of the second-to-last mode per lane when they divide it
         const int KBv = p.dtype == FCOO_F32 ? 4 : 2;
-        L.kb = (p.kron && L.vec && np >= 2 && p.kr[np - 2] % KBv == 0) ? KBv : 1;
-        const int AW = VW * L.kb;
+        L.kb = (p.kron && V > 1 && np >= 2 && p.kr[np - 2] % KBv == 0) ? KBv : 1;
+        const int AW = V * L.kb;
         const int lanes = (R + AW - 1) / AW;          // lanes per nonzero over the whole row
         int lpn = next_pow2(lanes);
         if (p.kron) {
             for (int q = 0; q < np; ++q) a.kr[q] = p.kr[q];
             if (lpn < 4) lpn = 4;
-            if (lpn > 64) lpn = 64;
-        } else if (L.vec && lpn > 16) {
+            if (lpn > 64 || V == 1) lpn = 64;
+        } else if (lpn > 16) {
             lpn = 16;
         }
-        if (!L.vec) lpn = 64;
         L.lpn = lpn;
-        const int rt = lpn * AW;
         const int nrt = (lanes + lpn - 1) / lpn;
-        if (resid && nrt > 1)
-            return fail(FCOO_EUNSUPPORTED, "fused residual needs R <= %d for this dtype (R = %d)", rt, R);
+        const int most = p.dtype == FCOO_BF16 && R % 8 == 0 ? 128 : 64;
+        if (resid && R > most)
+            return fail(FCOO_EUNSUPPORTED, "fused residual needs R <= %d for this dtype (R = %d)", most, R);
         L.npt = np <= 3 ? np : 0;
         L.rowmap = b.op == FCOO_OP_MTTKRP;
         a.nblk = b.nblk;
@@ -258,7 +265,9 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         L.grid = dim3((unsigned)gx, (unsigned)nrt, 1);
         hipError_t e;
         if (p.ev_before) FCOO_HIP(hipEventRecord(p.ev_before, s));
+        const bool narrow = !p.kron && !L.half && V < (p.dtype == FCOO_F32 ? 4 : 8);
         if (p.kron) e = p.dtype == FCOO_F32 ? seg_launch_f32_kron(L, s) : seg_launch_bf16_kron(L, s);
+        else if (narrow) e = p.dtype == FCOO_F32 ? seg_launch_f32_narrow(L, resid, s) : seg_launch_bf16_narrow(L, resid, s);
         else if (p.dtype == FCOO_F32) e = resid ? seg_launch_f32_resid(L, s) : seg_launch_f32(L, s);
         else if (L.half) e = seg_launch_bf16_half(L, s);
         else e = resid ? seg_launch_bf16_resid(L, s) : seg_launch_bf16(L, s);

@@ -1,7 +1,6 @@
 // Picks the tile-kernel instantiation for a (storage type, lane layout,
-// number of product modes) and launches it.  Included by the four
-// instantiation units (float32 / bfloat16, plain / fused residual), which
-// are compiled separately to keep build times short.
+// number of product modes) and launches it.  Included by the instantiation
+// units (seg_*.hip), which are compiled separately to keep build times short.
 #pragma once
 
 #include "fcoo_segscan.h"
@@ -10,12 +9,12 @@ namespace fcoo {
 
 struct SegLaunch {
     dev::SegArgs args;
-    bool vec;        // 16-byte row chunks per lane (R a multiple of the vector width)
-    int lpn;         // lanes per nonzero: 1, 2, 4, 8, 16 (vector; SpTTMc up to 64) or 64 (scalar)
+    int vw;          // columns per lane: 8 (bfloat16), 4, 2 or 1
+    int lpn;         // lanes per nonzero: 1, 2, 4, 8, 16 (SpTTMc: 4 .. 64)
     int npt;         // product modes as a template value: 1, 2, 3, or 0 (runtime count)
     bool rowmap;     // output row = seg_row[segment] (SpMTTKRP) or the segment ordinal (SpTTM)
     int kb;          // SpTTMc: column blocks per lane (1, or KronBlock<FT>::KB)
-    bool half;       // bfloat16 in 4-column (8-byte) lane chunks
+    bool half;       // bfloat16 in 4-column (8-byte) lane chunks, R <= 64
     dim3 grid;
 };
 
@@ -54,12 +53,6 @@ template <typename FT, bool RESID>
 static hipError_t seg_dispatch(const SegLaunch &L, hipStream_t s)
 {
     constexpr int V = dev::Elem<FT>::VEC;
-    if (!L.vec) {
-        if constexpr (!RESID) {
-            if (!L.rowmap) return seg_go<FT, 1, 64, 0, false, false>(L, s);
-        }
-        return seg_go<FT, 1, 64, 0, RESID, true>(L, s);
-    }
     switch (L.lpn) {
         case 1: return seg_np<FT, V, 1, RESID>(L, s);
         case 2: return seg_np<FT, V, 2, RESID>(L, s);
@@ -67,6 +60,22 @@ static hipError_t seg_dispatch(const SegLaunch &L, hipStream_t s)
         case 8: return seg_np<FT, V, 8, RESID>(L, s);
         default: return seg_np<FT, V, 16, RESID>(L, s);
     }
+}
+
+// Rows shorter than the vector of their type: pieces of 4 (bfloat16, R < 8),
+// 2 (R = 2, 3) or 1 column (R = 1, the generic path with a runtime mode count).
+template <typename FT, bool RESID>
+static hipError_t seg_dispatch_narrow(const SegLaunch &L, hipStream_t s)
+{
+    if (L.vw == 1) {
+        if constexpr (!RESID) {
+            if (!L.rowmap) return seg_go<FT, 1, 1, 0, false, false>(L, s);
+        }
+        return seg_go<FT, 1, 1, 0, RESID, true>(L, s);
+    }
+    if (L.vw == 2) return L.lpn == 1 ? seg_np<FT, 2, 1, RESID>(L, s) : seg_np<FT, 2, 2, RESID>(L, s);
+    if constexpr (sizeof(FT) == 2) return L.lpn == 1 ? seg_np<FT, 4, 1, RESID>(L, s) : seg_np<FT, 4, 2, RESID>(L, s);
+    return hipErrorInvalidValue;
 }
 
 // bfloat16 in 4-column lane chunks (SpMTTKRP with 1-3 product modes, or
@@ -127,7 +136,7 @@ static hipError_t seg_lpn_kron(const SegLaunch &L, hipStream_t s)
 template <typename FT>
 static hipError_t seg_dispatch_kron(const SegLaunch &L, hipStream_t s)
 {
-    if (!L.vec) return seg_go_k<FT, 1, 64, 0>(L, s);
+    if (L.vw == 1) return seg_go_k<FT, 1, 64, 0>(L, s);
     if (L.kb > 1) return seg_lpn_kron<FT, KronBlock<FT>::KB>(L, s);
     return seg_lpn_kron<FT, 1>(L, s);
 }
@@ -137,6 +146,8 @@ hipError_t seg_launch_bf16(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_half(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_f32_resid(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_resid(const SegLaunch &L, hipStream_t s);
+hipError_t seg_launch_f32_narrow(const SegLaunch &L, bool resid, hipStream_t s);
+hipError_t seg_launch_bf16_narrow(const SegLaunch &L, bool resid, hipStream_t s);
 hipError_t seg_launch_f32_kron(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_kron(const SegLaunch &L, hipStream_t s);
 

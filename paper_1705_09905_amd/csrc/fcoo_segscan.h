@@ -11,7 +11,9 @@
 // MI355X layout (the paper's Titan X design is one thread per partition of
 // threadlen nonzeros and one grid row per rank column; here):
 //   * a workgroup (4 wave64s) owns a tile of tile_nnz consecutive nonzeros
-//     and a rank tile of LPN * VW columns (grid.y counts rank tiles);
+//     and a rank tile of LPN * VW columns (grid.y counts rank tiles); the
+//     row's last piece ends at column R, overlapping the piece before it
+//     when VW does not divide R;
 //   * a lane group of LPN lanes owns a contiguous run of the tile and walks
 //     it in order; each lane holds VW columns, so one gather instruction
 //     fetches 64 / LPN whole rows (16 bytes per lane);
@@ -329,7 +331,8 @@ void seg_tile_kernel(SegArgs A)
     constexpr int NPM = NP > 0 ? NP : kMaxNP;         // product modes held per step
     constexpr int RAWREGS = (int)(sizeof(Raw<FT, VW>) / 4);
     // gathers in flight per lane: the batch that fits the wave count above
-    constexpr int CH0 = NP > 0 ? pow2_floor(TileShape<FT, VW, LPN, NP, RESID, KRON>::batch_regs / (NPM * RAWREGS)) : 2;
+    constexpr int CHB = NP > 0 ? pow2_floor(TileShape<FT, VW, LPN, NP, RESID, KRON>::batch_regs / (NPM * RAWREGS)) : 2;
+    constexpr int CH0 = CHB < 16 ? CHB : 16;          // (pieces of 1 or 2 registers: the loop body stays small)
     constexpr int CL = CH0 > LPN ? CH0 : LPN;         // steps per chunk (stream granule)
     constexpr int CH = CH0 < CL ? CH0 : CL;           // steps per gather batch
     constexpr int U = CL / LPN;                       // stream entries per lane per chunk
@@ -383,10 +386,16 @@ void seg_tile_kernel(SegArgs A)
     const int np = NP > 0 ? NP : A.np;
     int col, colc;
     bool cval;
+    int dup = 0;                                      // leading columns the lane before holds too
     if constexpr (KB == 1) {
-        col = ry * RT + j * VW;
-        cval = col < A.R;
+        const int c0 = ry * RT + j * VW;
+        cval = c0 < A.R;
+        // the last piece of a row is moved down to end at column R: its loads
+        // stay inside the row, and the columns it shares with the lane before
+        // take the same steps in both, so both store the same bits
+        col = c0 + VW <= A.R ? c0 : A.R - VW;
         colc = cval ? col : 0;                        // lanes past R read column 0, never store
+        dup = cval ? c0 - col : 0;
     } else {
         // lane gl: block gl % nb2 of the last mode, block (gl / nb2) % nb1 of
         // the one before, then the earlier modes' combined index
@@ -403,6 +412,12 @@ void seg_tile_kernel(SegArgs A)
     const uint32_t R4 = (uint32_t)R * (uint32_t)sizeof(FT);
     // RESID: factor row of the index mode for an output row (blocks add block * rows)
     auto own_row = [&](int r) -> int64_t { return A.nblk > 1 ? (int64_t)(r % A.rows_own) : (int64_t)r; };
+    // (a column two lanes hold counts once in the dot product: zero in the second)
+    auto load_own = [&](int r, float (&o)[VW]) {
+        load_row<FT, VW>(reinterpret_cast<const FT *>(A.own) + own_row(r) * R + colc, o);
+#pragma unroll
+        for (int k = 0; k < VW - 1; ++k) o[k] = k < dup ? 0.f : o[k];
+    };
     const char *fb[NPM];
     uint32_t R4k[NPM];                                // KRON: row bytes of each product mode
     if constexpr (KRON) {
@@ -515,7 +530,7 @@ void seg_tile_kernel(SegArgs A)
         zero(own);
         if (g >= 0 && rs < re) {
             currow = A.seg_row[g];
-            load_row<FT, VW>(reinterpret_cast<const FT *>(A.own) + own_row(currow) * R + colc, own);
+            load_own(currow, own);
         }
     }
 
@@ -534,8 +549,7 @@ void seg_tile_kernel(SegArgs A)
             zero(acc);
             ++g;
             if constexpr (ROWMAP) currow = A.seg_row[g];
-            if constexpr (RESID)
-                load_row<FT, VW>(reinterpret_cast<const FT *>(A.own) + own_row(currow) * R + colc, own);
+            if constexpr (RESID) load_own(currow, own);
         }
     };
     auto step = [&](const float (&h)[AW], float v, uint64_t hm, int st, int n) {
