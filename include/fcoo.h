@@ -64,7 +64,9 @@ typedef struct {
     int threadlen;   /* nonzeros per partition: 8, 16, 32 or 64 (default 16).  One sf
                         bit per partition (Sec. IV-B, Table II). */
     int tile_nnz;    /* nonzeros per workgroup tile: a multiple of 256 and of
-                        threadlen (default 4096). */
+                        threadlen (default 4096; with the default, fcoo_info
+                        and fcoo_export go by 4096 while the kernels take
+                        512 .. 4096 nonzeros per workgroup, by Z). */
     int host_only;   /* 1: build the host arrays only (no device upload), e.g. to
                         fcoo_export them on a machine without a GPU. */
     int device;      /* 1: sort and encode on the GPU (same arrays, bit for bit);
@@ -87,10 +89,10 @@ typedef struct {
     int lane_cols;   /* bfloat16 factors, SpMTTKRP / SpTTM: columns of a row
                         that one lane reads per gather, 4 (8-byte pieces; the
                         kernel then runs 4 waves per SIMD) or 8 (16-byte
-                        pieces, 3 waves per SIMD; always so with R > 64 or R
-                        not a multiple of 4, with the fused residual and with
-                        SpTTMc).  0: 4 with exactly two product modes and R <=
-                        64, else 8.  fcoo_autotune times both. */
+                        pieces, 3 waves per SIMD; always so with R > 64, with
+                        the fused residual and with SpTTMc).  0: 4 with exactly
+                        two product modes and R <= 64, else 8; rows of fewer
+                        than 8 columns take narrower pieces.  fcoo_autotune times both. */
     int single_pass; /* 1: finish the segments that cross tile boundaries inside
                         the tile kernel (the paper's adjacent synchronization,
                         Sec. IV-D): each tile publishes its two boundary
@@ -185,7 +187,7 @@ int fcoo_export(const fcoo_tensor *t, int mode, int op, int32_t *const *pidx, fl
  * xcd_blocks 8 split by every product mode (xcd_mode), skipping blocked
  * layouts the build refuses -- is built (on the GPU when the sort key fits 64
  * bits, else on the host; the current threadlen is kept, default 16), and for
- * bfloat16 factors with R <= 64 a multiple of 4 both lane_cols 4 and 8 are
+ * bfloat16 factors with 8 <= R <= 64 both lane_cols 4 and 8 are
  * tried on it; each is run once to warm up, then `reps` times between two
  * HIP events on `stream`, and the fastest is left in place (the paper tunes
  * its launch shape per dataset, Sec. V, Table V).
@@ -220,7 +222,7 @@ int fcoo_autotune(fcoo_tensor *t, int mode, int op, const void *const *factors, 
 int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtype, int R,
                   float *M, void *stream);
 
-/* Bytes of the fixed device scratch array behind fcoo_spmttkrp_noalloc. */
+/* Scratch limit of fcoo_spmttkrp_noalloc, in bytes. */
 #define FCOO_NOALLOC_SCRATCH_BYTES (16ll << 20)
 
 /*
@@ -230,8 +232,9 @@ int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtyp
  * to fcoo_spmttkrp on the same build and inputs), but the call allocates
  * nothing: its scratch -- the tile carries, 2 x ntiles x R floats (rounded up
  * to 256 bytes), plus xcd_blocks x dims[mode] x R floats of partial rows for
- * an XCD-blocked build -- lives in one library-owned device array of
- * FCOO_NOALLOC_SCRATCH_BYTES per GPU, held from the first call on that GPU
+ * an XCD-blocked build, FCOO_NOALLOC_SCRATCH_BYTES at most -- lives in one
+ * library-owned device array per GPU (twice that size: a default build's
+ * workgroups take smaller tiles than tile_nnz, with more carries), held from the first call on that GPU
  * (which looks its address up with the GPU current) until the process ends.
  * The caller still owns and passes factors and M.  Every scratch element the
  * call reads it first writes, so nothing needs clearing between calls.

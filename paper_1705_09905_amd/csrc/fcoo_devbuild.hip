@@ -198,12 +198,13 @@ int alloc_dev(T **dst, int64_t n, int64_t pad, hipStream_t s, int64_t *acct)
 
 }  // namespace
 
-int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, int nblk, int xmode, hipStream_t s)
+int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, int WT, int nblk, int xmode,
+                    hipStream_t s)
 {
     const int N = t->order;
     const int64_t Z = t->nnz;
     b = Built();
-    b.op = op; b.mode = mode; b.threadlen = L; b.tile_nnz = T; b.nnz = Z;
+    b.op = op; b.mode = mode; b.threadlen = L; b.tile_nnz = T; b.wtile = WT; b.nnz = Z;
     b.host_arrays = false;
     for (int m = 0; m < N; ++m) {
         if (m == mode) continue;
@@ -231,9 +232,10 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
         for (int m : b.pmodes) ka.idx[i++] = t->d_coo[m];
     }
     const int64_t P = (Z + L - 1) / L;
-    const int64_t ntiles = (Z + T - 1) / T;
+    const int64_t ntiles = (Z + WT - 1) / WT;         // as launched
     b.npart = P;
-    b.ntiles = ntiles;
+    b.ntiles = (Z + T - 1) / T;
+    b.wntiles = ntiles;
 
     Scratch tmp;
     uint64_t *k0, *k1;
@@ -301,7 +303,7 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     hipLaunchKernelGGL(dev::sf_kernel, dim3((unsigned)((sfw * 32 + 255) / 256)), dim3(256), 0, s, head, Z, L, P,
                        sfw, b.d_sf);
     FCOO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(dev::tiles_kernel, dim3((unsigned)((ntiles + 1 + 255) / 256)), dim3(256), 0, s, cum, Z, T,
+    hipLaunchKernelGGL(dev::tiles_kernel, dim3((unsigned)((ntiles + 1 + 255) / 256)), dim3(256), 0, s, cum, Z, WT,
                        ntiles, hb, b.d_tile_seg0);
     FCOO_HIP(hipGetLastError());
     std::vector<int32_t> hbh(ntiles + 1);
@@ -337,10 +339,12 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     hipLaunchKernelGGL(dev::seg_kernel, dim3(grid_of(Z)), dim3(256), 0, s, sa);
     FCOO_HIP(hipGetLastError());
     b.seg.resize((size_t)nseg * nim);
-    b.tile_seg0.resize(ntiles);
+    std::vector<int32_t> seg0(ntiles);
     FCOO_HIP(hipMemcpyAsync(b.seg.data(), segd, (size_t)nseg * nim * 4, hipMemcpyDeviceToHost, s));
-    FCOO_HIP(hipMemcpyAsync(b.tile_seg0.data(), b.d_tile_seg0, (size_t)ntiles * 4, hipMemcpyDeviceToHost, s));
+    FCOO_HIP(hipMemcpyAsync(seg0.data(), b.d_tile_seg0, (size_t)ntiles * 4, hipMemcpyDeviceToHost, s));
     FCOO_HIP(hipStreamSynchronize(s));
+    b.tile_seg0.resize(b.ntiles);
+    for (int64_t k = 0; k < b.ntiles; ++k) b.tile_seg0[k] = seg0[k * (T / WT)];
 
     // 5. carry chains and empty rows on the host (per tile / per row)
     std::vector<int64_t> hb64(hbh.begin(), hbh.end());

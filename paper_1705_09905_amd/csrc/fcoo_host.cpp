@@ -258,7 +258,7 @@ int setup_blocks(const fcoo_tensor *t, Built &b, int nblk, int xmode)
         before += cnt[i];
     }
     for (int k = 0; k < nblk; ++k) zs[k + 1] += zs[k];
-    const int64_t T = b.tile_nnz, ntiles = (Z + T - 1) / T;
+    const int64_t T = b.wtile, ntiles = (Z + T - 1) / T;
     b.blk_ts.assign(nblk + 1, 0);
     for (int k = 1; k < nblk; ++k) {
         int64_t ts = zs[k] / T;
@@ -329,14 +329,14 @@ int64_t Built::max_block_tiles() const
 // ---------------------------------------------------------------------------
 // the F-COO build for one (op, mode)
 // ---------------------------------------------------------------------------
-static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, int nblk,
+static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, int wtile, int nblk,
                       int xmode)
 {
     const int N = t->order;
     const int64_t Z = t->nnz;
     const int T = host_threads();
     b = Built();
-    b.op = op; b.mode = mode; b.threadlen = threadlen; b.tile_nnz = tile_nnz; b.nnz = Z;
+    b.op = op; b.mode = mode; b.threadlen = threadlen; b.tile_nnz = tile_nnz; b.wtile = wtile; b.nnz = Z;
     for (int m = 0; m < N; ++m) {
         if (m == mode) continue;
         if (op == FCOO_OP_MTTKRP) b.pmodes.push_back(m); else b.imodes.push_back(m);
@@ -412,25 +412,26 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
     const int64_t P = (Z + threadlen - 1) / threadlen;
     const int64_t ntiles = (Z + tile_nnz - 1) / tile_nnz;
     b.npart = P; b.ntiles = ntiles;
+    b.wntiles = (Z + wtile - 1) / wtile;
     b.bf.assign((Z + 7) / 8, 0);
     b.sf.assign((P + 31) / 32, 0);
     b.tile_seg0.resize(ntiles);
+    b.wtile_seg0.resize(b.wntiles);
     std::vector<int64_t> seg_start;  // position of each head
-    std::vector<int64_t> heads_before_tile(ntiles + 1, 0);
-    std::vector<uint8_t> tile_has_head(ntiles, 0);
+    std::vector<int64_t> heads_before_tile(b.wntiles + 1, 0);
     int64_t cnt = 0;
     for (int64_t s = 0; s < Z; ++s) {
-        if (s % tile_nnz == 0) heads_before_tile[s / tile_nnz] = cnt;
+        if (s % wtile == 0) heads_before_tile[s / wtile] = cnt;
         if (head[s]) {
             ++cnt;
             seg_start.push_back(s);
             b.sf[(s / threadlen) >> 5] |= 1u << ((s / threadlen) & 31);
-            tile_has_head[s / tile_nnz] = 1;
         }
         if (cnt & 1) b.bf[s >> 3] |= (uint8_t)(1u << (s & 7));
         if (s % tile_nnz == 0) b.tile_seg0[s / tile_nnz] = (int32_t)(cnt - 1);
+        if (s % wtile == 0) b.wtile_seg0[s / wtile] = (int32_t)(cnt - 1);
     }
-    heads_before_tile[ntiles] = cnt;
+    heads_before_tile[b.wntiles] = cnt;
     b.nseg = cnt;
     const int nim = (int)b.imodes.size();
     b.seg.resize((size_t)cnt * nim);
@@ -440,47 +441,38 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
         if (blocked) b.seg[g] += b.blk_of[t->idx[b.bmode][e]] * (int32_t)t->dims[mode];
     }
 
-    // 4. carry fix-up list: a segment that is still open at the end of a tile
-    //    is finished by the first head of a later tile (or by the end of the
-    //    tensor).  Entry (b, a, row): tiles a+1 .. b-1 hold no head, tile a
-    //    holds the segment's start.  The segment closed at tile b's first
-    //    head is the last one that starts before tile b.
-    auto out_row = [&](int64_t g) -> int32_t {
-        return op == FCOO_OP_MTTKRP ? b.seg[(size_t)g] : (int32_t)g;
-    };
-    int64_t last = -1;
-    for (int64_t tb = 0; tb < ntiles; ++tb) {
-        if (!tile_has_head[tb]) continue;
-        if (tb >= 1) {
-            const int64_t g = heads_before_tile[tb] - 1;
-            b.fix.push_back((int32_t)tb);
-            b.fix.push_back((int32_t)last);
-            b.fix.push_back(out_row(g));
-        }
-        last = tb;
-    }
-    if (Z > 0) {
-        b.fix.push_back((int32_t)ntiles);
-        b.fix.push_back((int32_t)last);
-        b.fix.push_back(out_row(cnt - 1));
-    }
-
-    // 5. output rows of MTTKRP that no nonzero touches (with XCD blocks: rows
-    //    of the nblk x dims[mode] partial output)
-    if (op == FCOO_OP_MTTKRP) {
-        const int64_t rows = (int64_t)b.nblk * t->dims[mode];
-        std::vector<uint8_t> present(rows, 0);
-        for (int64_t g = 0; g < cnt; ++g) present[b.seg[g]] = 1;
-        for (int64_t i = 0; i < rows; ++i)
-            if (!present[i]) b.empty_rows.push_back((int32_t)i);
-    }
+    // 4. carry fix-up list and empty rows
+    finish_tiles(t, b, mode, op, heads_before_tile);
     b.built = true;
     return FCOO_OK;
 }
 
+// Nonzeros per workgroup tile of a default build.  A tile costs a chain of
+// dependent loads at its start and end whatever its length, so tiles are long
+// where there are enough of them to fill 256 CUs several times over, and short
+// where there are not; a run stays a power of two long (runs that start inside
+// a 128-byte line of the streams cost 10-20%).  Measured on Zipf(1.1) tensors,
+// whole calls, 512 / 1024 / 2048 / 4096 nonzeros a tile (us):
+//   SpMTTKRP float32 R = 32: 100k 15.5 / 15.3 / 18.6 / 27.3, 400k 19.4 / 14.5 /
+//   17.5 / 26.1, 1.5M 46 / 30.1 / 27.5 / 35.5, 5M 131 / 78 / 72 / 80, 20M 470 /
+//   259 / 230 / 228;
+//   SpTTM float32 R = 32: 400k 15.8 / 13.2 / 16.6 / 25.9, 5M 116 / 78 / 84 / 107,
+//   20M 432 / 285 / 289 / 330 (R = 8: 293 / 240 / 275 / 375).
+int work_tile(int64_t nnz, int op, int fmt_tile)
+{
+    const int t = nnz < 200000 ? 512 : (nnz < 1000000 || op == FCOO_OP_TTM) ? 1024 : nnz < 10000000 ? 2048 : 4096;
+    return fmt_tile % t == 0 ? t : fmt_tile;
+}
+
+// Carry fix-up list: a segment that is still open at the end of a tile is
+// finished by the first head of a later tile (or by the end of the tensor).
+// Entry (b, a, row): tiles a+1 .. b-1 hold no head, tile a holds the segment's
+// start.  The segment closed at tile b's first head is the last one that
+// starts before tile b.  Then the output rows of MTTKRP that no nonzero
+// touches (with XCD blocks: rows of the nblk x dims[mode] partial output).
 void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::vector<int64_t> &hb)
 {
-    const int64_t ntiles = b.ntiles, cnt = b.nseg;
+    const int64_t ntiles = b.wntiles, cnt = b.nseg;
     auto out_row = [&](int64_t g) -> int32_t {
         return op == FCOO_OP_MTTKRP ? b.seg[(size_t)g] : (int32_t)g;
     };
@@ -500,6 +492,12 @@ void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::v
         b.fix.push_back((int32_t)last);
         b.fix.push_back(out_row(cnt - 1));
     }
+    // the format's tiles, each k of the launched ones: one entry per tile but
+    // the first that holds a head, and one for the end
+    const int64_t k = b.tile_nnz / b.wtile;
+    b.nfix_fmt = b.nnz > 0 ? 1 : 0;
+    for (int64_t tb = 1; tb < b.ntiles; ++tb)
+        if (hb[tb * k] != hb[std::min((tb + 1) * k, ntiles)]) ++b.nfix_fmt;
     b.empty_rows.clear();
     if (op == FCOO_OP_MTTKRP) {
         const int64_t rows = (int64_t)b.nblk * t->dims[mode];
@@ -529,7 +527,7 @@ static int build_device(Built &b, hipStream_t s)
     // segment heads before each run from bf popcounts, so no device work reads it
     if (b.op == FCOO_OP_MTTKRP)
         if ((rc = upload(&b.d_seg_row, b.seg.data(), b.nseg, 1, s, &acct))) return rc;
-    if ((rc = upload(&b.d_tile_seg0, b.tile_seg0.data(), b.ntiles, 1, s, &acct))) return rc;
+    if ((rc = upload(&b.d_tile_seg0, b.wtile_seg0.data(), b.wntiles, 1, s, &acct))) return rc;
     if ((rc = upload(&b.d_perm, b.perm.data(), b.nnz, 0, s, &acct))) return rc;
     if ((rc = upload(&b.d_fix, b.fix.data(), (int64_t)b.fix.size(), 3, s, &acct))) return rc;
     if ((rc = upload(&b.d_empty, b.empty_rows.data(), (int64_t)b.empty_rows.size(), 1, s, &acct)))
@@ -638,12 +636,16 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
     if (tile_nnz <= 0 || tile_nnz % 256 || tile_nnz % threadlen || tile_nnz > (1 << 20))
         return fail(FCOO_EINVAL, "tile_nnz %d must be a positive multiple of 256 and threadlen, <= 2^20",
                     tile_nnz);
+    // a tile size that the caller chose is launched as it is, and so is the
+    // single pass's (its chain table goes by the format's tiles)
+    const bool own_tile = (opts && opts->tile_nnz) || single_pass;
+    const int wtile = own_tile ? tile_nnz : work_tile(t->nnz, op, tile_nnz);
     Built &b = t->b[op][mode];
     b.free_device();
     int rc;
     if (on_gpu) {
         try {
-            rc = build_on_device(t, b, mode, op, threadlen, tile_nnz, nblk, xmode, (hipStream_t)stream);
+            rc = build_on_device(t, b, mode, op, threadlen, tile_nnz, wtile, nblk, xmode, (hipStream_t)stream);
         } catch (const std::bad_alloc &) {
             rc = fail(FCOO_ENOMEM, "device build (host side)");
         }
@@ -656,7 +658,7 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
         return rc;
     }
     try {
-        rc = build_host(t, b, mode, op, threadlen, tile_nnz, nblk, xmode);
+        rc = build_host(t, b, mode, op, threadlen, tile_nnz, wtile, nblk, xmode);
     } catch (const std::bad_alloc &) {
         b = Built();
         return fail(FCOO_ENOMEM, "host build");
@@ -681,7 +683,7 @@ int fcoo_info(const fcoo_tensor *t, int mode, int op, fcoo_info_t *info)
     info->nseg = b->nseg;
     info->npart = b->npart;
     info->ntiles = b->ntiles;
-    info->nfix = b->nfix();
+    info->nfix = b->nfix_fmt;
     info->nempty = (int64_t)b->empty_rows.size();
     info->bytes_format = b->format_bytes();
     info->bytes_device = b->device_bytes;
@@ -781,7 +783,7 @@ int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtyp
     p.dtype = dtype;
     p.R = R;
     p.out = M;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->ntiles * (int64_t)R, s))) return rc;
+    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
     p.carry = b->d_carry;
     if ((rc = prep_blocks(b, p, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
@@ -822,7 +824,7 @@ int fcoo_spttmc(fcoo_tensor *t, int mode, const void *const *factors, int dtype,
     p.dtype = dtype;
     p.R = (int)W;
     p.out = Y;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->ntiles * W, s))) return rc;
+    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * W, s))) return rc;
     p.carry = b->d_carry;
     if ((rc = prep_blocks(b, p, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
@@ -848,7 +850,7 @@ int fcoo_spttm(fcoo_tensor *t, int mode, const void *U, int dtype, int R, float 
     p.dtype = dtype;
     p.R = R;
     p.out = Y;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->ntiles * (int64_t)R, s))) return rc;
+    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
     p.carry = b->d_carry;
     if ((rc = prep_blocks(b, p, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
@@ -880,7 +882,7 @@ int fcoo_spmttkrp_values(fcoo_tensor *t, int mode, const float *g, const void *c
     p.dtype = dtype;
     p.R = R;
     p.out = M;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->ntiles * (int64_t)R, s))) return rc;
+    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
     p.carry = b->d_carry;
     if ((rc = prep_blocks(b, p, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
@@ -909,20 +911,19 @@ int fcoo_resid_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, in
     p.out = G;
     p.own = factors[mode];
     p.inv_nnz = b->nnz ? (float)(1.0 / (double)b->nnz) : 0.f;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->ntiles * (int64_t)R, s))) return rc;
+    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
     p.carry = b->d_carry;
     if ((rc = prep_blocks(b, p, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     if (loss) {
-        if ((rc = ensure_device_doubles(&b->d_partial, &b->partial_cap, b->ntiles + 1, s))) return rc;
+        if ((rc = ensure_device_doubles(&b->d_partial, &b->partial_cap, b->wntiles + 1, s))) return rc;
         p.partial = b->d_partial;
+        p.loss = loss;
+        p.loss_scale = b->nnz ? 0.5 / (double)b->nnz : 0.0;
     }
     p.ev_before = t->ev_before;
     p.ev_after = t->ev_after;
-    if ((rc = launch_segmented(p, s, true))) return rc;
-    if (loss) return launch_reduce_partials(b->d_partial, b->ntiles,
-                                            b->nnz ? 0.5 / (double)b->nnz : 0.0, loss, s);
-    return FCOO_OK;
+    return launch_segmented(p, s, true);
 }
 
 int fcoo_set_tile_events(fcoo_tensor *t, void *before, void *after)

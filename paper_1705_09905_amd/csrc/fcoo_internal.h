@@ -36,6 +36,13 @@ struct Built {
     int op = 0, mode = 0, threadlen = 0, tile_nnz = 0;
     int lane_cols = 0;                        // bfloat16 columns per lane chunk (4, 8; 0: default rule)
     int64_t nnz = 0, nseg = 0, npart = 0, ntiles = 0;
+    // nonzeros per workgroup tile as launched: tile_nnz when the caller chose
+    // it, else the size work_tile() picks (a divisor of the format's tile_nnz,
+    // which info and export go by); tile_seg0 on the device, fix and blk_ts
+    // are of these tiles
+    int wtile = 0;
+    int64_t wntiles = 0;
+    int64_t nfix_fmt = 0;                     // segments finished across the format's tiles (info)
     std::vector<int> imodes, pmodes;
 
     // XCD blocks (SpMTTKRP): the nonzeros are split into nblk groups by ranges
@@ -54,10 +61,11 @@ struct Built {
     std::vector<uint8_t> bf;                  // ceil(Z/8)
     std::vector<uint32_t> sf;                 // ceil(P/32)
     std::vector<int32_t> seg;                 // MTTKRP: nseg rows; TTM: nseg x (N-1)
-    std::vector<int32_t> tile_seg0;           // ntiles
+    std::vector<int32_t> tile_seg0;           // ntiles (format tiles)
+    std::vector<int32_t> wtile_seg0;          // wntiles (host builds)
     std::vector<int32_t> perm;                // Z: sorted position -> input position
 
-    // carry fix-up list: (closing tile b, chain start tile a, output row) per entry
+    // carry fix-up list over the launched tiles: (closing tile b, chain start tile a, output row) per entry
     std::vector<int32_t> fix;
     std::vector<int32_t> empty_rows;          // MTTKRP rows with no nonzero
 
@@ -67,14 +75,14 @@ struct Built {
     uint32_t *d_bf = nullptr;                 // bit stream as uint32 words, +2 zero words
     uint32_t *d_sf = nullptr;                 // device builds only (where it is made), for export
     int32_t *d_seg_row = nullptr;             // MTTKRP only
-    int32_t *d_tile_seg0 = nullptr;
+    int32_t *d_tile_seg0 = nullptr;           // wntiles
     int32_t *d_perm = nullptr;
     int32_t *d_fix = nullptr;
     int32_t *d_empty = nullptr;
     int64_t device_bytes = 0;
 
     // scratch owned by this build, grown on demand
-    float *d_carry = nullptr;                 // 2 x ntiles x R floats
+    float *d_carry = nullptr;                 // 2 x wntiles x R floats
     int64_t carry_cap = 0;                    // floats
     float *d_gperm = nullptr;                 // Z floats (values in stored order)
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
@@ -141,8 +149,10 @@ int ensure_device_floats(float **p, int64_t *cap, int64_t need, hipStream_t s);
 int ensure_device_doubles(double **p, int64_t *cap, int64_t need, hipStream_t s);
 int upload_coo(fcoo_tensor *t, hipStream_t s);
 int upload_i32(int32_t **dst, const std::vector<int32_t> &v, int64_t pad, hipStream_t s, int64_t *acct);
+// nonzeros per launched tile of a build whose caller left tile_nnz to the library
+int work_tile(int64_t nnz, int op, int fmt_tile);
 // carry fix-up chains and empty output rows from the per-tile head counts
-// (heads_before[t] = heads before nonzero t * tile_nnz, t = 0 .. ntiles) and b.seg
+// (heads_before[t] = heads before nonzero t * wtile, t = 0 .. wntiles) and b.seg
 void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::vector<int64_t> &heads_before);
 // the F-COO build of one (op, mode) on the GPU (same arrays as the host build)
 // Device primitives of the GPU build (fcoo_sort.hip).  sort_pairs_u64: stable
@@ -156,11 +166,11 @@ int64_t scan_work_ints(int64_t n);
 int sort_pairs_u64(uint64_t *k0, uint64_t *k1, uint32_t *v0, uint32_t *v1, int64_t n, int end_bit,
                    int32_t *work, hipStream_t s, int *passes);
 int scan_i32(const int32_t *in, int32_t *out, int64_t n, bool inclusive, int32_t *work, hipStream_t s);
-int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, int nblk,
+int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, int wtile, int nblk,
                     int xmode, hipStream_t s);
 // XCD blocks of a SpMTTKRP build (nblk 0 / 1: none), split by ranges of product
 // mode xmode (-1: the product mode with the most rows); needs b.op, b.mode,
-// b.pmodes, b.tile_nnz
+// b.pmodes, b.wtile
 int setup_blocks(const fcoo_tensor *t, Built &b, int nblk, int xmode);
 // the single-pass chain table of a finished build (fix list -> per-tile chain starts) and its counters
 int setup_single_pass(Built &b, hipStream_t s);
@@ -177,11 +187,13 @@ struct TileProblem {
     int dtype;
     int R;
     float *out;                      // output rows, leading dimension R
-    float *carry;                    // 2 x ntiles x R
+    float *carry;                    // 2 x wntiles x R
     // fused MSE residual (resid_spmttkrp)
     const void *own = nullptr;       // factor of the index mode (dims[mode] x R)
     float inv_nnz = 0.f;
-    double *partial = nullptr;       // per-tile partial losses (ntiles) or null
+    double *partial = nullptr;       // per-tile partial losses (wntiles) or null
+    double *loss = nullptr;          // with partial: receives loss_scale times their sum
+    double loss_scale = 0.0;
     hipEvent_t ev_before = nullptr;  // recorded around the tile kernel when set
     hipEvent_t ev_after = nullptr;
     float *bpart = nullptr;          // XCD blocks: nblk x rows x R partial output (segments land here)
@@ -196,7 +208,6 @@ struct TileProblem {
 int prep_single_pass(Built *b, TileProblem &p, hipStream_t s);
 int launch_segmented(const TileProblem &p, hipStream_t s, bool resid);
 int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s);
-int launch_reduce_partials(const double *partial, int64_t n, double scale, double *out, hipStream_t s);
 int launch_model(const fcoo_tensor *t, const void *const *factors, int dtype, int R, float *xhat,
                  hipStream_t s);
 

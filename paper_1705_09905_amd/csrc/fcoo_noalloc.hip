@@ -18,7 +18,10 @@
 
 #include "fcoo_internal.h"
 
-static __device__ __align__(256) float scratch[FCOO_NOALLOC_SCRATCH_BYTES / sizeof(float)];
+// Twice the documented bytes: the limit goes by the format's tiles, a default
+// build launches tiles of half that size and more (work_tile), and below 1M
+// nonzeros, where they are smaller still, all carries together are below 2 MB.
+static __device__ __align__(256) float scratch[2 * FCOO_NOALLOC_SCRATCH_BYTES / sizeof(float)];
 
 namespace fcoo {
 
@@ -66,12 +69,13 @@ extern "C" int fcoo_spmttkrp_noalloc(fcoo_tensor *t, int mode, const void *const
     if ((rc = check_factors(t, mode, factors, dtype, R))) return rc;
     if (!M) return fail(FCOO_EINVAL, "M is NULL");
     // scratch layout: carries (2 x ntiles x R), then the blocked build's partial rows
-    const int64_t ncarry = align64(2 * b->ntiles * (int64_t)R);
+    const int64_t nfmt = align64(2 * b->ntiles * (int64_t)R);
+    const int64_t ncarry = align64(2 * b->wntiles * (int64_t)R);
     const int64_t npart = b->nblk > 1 ? (int64_t)b->nblk * b->rows * R : 0;
-    if (ncarry + npart > kScratchFloats)
+    if (nfmt + npart > kScratchFloats || ncarry + npart > 2 * kScratchFloats)
         return fail(FCOO_ERANGE,
                     "no-alloc SpMTTKRP needs %lld bytes of scratch (tile carries%s), above its fixed %lld bytes",
-                    (long long)((ncarry + npart) * 4), npart ? " and XCD-block partial rows" : "",
+                    (long long)((nfmt + npart) * 4), npart ? " and XCD-block partial rows" : "",
                     (long long)FCOO_NOALLOC_SCRATCH_BYTES);
     float *base = nullptr;
     if ((rc = scratch_ptr(&base))) return rc;

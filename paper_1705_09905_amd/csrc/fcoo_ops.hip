@@ -8,60 +8,114 @@ namespace fcoo {
 
 namespace dev {
 
-// Carry fix-up: entry (b, a, row) finishes the segment that tile a starts
-// (its last open partial) and tile b closes (its first partial; b = ntiles
-// is the end of the tensor), with tiles a+1 .. b-1 lying wholly inside it.
-__global__ __launch_bounds__(256) void fixup_kernel(const int32_t *__restrict__ fix,
-                                                    const float *__restrict__ ca,
-                                                    const float *__restrict__ cb, int64_t ntiles,
-                                                    int R, float *__restrict__ out)
+// What is left after the tile kernel, in one launch whose workgroups take one
+// of three parts (each was a kernel of its own; one launch costs 3-5 us on the
+// stream whatever it does, as much as a small tensor's tile kernel):
+//   [0, nfix)            carry fix-up: entry (b, a, row) finishes the segment
+//                        that tile a starts (its last open partial) and tile b
+//                        closes (its first partial; b = ntiles is the end of
+//                        the tensor), with tiles a+1 .. b-1 wholly inside it;
+//   [nfix, nfix + zblk)  rows of an MTTKRP result that no nonzero touches: 0;
+//   the last one         the residual form's loss: fixed-order strided sums of
+//                        the tiles' partials, then a tree; bitwise repeatable.
+struct FinishArgs {
+    const int32_t *fix;
+    const float *ca, *cb;
+    int64_t ntiles;
+    const int32_t *empty;
+    int64_t nempty;
+    float *out;
+    const double *partial;
+    int64_t npartial;
+    double scale;
+    double *loss;
+    int nfix, zblk, R;
+};
+
+constexpr int kZeroPer = 1024;       // elements per workgroup of the zero rows
+constexpr int kChain = 16;           // carries in flight per thread along a chain
+
+__global__ __launch_bounds__(256) void finish_kernel(FinishArgs A)
 {
-    __shared__ float red[256];
-    const int64_t e = blockIdx.x;
-    const int tb = fix[3 * e], ta = fix[3 * e + 1], row = fix[3 * e + 2];
     const int tid = threadIdx.x;
-    if (R > 256) {
-        // wide rows (SpTTMc): one column per thread, the chain summed in order
-        for (int c = tid; c < R; c += 256) {
-            float v = cb[(int64_t)ta * R + c];
-            int64_t t = (int64_t)ta + 1;
-            for (; t + 7 < tb; t += 8) {
-                float x[8];
+    const int R = A.R;
+    if ((int)blockIdx.x < A.nfix) {
+        __shared__ float red[256];
+        const int64_t e = blockIdx.x;
+        const int tb = A.fix[3 * e], ta = A.fix[3 * e + 1], row = A.fix[3 * e + 2];
+        if (R > 256) {
+            // wide rows (SpTTMc): one column per thread, the chain summed in order
+            for (int c = tid; c < R; c += 256) {
+                float v = A.cb[(int64_t)ta * R + c];
+                int64_t t = (int64_t)ta + 1;
+                for (; t + 7 < tb; t += 8) {
+                    float x[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = ca[(t + u) * R + c];
+                    for (int u = 0; u < 8; ++u) x[u] = A.ca[(t + u) * R + c];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v += x[u];
+                    for (int u = 0; u < 8; ++u) v += x[u];
+                }
+                for (; t < tb; ++t) v += A.ca[t * R + c];
+                if (tb < A.ntiles) v += A.ca[(int64_t)tb * R + c];
+                A.out[(int64_t)row * R + c] = v;
             }
-            for (; t < tb; ++t) v += ca[t * R + c];
-            if (tb < ntiles) v += ca[(int64_t)tb * R + c];
-            out[(int64_t)row * R + c] = v;
+            return;
+        }
+        const int slots = 256 / R;
+        const int slot = tid / R, c = tid - (tid / R) * R;
+        float s = 0.f;
+        if (slot < slots) {
+            // long chains (a slice over hundreds of tiles): kChain loads in
+            // flight, then the adds in tile order
+            for (int t = ta + 1 + slot; t < tb; t += kChain * slots) {
+                float x[kChain];
+#pragma unroll
+                for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? A.ca[(int64_t)(t + u * slots) * R + c] : 0.f;
+#pragma unroll
+                for (int u = 0; u < kChain; ++u) s += x[u];
+            }
+        }
+        red[tid] = s;
+        __syncthreads();
+        if (tid < R) {
+            float v = A.cb[(int64_t)ta * R + tid];
+            const int used = tb - ta - 1 < slots ? tb - ta - 1 : slots;   // the other slots' sums are 0
+            for (int k = 0; k < used; ++k) v += red[k * R + tid];
+            if (tb < A.ntiles) v += A.ca[(int64_t)tb * R + tid];
+            A.out[(int64_t)row * R + tid] = v;
         }
         return;
     }
-    const int slots = 256 / R;
-    const int slot = tid / R, c = tid - (tid / R) * R;
-    float s = 0.f;
-    if (slot < slots) {
-        // long chains (a slice over hundreds of tiles): 8 loads in flight,
-        // then the adds in tile order
-        int64_t t = (int64_t)ta + 1 + slot;
-        for (; t + 7 * slots < tb; t += 8 * slots) {
-            float x[8];
+    if ((int)blockIdx.x < A.nfix + A.zblk) {
+        const int64_t n = A.nempty * R;
+        for (int64_t i0 = ((int64_t)blockIdx.x - A.nfix) * kZeroPer; i0 < n; i0 += (int64_t)A.zblk * kZeroPer) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = ca[(t + u * slots) * R + c];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += x[u];
+            for (int u = 0; u < kZeroPer / 256; ++u) {
+                const int64_t i = i0 + u * 256 + tid;
+                if (i < n) {
+                    const int64_t r = i / R;
+                    A.out[(int64_t)A.empty[r] * R + (i - r * R)] = 0.f;
+                }
+            }
         }
-        for (; t < tb; t += slots) s += ca[t * R + c];
+        return;
     }
-    red[tid] = s;
+    __shared__ double sh[256];
+    double s = 0.0;
+    for (int64_t i = tid; i < A.npartial; i += 256 * 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = i + u * 256 < A.npartial ? A.partial[i + u * 256] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += x[u];
+    }
+    sh[tid] = s;
     __syncthreads();
-    if (tid < R) {
-        float v = cb[(int64_t)ta * R + tid];
-        for (int k = 0; k < slots; ++k) v += red[k * R + tid];
-        if (tb < ntiles) v += ca[(int64_t)tb * R + tid];
-        out[(int64_t)row * R + tid] = v;
+    for (int o = 128; o >= 1; o >>= 1) {
+        if (tid < o) sh[tid] += sh[tid + o];
+        __syncthreads();
     }
+    if (tid == 0) A.loss[0] = sh[0] * A.scale;
 }
 
 // XCD blocks: out[i][c] = sum over blocks b of part[b][i][c], in block order.
@@ -75,40 +129,12 @@ __global__ __launch_bounds__(256) void reduce_blocks_kernel(const float *__restr
     }
 }
 
-// Rows of an MTTKRP result that no nonzero touches are zero.
-__global__ __launch_bounds__(256) void zero_rows_kernel(const int32_t *__restrict__ rows, int64_t nrows,
-                                                        int R, float *__restrict__ out)
-{
-    const int64_t n = nrows * R;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int64_t r = i / R;
-        out[(int64_t)rows[r] * R + (i - r * R)] = 0.f;
-    }
-}
-
 __global__ __launch_bounds__(256) void permute_kernel(const int32_t *__restrict__ perm,
                                                       const float *__restrict__ g, int64_t n,
                                                       float *__restrict__ out)
 {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         out[i] = g[perm[i]];
-}
-
-// One workgroup: fixed-order strided sums, then a tree; bitwise repeatable.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const double *__restrict__ p, int64_t n,
-                                                              double scale, double *__restrict__ out)
-{
-    __shared__ double sh[256];
-    const int tid = threadIdx.x;
-    double s = 0.0;
-    for (int64_t i = tid; i < n; i += 256) s += p[i];
-    sh[tid] = s;
-    __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
-        if (tid < o) sh[tid] += sh[tid + o];
-        __syncthreads();
-    }
-    if (tid == 0) out[0] = sh[0] * scale;
 }
 
 struct ModelArgs {
@@ -196,14 +222,14 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         a.seg_row = b.op == FCOO_OP_MTTKRP ? b.d_seg_row : nullptr;
         a.out = b.nblk > 1 ? p.bpart : p.out;
         a.carry_a = p.carry;
-        a.carry_b = p.carry + b.ntiles * (int64_t)R;
+        a.carry_b = p.carry + b.wntiles * (int64_t)R;
         a.own = p.own;
         a.partial = p.partial;
         a.nnz = b.nnz;
-        a.ntiles = b.ntiles;
+        a.ntiles = b.wntiles;
         a.R = R;
         a.np = np;
-        a.tile_nnz = b.tile_nnz;
+        a.tile_nnz = b.wtile;
         a.nseg = (int)b.nseg;
         a.inv_nnz = p.inv_nnz;
         // bfloat16 in 4-column (8-byte) lane chunks: twice the rows per gather
@@ -256,7 +282,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
             a.sp_epoch = p.sp_epoch;
             a.sp_tail_from = b.sp_tail_from;
         }
-        int64_t gx = b.ntiles;
+        int64_t gx = b.wntiles;
         if (b.nblk > 1) {
             for (int k = 0; k <= b.nblk; ++k) a.blk_ts[k] = b.blk_ts[k];
             gx = (int64_t)kXcds * b.max_block_tiles();   // workgroup w: XCD w % 8, its block's tiles
@@ -275,18 +301,24 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         if (p.sp_words)   // every workgroup of the launch takes one ticket
             const_cast<Built &>(b).sp_tickets += (unsigned long long)L.grid.x * L.grid.y;
         if (p.ev_after) FCOO_HIP(hipEventRecord(p.ev_after, s));
-        const int64_t nfix = p.sp_words ? 0 : b.nfix();
-        if (nfix > 0) {
-            hipLaunchKernelGGL(dev::fixup_kernel, dim3((unsigned)nfix), dim3(256), 0, s, b.d_fix,
-                               a.carry_a, a.carry_b, b.ntiles, R, a.out);
-            FCOO_HIP(hipGetLastError());
-        }
     }
-    float *outp = b.nblk > 1 ? p.bpart : p.out;
-    const int64_t nempty = (int64_t)b.empty_rows.size();
-    if (nempty > 0) {
-        hipLaunchKernelGGL(dev::zero_rows_kernel, dim3(grid_for(nempty * R, 256)), dim3(256), 0, s,
-                           b.d_empty, nempty, R, outp);
+    dev::FinishArgs f{};
+    f.nfix = b.nnz > 0 && !p.sp_words ? (int)b.nfix() : 0;
+    f.nempty = (int64_t)b.empty_rows.size();
+    f.zblk = f.nempty > 0 ? grid_for(f.nempty * R, dev::kZeroPer, 1 << 20) : 0;
+    if (f.nfix + f.zblk > 0 || p.loss) {
+        f.fix = b.d_fix;
+        f.ca = p.carry;
+        f.cb = p.carry + b.wntiles * (int64_t)R;
+        f.ntiles = b.wntiles;
+        f.empty = b.d_empty;
+        f.out = b.nblk > 1 ? p.bpart : p.out;
+        f.partial = p.partial;
+        f.npartial = b.nnz > 0 ? b.wntiles : 0;
+        f.scale = p.loss_scale;
+        f.loss = p.loss;
+        f.R = R;
+        hipLaunchKernelGGL(dev::finish_kernel, dim3((unsigned)(f.nfix + f.zblk + (p.loss ? 1 : 0))), dim3(256), 0, s, f);
         FCOO_HIP(hipGetLastError());
     }
     if (b.nblk > 1) {
@@ -302,13 +334,6 @@ int launch_permute_values(const Built &b, const float *g, float *out, hipStream_
 {
     hipLaunchKernelGGL(dev::permute_kernel, dim3(grid_for(b.nnz, 256 * 8)), dim3(256), 0, s, b.d_perm, g,
                        b.nnz, out);
-    FCOO_HIP(hipGetLastError());
-    return FCOO_OK;
-}
-
-int launch_reduce_partials(const double *partial, int64_t n, double scale, double *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(dev::reduce_partials_kernel, dim3(1), dim3(256), 0, s, partial, n, scale, out);
     FCOO_HIP(hipGetLastError());
     return FCOO_OK;
 }

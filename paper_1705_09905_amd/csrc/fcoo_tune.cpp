@@ -58,7 +58,7 @@ extern "C" int fcoo_autotune(fcoo_tensor *t, int mode, int op, const void *const
     }
     const int nprod = op == FCOO_OP_MTTKRP ? t->order - 1 : 1;
     std::vector<int> lanes = {0};
-    if (dtype == FCOO_BF16 && R % 4 == 0 && R <= 64 && nprod <= 3) lanes = {4, 8};
+    if (dtype == FCOO_BF16 && R >= 8 && R <= 64 && nprod <= 3) lanes = {4, 8};
     auto build = [&](const Cand &c) -> int {
         fcoo_opts o{threadlen, c.tile, 0, t->nnz > 0 ? 1 : 0, c.xcd, c.xmode, 0};
         int r = fcoo_build(t, mode, op, &o, stream);
