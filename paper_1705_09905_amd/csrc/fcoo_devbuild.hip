@@ -93,6 +93,20 @@ __global__ __launch_bounds__(256) void bf_kernel(const int32_t *__restrict__ cum
     if (lane == 32 && w + 1 < nwords) bf[w + 1] = (uint32_t)(m >> 32);
 }
 
+// The same heads for the kernels: per word the bits themselves and the heads
+// before its first nonzero.
+__global__ __launch_bounds__(256) void hr_kernel(const int32_t *__restrict__ head, const int32_t *__restrict__ cum,
+                                                 int64_t nnz, int64_t nwords, uint2 *__restrict__ hr)
+{
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int h = s < nnz ? head[s] : 0;
+    const uint64_t m = __ballot(h != 0);
+    const int lane = threadIdx.x & 63;
+    const int64_t w = s >> 5;
+    if ((lane & 31) == 0 && w < nwords)
+        hr[w] = make_uint2(lane ? (uint32_t)(m >> 32) : (uint32_t)m, (uint32_t)(cum[s] - h));
+}
+
 // sf word w: bit i = some head in partition 32 w + i (partitions of L nonzeros).
 __global__ __launch_bounds__(256) void sf_kernel(const int32_t *__restrict__ head, int64_t nnz, int L,
                                                  int64_t npart, int64_t nwords, uint32_t *__restrict__ sf)
@@ -240,9 +254,10 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     Scratch tmp;
     uint64_t *k0, *k1;
     uint32_t *p0, *p1;
-    int32_t *head, *cum, *hb;
+    int32_t *head, *cum, *hb, *seg0d;
     if ((rc = tmp.get(&k0, Z)) || (rc = tmp.get(&k1, Z)) || (rc = tmp.get(&p0, Z)) || (rc = tmp.get(&p1, Z)) ||
-        (rc = tmp.get(&head, Z)) || (rc = tmp.get(&cum, Z)) || (rc = tmp.get(&hb, ntiles + 1)))
+        (rc = tmp.get(&head, Z)) || (rc = tmp.get(&cum, Z)) || (rc = tmp.get(&hb, ntiles + 1)) ||
+        (rc = tmp.get(&seg0d, ntiles)))
         return rc;
 
     int32_t *blk_d = nullptr;
@@ -296,7 +311,10 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     const int64_t bfw = (Z + 31) / 32, sfw = (P + 31) / 32;
     if ((rc = alloc_dev(&b.d_bf, bfw, 2, s, &acct))) return rc;
     if ((rc = alloc_dev(&b.d_sf, sfw, 1, s, &acct))) return rc;
-    if ((rc = alloc_dev(&b.d_tile_seg0, ntiles, 1, s, &acct))) return rc;
+    if ((rc = alloc_dev(&b.d_hr, 2 * bfw, 4, s, &acct))) return rc;
+    hipLaunchKernelGGL(dev::hr_kernel, dim3((unsigned)((bfw * 32 + 255) / 256)), dim3(256), 0, s, head, cum, Z, bfw,
+                       reinterpret_cast<uint2 *>(b.d_hr));
+    FCOO_HIP(hipGetLastError());
     hipLaunchKernelGGL(dev::bf_kernel, dim3((unsigned)((bfw * 32 + 255) / 256)), dim3(256), 0, s, cum, Z, bfw,
                        b.d_bf);
     FCOO_HIP(hipGetLastError());
@@ -304,7 +322,7 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
                        sfw, b.d_sf);
     FCOO_HIP(hipGetLastError());
     hipLaunchKernelGGL(dev::tiles_kernel, dim3((unsigned)((ntiles + 1 + 255) / 256)), dim3(256), 0, s, cum, Z, WT,
-                       ntiles, hb, b.d_tile_seg0);
+                       ntiles, hb, seg0d);
     FCOO_HIP(hipGetLastError());
     std::vector<int32_t> hbh(ntiles + 1);
     FCOO_HIP(hipMemcpyAsync(hbh.data(), hb, (size_t)(ntiles + 1) * 4, hipMemcpyDeviceToHost, s));
@@ -314,7 +332,7 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     const int nim = (int)b.imodes.size();
     int32_t *segd;
     if (op == FCOO_OP_MTTKRP) {
-        if ((rc = alloc_dev(&b.d_seg_row, nseg, 1, s, &acct))) return rc;
+        if ((rc = alloc_dev(&b.d_seg_row, nseg, 2, s, &acct))) return rc;
         segd = b.d_seg_row;
     } else if ((rc = tmp.get(&segd, nseg * nim))) {
         return rc;
@@ -341,7 +359,7 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     b.seg.resize((size_t)nseg * nim);
     std::vector<int32_t> seg0(ntiles);
     FCOO_HIP(hipMemcpyAsync(b.seg.data(), segd, (size_t)nseg * nim * 4, hipMemcpyDeviceToHost, s));
-    FCOO_HIP(hipMemcpyAsync(seg0.data(), b.d_tile_seg0, (size_t)ntiles * 4, hipMemcpyDeviceToHost, s));
+    FCOO_HIP(hipMemcpyAsync(seg0.data(), seg0d, (size_t)ntiles * 4, hipMemcpyDeviceToHost, s));
     FCOO_HIP(hipStreamSynchronize(s));
     b.tile_seg0.resize(b.ntiles);
     for (int64_t k = 0; k < b.ntiles; ++k) b.tile_seg0[k] = seg0[k * (T / WT)];

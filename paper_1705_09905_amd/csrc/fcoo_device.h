@@ -1,4 +1,4 @@
-// Device-side building blocks for gfx950 (CDNA4, wave64): F-COO flag
+// Device-side building blocks for gfx950 (CDNA4, wave64): segment-head
 // decoding, cross-lane moves inside a lane group, row loads of float32 /
 // bfloat16 factor matrices.
 #pragma once
@@ -9,39 +9,26 @@
 namespace fcoo {
 namespace dev {
 
-// ----- F-COO flags ----------------------------------------------------------
-// bf is one bit per nonzero (a parity bit toggled at each segment start,
-// Sec. IV-B), stored as uint32 words with two zero words of padding, so any
-// 64-bit window that starts below Z can be read.
+// ----- segment heads --------------------------------------------------------
+// The kernels read the bf bits (Sec. IV-B) decoded: per 32 nonzeros one pair
+// (.x: bit i set iff nonzero 32 w + i starts a segment, .y: heads before
+// nonzero 32 w), with two zero pairs of padding, so the words of any 64
+// nonzeros that start below Z can be read.  A run's first segment ordinal then
+// takes one load and a popcount where it is wanted, not a count over the tile.
 
-__device__ __forceinline__ uint64_t fetch64(const uint32_t *__restrict__ bf, int64_t pos)
+// Heads of the nonzeros from bit `sh` of the first word on (the third word only
+// counts past 32 - sh + 32), of which the first n <= 64 are kept.
+__device__ __forceinline__ uint64_t head_bits(uint32_t h0, uint32_t h1, uint32_t h2, int sh, int n)
 {
-    const int64_t w0 = pos >> 5;
-    const int sh = (int)(pos & 31);
-    const uint64_t lo = (uint64_t)bf[w0] | ((uint64_t)bf[w0 + 1] << 32);
-    if (sh == 0) return lo;
-    const uint64_t hi = (uint64_t)bf[w0 + 2];
-    return (lo >> sh) | (hi << (64 - sh));
-}
-
-__device__ __forceinline__ uint32_t bit_at(const uint32_t *__restrict__ bf, int64_t pos)
-{
-    return pos < 0 ? 0u : (bf[pos >> 5] >> (pos & 31)) & 1u;
-}
-
-// Segment heads of nonzeros [pos, pos + n), n <= 64: bit k set iff nonzero
-// pos + k starts a segment, i.e. its bf bit differs from the previous one
-// (the bit before nonzero 0 counts as 0, so nonzero 0 is always a head).
-__device__ __forceinline__ uint64_t head_window(const uint32_t *__restrict__ bf, int64_t pos, int n)
-{
-    const uint64_t cur = fetch64(bf, pos);
-    const uint64_t hm = cur ^ ((cur << 1) | (uint64_t)bit_at(bf, pos - 1));
+    const uint64_t lo = (uint64_t)h0 | ((uint64_t)h1 << 32);
+    const uint64_t hm = sh ? ((lo >> sh) | ((uint64_t)h2 << (64 - sh))) : lo;
     return n >= 64 ? hm : (hm & ((1ull << n) - 1ull));
 }
 
-__device__ __forceinline__ uint32_t head_at(const uint32_t *__restrict__ bf, int64_t pos)
+// Heads before nonzero 32 w + sh, from its pair.
+__device__ __forceinline__ int heads_before(uint32_t h0, uint32_t rank, int sh)
 {
-    return bit_at(bf, pos) ^ bit_at(bf, pos - 1);
+    return (int)rank + __popc(h0 & ((1u << sh) - 1u));
 }
 
 // ----- lane-group moves -------------------------------------------------------

@@ -130,10 +130,10 @@ void Built::free_device()
     d_bpart = nullptr;
     bpart_cap = 0;
     for (auto &p : d_pidx) { if (p) (void)hipFree(p); p = nullptr; }
-    void *ptrs[] = {d_val, d_bf, d_sf, d_seg_row, d_tile_seg0, d_perm, d_fix, d_empty, d_carry,
+    void *ptrs[] = {d_val, d_hr, d_bf, d_sf, d_seg_row, d_perm, d_fix, d_empty, d_carry,
                     d_gperm, d_partial, d_sp_from, d_sp_words, d_sp_ticket, d_sp_err};
     for (void *p : ptrs) if (p) (void)hipFree(p);
-    d_val = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr; d_tile_seg0 = nullptr;
+    d_val = nullptr; d_hr = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr;
     d_perm = nullptr; d_fix = nullptr; d_empty = nullptr; d_carry = nullptr; d_gperm = nullptr;
     d_partial = nullptr; d_sp_from = nullptr; d_sp_words = nullptr; d_sp_ticket = nullptr; d_sp_err = nullptr;
     carry_cap = 0; partial_cap = 0; device_bytes = 0; sp_words_cap = 0; sp_tickets = 0; sp_epoch = 0;
@@ -416,7 +416,6 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
     b.bf.assign((Z + 7) / 8, 0);
     b.sf.assign((P + 31) / 32, 0);
     b.tile_seg0.resize(ntiles);
-    b.wtile_seg0.resize(b.wntiles);
     std::vector<int64_t> seg_start;  // position of each head
     std::vector<int64_t> heads_before_tile(b.wntiles + 1, 0);
     int64_t cnt = 0;
@@ -429,7 +428,6 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
         }
         if (cnt & 1) b.bf[s >> 3] |= (uint8_t)(1u << (s & 7));
         if (s % tile_nnz == 0) b.tile_seg0[s / tile_nnz] = (int32_t)(cnt - 1);
-        if (s % wtile == 0) b.wtile_seg0[s / wtile] = (int32_t)(cnt - 1);
     }
     heads_before_tile[b.wntiles] = cnt;
     b.nseg = cnt;
@@ -516,18 +514,28 @@ static int build_device(Built &b, hipStream_t s)
         if ((rc = upload(&b.d_pidx[q], b.pidx[q].data(), b.nnz, 4, s, &acct))) return rc;
     // 4 entries of zero padding: 16-byte stream vectors never read past the allocation
     if ((rc = upload(&b.d_val, b.val.data(), b.nnz, 4, s, &acct))) return rc;
-    {   // bit stream as uint32 words plus two zero words (64-bit windows never read past it)
+    {   // the bf bits decoded for the kernels: per 32 nonzeros the heads (where bf
+        // changes) and their running count, plus two zero pairs
         const int64_t words = (b.nnz + 31) / 32;
-        std::vector<uint32_t> w(words, 0);
-        if (!b.bf.empty()) memcpy(w.data(), b.bf.data(), b.bf.size());
-        if ((rc = upload(&b.d_bf, w.data(), words, 2, s, &acct))) return rc;
+        std::vector<uint32_t> w(2 * words, 0);
+        uint32_t last = 0, rank = 0;
+        for (int64_t i = 0; i < words; ++i) {
+            uint32_t x = 0;
+            const int64_t left = (int64_t)b.bf.size() - 4 * i;
+            memcpy(&x, b.bf.data() + 4 * i, (size_t)(left < 4 ? left : 4));
+            uint32_t h = x ^ ((x << 1) | last);
+            if (i == words - 1 && (b.nnz & 31)) h &= (1u << (b.nnz & 31)) - 1u;   // bf is 0 past Z
+            w[2 * i] = h;
+            w[2 * i + 1] = rank;
+            rank += (uint32_t)__builtin_popcount(h);
+            last = x >> 31;
+        }
+        if ((rc = upload(&b.d_hr, w.data(), 2 * words, 4, s, &acct))) return rc;
         FCOO_HIP(hipStreamSynchronize(s));
     }
-    // sf stays on the host (exported with the format): the kernels count the
-    // segment heads before each run from bf popcounts, so no device work reads it
+    // bf itself and sf stay on the host (exported with the format)
     if (b.op == FCOO_OP_MTTKRP)
-        if ((rc = upload(&b.d_seg_row, b.seg.data(), b.nseg, 1, s, &acct))) return rc;
-    if ((rc = upload(&b.d_tile_seg0, b.wtile_seg0.data(), b.wntiles, 1, s, &acct))) return rc;
+        if ((rc = upload(&b.d_seg_row, b.seg.data(), b.nseg, 2, s, &acct))) return rc;
     if ((rc = upload(&b.d_perm, b.perm.data(), b.nnz, 0, s, &acct))) return rc;
     if ((rc = upload(&b.d_fix, b.fix.data(), (int64_t)b.fix.size(), 3, s, &acct))) return rc;
     if ((rc = upload(&b.d_empty, b.empty_rows.data(), (int64_t)b.empty_rows.size(), 1, s, &acct)))

@@ -38,8 +38,7 @@ struct Built {
     int64_t nnz = 0, nseg = 0, npart = 0, ntiles = 0;
     // nonzeros per workgroup tile as launched: tile_nnz when the caller chose
     // it, else the size work_tile() picks (a divisor of the format's tile_nnz,
-    // which info and export go by); tile_seg0 on the device, fix and blk_ts
-    // are of these tiles
+    // which info and export go by); fix and blk_ts are of these tiles
     int wtile = 0;
     int64_t wntiles = 0;
     int64_t nfix_fmt = 0;                     // segments finished across the format's tiles (info)
@@ -62,7 +61,6 @@ struct Built {
     std::vector<uint32_t> sf;                 // ceil(P/32)
     std::vector<int32_t> seg;                 // MTTKRP: nseg rows; TTM: nseg x (N-1)
     std::vector<int32_t> tile_seg0;           // ntiles (format tiles)
-    std::vector<int32_t> wtile_seg0;          // wntiles (host builds)
     std::vector<int32_t> perm;                // Z: sorted position -> input position
 
     // carry fix-up list over the launched tiles: (closing tile b, chain start tile a, output row) per entry
@@ -72,10 +70,10 @@ struct Built {
     // device copies
     int32_t *d_pidx[kMaxOrder] = {};
     float *d_val = nullptr;
-    uint32_t *d_bf = nullptr;                 // bit stream as uint32 words, +2 zero words
-    uint32_t *d_sf = nullptr;                 // device builds only (where it is made), for export
+    uint32_t *d_hr = nullptr;                 // per 32 nonzeros: segment heads, heads before; +2 zero pairs
+    uint32_t *d_bf = nullptr;                 // device builds only (where they are made), for export
+    uint32_t *d_sf = nullptr;
     int32_t *d_seg_row = nullptr;             // MTTKRP only
-    int32_t *d_tile_seg0 = nullptr;           // wntiles
     int32_t *d_perm = nullptr;
     int32_t *d_fix = nullptr;
     int32_t *d_empty = nullptr;

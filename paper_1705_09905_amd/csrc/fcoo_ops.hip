@@ -217,8 +217,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
             a.fac[q] = p.fac[q];
         }
         a.vals = p.vals;
-        a.bf = b.d_bf;
-        a.tile_seg0 = b.d_tile_seg0;
+        a.hr = reinterpret_cast<const uint2 *>(b.d_hr);
         a.seg_row = b.op == FCOO_OP_MTTKRP ? b.d_seg_row : nullptr;
         a.out = b.nblk > 1 ? p.bpart : p.out;
         a.carry_a = p.carry;

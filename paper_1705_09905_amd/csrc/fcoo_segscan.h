@@ -54,9 +54,8 @@ struct SegArgs {
     const int32_t *pidx[kMaxNP];     // product-mode index streams (stored order)
     const void *fac[kMaxNP];         // factor matrix of each product mode
     const float *vals;               // values in stored order
-    const uint32_t *bf;              // bit stream, padded
-    const int32_t *tile_seg0;        // per tile: segment ordinal of its first nonzero
-    const int32_t *seg_row;          // per segment output row (NULL: row = ordinal)
+    const uint2 *hr;                 // per 32 nonzeros: (segment heads, heads before), padded
+    const int32_t *seg_row;          // per segment output row (NULL: row = ordinal), 2 entries of padding
     float *out;                      // output rows, leading dimension R
     float *carry_a;                  // ntiles x R
     float *carry_b;                  // ntiles x R
@@ -171,17 +170,32 @@ constexpr int pow2_floor(int x)
 }
 
 // The stream of one chunk as held by one lane: U entries per array (entry
-// u of lane j is step u * LPN + j of the chunk), the three bf words that
-// cover nonzeros [base - 1, base + 63] (decoded only when the chunk is
-// used, so that loading the next chunk never waits), and the chunk length.
+// u of lane j is step u * LPN + j of the chunk), the head words that cover
+// the chunk (decoded only when the chunk is used, so that loading the next
+// chunk never waits), and the chunk length.  Lanes past the chunk's end read
+// what follows (steps past n are never summed), lanes past the stream its
+// padding, so no load sits behind a branch of its own.
 template <int U, int NPM>
 struct Chunk {
     int idx[U][NPM];
     float v[U];
-    uint32_t w0, w1, w2;
-    int sh;                      // bit of nonzero base - 1 in w0; -1 when base == 0
+    uint32_t h0, h1, h2, rank;   // rank: heads before the first word
+    int sh;                      // bit of the chunk's first nonzero in h0
     int n;
 };
+
+template <int SPAN, class C>
+__device__ __forceinline__ void load_heads(const SegArgs &A, int64_t base, C &c)
+{
+    const uint2 *p = A.hr + (base >> 5);
+    c.sh = (int)(base & 31);
+    const uint2 a = p[0], b = p[1];
+    c.h0 = a.x;
+    c.rank = a.y;
+    c.h1 = b.x;
+    if constexpr (SPAN > 33) c.h2 = p[2].x;          // 33 nonzeros lie within two words wherever they start
+    else c.h2 = 0;
+}
 
 template <int LPN, int CL, int U, int NPM>
 __device__ __forceinline__ void load_chunk(const SegArgs &A, int np, int j, int64_t base, int64_t re,
@@ -189,43 +203,29 @@ __device__ __forceinline__ void load_chunk(const SegArgs &A, int np, int j, int6
 {
     const int64_t rem = re - base;
     c.n = rem < CL ? (int)rem : CL;
-    const int64_t p1 = base - 1;
-    const int64_t wi = p1 < 0 ? 0 : (p1 >> 5);
-    c.sh = p1 < 0 ? -1 : (int)(p1 & 31);
-    c.w0 = A.bf[wi];
-    c.w1 = A.bf[wi + 1];
-    c.w2 = A.bf[wi + 2];
+    load_heads<CL>(A, base, c);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int el = u * LPN + j;
-        const bool ev = el < c.n;
-        const int64_t e = base + el;
+        const int64_t e0 = base + u * LPN + j;
+        const int64_t e = e0 < A.nnz ? e0 : A.nnz;
 #pragma unroll
         for (int qq = 0; qq < NPM; ++qq)
-            c.idx[u][qq] = (ev && qq < np) ? __builtin_nontemporal_load(A.pidx[qq] + e) : 0;
-        c.v[u] = ev ? __builtin_nontemporal_load(A.vals + e) : 0.f;
+            c.idx[u][qq] = qq < np ? __builtin_nontemporal_load(A.pidx[qq] + e) : 0;
+        c.v[u] = __builtin_nontemporal_load(A.vals + e);
     }
 }
 
-// Segment heads of the chunk's n steps (bit s: step s starts a segment).
-template <int U, int NPM>
-__device__ __forceinline__ uint64_t chunk_heads(const Chunk<U, NPM> &c)
+template <class C>
+__device__ __forceinline__ uint64_t chunk_heads(const C &c)
 {
-    const uint64_t lo = (uint64_t)c.w0 | ((uint64_t)c.w1 << 32);
-    const int sh = c.sh < 0 ? 0 : c.sh;
-    const uint64_t x = sh ? ((lo >> sh) | ((uint64_t)c.w2 << (64 - sh))) : lo;  // from nonzero base - 1
-    const uint64_t top = (c.w2 >> sh) & 1u;                                       // nonzero base + 63
-    const uint64_t cur = c.sh < 0 ? lo : ((x >> 1) | (top << 63));
-    const uint64_t prev = c.sh < 0 ? 0ull : (x & 1ull);
-    const uint64_t hm = cur ^ ((cur << 1) | prev);
-    return c.n >= 64 ? hm : (hm & ((1ull << c.n) - 1ull));
+    return head_bits(c.h0, c.h1, c.h2, c.sh, c.n);
 }
 
 // Stream of a super-chunk of SC = 4 * LPN * K steps, read with 16-byte loads:
 // vector k of lane j holds steps (k * LPN + j) * 4 .. + 3, so each lane
 // group reads whole 16-byte pieces of its run (a full 128-byte line per
 // index array when LPN = 8).  Device streams carry 4 entries of padding, so
-// a vector that starts below the run end never reads past the allocation.
+// a vector that starts at most at nonzero Z never reads past the allocation.
 typedef int int4a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float float4a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -233,7 +233,7 @@ template <int K, int NPM>
 struct SChunk {
     int4a4 idx[K][NPM];
     float4a4 v[K];
-    uint32_t w0, w1, w2;
+    uint32_t h0, h1, h2, rank;
     int sh;
     int n;
 };
@@ -244,37 +244,16 @@ __device__ __forceinline__ void load_schunk(const SegArgs &A, int j, int64_t bas
 {
     const int64_t rem = re - base;
     c.n = rem < SC ? (int)rem : SC;
-    const int64_t p1 = base - 1;
-    const int64_t wi = p1 < 0 ? 0 : (p1 >> 5);
-    c.sh = p1 < 0 ? -1 : (int)(p1 & 31);
-    c.w0 = A.bf[wi];
-    c.w1 = A.bf[wi + 1];
-    c.w2 = A.bf[wi + 2];
+    load_heads<SC>(A, base, c);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int el = (k * LPN + j) * 4;
-        const bool ev = el < c.n;
-        const int64_t e = base + el;
+        const int64_t e0 = base + (k * LPN + j) * 4;
+        const int64_t e = e0 < A.nnz ? e0 : A.nnz;
 #pragma unroll
         for (int qq = 0; qq < NPM; ++qq)
-            c.idx[k][qq] = ev ? __builtin_nontemporal_load(reinterpret_cast<const int4a4 *>(A.pidx[qq] + e))
-                              : int4a4{0, 0, 0, 0};
-        c.v[k] = ev ? __builtin_nontemporal_load(reinterpret_cast<const float4a4 *>(A.vals + e))
-                    : float4a4{0.f, 0.f, 0.f, 0.f};
+            c.idx[k][qq] = __builtin_nontemporal_load(reinterpret_cast<const int4a4 *>(A.pidx[qq] + e));
+        c.v[k] = __builtin_nontemporal_load(reinterpret_cast<const float4a4 *>(A.vals + e));
     }
-}
-
-template <int K, int NPM>
-__device__ __forceinline__ uint64_t schunk_heads(const SChunk<K, NPM> &c)
-{
-    const uint64_t lo = (uint64_t)c.w0 | ((uint64_t)c.w1 << 32);
-    const int sh = c.sh < 0 ? 0 : c.sh;
-    const uint64_t x = sh ? ((lo >> sh) | ((uint64_t)c.w2 << (64 - sh))) : lo;
-    const uint64_t top = (c.w2 >> sh) & 1u;
-    const uint64_t cur = c.sh < 0 ? lo : ((x >> 1) | (top << 63));
-    const uint64_t prev = c.sh < 0 ? 0ull : (x & 1ull);
-    const uint64_t hm = cur ^ ((cur << 1) | prev);
-    return c.n >= 64 ? hm : (hm & ((1ull << c.n) - 1ull));
 }
 
 template <int LPN, int ST, int K, int NPM>
@@ -349,7 +328,6 @@ void seg_tile_kernel(SegArgs A)
     float (*s_a)[RT] = s_ab;
     float (*s_b)[RT] = s_ab + 4;
     __shared__ double s_loss[4];
-    __shared__ int s_hw[4];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
@@ -413,8 +391,11 @@ void seg_tile_kernel(SegArgs A)
     // RESID: factor row of the index mode for an output row (blocks add block * rows)
     auto own_row = [&](int r) -> int64_t { return A.nblk > 1 ? (int64_t)(r % A.rows_own) : (int64_t)r; };
     // (a column two lanes hold counts once in the dot product: zero in the second)
-    auto load_own = [&](int r, float (&o)[VW]) {
-        load_row<FT, VW>(reinterpret_cast<const FT *>(A.own) + own_row(r) * R + colc, o);
+    auto load_own = [&](int r, Raw<FT, VW> &o) {
+        load_raw<FT, VW>(reinterpret_cast<const FT *>(A.own) + own_row(r) * R + colc, o);
+    };
+    auto take_own = [&](const Raw<FT, VW> &x, float (&o)[VW]) {
+        to_float<FT, VW>(x, o);
 #pragma unroll
         for (int k = 0; k < VW - 1; ++k) o[k] = k < dup ? 0.f : o[k];
     };
@@ -485,36 +466,13 @@ void seg_tile_kernel(SegArgs A)
         if constexpr (FAST) load_schunk<LPN, SC, K, NPM>(A, j, rs, re, scur);
         else load_chunk<LPN, CL, U, NPM>(A, np, j, rs, re, cur);
     }
-    const int ts0 = A.tile_seg0[tile];
-    const int h0 = (int)head_at(A.bf, t0);
 
-    // ---- 1. heads before each run.  Heads in [t0, wave start): counted by
-    //         the whole wave; heads of the earlier runs of this wave: a scan
-    //         across lane groups.  No barrier.
-    int wc = 0;
-    const int64_t wend = wstart < A.nnz ? wstart : A.nnz;   // no bits exist at or past Z
-    for (int64_t p = t0 + 64 * (int64_t)lane; p < wend; p += 64 * 64) {
-        const int n = (int)(wend - p < 64 ? wend - p : 64);
-        wc += __popcll(head_window(A.bf, p, n));
+    // ---- 1. heads before the run: from its first chunk's head words
+    int H_run = 0;
+    if (rs < re) {
+        if constexpr (FAST) H_run = heads_before(scur.h0, scur.rank, scur.sh);
+        else H_run = heads_before(cur.h0, cur.rank, cur.sh);
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) wc += __shfl_xor(wc, o, 64);
-    int cnt = 0;
-    for (int64_t base = rs; base < re; base += 64) {
-        const int n = (int)(re - base < 64 ? re - base : 64);
-        cnt += __popcll(head_window(A.bf, base, n));
-    }
-    int inc = cnt;
-#pragma unroll
-    for (int d = 1; d < Q; d <<= 1) {
-        const int u = __shfl_up(inc, d * LPN, 64);
-        if (q >= d) inc += u;
-    }
-    // heads strictly before the tile: ordinal of its first nonzero + 1, less
-    // one if that nonzero is itself a head
-    const int H_tile = ts0 + 1 - h0;
-    const int H_wave = H_tile + wc;
-    const int H_run = H_wave + inc - cnt;
 
     // ---- 2. walk the run, one chunk at a time: gather this chunk's rows,
     //         then put the next chunk's stream in flight, then reduce
@@ -523,14 +481,23 @@ void seg_tile_kernel(SegArgs A)
     zero(pre);
     int have = 0;
     int g = H_run - 1;                                // segment open before the run
-    int currow = 0;                                   // ROWMAP: output row of segment g
+    // ROWMAP: output rows of segments g, g + 1 and g + 2, the later ones read
+    // ahead so that a head waits for no load; RESID: factor rows of g and g + 1
+    int row0 = 0, currow = 0, row1 = 0, row2 = 0;     // row0: of the segment open before the run
     float own[VW];
+    Raw<FT, VW> own1;
     float lsum = 0.f;
-    if constexpr (RESID) {
-        zero(own);
-        if (g >= 0 && rs < re) {
-            currow = A.seg_row[g];
-            load_own(currow, own);
+    if constexpr (ROWMAP) {
+        if (rs < re) {
+            row0 = A.seg_row[g >= 0 ? g : 0];
+            row1 = A.seg_row[g + 1];
+            if constexpr (RESID) {
+                row2 = A.seg_row[g + 2];
+                Raw<FT, VW> own0;
+                load_own(row0, own0);
+                load_own(row1, own1);
+                take_own(own0, own);
+            }
         }
     }
 
@@ -548,8 +515,16 @@ void seg_tile_kernel(SegArgs A)
             have = 1;
             zero(acc);
             ++g;
-            if constexpr (ROWMAP) currow = A.seg_row[g];
-            if constexpr (RESID) load_own(currow, own);
+            if constexpr (RESID) {
+                currow = row1;
+                row1 = row2;
+                take_own(own1, own);
+                load_own(row1, own1);
+                row2 = A.seg_row[g + 2];
+            } else if constexpr (ROWMAP) {
+                currow = row1;
+                row1 = A.seg_row[g + 1];
+            }
         }
     };
     auto step = [&](const float (&h)[AW], float v, uint64_t hm, int st, int n) {
@@ -580,7 +555,7 @@ void seg_tile_kernel(SegArgs A)
         for (int64_t base = rs; base < re; base += SC) {
             SChunk<K, NPM> snxt;
             const bool more = base + SC < re;
-            const uint64_t hms = schunk_heads(scur);
+            const uint64_t hms = chunk_heads(scur);
             const int nsc = scur.n;
             static_for<SC / CLF>([&](auto cc) {
                 constexpr int C0 = decltype(cc)::value * CLF;
@@ -786,8 +761,7 @@ void seg_tile_kernel(SegArgs A)
             float v[AW];
 #pragma unroll
             for (int k = 0; k < AW; ++k) v[k] = bp[k] + ao[k];
-            const int gc = H_run - 1;
-            const int64_t row = ROWMAP ? (int64_t)A.seg_row[gc] : (int64_t)gc;
+            const int64_t row = ROWMAP ? (int64_t)row0 : (int64_t)(H_run - 1);
             store_acc(A.out + row * R, v);
         }
     }
@@ -805,7 +779,6 @@ void seg_tile_kernel(SegArgs A)
         for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o, 64);
         if (lane == 0) s_loss[w] = (double)l;
     }
-    if (lane == 0) s_hw[w] = H_wave;
     __syncthreads();
 
     // ---- 4. tile level: a wave's first closing whose segment started in an
@@ -824,8 +797,7 @@ void seg_tile_kernel(SegArgs A)
             float v[AW];
 #pragma unroll
             for (int k = 0; k < AW; ++k) v[k] = bx[k] + s_a[w][j * AW + k];
-            const int gc = s_hw[w] - 1;
-            const int64_t row = ROWMAP ? (int64_t)A.seg_row[gc] : (int64_t)gc;
+            const int64_t row = ROWMAP ? (int64_t)row0 : (int64_t)(H_run - 1);
             store_acc(A.out + row * R, v);
         }
     }
@@ -924,7 +896,7 @@ void seg_tile_kernel(SegArgs A)
 #pragma unroll
                     for (int k = 0; k < AW; ++k) v[k] += at[k];
                 }
-                const int gc = tail ? A.nseg - 1 : H_tile - 1;
+                const int gc = tail ? A.nseg - 1 : H_run - 1;   // (the first run starts with the tile)
                 const int64_t row = ROWMAP ? (int64_t)A.seg_row[gc] : (int64_t)gc;
                 store_acc(A.out + row * R, v);
             }
