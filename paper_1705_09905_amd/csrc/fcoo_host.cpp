@@ -878,9 +878,10 @@ int fcoo_spmttkrp_values(fcoo_tensor *t, int mode, const float *g, const void *c
     if (rc) return rc;
     if (!M || (!g && b->nnz)) return fail(FCOO_EINVAL, "M or g is NULL");
     hipStream_t s = (hipStream_t)stream;
-    int64_t cap = b->d_gperm ? b->nnz : 0;
+    // (4 entries past the values, read but not used, as the build's streams have)
+    int64_t cap = b->d_gperm ? b->nnz + 4 : 0;
     if (!b->d_gperm && b->nnz) {
-        if ((rc = ensure_device_floats(&b->d_gperm, &cap, b->nnz, s))) return rc;
+        if ((rc = ensure_device_floats(&b->d_gperm, &cap, b->nnz + 4, s))) return rc;
     }
     if (b->nnz && (rc = launch_permute_values(*b, g, b->d_gperm, s))) return rc;
     TileProblem p{};
