@@ -31,6 +31,7 @@ SOURCES = [
     "fcoo_sort.hip",
     "fcoo_ops.hip",
     "fcoo_cp.hip",
+    "fcoo_ttmc.hip",
     "fcoo_noalloc.hip",
     "fcoo_copy.hip",
     "seg_f32.hip",
@@ -40,8 +41,6 @@ SOURCES = [
     "seg_bf16_resid.hip",
     "seg_f32_narrow.hip",
     "seg_bf16_narrow.hip",
-    "seg_f32_kron.hip",
-    "seg_bf16_kron.hip",
 ]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function", "-I", INCLUDE, "-I", CSRC]

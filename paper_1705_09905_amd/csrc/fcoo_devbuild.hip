@@ -212,13 +212,14 @@ int alloc_dev(T **dst, int64_t n, int64_t pad, hipStream_t s, int64_t *acct)
 
 }  // namespace
 
-int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, int WT, int nblk, int xmode,
+int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bool own_tile, int nblk, int xmode,
                     hipStream_t s)
 {
     const int N = t->order;
     const int64_t Z = t->nnz;
     b = Built();
-    b.op = op; b.mode = mode; b.threadlen = L; b.tile_nnz = T; b.wtile = WT; b.nnz = Z;
+    b.op = op; b.mode = mode; b.threadlen = L; b.tile_nnz = T; b.nnz = Z;
+    b.set_plans(T, own_tile);
     b.host_arrays = false;
     for (int m = 0; m < N; ++m) {
         if (m == mode) continue;
@@ -246,10 +247,10 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
         for (int m : b.pmodes) ka.idx[i++] = t->d_coo[m];
     }
     const int64_t P = (Z + L - 1) / L;
-    const int64_t ntiles = (Z + WT - 1) / WT;         // as launched
+    const int WT = b.plan.back().T;                   // the shortest tiles as launched
+    const int64_t ntiles = b.plan.back().ntiles;
     b.npart = P;
     b.ntiles = (Z + T - 1) / T;
-    b.wntiles = ntiles;
 
     Scratch tmp;
     uint64_t *k0, *k1;
@@ -367,7 +368,7 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, in
     // 5. carry chains and empty rows on the host (per tile / per row)
     std::vector<int64_t> hb64(hbh.begin(), hbh.end());
     finish_tiles(t, b, mode, op, hb64);
-    if ((rc = upload_i32(&b.d_fix, b.fix, 3, s, &acct))) return rc;
+    if ((rc = upload_plans(b, s, &acct))) return rc;
     if ((rc = upload_i32(&b.d_empty, b.empty_rows, 1, s, &acct))) return rc;
     FCOO_HIP(hipStreamSynchronize(s));
     b.device_bytes = acct;

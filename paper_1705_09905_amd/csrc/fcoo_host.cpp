@@ -229,7 +229,6 @@ int setup_blocks(const fcoo_tensor *t, Built &b, int nblk, int xmode)
     b.nblk = 1;
     b.bmode = -1;
     b.blk_of.clear();
-    b.blk_ts.clear();
     b.rows = b.op == FCOO_OP_MTTKRP ? t->dims[b.mode] : 0;
     if (nblk <= 1) return FCOO_OK;
     if (nblk != kXcds) return fail(FCOO_EINVAL, "xcd_blocks must be 0, 1 or %d (got %d)", kXcds, nblk);
@@ -258,14 +257,14 @@ int setup_blocks(const fcoo_tensor *t, Built &b, int nblk, int xmode)
         before += cnt[i];
     }
     for (int k = 0; k < nblk; ++k) zs[k + 1] += zs[k];
-    const int64_t T = b.wtile, ntiles = (Z + T - 1) / T;
-    b.blk_ts.assign(nblk + 1, 0);
-    for (int k = 1; k < nblk; ++k) {
-        int64_t ts = zs[k] / T;
-        if (ts > ntiles) ts = ntiles;
-        b.blk_ts[k] = ts < b.blk_ts[k - 1] ? b.blk_ts[k - 1] : ts;
+    for (Plan &pl : b.plan) {
+        pl.blk_ts.assign(nblk + 1, 0);
+        for (int k = 1; k < nblk; ++k) {
+            const int64_t ts = std::min(zs[k] / pl.T, pl.ntiles);
+            pl.blk_ts[k] = std::max(ts, pl.blk_ts[k - 1]);
+        }
+        pl.blk_ts[nblk] = pl.ntiles;
     }
-    b.blk_ts[nblk] = ntiles;
     b.nblk = nblk;
     b.bmode = bm;
     return FCOO_OK;
@@ -275,10 +274,11 @@ int setup_single_pass(Built &b, hipStream_t s)
 {
     if (b.nblk > 1) return fail(FCOO_EINVAL, "single_pass needs the plain layout (no xcd_blocks)");
     if (b.ntiles > (int64_t)0x7fffffff) return fail(FCOO_EUNSUPPORTED, "single_pass: too many tiles");
+    const Plan &pl = b.plan[0];
     std::vector<int32_t> from(b.ntiles + 1, -1);
     b.sp_tail_from = -1;
-    for (int64_t e = 0; e < b.nfix(); ++e) {
-        const int32_t tb = b.fix[3 * e], ta = b.fix[3 * e + 1];
+    for (int64_t e = 0; e < pl.nfix(); ++e) {
+        const int32_t tb = pl.fix[3 * e], ta = pl.fix[3 * e + 1];
         if (tb < b.ntiles) from[tb] = ta;
         else b.sp_tail_from = ta;
     }
@@ -299,7 +299,7 @@ int setup_single_pass(Built &b, hipStream_t s)
 
 int prep_single_pass(Built *b, TileProblem &p, hipStream_t s)
 {
-    if (!b->sp || b->nnz == 0) return FCOO_OK;
+    if (!b->sp || b->nnz == 0 || p.kron) return FCOO_OK;
     const int64_t need = 2 * b->ntiles * (int64_t)p.R;
     if (need > b->sp_words_cap) {
         // fresh words hold tag 0, which no launch uses
@@ -319,24 +319,69 @@ int prep_single_pass(Built *b, TileProblem &p, hipStream_t s)
     return FCOO_OK;
 }
 
-int64_t Built::max_block_tiles() const
+// The tile sizes a build can be launched with: the format's, and below it those
+// that pick_plan chooses from (with a caller's own size only the one that
+// SpTTMc's waves take).
+void Built::set_plans(int fmt_tile, bool own)
 {
-    int64_t m = 0;
-    for (int k = 0; k < nblk; ++k) m = blk_ts[k + 1] - blk_ts[k] > m ? blk_ts[k + 1] - blk_ts[k] : m;
-    return m;
+    own_tile = own;
+    plan.clear();
+    plan.resize(1);
+    plan[0].T = fmt_tile;
+    for (int t : {2048, 1024, 512}) {
+        if (t >= plan.back().T || fmt_tile % t || (own && t != 1024)) continue;
+        plan.emplace_back();
+        plan.back().T = t;
+    }
+    for (Plan &pl : plan) pl.ntiles = (nnz + pl.T - 1) / pl.T;
+}
+
+// A tile costs a chain of dependent loads at its start and end whatever its
+// length, so tiles are long where there are enough of them to fill 256 CUs
+// several times over and short where there are not; a run stays a power of two
+// long (runs that start inside a 128-byte line of the streams cost 10-20%), and
+// with 4 lanes a row or fewer a lane group's stream vectors cover less than a
+// line, so neighbouring runs should share it: 1024 nonzeros, one super-chunk a
+// run.  Measured on Zipf(1.1) tensors, whole calls, 512 / 1024 / 2048 / 4096
+// nonzeros a tile (us):
+//   SpMTTKRP float32 R = 32 (8 lanes): 100k 13.6 / 13.7 / 16.3 / 24.9, 400k 17.1 /
+//   13.5 / 16.9 / 26.0, 1.5M 40.5 / 26.1 / 26.1 / 33.6, 5M 113 / 67 / 67 / 77, 20M
+//   412 / 226 / 216 / 219; R = 16 (4 lanes): 20M 326 / 187 / 196 / 205; R = 8: 289 /
+//   169 / 177 / 242;
+//   residual R = 64: 5M 209 / 133 / 139 / 168, 20M 792 / 470 / 444 / 438;
+//   SpTTM R = 32: 400k 15.4 / 13.1 / 15.6 / 24.8, 5M 114 / 75 / 78 / 102, 20M 419 /
+//   262 / 272 / 320; R = 8: 248 / 236 / 284 / 381.
+// SpTTMc: a wave takes a tile, so short ones, unless the carries of wide rows
+// would outweigh the work.  Past 64M nonzeros short tiles gain nothing that their
+// carries' scratch would be worth.
+const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron)
+{
+    int want = b.plan[0].T;
+    if (kron) want = R <= 1024 ? 1024 : want;
+    else if (b.own_tile || b.nnz > (int64_t)64000000) return b.plan[0];
+    else if (b.op == FCOO_OP_TTM || lane_shape(b, dtype, R, resid).lpn <= 4) want = 1024;
+    else want = resid && b.nnz >= 10000000 ? 4096 : 2048;
+    if (!b.own_tile) {
+        if (b.nnz < 1000000 && want > 1024) want = 1024;
+        if (b.nnz < 200000 && want > 512) want = 512;
+    }
+    for (const Plan &pl : b.plan)
+        if (pl.T <= want) return pl;
+    return b.plan.back();
 }
 
 // ---------------------------------------------------------------------------
 // the F-COO build for one (op, mode)
 // ---------------------------------------------------------------------------
-static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, int wtile, int nblk,
+static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, bool own_tile, int nblk,
                       int xmode)
 {
     const int N = t->order;
     const int64_t Z = t->nnz;
     const int T = host_threads();
     b = Built();
-    b.op = op; b.mode = mode; b.threadlen = threadlen; b.tile_nnz = tile_nnz; b.wtile = wtile; b.nnz = Z;
+    b.op = op; b.mode = mode; b.threadlen = threadlen; b.tile_nnz = tile_nnz; b.nnz = Z;
+    b.set_plans(tile_nnz, own_tile);
     for (int m = 0; m < N; ++m) {
         if (m == mode) continue;
         if (op == FCOO_OP_MTTKRP) b.pmodes.push_back(m); else b.imodes.push_back(m);
@@ -412,12 +457,13 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
     const int64_t P = (Z + threadlen - 1) / threadlen;
     const int64_t ntiles = (Z + tile_nnz - 1) / tile_nnz;
     b.npart = P; b.ntiles = ntiles;
-    b.wntiles = (Z + wtile - 1) / wtile;
+    const Plan &fine = b.plan.back();
+    const int wtile = fine.T;
     b.bf.assign((Z + 7) / 8, 0);
     b.sf.assign((P + 31) / 32, 0);
     b.tile_seg0.resize(ntiles);
     std::vector<int64_t> seg_start;  // position of each head
-    std::vector<int64_t> heads_before_tile(b.wntiles + 1, 0);
+    std::vector<int64_t> heads_before_tile(fine.ntiles + 1, 0);
     int64_t cnt = 0;
     for (int64_t s = 0; s < Z; ++s) {
         if (s % wtile == 0) heads_before_tile[s / wtile] = cnt;
@@ -429,7 +475,7 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
         if (cnt & 1) b.bf[s >> 3] |= (uint8_t)(1u << (s & 7));
         if (s % tile_nnz == 0) b.tile_seg0[s / tile_nnz] = (int32_t)(cnt - 1);
     }
-    heads_before_tile[b.wntiles] = cnt;
+    heads_before_tile[fine.ntiles] = cnt;
     b.nseg = cnt;
     const int nim = (int)b.imodes.size();
     b.seg.resize((size_t)cnt * nim);
@@ -445,23 +491,6 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
     return FCOO_OK;
 }
 
-// Nonzeros per workgroup tile of a default build.  A tile costs a chain of
-// dependent loads at its start and end whatever its length, so tiles are long
-// where there are enough of them to fill 256 CUs several times over, and short
-// where there are not; a run stays a power of two long (runs that start inside
-// a 128-byte line of the streams cost 10-20%).  Measured on Zipf(1.1) tensors,
-// whole calls, 512 / 1024 / 2048 / 4096 nonzeros a tile (us):
-//   SpMTTKRP float32 R = 32: 100k 15.5 / 15.3 / 18.6 / 27.3, 400k 19.4 / 14.5 /
-//   17.5 / 26.1, 1.5M 46 / 30.1 / 27.5 / 35.5, 5M 131 / 78 / 72 / 80, 20M 470 /
-//   259 / 230 / 228;
-//   SpTTM float32 R = 32: 400k 15.8 / 13.2 / 16.6 / 25.9, 5M 116 / 78 / 84 / 107,
-//   20M 432 / 285 / 289 / 330 (R = 8: 293 / 240 / 275 / 375).
-int work_tile(int64_t nnz, int op, int fmt_tile)
-{
-    const int t = nnz < 200000 ? 512 : (nnz < 1000000 || op == FCOO_OP_TTM) ? 1024 : nnz < 10000000 ? 2048 : 4096;
-    return fmt_tile % t == 0 ? t : fmt_tile;
-}
-
 // Carry fix-up list: a segment that is still open at the end of a tile is
 // finished by the first head of a later tile (or by the end of the tensor).
 // Entry (b, a, row): tiles a+1 .. b-1 hold no head, tile a holds the segment's
@@ -470,32 +499,33 @@ int work_tile(int64_t nnz, int op, int fmt_tile)
 // touches (with XCD blocks: rows of the nblk x dims[mode] partial output).
 void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::vector<int64_t> &hb)
 {
-    const int64_t ntiles = b.wntiles, cnt = b.nseg;
+    const int64_t cnt = b.nseg;
     auto out_row = [&](int64_t g) -> int32_t {
         return op == FCOO_OP_MTTKRP ? b.seg[(size_t)g] : (int32_t)g;
     };
-    b.fix.clear();
-    int64_t last = -1;
-    for (int64_t tb = 0; tb < ntiles; ++tb) {
-        if (hb[tb + 1] == hb[tb]) continue;          // no head in tile tb
-        if (tb >= 1) {
-            b.fix.push_back((int32_t)tb);
-            b.fix.push_back((int32_t)last);
-            b.fix.push_back(out_row(hb[tb] - 1));
+    int64_t at = 0;
+    for (Plan &pl : b.plan) {
+        const int64_t ntiles = pl.ntiles, k = pl.T / b.plan.back().T, nfine = b.plan.back().ntiles;
+        pl.fix.clear();
+        int64_t last = -1;
+        for (int64_t tb = 0; tb < ntiles; ++tb) {
+            const int64_t h0 = hb[tb * k], h1 = hb[std::min((tb + 1) * k, nfine)];
+            if (h1 == h0) continue;                  // no head in tile tb
+            if (tb >= 1) {
+                pl.fix.push_back((int32_t)tb);
+                pl.fix.push_back((int32_t)last);
+                pl.fix.push_back(out_row(h0 - 1));
+            }
+            last = tb;
         }
-        last = tb;
+        if (b.nnz > 0) {
+            pl.fix.push_back((int32_t)ntiles);
+            pl.fix.push_back((int32_t)last);
+            pl.fix.push_back(out_row(cnt - 1));
+        }
+        pl.fix_at = at;
+        at += pl.nfix();
     }
-    if (b.nnz > 0) {
-        b.fix.push_back((int32_t)ntiles);
-        b.fix.push_back((int32_t)last);
-        b.fix.push_back(out_row(cnt - 1));
-    }
-    // the format's tiles, each k of the launched ones: one entry per tile but
-    // the first that holds a head, and one for the end
-    const int64_t k = b.tile_nnz / b.wtile;
-    b.nfix_fmt = b.nnz > 0 ? 1 : 0;
-    for (int64_t tb = 1; tb < b.ntiles; ++tb)
-        if (hb[tb * k] != hb[std::min((tb + 1) * k, ntiles)]) ++b.nfix_fmt;
     b.empty_rows.clear();
     if (op == FCOO_OP_MTTKRP) {
         const int64_t rows = (int64_t)b.nblk * t->dims[mode];
@@ -504,6 +534,26 @@ void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::v
         for (int64_t i = 0; i < rows; ++i)
             if (!present[i]) b.empty_rows.push_back((int32_t)i);
     }
+}
+
+// the plans' fix-up lists, one after the other (the copy ends before it returns)
+int upload_plans(Built &b, hipStream_t s, int64_t *acct)
+{
+    std::vector<int32_t> all;
+    for (const Plan &pl : b.plan) all.insert(all.end(), pl.fix.begin(), pl.fix.end());
+    int rc = upload(&b.d_fix, all.data(), (int64_t)all.size(), 3, s, acct);
+    if (!rc) FCOO_HIP(hipStreamSynchronize(s));
+    return rc;
+}
+
+// Carries for rows of up to 64 columns (4 bytes for every 16 nonzeros), so that
+// the first operation need not allocate them; wider rows grow them.
+static int first_carries(Built &b, hipStream_t s)
+{
+    int64_t need = 0;
+    for (int R : {16, 32, 64})
+        need = std::max(need, 2 * pick_plan(b, FCOO_F32, R, false, false).ntiles * R);
+    return need > 0 ? ensure_device_floats(&b.d_carry, &b.carry_cap, need, s) : FCOO_OK;
 }
 
 static int build_device(Built &b, hipStream_t s)
@@ -537,7 +587,7 @@ static int build_device(Built &b, hipStream_t s)
     if (b.op == FCOO_OP_MTTKRP)
         if ((rc = upload(&b.d_seg_row, b.seg.data(), b.nseg, 2, s, &acct))) return rc;
     if ((rc = upload(&b.d_perm, b.perm.data(), b.nnz, 0, s, &acct))) return rc;
-    if ((rc = upload(&b.d_fix, b.fix.data(), (int64_t)b.fix.size(), 3, s, &acct))) return rc;
+    if ((rc = upload_plans(b, s, &acct))) return rc;
     if ((rc = upload(&b.d_empty, b.empty_rows.data(), (int64_t)b.empty_rows.size(), 1, s, &acct)))
         return rc;
     FCOO_HIP(hipStreamSynchronize(s));
@@ -647,17 +697,17 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
     // a tile size that the caller chose is launched as it is, and so is the
     // single pass's (its chain table goes by the format's tiles)
     const bool own_tile = (opts && opts->tile_nnz) || single_pass;
-    const int wtile = own_tile ? tile_nnz : work_tile(t->nnz, op, tile_nnz);
     Built &b = t->b[op][mode];
     b.free_device();
     int rc;
     if (on_gpu) {
         try {
-            rc = build_on_device(t, b, mode, op, threadlen, tile_nnz, wtile, nblk, xmode, (hipStream_t)stream);
+            rc = build_on_device(t, b, mode, op, threadlen, tile_nnz, own_tile, nblk, xmode, (hipStream_t)stream);
         } catch (const std::bad_alloc &) {
             rc = fail(FCOO_ENOMEM, "device build (host side)");
         }
         if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
+        if (!rc) rc = first_carries(b, (hipStream_t)stream);
         if (rc) {
             b.free_device();
             b = Built();
@@ -666,7 +716,7 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
         return rc;
     }
     try {
-        rc = build_host(t, b, mode, op, threadlen, tile_nnz, wtile, nblk, xmode);
+        rc = build_host(t, b, mode, op, threadlen, tile_nnz, own_tile, nblk, xmode);
     } catch (const std::bad_alloc &) {
         b = Built();
         return fail(FCOO_ENOMEM, "host build");
@@ -676,6 +726,7 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
     if (host_only) return FCOO_OK;
     rc = build_device(b, (hipStream_t)stream);
     if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
+    if (!rc) rc = first_carries(b, (hipStream_t)stream);
     if (rc) { b.free_device(); return rc; }
     return FCOO_OK;
 }
@@ -691,7 +742,7 @@ int fcoo_info(const fcoo_tensor *t, int mode, int op, fcoo_info_t *info)
     info->nseg = b->nseg;
     info->npart = b->npart;
     info->ntiles = b->ntiles;
-    info->nfix = b->nfix_fmt;
+    info->nfix = b->plan[0].nfix();
     info->nempty = (int64_t)b->empty_rows.size();
     info->bytes_format = b->format_bytes();
     info->bytes_device = b->device_bytes;
@@ -764,15 +815,21 @@ void fcoo_destroy(fcoo_tensor *t)
 // sparse operations: argument checks, then the HIP launchers
 // ---------------------------------------------------------------------------
 
-// XCD blocks: the partial output (nblk x rows x width floats) of this build
-static int prep_blocks(Built *b, TileProblem &p, hipStream_t s)
+// The tiles of a launch and its scratch: the carries, and with XCD blocks the
+// partial output (nblk x rows x width floats) of the build.
+static int prep_tiles(Built *b, TileProblem &p, bool resid, hipStream_t s)
 {
+    p.plan = &pick_plan(*b, p.dtype, p.R, resid, p.kron);
+    int rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * p.plan->ntiles * (int64_t)p.R, s);
+    if (rc) return rc;
+    p.carry = b->d_carry;
     if (b->nblk <= 1) return FCOO_OK;
-    int rc = ensure_device_floats(&b->d_bpart, &b->bpart_cap, (int64_t)b->nblk * b->rows * p.R, s);
+    rc = ensure_device_floats(&b->d_bpart, &b->bpart_cap, (int64_t)b->nblk * b->rows * p.R, s);
     if (rc) return rc;
     p.bpart = b->d_bpart;
     return FCOO_OK;
 }
+
 int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtype, int R, float *M,
                   void *stream)
 {
@@ -791,9 +848,7 @@ int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtyp
     p.dtype = dtype;
     p.R = R;
     p.out = M;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
-    p.carry = b->d_carry;
-    if ((rc = prep_blocks(b, p, s))) return rc;
+    if ((rc = prep_tiles(b, p, false, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     p.ev_before = t->ev_before;
     p.ev_after = t->ev_after;
@@ -823,18 +878,17 @@ int fcoo_spttmc(fcoo_tensor *t, int mode, const void *const *factors, int dtype,
     hipStream_t s = (hipStream_t)stream;
     TileProblem p{};
     p.b = b;
-    p.kron = true;
+    p.kron = b->pmodes.size() > 1;   // (a chain of one matrix is SpMTTKRP)
     for (size_t q = 0; q < b->pmodes.size(); ++q) {
         p.fac[q] = factors[b->pmodes[q]];
         p.kr[q] = ranks[b->pmodes[q]];
+        p.fac_rows[q] = t->dims[b->pmodes[q]];
     }
     p.vals = b->d_val;
     p.dtype = dtype;
     p.R = (int)W;
     p.out = Y;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * W, s))) return rc;
-    p.carry = b->d_carry;
-    if ((rc = prep_blocks(b, p, s))) return rc;
+    if ((rc = prep_tiles(b, p, false, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     p.ev_before = t->ev_before;
     p.ev_after = t->ev_after;
@@ -858,9 +912,7 @@ int fcoo_spttm(fcoo_tensor *t, int mode, const void *U, int dtype, int R, float 
     p.dtype = dtype;
     p.R = R;
     p.out = Y;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
-    p.carry = b->d_carry;
-    if ((rc = prep_blocks(b, p, s))) return rc;
+    if ((rc = prep_tiles(b, p, false, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     p.ev_before = t->ev_before;
     p.ev_after = t->ev_after;
@@ -891,9 +943,7 @@ int fcoo_spmttkrp_values(fcoo_tensor *t, int mode, const float *g, const void *c
     p.dtype = dtype;
     p.R = R;
     p.out = M;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
-    p.carry = b->d_carry;
-    if ((rc = prep_blocks(b, p, s))) return rc;
+    if ((rc = prep_tiles(b, p, false, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     p.ev_before = t->ev_before;
     p.ev_after = t->ev_after;
@@ -920,12 +970,10 @@ int fcoo_resid_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, in
     p.out = G;
     p.own = factors[mode];
     p.inv_nnz = b->nnz ? (float)(1.0 / (double)b->nnz) : 0.f;
-    if ((rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * b->wntiles * (int64_t)R, s))) return rc;
-    p.carry = b->d_carry;
-    if ((rc = prep_blocks(b, p, s))) return rc;
+    if ((rc = prep_tiles(b, p, true, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     if (loss) {
-        if ((rc = ensure_device_doubles(&b->d_partial, &b->partial_cap, b->wntiles + 1, s))) return rc;
+        if ((rc = ensure_device_doubles(&b->d_partial, &b->partial_cap, p.plan->ntiles + 1, s))) return rc;
         p.partial = b->d_partial;
         p.loss = loss;
         p.loss_scale = b->nnz ? 0.5 / (double)b->nnz : 0.0;

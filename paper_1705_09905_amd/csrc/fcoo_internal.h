@@ -28,6 +28,18 @@ void clear_error();
         if (e_ != hipSuccess) return ::fcoo::hip_fail(e_, #call); \
     } while (0)
 
+// A split of a build's nonzeros into tiles of T as launched: which segments
+// are finished across tiles, and with XCD blocks each block's tiles.
+struct Plan {
+    int T = 0;
+    int64_t ntiles = 0;
+    // carry fix-up list: (closing tile b, chain start tile a, output row) per entry
+    std::vector<int32_t> fix;
+    int64_t fix_at = 0;                       // its first entry in d_fix
+    std::vector<int64_t> blk_ts;              // nblk + 1 tile starts: block b's tiles [blk_ts[b], blk_ts[b+1])
+    int64_t nfix() const { return (int64_t)fix.size() / 3; }
+};
+
 // One (op, mode) F-COO build: host arrays (kept for export) and device copies.
 struct Built {
     bool built = false;
@@ -36,23 +48,21 @@ struct Built {
     int op = 0, mode = 0, threadlen = 0, tile_nnz = 0;
     int lane_cols = 0;                        // bfloat16 columns per lane chunk (4, 8; 0: default rule)
     int64_t nnz = 0, nseg = 0, npart = 0, ntiles = 0;
-    // nonzeros per workgroup tile as launched: tile_nnz when the caller chose
-    // it, else the size work_tile() picks (a divisor of the format's tile_nnz,
-    // which info and export go by); fix and blk_ts are of these tiles
-    int wtile = 0;
-    int64_t wntiles = 0;
-    int64_t nfix_fmt = 0;                     // segments finished across the format's tiles (info)
+    // tiles as launched, by descending T; plan[0] is the format's tile_nnz, which
+    // info and export go by, and the only choice of most operations when the
+    // caller gave it (own_tile); see pick_plan
+    std::vector<Plan> plan;
+    bool own_tile = false;
     std::vector<int> imodes, pmodes;
 
     // XCD blocks (SpMTTKRP): the nonzeros are split into nblk groups by ranges
     // of product mode bmode's index (blk_of), each group leading the sort key;
     // a segment is a (block, row) pair written to partial row block * I + row,
-    // and block b's tiles [blk_ts[b], blk_ts[b+1]) run on XCD b
+    // and block b's tiles run on XCD b
     int nblk = 1;
     int bmode = -1;
     int64_t rows = 0;                         // SpMTTKRP: dims[mode] (rows of the result)
     std::vector<int32_t> blk_of;              // dims[bmode]: block of each index
-    std::vector<int64_t> blk_ts;              // nblk + 1 tile starts
 
     // F-COO arrays (Sec. IV-B) and per-segment / per-tile indexing
     std::vector<std::vector<int32_t>> pidx;   // |pmodes| x Z
@@ -63,8 +73,6 @@ struct Built {
     std::vector<int32_t> tile_seg0;           // ntiles (format tiles)
     std::vector<int32_t> perm;                // Z: sorted position -> input position
 
-    // carry fix-up list over the launched tiles: (closing tile b, chain start tile a, output row) per entry
-    std::vector<int32_t> fix;
     std::vector<int32_t> empty_rows;          // MTTKRP rows with no nonzero
 
     // device copies
@@ -75,12 +83,12 @@ struct Built {
     uint32_t *d_sf = nullptr;
     int32_t *d_seg_row = nullptr;             // MTTKRP only
     int32_t *d_perm = nullptr;
-    int32_t *d_fix = nullptr;
+    int32_t *d_fix = nullptr;                 // the plans' fix-up lists, one after the other
     int32_t *d_empty = nullptr;
     int64_t device_bytes = 0;
 
     // scratch owned by this build, grown on demand
-    float *d_carry = nullptr;                 // 2 x wntiles x R floats
+    float *d_carry = nullptr;                 // 2 x tiles x R floats
     int64_t carry_cap = 0;                    // floats
     float *d_gperm = nullptr;                 // Z floats (values in stored order)
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
@@ -100,8 +108,7 @@ struct Built {
     unsigned long long sp_tickets = 0;        // tickets taken by earlier launches
     uint32_t sp_epoch = 0;                    // tag of the last launch
 
-    int64_t nfix() const { return (int64_t)fix.size() / 3; }
-    int64_t max_block_tiles() const;
+    void set_plans(int fmt_tile, bool own);
     int64_t format_bytes() const;
     void free_device();
 };
@@ -146,11 +153,11 @@ namespace fcoo {
 int ensure_device_floats(float **p, int64_t *cap, int64_t need, hipStream_t s);
 int ensure_device_doubles(double **p, int64_t *cap, int64_t need, hipStream_t s);
 int upload_coo(fcoo_tensor *t, hipStream_t s);
+int upload_plans(Built &b, hipStream_t s, int64_t *acct);
 int upload_i32(int32_t **dst, const std::vector<int32_t> &v, int64_t pad, hipStream_t s, int64_t *acct);
-// nonzeros per launched tile of a build whose caller left tile_nnz to the library
-int work_tile(int64_t nnz, int op, int fmt_tile);
-// carry fix-up chains and empty output rows from the per-tile head counts
-// (heads_before[t] = heads before nonzero t * wtile, t = 0 .. wntiles) and b.seg
+// the plans' carry fix-up chains and the empty output rows from the head counts
+// of the shortest tiles (heads_before[t] = heads before nonzero t * T, t = 0 ..
+// ntiles, of the last plan) and b.seg
 void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::vector<int64_t> &heads_before);
 // the F-COO build of one (op, mode) on the GPU (same arrays as the host build)
 // Device primitives of the GPU build (fcoo_sort.hip).  sort_pairs_u64: stable
@@ -164,11 +171,11 @@ int64_t scan_work_ints(int64_t n);
 int sort_pairs_u64(uint64_t *k0, uint64_t *k1, uint32_t *v0, uint32_t *v1, int64_t n, int end_bit,
                    int32_t *work, hipStream_t s, int *passes);
 int scan_i32(const int32_t *in, int32_t *out, int64_t n, bool inclusive, int32_t *work, hipStream_t s);
-int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, int wtile, int nblk,
+int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int threadlen, int tile_nnz, bool own_tile, int nblk,
                     int xmode, hipStream_t s);
 // XCD blocks of a SpMTTKRP build (nblk 0 / 1: none), split by ranges of product
 // mode xmode (-1: the product mode with the most rows); needs b.op, b.mode,
-// b.pmodes, b.wtile
+// b.pmodes, the plans' T
 int setup_blocks(const fcoo_tensor *t, Built &b, int nblk, int xmode);
 // the single-pass chain table of a finished build (fix list -> per-tile chain starts) and its counters
 int setup_single_pass(Built &b, hipStream_t s);
@@ -180,16 +187,17 @@ Built *get_built(fcoo_tensor *t, int mode, int op, bool need_device, int *rc);
 // launchers implemented in the .hip files (return FCOO_OK or an error code)
 struct TileProblem {
     const Built *b;
+    const Plan *plan;                // set by prep_tiles, with the scratch it needs
     const void *fac[kMaxOrder];      // per product mode q: factor base pointer
     const float *vals;               // values in stored order (b->d_val or a permuted copy)
     int dtype;
     int R;
     float *out;                      // output rows, leading dimension R
-    float *carry;                    // 2 x wntiles x R
+    float *carry;                    // 2 x the plan's tiles x R
     // fused MSE residual (resid_spmttkrp)
     const void *own = nullptr;       // factor of the index mode (dims[mode] x R)
     float inv_nnz = 0.f;
-    double *partial = nullptr;       // per-tile partial losses (wntiles) or null
+    double *partial = nullptr;       // per-tile partial losses or null
     double *loss = nullptr;          // with partial: receives loss_scale times their sum
     double loss_scale = 0.0;
     hipEvent_t ev_before = nullptr;  // recorded around the tile kernel when set
@@ -198,12 +206,20 @@ struct TileProblem {
     // SpTTMc: Kronecker rows; R is then the output width prod kr[q]
     bool kron = false;
     int kr[kMaxOrder] = {};          // per product mode q: columns of its factor
+    int64_t fac_rows[kMaxOrder] = {};   // and its rows
     // single pass (set by prep_single_pass; sp_words null: carries + fix-up)
     uint64_t *sp_words = nullptr;
     uint32_t sp_epoch = 0;
 };
 // single-pass words of a build for a launch of width R (no-op for other builds)
 int prep_single_pass(Built *b, TileProblem &p, hipStream_t s);
+// how rows of R columns are spread over lanes: columns per lane, lanes per
+// nonzero (at most 16), bfloat16 in 4-column chunks
+struct LaneShape { int vw, lpn; bool half; };
+LaneShape lane_shape(const Built &b, int dtype, int R, bool resid);
+// the tiles a launch over rows of width R takes
+const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron);
+int launch_ttmc(const TileProblem &p, float *out, hipStream_t s);
 int launch_segmented(const TileProblem &p, hipStream_t s, bool resid);
 int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s);
 int launch_model(const fcoo_tensor *t, const void *const *factors, int dtype, int R, float *xhat,

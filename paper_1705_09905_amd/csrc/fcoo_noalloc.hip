@@ -18,9 +18,10 @@
 
 #include "fcoo_internal.h"
 
-// Twice the documented bytes: the limit goes by the format's tiles, a default
-// build launches tiles of half that size and more (work_tile), and below 1M
-// nonzeros, where they are smaller still, all carries together are below 2 MB.
+// Twice the documented bytes: the limit goes by the format's tiles, and a default
+// build launches tiles of half that size, or, up to 64M nonzeros with rows of 32
+// columns at most (16 MB of carries) and below 1M nonzeros (2 MB), of a quarter
+// or an eighth (pick_plan).
 static __device__ __align__(256) float scratch[2 * FCOO_NOALLOC_SCRATCH_BYTES / sizeof(float)];
 
 namespace fcoo {
@@ -70,7 +71,8 @@ extern "C" int fcoo_spmttkrp_noalloc(fcoo_tensor *t, int mode, const void *const
     if (!M) return fail(FCOO_EINVAL, "M is NULL");
     // scratch layout: carries (2 x ntiles x R), then the blocked build's partial rows
     const int64_t nfmt = align64(2 * b->ntiles * (int64_t)R);
-    const int64_t ncarry = align64(2 * b->wntiles * (int64_t)R);
+    const Plan &plan = pick_plan(*b, dtype, R, false, false);
+    const int64_t ncarry = align64(2 * plan.ntiles * (int64_t)R);
     const int64_t npart = b->nblk > 1 ? (int64_t)b->nblk * b->rows * R : 0;
     if (nfmt + npart > kScratchFloats || ncarry + npart > 2 * kScratchFloats)
         return fail(FCOO_ERANGE,
@@ -87,6 +89,7 @@ extern "C" int fcoo_spmttkrp_noalloc(fcoo_tensor *t, int mode, const void *const
     p.dtype = dtype;
     p.R = R;
     p.out = M;
+    p.plan = &plan;
     p.carry = base;
     p.bpart = npart ? base + ncarry : nullptr;
     p.ev_before = t->ev_before;

@@ -1,6 +1,8 @@
 // Launch plans of the segmented F-COO operations, the carry fix-up, empty
 // rows, value permutation, deterministic float64 reductions and the CP
 // model at the nonzeros.
+#include <algorithm>
+
 #include "fcoo_internal.h"
 #include "fcoo_seg_dispatch.h"
 
@@ -65,14 +67,18 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs A)
         const int slot = tid / R, c = tid - (tid / R) * R;
         float s = 0.f;
         if (slot < slots) {
-            // long chains (a slice over hundreds of tiles): kChain loads in
-            // flight, then the adds in tile order
+            // long chains (a slice over hundreds of tiles): kChain loads in flight
             for (int t = ta + 1 + slot; t < tb; t += kChain * slots) {
                 float x[kChain];
 #pragma unroll
                 for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? A.ca[(int64_t)(t + u * slots) * R + c] : 0.f;
+                // (in pairs: a wide row has one slot, and a chain of a thousand
+                // tiles would be as many roundings in a row)
 #pragma unroll
-                for (int u = 0; u < kChain; ++u) s += x[u];
+                for (int o = kChain / 2; o >= 1; o >>= 1)
+#pragma unroll
+                    for (int u = 0; u < o; ++u) x[u] += x[u + o];
+                s += x[0];
             }
         }
         red[tid] = s;
@@ -204,11 +210,40 @@ static int grid_for(int64_t work, int64_t per_block, int cap = 65535 * 8)
     return (int)g;
 }
 
+LaneShape lane_shape(const Built &b, int dtype, int R, bool resid)
+{
+    // bfloat16 in 4-column (8-byte) lane chunks: twice the rows per gather
+    // batch at 4 waves per SIMD, against 8-column chunks at 3 waves.  The
+    // build's lane_cols picks (fcoo_autotune times both); by default 4
+    // columns with exactly two product modes (with three, the batch per mode
+    // gets short and 8-column chunks won on the order-4 Zipf tensor)
+    const int np = (int)b.pmodes.size();
+    const bool half_ok = dtype == FCOO_BF16 && !resid && np <= 3 && R >= 4 && R <= 64;
+    LaneShape sh;
+    sh.half = half_ok && (b.lane_cols == 4 || R < 8 || (b.lane_cols == 0 && np == 2 && b.op == FCOO_OP_MTTKRP));
+    // columns per lane: the type's vector, or the widest piece a shorter row
+    // holds.  A row need not be a multiple of it: its last piece ends at
+    // column R and overlaps the one before.  (Such rows once ran one column
+    // per lane, 64 lanes a nonzero: SpMTTKRP of 4M nonzeros, order 4, R = 25
+    // took 323 us and takes 100; SpTTM of 300k, bfloat16 R = 10, 321 and 16)
+    sh.vw = (dtype == FCOO_F32 || sh.half) ? 4 : 8;
+    while (sh.vw > R) sh.vw >>= 1;
+    sh.lpn = next_pow2((R + sh.vw - 1) / sh.vw);
+    if (sh.lpn > 16) sh.lpn = 16;
+    return sh;
+}
+
 int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
 {
     const Built &b = *p.b;
+    const Plan &pl = *p.plan;
     const int R = p.R;
-    if (b.nnz > 0) {
+    if (b.nnz > 0 && p.kron) {
+        if (p.ev_before) FCOO_HIP(hipEventRecord(p.ev_before, s));
+        const int rc = launch_ttmc(p, b.nblk > 1 ? p.bpart : p.out, s);
+        if (rc) return rc;
+        if (p.ev_after) FCOO_HIP(hipEventRecord(p.ev_after, s));
+    } else if (b.nnz > 0) {
         SegLaunch L{};
         dev::SegArgs &a = L.args;
         const int np = (int)b.pmodes.size();
@@ -221,50 +256,22 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         a.seg_row = b.op == FCOO_OP_MTTKRP ? b.d_seg_row : nullptr;
         a.out = b.nblk > 1 ? p.bpart : p.out;
         a.carry_a = p.carry;
-        a.carry_b = p.carry + b.wntiles * (int64_t)R;
+        a.carry_b = p.carry + pl.ntiles * (int64_t)R;
         a.own = p.own;
         a.partial = p.partial;
         a.nnz = b.nnz;
-        a.ntiles = b.wntiles;
+        a.ntiles = pl.ntiles;
         a.R = R;
         a.np = np;
-        a.tile_nnz = b.wtile;
+        a.tile_nnz = pl.T;
         a.nseg = (int)b.nseg;
         a.inv_nnz = p.inv_nnz;
-        // bfloat16 in 4-column (8-byte) lane chunks: twice the rows per gather
-        // batch at 4 waves per SIMD, against 8-column chunks at 3 waves.  The
-        // build's lane_cols picks (fcoo_autotune times both); by default 4
-        // columns with exactly two product modes (with three, the batch per mode
-        // gets short and 8-column chunks won on the order-4 Zipf tensor)
-        const bool half_ok = p.dtype == FCOO_BF16 && !resid && !p.kron && np <= 3 && R >= 4 && R <= 64;
-        L.half = half_ok && (b.lane_cols == 4 || R < 8 || (b.lane_cols == 0 && np == 2 && b.op == FCOO_OP_MTTKRP));
-        // columns per lane: the type's vector, or the widest piece a shorter row
-        // holds.  A row need not be a multiple of it: its last piece ends at
-        // column R and overlaps the one before.  (Such rows once ran one column
-        // per lane, 64 lanes a nonzero: SpMTTKRP of 4M nonzeros, order 4, R = 25
-        // took 323 us and takes 100; SpTTM of 300k, bfloat16 R = 10, 321 and 16)
-        int V = (p.dtype == FCOO_F32 || L.half) ? 4 : 8;
-        if (p.kron) {
-            if (p.kr[np - 1] % V) V = 1;              // a lane's columns lie in one row piece of the last factor
-        } else {
-            while (V > R) V >>= 1;
-        }
-        L.vw = V;
-        // SpTTMc: KB columns of the second-to-last mode per lane when they divide it
-        const int KBv = p.dtype == FCOO_F32 ? 4 : 2;
-        L.kb = (p.kron && V > 1 && np >= 2 && p.kr[np - 2] % KBv == 0) ? KBv : 1;
-        const int AW = V * L.kb;
-        const int lanes = (R + AW - 1) / AW;          // lanes per nonzero over the whole row
-        int lpn = next_pow2(lanes);
-        if (p.kron) {
-            for (int q = 0; q < np; ++q) a.kr[q] = p.kr[q];
-            if (lpn < 4) lpn = 4;
-            if (lpn > 64 || V == 1) lpn = 64;
-        } else if (lpn > 16) {
-            lpn = 16;
-        }
-        L.lpn = lpn;
-        const int nrt = (lanes + lpn - 1) / lpn;
+        const LaneShape sh = lane_shape(b, p.dtype, R, resid);
+        L.vw = sh.vw;
+        L.half = sh.half;
+        L.lpn = sh.lpn;
+        const int rt = sh.lpn * sh.vw;
+        const int nrt = (R + rt - 1) / rt;
         const int most = p.dtype == FCOO_BF16 && R % 8 == 0 ? 128 : 64;
         if (resid && R > most)
             return fail(FCOO_EUNSUPPORTED, "fused residual needs R <= %d for this dtype (R = %d)", most, R);
@@ -281,18 +288,18 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
             a.sp_epoch = p.sp_epoch;
             a.sp_tail_from = b.sp_tail_from;
         }
-        int64_t gx = b.wntiles;
+        int64_t gx = pl.ntiles;
         if (b.nblk > 1) {
-            for (int k = 0; k <= b.nblk; ++k) a.blk_ts[k] = b.blk_ts[k];
-            gx = (int64_t)kXcds * b.max_block_tiles();   // workgroup w: XCD w % 8, its block's tiles
-            if (gx < 1) gx = 1;
+            int64_t most_tiles = 1;
+            for (int k = 0; k <= b.nblk; ++k) a.blk_ts[k] = pl.blk_ts[k];
+            for (int k = 0; k < b.nblk; ++k) most_tiles = std::max(most_tiles, pl.blk_ts[k + 1] - pl.blk_ts[k]);
+            gx = (int64_t)kXcds * most_tiles;            // workgroup w: XCD w % 8, its block's tiles
         }
         L.grid = dim3((unsigned)gx, (unsigned)nrt, 1);
         hipError_t e;
         if (p.ev_before) FCOO_HIP(hipEventRecord(p.ev_before, s));
-        const bool narrow = !p.kron && !L.half && V < (p.dtype == FCOO_F32 ? 4 : 8);
-        if (p.kron) e = p.dtype == FCOO_F32 ? seg_launch_f32_kron(L, s) : seg_launch_bf16_kron(L, s);
-        else if (narrow) e = p.dtype == FCOO_F32 ? seg_launch_f32_narrow(L, resid, s) : seg_launch_bf16_narrow(L, resid, s);
+        const bool narrow = !L.half && sh.vw < (p.dtype == FCOO_F32 ? 4 : 8);
+        if (narrow) e = p.dtype == FCOO_F32 ? seg_launch_f32_narrow(L, resid, s) : seg_launch_bf16_narrow(L, resid, s);
         else if (p.dtype == FCOO_F32) e = resid ? seg_launch_f32_resid(L, s) : seg_launch_f32(L, s);
         else if (L.half) e = seg_launch_bf16_half(L, s);
         else e = resid ? seg_launch_bf16_resid(L, s) : seg_launch_bf16(L, s);
@@ -302,18 +309,18 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         if (p.ev_after) FCOO_HIP(hipEventRecord(p.ev_after, s));
     }
     dev::FinishArgs f{};
-    f.nfix = b.nnz > 0 && !p.sp_words ? (int)b.nfix() : 0;
+    f.nfix = b.nnz > 0 && !p.sp_words ? (int)pl.nfix() : 0;
     f.nempty = (int64_t)b.empty_rows.size();
     f.zblk = f.nempty > 0 ? grid_for(f.nempty * R, dev::kZeroPer, 1 << 20) : 0;
     if (f.nfix + f.zblk > 0 || p.loss) {
-        f.fix = b.d_fix;
+        f.fix = b.d_fix + 3 * pl.fix_at;
         f.ca = p.carry;
-        f.cb = p.carry + b.wntiles * (int64_t)R;
-        f.ntiles = b.wntiles;
+        f.cb = p.carry + pl.ntiles * (int64_t)R;
+        f.ntiles = pl.ntiles;
         f.empty = b.d_empty;
         f.out = b.nblk > 1 ? p.bpart : p.out;
         f.partial = p.partial;
-        f.npartial = b.nnz > 0 ? b.wntiles : 0;
+        f.npartial = b.nnz > 0 ? pl.ntiles : 0;
         f.scale = p.loss_scale;
         f.loss = p.loss;
         f.R = R;

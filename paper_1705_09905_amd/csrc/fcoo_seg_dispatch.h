@@ -10,10 +10,9 @@ namespace fcoo {
 struct SegLaunch {
     dev::SegArgs args;
     int vw;          // columns per lane: 8 (bfloat16), 4, 2 or 1
-    int lpn;         // lanes per nonzero: 1, 2, 4, 8, 16 (SpTTMc: 4 .. 64)
+    int lpn;         // lanes per nonzero: 1, 2, 4, 8 or 16
     int npt;         // product modes as a template value: 1, 2, 3, or 0 (runtime count)
     bool rowmap;     // output row = seg_row[segment] (SpMTTKRP) or the segment ordinal (SpTTM)
-    int kb;          // SpTTMc: column blocks per lane (1, or KronBlock<FT>::KB)
     bool half;       // bfloat16 in 4-column (8-byte) lane chunks, R <= 64
     dim3 grid;
 };
@@ -22,14 +21,6 @@ template <typename FT, int VW, int LPN, int NP, bool RESID, bool ROWMAP>
 static hipError_t seg_go(const SegLaunch &L, hipStream_t s)
 {
     hipLaunchKernelGGL((dev::seg_tile_kernel<FT, VW, LPN, NP, RESID, ROWMAP>), L.grid, dim3(256), 0, s,
-                       L.args);
-    return hipGetLastError();
-}
-
-template <typename FT, int VW, int LPN, int NP, int KB = 1>
-static hipError_t seg_go_k(const SegLaunch &L, hipStream_t s)
-{
-    hipLaunchKernelGGL((dev::seg_tile_kernel<FT, VW, LPN, NP, false, true, true, KB>), L.grid, dim3(256), 0, s,
                        L.args);
     return hipGetLastError();
 }
@@ -103,44 +94,6 @@ static hipError_t seg_dispatch_half(const SegLaunch &L, hipStream_t s)
     }
 }
 
-// SpTTMc: Kronecker rows (generic path), output row = seg_row[segment].
-// Lanes per nonzero: 4 .. 64 (vector) or 64 (scalar); product modes 2, 3 or
-// a runtime count.
-template <typename FT, int VW, int LPN, int KB>
-static hipError_t seg_np_kron(const SegLaunch &L, hipStream_t s)
-{
-    switch (L.npt) {
-        case 2: return seg_go_k<FT, VW, LPN, 2, KB>(L, s);
-        case 3: return seg_go_k<FT, VW, LPN, 3, KB>(L, s);
-        default: return seg_go_k<FT, VW, LPN, 0, KB>(L, s);
-    }
-}
-
-// column blocks per lane with SpTTMc: 4 (float32) / 2 (bfloat16) elements of
-// the second-to-last product mode, or 1
-template <typename FT> struct KronBlock { static constexpr int KB = sizeof(FT) == 4 ? 4 : 2; };
-
-template <typename FT, int KB>
-static hipError_t seg_lpn_kron(const SegLaunch &L, hipStream_t s)
-{
-    constexpr int V = dev::Elem<FT>::VEC;
-    switch (L.lpn) {
-        case 4: return seg_np_kron<FT, V, 4, KB>(L, s);
-        case 8: return seg_np_kron<FT, V, 8, KB>(L, s);
-        case 16: return seg_np_kron<FT, V, 16, KB>(L, s);
-        case 32: return seg_np_kron<FT, V, 32, KB>(L, s);
-        default: return seg_np_kron<FT, V, 64, KB>(L, s);
-    }
-}
-
-template <typename FT>
-static hipError_t seg_dispatch_kron(const SegLaunch &L, hipStream_t s)
-{
-    if (L.vw == 1) return seg_go_k<FT, 1, 64, 0>(L, s);
-    if (L.kb > 1) return seg_lpn_kron<FT, KronBlock<FT>::KB>(L, s);
-    return seg_lpn_kron<FT, 1>(L, s);
-}
-
 hipError_t seg_launch_f32(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_half(const SegLaunch &L, hipStream_t s);
@@ -148,7 +101,5 @@ hipError_t seg_launch_f32_resid(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_resid(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_f32_narrow(const SegLaunch &L, bool resid, hipStream_t s);
 hipError_t seg_launch_bf16_narrow(const SegLaunch &L, bool resid, hipStream_t s);
-hipError_t seg_launch_f32_kron(const SegLaunch &L, hipStream_t s);
-hipError_t seg_launch_bf16_kron(const SegLaunch &L, hipStream_t s);
 
 }  // namespace fcoo

@@ -33,13 +33,6 @@
 //   f = fX | fY,  a = fX ? aX : aX + aY,  b = fY ? bY : bX + aY,
 // and the segment closed at Y's first start is complete (started inside the
 // combined range) iff fX, with value bX + aY.
-//
-// SpTTMc (Eq. 4, Table I third row) uses the SpMTTKRP encoding of its mode
-// and the same scan; only the per-nonzero product changes: output column c
-// of a row is a digit tuple (p_1, .., p_k) over the product modes (the last
-// runs fastest) and takes val * U_1(i_1, p_1) * .. * U_k(i_k, p_k).  A lane
-// owns VW consecutive columns inside one block of the last mode, so it
-// gathers one element of every other mode's row and VW of the last one.
 #pragma once
 
 #include "fcoo_device.h"
@@ -68,7 +61,6 @@ struct SegArgs {
     int tile_nnz;
     int nseg;                        // number of segments
     float inv_nnz;                   // RESID: 1 / Z
-    int kr[kMaxNP];                  // KRON: columns of each product mode's factor (R = their product)
     // XCD blocks: workgroup w runs tile blk_ts[w % 8] + w / 8 of block w % 8
     // (none past blk_ts[w % 8 + 1]); output rows are block * rows_own + row
     int64_t blk_ts[kXcdBlocks + 1];
@@ -287,13 +279,13 @@ __device__ __forceinline__ void select_raw(bool take_a, const Raw<FT, VW> &a, co
 // batch, except the fused residual form, which runs 4 with a quarter batch
 // (it holds no repeated row; a few registers spill); the one-lane residual
 // form is left unconstrained.
-template <typename FT, int VW, int LPN, int NP, bool RESID, bool KRON>
+template <typename FT, int VW, int LPN, int NP, bool RESID>
 struct TileShape {
     static constexpr bool F32PLAIN = sizeof(FT) == 4 && NP >= 1 && (!RESID || LPN > 1);
     // float32 SpMTTKRP (two or more product modes): 3 waves with a double batch
-    static constexpr bool F32MULTI = F32PLAIN && !RESID && !KRON && NP >= 2;
-    static constexpr bool B16HALF = sizeof(FT) == 2 && VW == 4 && NP >= 1 && !RESID && !KRON;
-    static constexpr bool B16ONE = sizeof(FT) == 2 && NP == 1 && !RESID && !KRON;
+    static constexpr bool F32MULTI = F32PLAIN && !RESID && NP >= 2;
+    static constexpr bool B16HALF = sizeof(FT) == 2 && VW == 4 && NP >= 1 && !RESID;
+    static constexpr bool B16ONE = sizeof(FT) == 2 && NP == 1 && !RESID;
     static constexpr bool B16RES = sizeof(FT) == 2 && RESID && NP >= 2;
     static constexpr int waves = F32MULTI ? 3 : (F32PLAIN || B16HALF || B16RES) ? 4 : B16ONE ? 3
                                : (((LPN > 1 || !RESID) && !(sizeof(FT) == 2 && NP == 1)) ? 3 : 1);
@@ -302,24 +294,20 @@ struct TileShape {
                                     : (F32PLAIN || B16ONE || (sizeof(FT) == 2 && NP >= 2)) ? 32 : 64;
 };
 
-template <typename FT, int VW, int LPN, int NP, bool RESID, bool ROWMAP, bool KRON = false, int KB = 1>
-__global__ __launch_bounds__(256, (TileShape<FT, VW, LPN, NP, RESID, KRON>::waves))
+template <typename FT, int VW, int LPN, int NP, bool RESID, bool ROWMAP>
+__global__ __launch_bounds__(256, (TileShape<FT, VW, LPN, NP, RESID>::waves))
 void seg_tile_kernel(SegArgs A)
 {
     constexpr int Q = 64 / LPN;                       // lane groups per wave
     constexpr int NPM = NP > 0 ? NP : kMaxNP;         // product modes held per step
     constexpr int RAWREGS = (int)(sizeof(Raw<FT, VW>) / 4);
     // gathers in flight per lane: the batch that fits the wave count above
-    constexpr int CHB = NP > 0 ? pow2_floor(TileShape<FT, VW, LPN, NP, RESID, KRON>::batch_regs / (NPM * RAWREGS)) : 2;
+    constexpr int CHB = NP > 0 ? pow2_floor(TileShape<FT, VW, LPN, NP, RESID>::batch_regs / (NPM * RAWREGS)) : 2;
     constexpr int CH0 = CHB < 16 ? CHB : 16;          // (pieces of 1 or 2 registers: the loop body stays small)
     constexpr int CL = CH0 > LPN ? CH0 : LPN;         // steps per chunk (stream granule)
     constexpr int CH = CH0 < CL ? CH0 : CL;           // steps per gather batch
     constexpr int U = CL / LPN;                       // stream entries per lane per chunk
-    // KRON with KB > 1: a lane owns KB blocks of VW columns, one per element of
-    // a KB-wide piece of the second-to-last product mode's row
-    static_assert(KB == 1 || (KRON && !RESID), "column blocks are for SpTTMc");
-    constexpr int AW = VW * KB;                       // accumulated columns per lane
-    constexpr int RT = LPN * AW;                      // columns of this rank tile
+    constexpr int RT = LPN * VW;                      // columns of this rank tile
 
     __shared__ int s_f[4];
     // the four waves' boundary partials (a: rows 0-3, b: rows 4-7); the single
@@ -365,7 +353,7 @@ void seg_tile_kernel(SegArgs A)
     int col, colc;
     bool cval;
     int dup = 0;                                      // leading columns the lane before holds too
-    if constexpr (KB == 1) {
+    {
         const int c0 = ry * RT + j * VW;
         cval = c0 < A.R;
         // the last piece of a row is moved down to end at column R: its loads
@@ -374,15 +362,6 @@ void seg_tile_kernel(SegArgs A)
         col = c0 + VW <= A.R ? c0 : A.R - VW;
         colc = cval ? col : 0;                        // lanes past R read column 0, never store
         dup = cval ? c0 - col : 0;
-    } else {
-        // lane gl: block gl % nb2 of the last mode, block (gl / nb2) % nb1 of
-        // the one before, then the earlier modes' combined index
-        const int gl = ry * LPN + j;
-        const int nb2 = A.kr[np - 1] / VW, nb1 = A.kr[np - 2] / KB;
-        cval = gl < A.R / AW;
-        const int g2 = cval ? gl : 0;
-        col = ((g2 / (nb2 * nb1)) * A.kr[np - 2] + ((g2 / nb2) % nb1) * KB) * A.kr[np - 1] + (g2 % nb2) * VW;
-        colc = col;
     }
     const int R = A.R;
     // row bytes fit 32 bits (R <= 256), so a gather address is one 32 x 32 -> 64
@@ -400,52 +379,18 @@ void seg_tile_kernel(SegArgs A)
         for (int k = 0; k < VW - 1; ++k) o[k] = k < dup ? 0.f : o[k];
     };
     const char *fb[NPM];
-    uint32_t R4k[NPM];                                // KRON: row bytes of each product mode
-    if constexpr (KRON) {
-        // digits of this lane's first column, last product mode fastest (with
-        // column blocks, the second-to-last digit starts this lane's KB-piece)
-        int rem = colc;
 #pragma unroll
-        for (int qq = NPM - 1; qq >= 0; --qq) {
-            if (qq < np) {
-                const int d = rem % A.kr[qq];
-                rem /= A.kr[qq];
-                fb[qq] = reinterpret_cast<const char *>(A.fac[qq]) + (size_t)d * sizeof(FT);
-                R4k[qq] = (uint32_t)A.kr[qq] * (uint32_t)sizeof(FT);
-            } else {
-                fb[qq] = nullptr;
-                R4k[qq] = 0;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int qq = 0; qq < NPM; ++qq) {
-            fb[qq] = reinterpret_cast<const char *>(A.fac[qq]) + (size_t)colc * sizeof(FT);
-            R4k[qq] = R4;
-        }
-    }
+    for (int qq = 0; qq < NPM; ++qq) fb[qq] = reinterpret_cast<const char *>(A.fac[qq]) + (size_t)colc * sizeof(FT);
 
-    // store the lane's AW columns of one output (or carry) row
-    const int kstride = KB > 1 ? A.kr[np - 1] : 0;   // column distance between a lane's blocks
-    auto store_acc = [&](float *rowp, const float (&v)[AW]) {
-        if constexpr (KB == 1 && !ROWMAP && !KRON) {
-            store_row_stream<VW>(rowp + col, v);      // SpTTM: one row per fibre, never re-read
-        } else if constexpr (KB == 1) {
-            store_row<VW>(rowp + col, v);
-        } else {
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                float tv[VW];
-#pragma unroll
-                for (int k = 0; k < VW; ++k) tv[k] = v[kb * VW + k];
-                store_row<VW>(rowp + col + kb * kstride, tv);
-            }
-        }
+    // store the lane's VW columns of one output (or carry) row
+    auto store_acc = [&](float *rowp, const float (&v)[VW]) {
+        if constexpr (!ROWMAP) store_row_stream<VW>(rowp + col, v);   // SpTTM: one row per fibre, never re-read
+        else store_row<VW>(rowp + col, v);
     };
 
     // first chunk of the stream and the tile's segment ordinal: issued first
     // fast path: 16-byte stream vectors in super-chunks; generic path: chunks
-    constexpr bool FAST = (NP > 0) && (VW > 1) && !KRON;
+    constexpr bool FAST = (NP > 0) && (VW > 1);
     constexpr int CLF = CH0;                                           // gather batch (register budget)
     constexpr int K = FAST ? ((CLF + 4 * LPN - 1) / (4 * LPN)) : 1;  // vectors per lane per array
     constexpr int SC = FAST ? 4 * LPN * K : CL;                        // steps per super-chunk
@@ -476,7 +421,7 @@ void seg_tile_kernel(SegArgs A)
 
     // ---- 2. walk the run, one chunk at a time: gather this chunk's rows,
     //         then put the next chunk's stream in flight, then reduce
-    float acc[AW], pre[AW];
+    float acc[VW], pre[VW];
     zero(acc);
     zero(pre);
     int have = 0;
@@ -510,7 +455,7 @@ void seg_tile_kernel(SegArgs A)
             }
             if (!have) {
 #pragma unroll
-                for (int k = 0; k < AW; ++k) pre[k] = acc[k];
+                for (int k = 0; k < VW; ++k) pre[k] = acc[k];
             }
             have = 1;
             zero(acc);
@@ -527,7 +472,7 @@ void seg_tile_kernel(SegArgs A)
             }
         }
     };
-    auto step = [&](const float (&h)[AW], float v, uint64_t hm, int st, int n) {
+    auto step = [&](const float (&h)[VW], float v, uint64_t hm, int st, int n) {
         on_head(hm, st);
         if (st < n) {
             if constexpr (RESID) {
@@ -543,7 +488,7 @@ void seg_tile_kernel(SegArgs A)
                 if (j == 0) lsum += r * r;
             } else {
 #pragma unroll
-                for (int k = 0; k < AW; ++k) acc[k] += v * h[k];
+                for (int k = 0; k < VW; ++k) acc[k] += v * h[k];
             }
         }
     };
@@ -658,80 +603,27 @@ void seg_tile_kernel(SegArgs A)
             static_for<CL / CH>([&](auto sbc) {
                 constexpr int S0 = decltype(sbc)::value * CH;
                 Raw<FT, VW> rows[CH][NPM];
-                Raw<FT, 1> ks[CH][NPM];                 // KRON: one element of each non-last mode
-                Raw<FT, KB> kp[CH];                     // KRON, KB > 1: KB elements of the second-to-last mode
                 static_for<CH>([&](auto jjc) {
                     constexpr int ST = S0 + decltype(jjc)::value;
 #pragma unroll
                     for (int qq = 0; qq < NPM; ++qq) {
                         const int idx = bcast_imm<LPN, ST % LPN>(cur.idx[ST / LPN][qq]);
-                        const FT *p = reinterpret_cast<const FT *>(fb[qq] + (uint64_t)(uint32_t)idx * (uint64_t)R4k[qq]);
-                        if constexpr (KRON && KB > 1) {
-                            if (qq < np - 2) load_raw<FT, 1>(p, ks[ST - S0][qq]);
-                            else if (qq == np - 2) load_raw<FT, KB>(p, kp[ST - S0]);
-                            else if (qq == np - 1) load_raw<FT, VW>(p, rows[ST - S0][0]);
-                        } else if constexpr (KRON) {
-                            if (qq < np - 1) load_raw<FT, 1>(p, ks[ST - S0][qq]);
-                            else if (qq == np - 1) load_raw<FT, VW>(p, rows[ST - S0][0]);
-                        } else {
-                            if (qq < np) load_raw<FT, VW>(p, rows[ST - S0][qq]);
-                            else set_one<FT, VW>(rows[ST - S0][qq]);
-                        }
+                        const FT *p = reinterpret_cast<const FT *>(fb[qq] + (uint64_t)(uint32_t)idx * (uint64_t)R4);
+                        if (qq < np) load_raw<FT, VW>(p, rows[ST - S0][qq]);
+                        else set_one<FT, VW>(rows[ST - S0][qq]);
                     }
                 });
                 static_for<CH>([&](auto jjc) {
                     constexpr int ST = S0 + decltype(jjc)::value;
                     const float v = bcast_imm_f<LPN, ST % LPN>(cur.v[ST / LPN]);
-                    float h[AW];
-                    if constexpr (KRON && KB > 1) {
-                        (void)h;
-                        float u2[VW], u1[KB];
-                        to_float<FT, VW>(rows[ST - S0][0], u2);
-                        to_float<FT, KB>(kp[ST - S0], u1);
-                        float m = 1.f;
+                    float h[VW];
+                    to_float<FT, VW>(rows[ST - S0][0], h);
 #pragma unroll
-                        for (int qq = 0; qq < NPM - 2; ++qq) {
-                            if (qq < np - 2) {
-                                float x[1];
-                                to_float<FT, 1>(ks[ST - S0][qq], x);
-                                m *= x[0];
-                            }
-                        }
-                        // column (kb, k) gains (v m u1[kb]) u2[k]: one multiply-add per column
-                        on_head(hm, ST);
-                        if (ST < n) {
-                            const float vm = v * m;
+                    for (int qq = 1; qq < NPM; ++qq) {
+                        float x[VW];
+                        to_float<FT, VW>(rows[ST - S0][qq], x);
 #pragma unroll
-                            for (int kb = 0; kb < KB; ++kb) {
-                                const float c1 = vm * u1[kb];
-#pragma unroll
-                                for (int k = 0; k < VW; ++k) acc[kb * VW + k] += c1 * u2[k];
-                            }
-                        }
-                        return;
-                    } else {
-                        to_float<FT, VW>(rows[ST - S0][0], h);
-                    }
-                    if constexpr (KRON) {
-                        float m = 1.f;
-#pragma unroll
-                        for (int qq = 0; qq < NPM - 1; ++qq) {
-                            if (qq < np - 1) {
-                                float x[1];
-                                to_float<FT, 1>(ks[ST - S0][qq], x);
-                                m *= x[0];
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < VW; ++k) h[k] *= m;
-                    } else {
-#pragma unroll
-                        for (int qq = 1; qq < NPM; ++qq) {
-                            float x[VW];
-                            to_float<FT, VW>(rows[ST - S0][qq], x);
-#pragma unroll
-                            for (int k = 0; k < VW; ++k) h[k] *= x[k];
-                        }
+                        for (int k = 0; k < VW; ++k) h[k] *= x[k];
                     }
                     step(h, v, hm, ST, n);
                 });
@@ -742,34 +634,34 @@ void seg_tile_kernel(SegArgs A)
 
     // ---- 3. wave-level segmented scan of the runs' (f, a, b)
     const int fo = have;
-    float ao[AW];
+    float ao[VW];
     int f = have;
-    float a[AW], b[AW];
+    float a[VW], b[VW];
 #pragma unroll
-    for (int k = 0; k < AW; ++k) {
+    for (int k = 0; k < VW; ++k) {
         ao[k] = have ? pre[k] : acc[k];
         a[k] = ao[k];
         b[k] = acc[k];
     }
-    wave_segscan<LPN, AW>(f, a, b, q);
+    wave_segscan<LPN, VW>(f, a, b, q);
     {   // exclusive prefix of this group: the inclusive value of group q - 1
         const int fp = __shfl_up(f, LPN, 64);
-        float bp[AW];
+        float bp[VW];
 #pragma unroll
-        for (int k = 0; k < AW; ++k) bp[k] = __shfl_up(b[k], LPN, 64);
+        for (int k = 0; k < VW; ++k) bp[k] = __shfl_up(b[k], LPN, 64);
         if (q >= 1 && fo && fp && cval) {
-            float v[AW];
+            float v[VW];
 #pragma unroll
-            for (int k = 0; k < AW; ++k) v[k] = bp[k] + ao[k];
+            for (int k = 0; k < VW; ++k) v[k] = bp[k] + ao[k];
             const int64_t row = ROWMAP ? (int64_t)row0 : (int64_t)(H_run - 1);
             store_acc(A.out + row * R, v);
         }
     }
     if (q == Q - 1) {
 #pragma unroll
-        for (int k = 0; k < AW; ++k) {
-            s_a[w][j * AW + k] = a[k];
-            s_b[w][j * AW + k] = b[k];
+        for (int k = 0; k < VW; ++k) {
+            s_a[w][j * VW + k] = a[k];
+            s_b[w][j * VW + k] = b[k];
         }
         if (j == 0) s_f[w] = f;
     }
@@ -785,31 +677,31 @@ void seg_tile_kernel(SegArgs A)
     //         earlier wave of the tile; then the tile's carries
     if (q == 0 && w >= 1 && s_f[w] && cval) {
         int fx = s_f[0];
-        float bx[AW];
+        float bx[VW];
 #pragma unroll
-        for (int k = 0; k < AW; ++k) bx[k] = s_b[0][j * AW + k];
+        for (int k = 0; k < VW; ++k) bx[k] = s_b[0][j * VW + k];
         for (int i = 1; i < w; ++i) {
 #pragma unroll
-            for (int k = 0; k < AW; ++k) bx[k] = s_f[i] ? s_b[i][j * AW + k] : bx[k] + s_a[i][j * AW + k];
+            for (int k = 0; k < VW; ++k) bx[k] = s_f[i] ? s_b[i][j * VW + k] : bx[k] + s_a[i][j * VW + k];
             fx |= s_f[i];
         }
         if (fx) {
-            float v[AW];
+            float v[VW];
 #pragma unroll
-            for (int k = 0; k < AW; ++k) v[k] = bx[k] + s_a[w][j * AW + k];
+            for (int k = 0; k < VW; ++k) v[k] = bx[k] + s_a[w][j * VW + k];
             const int64_t row = ROWMAP ? (int64_t)row0 : (int64_t)(H_run - 1);
             store_acc(A.out + row * R, v);
         }
     }
-    float at[AW], bt[AW];                             // the tile's carries (wave 0, group 0)
+    float at[VW], bt[VW];                             // the tile's carries (wave 0, group 0)
     if (w == 0 && q == 0 && cval) {
         int ft = s_f[0];
 #pragma unroll
-        for (int k = 0; k < AW; ++k) { at[k] = s_a[0][j * AW + k]; bt[k] = s_b[0][j * AW + k]; }
+        for (int k = 0; k < VW; ++k) { at[k] = s_a[0][j * VW + k]; bt[k] = s_b[0][j * VW + k]; }
         for (int i = 1; i < 4; ++i) {
 #pragma unroll
-            for (int k = 0; k < AW; ++k) {
-                const float ai = s_a[i][j * AW + k], bi = s_b[i][j * AW + k];
+            for (int k = 0; k < VW; ++k) {
+                const float ai = s_a[i][j * VW + k], bi = s_b[i][j * VW + k];
                 const float na = ft ? at[k] : at[k] + ai;
                 const float nb = s_f[i] ? bi : bt[k] + ai;
                 at[k] = na;
@@ -819,8 +711,8 @@ void seg_tile_kernel(SegArgs A)
         }
         if (A.sp_words) {
 #pragma unroll
-            for (int k = 0; k < AW; ++k) {
-                const int c = col + (k / VW) * kstride + (k % VW);
+            for (int k = 0; k < VW; ++k) {
+                const int c = col + k;
                 sp_put(A.sp_words + (tile * 2) * R + c, at[k], A.sp_epoch);
                 sp_put(A.sp_words + (tile * 2 + 1) * R + c, bt[k], A.sp_epoch);
             }
@@ -837,21 +729,21 @@ void seg_tile_kernel(SegArgs A)
         // group 0 adds the shares in a fixed order to the chain start's closing
         // partial and the tile's own.
         constexpr int SPG = 4 * Q < 8 ? 4 * Q : 8;       // lane groups summing a chain
-        constexpr int UW = AW >= 16 ? 1 : 16 / AW;       // tiles in flight per group
+        constexpr int UW = VW >= 16 ? 1 : 16 / VW;       // tiles in flight per group
         const int G = w * Q + q;
         __syncthreads();                                  // s_ab has been read above
         auto chain = [&](int64_t from, bool tail) {
-            float part[AW];
+            float part[VW];
             zero(part);
             if (G < SPG && cval) {
                 for (int64_t t0 = from + 1 + G; t0 < tile; t0 += (int64_t)UW * SPG) {
-                    uint64_t wv[UW][AW];
+                    uint64_t wv[UW][VW];
 #pragma unroll
                     for (int u = 0; u < UW; ++u) {
                         const int64_t tt = t0 + (int64_t)u * SPG;
 #pragma unroll
-                        for (int k = 0; k < AW; ++k) {
-                            const int c = col + (k / VW) * kstride + (k % VW);
+                        for (int k = 0; k < VW; ++k) {
+                            const int c = col + k;
                             wv[u][k] = tt < tile ? __hip_atomic_load(A.sp_words + (tt * 2) * R + c, __ATOMIC_RELAXED,
                                                                      __HIP_MEMORY_SCOPE_AGENT)
                                                  : ((uint64_t)A.sp_epoch << 32);
@@ -861,10 +753,10 @@ void seg_tile_kernel(SegArgs A)
                     for (int u = 0; u < UW; ++u) {
                         const int64_t tt = t0 + (int64_t)u * SPG;
 #pragma unroll
-                        for (int k = 0; k < AW; ++k) {
+                        for (int k = 0; k < VW; ++k) {
                             float x = __uint_as_float((uint32_t)wv[u][k]);
                             if ((uint32_t)(wv[u][k] >> 32) != A.sp_epoch) {   // not published yet: wait
-                                const int c = col + (k / VW) * kstride + (k % VW);
+                                const int c = col + k;
                                 x = sp_get(A.sp_words + (tt * 2) * R + c, A.sp_epoch, A.sp_err);
                             }
                             part[k] += x;
@@ -874,27 +766,27 @@ void seg_tile_kernel(SegArgs A)
             }
             if (G < SPG) {
 #pragma unroll
-                for (int k = 0; k < AW; ++k) s_ab[G][j * AW + k] = part[k];
+                for (int k = 0; k < VW; ++k) s_ab[G][j * VW + k] = part[k];
             }
             __syncthreads();
             if (G == 0 && cval) {
-                float v[AW];
+                float v[VW];
                 if (tail && from == tile) {
                     // the last tile holds the last segment's head: its own closing partial
 #pragma unroll
-                    for (int k = 0; k < AW; ++k) v[k] = bt[k];
+                    for (int k = 0; k < VW; ++k) v[k] = bt[k];
                 } else {
 #pragma unroll
-                    for (int k = 0; k < AW; ++k) {
-                        const int c = col + (k / VW) * kstride + (k % VW);
+                    for (int k = 0; k < VW; ++k) {
+                        const int c = col + k;
                         v[k] = sp_get(A.sp_words + (from * 2 + 1) * R + c, A.sp_epoch, A.sp_err);
                     }
                     for (int g2 = 0; g2 < SPG; ++g2) {
 #pragma unroll
-                        for (int k = 0; k < AW; ++k) v[k] += s_ab[g2][j * AW + k];
+                        for (int k = 0; k < VW; ++k) v[k] += s_ab[g2][j * VW + k];
                     }
 #pragma unroll
-                    for (int k = 0; k < AW; ++k) v[k] += at[k];
+                    for (int k = 0; k < VW; ++k) v[k] += at[k];
                 }
                 const int gc = tail ? A.nseg - 1 : H_run - 1;   // (the first run starts with the tile)
                 const int64_t row = ROWMAP ? (int64_t)A.seg_row[gc] : (int64_t)gc;
