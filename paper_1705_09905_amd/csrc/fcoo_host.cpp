@@ -320,16 +320,15 @@ int prep_single_pass(Built *b, TileProblem &p, hipStream_t s)
 }
 
 // The tile sizes a build can be launched with: the format's, and below it those
-// that pick_plan chooses from (with a caller's own size only the one that
-// SpTTMc's waves take).
+// that pick_plan chooses from (with a caller's own size for SpTTMc only).
 void Built::set_plans(int fmt_tile, bool own)
 {
     own_tile = own;
     plan.clear();
     plan.resize(1);
     plan[0].T = fmt_tile;
-    for (int t : {2048, 1024, 512}) {
-        if (t >= plan.back().T || fmt_tile % t || (own && t != 1024)) continue;
+    for (int t : {2048, 1024, 512, 256}) {
+        if (t >= plan.back().T || fmt_tile % t) continue;
         plan.emplace_back();
         plan.back().T = t;
     }
@@ -351,17 +350,18 @@ void Built::set_plans(int fmt_tile, bool own)
 //   residual R = 64: 5M 209 / 133 / 139 / 168, 20M 792 / 470 / 444 / 438;
 //   SpTTM R = 32: 400k 15.4 / 13.1 / 15.6 / 24.8, 5M 114 / 75 / 78 / 102, 20M 419 /
 //   262 / 272 / 320; R = 8: 248 / 236 / 284 / 381.
-// SpTTMc: a wave takes a tile, so short ones, unless the carries of wide rows
+// SpTTMc: a wave takes a tile, so short ones (512 / 1024 / 2048 / 4096 at R = 16: 1M
+// 46 / 59 / 96 / 168, 10M 175 / 175 / 181 / 221), unless the carries of wide rows
 // would outweigh the work.  Past 64M nonzeros short tiles gain nothing that their
 // carries' scratch would be worth.
 const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron)
 {
     int want = b.plan[0].T;
-    if (kron) want = R <= 1024 ? 1024 : want;
+    if (kron) want = R > 1024 ? want : b.nnz < 400000 ? 256 : b.nnz < 4000000 ? 512 : 1024;
     else if (b.own_tile || b.nnz > (int64_t)64000000) return b.plan[0];
     else if (b.op == FCOO_OP_TTM || lane_shape(b, dtype, R, resid).lpn <= 4) want = 1024;
     else want = resid && b.nnz >= 10000000 ? 4096 : 2048;
-    if (!b.own_tile) {
+    if (!kron) {
         if (b.nnz < 1000000 && want > 1024) want = 1024;
         if (b.nnz < 200000 && want > 512) want = 512;
     }
@@ -506,23 +506,24 @@ void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::v
     int64_t at = 0;
     for (Plan &pl : b.plan) {
         const int64_t ntiles = pl.ntiles, k = pl.T / b.plan.back().T, nfine = b.plan.back().ntiles;
+        std::vector<int32_t> shorter;
         pl.fix.clear();
         int64_t last = -1;
+        auto add = [&](int64_t tb, int64_t g) {
+            std::vector<int32_t> &to = tb - last > kLongChain ? pl.fix : shorter;
+            to.push_back((int32_t)tb);
+            to.push_back((int32_t)last);
+            to.push_back(out_row(g));
+        };
         for (int64_t tb = 0; tb < ntiles; ++tb) {
             const int64_t h0 = hb[tb * k], h1 = hb[std::min((tb + 1) * k, nfine)];
             if (h1 == h0) continue;                  // no head in tile tb
-            if (tb >= 1) {
-                pl.fix.push_back((int32_t)tb);
-                pl.fix.push_back((int32_t)last);
-                pl.fix.push_back(out_row(h0 - 1));
-            }
+            if (tb >= 1) add(tb, h0 - 1);
             last = tb;
         }
-        if (b.nnz > 0) {
-            pl.fix.push_back((int32_t)ntiles);
-            pl.fix.push_back((int32_t)last);
-            pl.fix.push_back(out_row(cnt - 1));
-        }
+        if (b.nnz > 0) add(ntiles, cnt - 1);
+        pl.nlong = pl.nfix();
+        pl.fix.insert(pl.fix.end(), shorter.begin(), shorter.end());
         pl.fix_at = at;
         at += pl.nfix();
     }

@@ -15,6 +15,7 @@ constexpr int kMaxOrder = 8;
 constexpr int kMaxR = 256;
 constexpr int kMaxKronWidth = 16384;   // SpTTMc output columns (prod of the product-mode ranks)
 constexpr int kBlock = 256;        // threads per workgroup of the tile kernels (4 waves)
+constexpr int kLongChain = 64;     // tiles between the ends of a long carry chain
 constexpr int kXcds = 8;           // XCDs of an MI355X: workgroup w runs on XCD w % 8
 
 // error reporting (thread-local message, negative code returned)
@@ -33,8 +34,10 @@ void clear_error();
 struct Plan {
     int T = 0;
     int64_t ntiles = 0;
-    // carry fix-up list: (closing tile b, chain start tile a, output row) per entry
+    // carry fix-up list: (closing tile b, chain start tile a, output row) per
+    // entry, the nlong chains of more than kLongChain tiles first
     std::vector<int32_t> fix;
+    int64_t nlong = 0;
     int64_t fix_at = 0;                       // its first entry in d_fix
     std::vector<int64_t> blk_ts;              // nblk + 1 tile starts: block b's tiles [blk_ts[b], blk_ts[b+1])
     int64_t nfix() const { return (int64_t)fix.size() / 3; }

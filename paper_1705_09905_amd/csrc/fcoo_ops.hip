@@ -13,13 +13,18 @@ namespace dev {
 // What is left after the tile kernel, in one launch whose workgroups take one
 // of three parts (each was a kernel of its own; one launch costs 3-5 us on the
 // stream whatever it does, as much as a small tensor's tile kernel):
-//   [0, nfix)            carry fix-up: entry (b, a, row) finishes the segment
-//                        that tile a starts (its last open partial) and tile b
-//                        closes (its first partial; b = ntiles is the end of
-//                        the tensor), with tiles a+1 .. b-1 wholly inside it;
-//   [nfix, nfix + zblk)  rows of an MTTKRP result that no nonzero touches: 0;
-//   the last one         the residual form's loss: fixed-order strided sums of
-//                        the tiles' partials, then a tree; bitwise repeatable.
+//   the first fblk   carry fix-up: entry (b, a, row) finishes the segment that
+//                    tile a starts (its last open partial) and tile b closes
+//                    (its first partial; b = ntiles is the end of the tensor),
+//                    with tiles a+1 .. b-1 wholly inside it.  The nlong chains
+//                    of more than kLongChain tiles come first, a workgroup
+//                    each; of the others (most have no tile between) four
+//                    share one.  (With 256 threads for every chain a slice of
+//                    1.3M nonzeros over 1300 tiles took 40 us at R = 256: one
+//                    thread a column);
+//   the next zblk    rows of an MTTKRP result that no nonzero touches: 0;
+//   the last one     the residual form's loss: fixed-order strided sums of the
+//                    tiles' partials, then a tree; bitwise repeatable.
 struct FinishArgs {
     const int32_t *fix;
     const float *ca, *cb;
@@ -31,73 +36,72 @@ struct FinishArgs {
     int64_t npartial;
     double scale;
     double *loss;
-    int nfix, zblk, R;
+    int nfix, nlong, fblk, zblk, R;
 };
 
-constexpr int kZeroPer = 1024;       // elements per workgroup of the zero rows
+constexpr int kFinish = 1024;        // threads per workgroup
+constexpr int kZeroPer = 4096;       // elements per workgroup of the zero rows
 constexpr int kChain = 16;           // carries in flight per thread along a chain
 
-__global__ __launch_bounds__(256) void finish_kernel(FinishArgs A)
+__global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
 {
-    const int tid = threadIdx.x;
     const int R = A.R;
-    if ((int)blockIdx.x < A.nfix) {
-        __shared__ float red[256];
-        const int64_t e = blockIdx.x;
-        const int tb = A.fix[3 * e], ta = A.fix[3 * e + 1], row = A.fix[3 * e + 2];
-        if (R > 256) {
-            // wide rows (SpTTMc): one column per thread, the chain summed in order
-            for (int c = tid; c < R; c += 256) {
-                float v = A.cb[(int64_t)ta * R + c];
-                int64_t t = (int64_t)ta + 1;
-                for (; t + 7 < tb; t += 8) {
-                    float x[8];
+    if ((int)blockIdx.x < A.fblk) {
+        __shared__ float red_s[kFinish];
+        const bool is_long = (int)blockIdx.x < A.nlong;
+        const int n = is_long ? kFinish : 256;                       // threads of a chain
+        const int part = is_long ? 0 : (int)threadIdx.x / 256, tid = (int)threadIdx.x - part * 256;
+        const int e = is_long ? (int)blockIdx.x : A.nlong + ((int)blockIdx.x - A.nlong) * 4 + part;
+        float *red = red_s + part * 256;
+        const bool on = e < A.nfix;
+        int tb = 0, ta = 0, row = 0;
+        if (on) { tb = A.fix[3 * e]; ta = A.fix[3 * e + 1]; row = A.fix[3 * e + 2]; }
+        // columns cw at a time (SpTTMc's rows may be wider than the threads)
+        const int cw = R < n ? R : n;
+        const int slots = n / cw, slot = tid / cw, c0 = tid - slot * cw;
+        for (int cb = 0; cb < R; cb += cw) {
+            const int c = cb + c0;
+            float s = 0.f;
+            if (on && slot < slots && c < R) {
+                // long chains (a slice over hundreds of tiles): kChain loads in flight
+                for (int t = ta + 1 + slot; t < tb; t += kChain * slots) {
+                    float x[kChain];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) x[u] = A.ca[(t + u) * R + c];
+                    for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? A.ca[(int64_t)(t + u * slots) * R + c] : 0.f;
+                    // (in pairs: a wide row has one slot, and a chain of a thousand
+                    // tiles would be as many roundings in a row)
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v += x[u];
+                    for (int o = kChain / 2; o >= 1; o >>= 1)
+#pragma unroll
+                        for (int u = 0; u < o; ++u) x[u] += x[u + o];
+                    s += x[0];
                 }
-                for (; t < tb; ++t) v += A.ca[t * R + c];
+            }
+            if (slots > 1) {
+                red[tid] = s;
+                __syncthreads();                                     // (R decides: the same in every part)
+            }
+            if (on && tid < cw && c < R) {
+                float v = A.cb[(int64_t)ta * R + c];
+                const int used = tb - ta - 1 < slots ? tb - ta - 1 : slots;   // the other slots' sums are 0
+                if (slots > 1) {
+                    for (int k = 0; k < used; ++k) v += red[k * cw + tid];
+                } else {
+                    v += s;
+                }
                 if (tb < A.ntiles) v += A.ca[(int64_t)tb * R + c];
                 A.out[(int64_t)row * R + c] = v;
             }
-            return;
-        }
-        const int slots = 256 / R;
-        const int slot = tid / R, c = tid - (tid / R) * R;
-        float s = 0.f;
-        if (slot < slots) {
-            // long chains (a slice over hundreds of tiles): kChain loads in flight
-            for (int t = ta + 1 + slot; t < tb; t += kChain * slots) {
-                float x[kChain];
-#pragma unroll
-                for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? A.ca[(int64_t)(t + u * slots) * R + c] : 0.f;
-                // (in pairs: a wide row has one slot, and a chain of a thousand
-                // tiles would be as many roundings in a row)
-#pragma unroll
-                for (int o = kChain / 2; o >= 1; o >>= 1)
-#pragma unroll
-                    for (int u = 0; u < o; ++u) x[u] += x[u + o];
-                s += x[0];
-            }
-        }
-        red[tid] = s;
-        __syncthreads();
-        if (tid < R) {
-            float v = A.cb[(int64_t)ta * R + tid];
-            const int used = tb - ta - 1 < slots ? tb - ta - 1 : slots;   // the other slots' sums are 0
-            for (int k = 0; k < used; ++k) v += red[k * R + tid];
-            if (tb < A.ntiles) v += A.ca[(int64_t)tb * R + tid];
-            A.out[(int64_t)row * R + tid] = v;
         }
         return;
     }
-    if ((int)blockIdx.x < A.nfix + A.zblk) {
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < A.fblk + A.zblk) {
         const int64_t n = A.nempty * R;
-        for (int64_t i0 = ((int64_t)blockIdx.x - A.nfix) * kZeroPer; i0 < n; i0 += (int64_t)A.zblk * kZeroPer) {
+        for (int64_t i0 = ((int64_t)blockIdx.x - A.fblk) * kZeroPer; i0 < n; i0 += (int64_t)A.zblk * kZeroPer) {
 #pragma unroll
-            for (int u = 0; u < kZeroPer / 256; ++u) {
-                const int64_t i = i0 + u * 256 + tid;
+            for (int u = 0; u < kZeroPer / kFinish; ++u) {
+                const int64_t i = i0 + u * kFinish + tid;
                 if (i < n) {
                     const int64_t r = i / R;
                     A.out[(int64_t)A.empty[r] * R + (i - r * R)] = 0.f;
@@ -106,18 +110,18 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs A)
         }
         return;
     }
-    __shared__ double sh[256];
+    __shared__ double sh[kFinish];
     double s = 0.0;
-    for (int64_t i = tid; i < A.npartial; i += 256 * 8) {
+    for (int64_t i = tid; i < A.npartial; i += kFinish * 8) {
         double x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = i + u * 256 < A.npartial ? A.partial[i + u * 256] : 0.0;
+        for (int u = 0; u < 8; ++u) x[u] = i + u * kFinish < A.npartial ? A.partial[i + u * kFinish] : 0.0;
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += x[u];
     }
     sh[tid] = s;
     __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
+    for (int o = kFinish / 2; o >= 1; o >>= 1) {
         if (tid < o) sh[tid] += sh[tid + o];
         __syncthreads();
     }
@@ -311,6 +315,8 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
     dev::FinishArgs f{};
     f.nfix = b.nnz > 0 && !p.sp_words ? (int)pl.nfix() : 0;
     f.nempty = (int64_t)b.empty_rows.size();
+    f.nlong = f.nfix > 0 ? (int)pl.nlong : 0;
+    f.fblk = f.nlong + (f.nfix - f.nlong + 3) / 4;
     f.zblk = f.nempty > 0 ? grid_for(f.nempty * R, dev::kZeroPer, 1 << 20) : 0;
     if (f.nfix + f.zblk > 0 || p.loss) {
         f.fix = b.d_fix + 3 * pl.fix_at;
@@ -324,7 +330,8 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         f.scale = p.loss_scale;
         f.loss = p.loss;
         f.R = R;
-        hipLaunchKernelGGL(dev::finish_kernel, dim3((unsigned)(f.nfix + f.zblk + (p.loss ? 1 : 0))), dim3(256), 0, s, f);
+        hipLaunchKernelGGL(dev::finish_kernel, dim3((unsigned)(f.fblk + f.zblk + (p.loss ? 1 : 0))), dim3(dev::kFinish), 0,
+                           s, f);
         FCOO_HIP(hipGetLastError());
     }
     if (b.nblk > 1) {
