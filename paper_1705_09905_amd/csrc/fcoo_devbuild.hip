@@ -184,31 +184,34 @@ int grid_of(int64_t n, int cap = 65535 * 16)
     return (int)(g < cap ? g : cap);
 }
 
-// device temporaries of one build, freed on every exit path
-struct Scratch {
-    std::vector<void *> p;
-    ~Scratch() { for (void *x : p) (void)hipFree(x); }
+// Arrays laid out one after the other in a block: first every size is added
+// (add), then the block's address gives the pointers (set).
+struct Layout {
+    size_t bytes = 0;
     template <typename T>
-    int get(T **out, int64_t n)
+    size_t add(int64_t n)
     {
-        void *x = nullptr;
-        if (hipMalloc(&x, (size_t)(n > 0 ? n : 1) * sizeof(T)) != hipSuccess)
-            return fail(FCOO_ENOMEM, "device build scratch (%lld elements)", (long long)n);
-        p.push_back(x);
-        *out = (T *)x;
-        return FCOO_OK;
+        const size_t at = bytes;
+        bytes += ((size_t)(n > 0 ? n : 1) * sizeof(T) + 255) / 256 * 256;
+        return at;
     }
 };
 
 template <typename T>
-int alloc_dev(T **dst, int64_t n, int64_t pad, hipStream_t s, int64_t *acct)
-{
-    const size_t bytes = (size_t)(n + pad > 0 ? n + pad : 1) * sizeof(T);
-    FCOO_HIP(hipMalloc((void **)dst, bytes));
-    if (pad) FCOO_HIP(hipMemsetAsync(*dst, 0, bytes, s));
-    *acct += (int64_t)bytes;
-    return FCOO_OK;
-}
+T *at(const PoolBlock &b, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(b.p) + off); }
+
+// one build's scratch, back to the pool on every exit path once its work is done
+struct Scratch {
+    PoolBlock b;
+    hipStream_t s;
+    explicit Scratch(hipStream_t st) : s(st) {}
+    ~Scratch()
+    {
+        if (!b.p) return;
+        if (hipStreamSynchronize(s) == hipSuccess) pool_put(&b);
+        else pool_free(&b);
+    }
+};
 
 }  // namespace
 
@@ -252,52 +255,85 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bo
     b.npart = P;
     b.ntiles = (Z + T - 1) / T;
 
-    Scratch tmp;
+    // scratch and arrays: one block each
+    const int64_t bfw = (Z + 31) / 32, sfw = (P + 31) / 32;
+    const int64_t wsort = sort_work_ints(Z), wscan = scan_work_ints(Z);
+    Scratch tmp(s);
     uint64_t *k0, *k1;
     uint32_t *p0, *p1;
-    int32_t *head, *cum, *hb, *seg0d;
-    if ((rc = tmp.get(&k0, Z)) || (rc = tmp.get(&k1, Z)) || (rc = tmp.get(&p0, Z)) || (rc = tmp.get(&p1, Z)) ||
-        (rc = tmp.get(&head, Z)) || (rc = tmp.get(&cum, Z)) || (rc = tmp.get(&hb, ntiles + 1)) ||
-        (rc = tmp.get(&seg0d, ntiles)))
-        return rc;
+    int32_t *head, *cum, *hb, *seg0d, *work;
+    {
+        Layout l;
+        const size_t ok0 = l.add<uint64_t>(Z), ok1 = l.add<uint64_t>(Z), op0 = l.add<uint32_t>(Z), op1 = l.add<uint32_t>(Z);
+        const size_t oh = l.add<int32_t>(Z), oc = l.add<int32_t>(Z), ob = l.add<int32_t>(ntiles + 1);
+        const size_t os = l.add<int32_t>(ntiles), ow = l.add<int32_t>(wsort > wscan ? wsort : wscan);
+        const size_t obl = l.add<int32_t>((int64_t)b.blk_of.size());
+        if ((rc = pool_get(l.bytes, &tmp.b))) return rc;
+        k0 = at<uint64_t>(tmp.b, ok0); k1 = at<uint64_t>(tmp.b, ok1);
+        p0 = at<uint32_t>(tmp.b, op0); p1 = at<uint32_t>(tmp.b, op1);
+        head = at<int32_t>(tmp.b, oh); cum = at<int32_t>(tmp.b, oc); hb = at<int32_t>(tmp.b, ob);
+        seg0d = at<int32_t>(tmp.b, os); work = at<int32_t>(tmp.b, ow); ka.blk_of = at<int32_t>(tmp.b, obl);
+    }
+    int64_t acct = 0;
+    const int64_t rows = op == FCOO_OP_MTTKRP ? (int64_t)b.nblk * t->dims[mode] : 0;
+    const int64_t most_seg = rows < Z ? rows : Z;
+    size_t oseg, ofix, oempty;
+    {
+        int64_t nfix = 0;
+        for (const Plan &pl : b.plan) nfix += pl.ntiles + 1;
+        Layout l;
+        size_t opx[kMaxOrder];
+        const int np = (int)b.pmodes.size();
+        for (int q = 0; q < np; ++q) opx[q] = l.add<int32_t>(Z + 4);
+        const size_t ov = l.add<float>(Z + 4), op_ = l.add<int32_t>(Z), oh = l.add<uint32_t>(2 * bfw + 4);
+        const size_t obf = l.add<uint32_t>(bfw + 2), osf = l.add<uint32_t>(sfw + 1);
+        oseg = l.add<int32_t>(most_seg + 2);
+        ofix = l.add<int32_t>(3 * nfix + 3);
+        oempty = l.add<int32_t>(rows + 1);
+        if ((rc = pool_get(l.bytes, &b.arena))) return rc;
+        for (int q = 0; q < np; ++q) b.d_pidx[q] = at<int32_t>(b.arena, opx[q]);
+        b.d_val = at<float>(b.arena, ov);
+        b.d_perm = at<int32_t>(b.arena, op_);
+        b.d_hr = at<uint32_t>(b.arena, oh);
+        b.d_bf = at<uint32_t>(b.arena, obf);
+        b.d_sf = at<uint32_t>(b.arena, osf);
+        // the streams' padding, which kernels read (and do not use): index 0, no head
+        for (int q = 0; q < np; ++q) FCOO_HIP(hipMemsetAsync(b.d_pidx[q] + Z, 0, 4 * 4, s));
+        FCOO_HIP(hipMemsetAsync(b.d_val + Z, 0, 4 * 4, s));
+        FCOO_HIP(hipMemsetAsync(b.d_hr + 2 * bfw, 0, 4 * 4, s));
+        acct = (int64_t)np * (Z + 4) * 4 + (Z + 4) * 4 + Z * 4 + (2 * bfw + 4) * 4 + (bfw + 2) * 4 + (sfw + 1) * 4;
+    }
 
-    int32_t *blk_d = nullptr;
     if (blocked) {
-        if ((rc = tmp.get(&blk_d, (int64_t)b.blk_of.size()))) return rc;
-        FCOO_HIP(hipMemcpyAsync(blk_d, b.blk_of.data(), b.blk_of.size() * 4, hipMemcpyHostToDevice, s));
-        ka.blk_of = blk_d;
+        FCOO_HIP(hipMemcpyAsync(const_cast<int32_t *>(ka.blk_of), b.blk_of.data(), b.blk_of.size() * 4,
+                                hipMemcpyHostToDevice, s));
         ka.bidx = t->d_coo[b.bmode];
+    } else {
+        ka.blk_of = nullptr;
     }
 
     // 1. keys and the stable radix sort
     hipLaunchKernelGGL(dev::key_kernel, dim3(grid_of(Z)), dim3(256), 0, s, ka, k0, p0);
     FCOO_HIP(hipGetLastError());
     const int end_bit = total > 0 ? total : 1;
-    const int64_t wsort = sort_work_ints(Z), wscan = scan_work_ints(Z);
-    int32_t *work;
-    if ((rc = tmp.get(&work, wsort > wscan ? wsort : wscan))) return rc;
     int passes = 0;
     if ((rc = sort_pairs_u64(k0, k1, p0, p1, Z, end_bit, work, s, &passes))) return rc;
     uint64_t *ks = (passes & 1) ? k1 : k0;            // the sorted pairs
     uint32_t *ps = (passes & 1) ? p1 : p0;
 
-    // 2. sorted per-nonzero arrays (4 zero entries of padding, as uploaded by the host builder)
-    int64_t acct = 0;
+    // 2. sorted per-nonzero arrays
     dev::GatherArgs ga{};
     ga.vals = t->d_coo_val;
     ga.key = ks;
     ga.pos = ps;
     ga.np = (int)b.pmodes.size();
     for (int q = ga.np - 1, sh = 0; q >= 0; --q) {   // last product mode in the lowest bits
-        if ((rc = alloc_dev(&b.d_pidx[q], Z, 4, s, &acct))) return rc;
         ga.pidx[q] = b.d_pidx[q];
         ga.pwidth[q] = bits_of(t->dims[b.pmodes[q]]);
         ga.pshift[q] = sh;
         sh += ga.pwidth[q];
     }
     ga.pbits = pbits;
-    if ((rc = alloc_dev(&b.d_val, Z, 4, s, &acct))) return rc;
-    if ((rc = alloc_dev(&b.d_perm, Z, 0, s, &acct))) return rc;
     ga.val = b.d_val;
     ga.perm = b.d_perm;
     ga.head = head;
@@ -309,10 +345,6 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bo
     if ((rc = scan_i32(head, cum, Z, true, work, s))) return rc;
 
     // 4. flags, tiles, segments
-    const int64_t bfw = (Z + 31) / 32, sfw = (P + 31) / 32;
-    if ((rc = alloc_dev(&b.d_bf, bfw, 2, s, &acct))) return rc;
-    if ((rc = alloc_dev(&b.d_sf, sfw, 1, s, &acct))) return rc;
-    if ((rc = alloc_dev(&b.d_hr, 2 * bfw, 4, s, &acct))) return rc;
     hipLaunchKernelGGL(dev::hr_kernel, dim3((unsigned)((bfw * 32 + 255) / 256)), dim3(256), 0, s, head, cum, Z, bfw,
                        reinterpret_cast<uint2 *>(b.d_hr));
     FCOO_HIP(hipGetLastError());
@@ -331,12 +363,18 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bo
     const int64_t nseg = hbh[ntiles];
     b.nseg = nseg;
     const int nim = (int)b.imodes.size();
-    int32_t *segd;
+    // TTM's fibre coordinates go to the host only: through the sort's spent keys
+    // (8 bytes a nonzero), or where they are longer through a block of their own
+    int32_t *segd = reinterpret_cast<int32_t *>((passes & 1) ? k0 : k1);
+    Scratch extra(s);
+    if (op == FCOO_OP_TTM && nseg * nim * 4 > Z * 8) {
+        if ((rc = pool_get((size_t)(nseg * nim) * 4, &extra.b))) return rc;
+        segd = at<int32_t>(extra.b, 0);
+    }
     if (op == FCOO_OP_MTTKRP) {
-        if ((rc = alloc_dev(&b.d_seg_row, nseg, 2, s, &acct))) return rc;
-        segd = b.d_seg_row;
-    } else if ((rc = tmp.get(&segd, nseg * nim))) {
-        return rc;
+        segd = b.d_seg_row = at<int32_t>(b.arena, oseg);
+        FCOO_HIP(hipMemsetAsync(b.d_seg_row + nseg, 0, 2 * 4, s));
+        acct += (nseg + 2) * 4;
     }
     dev::SegArgsB sa{};
     sa.key = ks;
@@ -368,9 +406,14 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bo
     // 5. carry chains and empty rows on the host (per tile / per row)
     std::vector<int64_t> hb64(hbh.begin(), hbh.end());
     finish_tiles(t, b, mode, op, hb64);
-    if ((rc = upload_plans(b, s, &acct))) return rc;
-    if ((rc = upload_i32(&b.d_empty, b.empty_rows, 1, s, &acct))) return rc;
+    const std::vector<int32_t> fixes = all_fixes(b);
+    b.d_fix = at<int32_t>(b.arena, ofix);
+    b.d_empty = at<int32_t>(b.arena, oempty);
+    FCOO_HIP(hipMemcpyAsync(b.d_fix, fixes.data(), fixes.size() * 4, hipMemcpyHostToDevice, s));
+    if (!b.empty_rows.empty())
+        FCOO_HIP(hipMemcpyAsync(b.d_empty, b.empty_rows.data(), b.empty_rows.size() * 4, hipMemcpyHostToDevice, s));
     FCOO_HIP(hipStreamSynchronize(s));
+    acct += (int64_t)(fixes.size() + 3) * 4 + (int64_t)(b.empty_rows.size() + 1) * 4;
     b.device_bytes = acct;
     b.built = true;
     b.on_device = true;

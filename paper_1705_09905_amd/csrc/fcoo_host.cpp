@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <thread>
 
@@ -124,19 +125,109 @@ int64_t Built::format_bytes() const
     return 4 * nnz * (int64_t)pmodes.size() + 4 * nnz + (nnz + 7) / 8 + 4 * ((npart + 31) / 32);
 }
 
+namespace {
+std::mutex g_pool_mu;
+std::vector<PoolBlock> g_pool;               // idle blocks
+size_t g_pool_bytes = 0;
+int g_handles = 0;
+
+// every idle block that `which` picks, back to the driver (g_pool_mu held)
+template <class F>
+void pool_trim(F which)
+{
+    for (size_t i = 0; i < g_pool.size();) {
+        if (!which(g_pool[i])) { ++i; continue; }
+        (void)hipFree(g_pool[i].p);
+        g_pool_bytes -= g_pool[i].bytes;
+        g_pool[i] = g_pool.back();
+        g_pool.pop_back();
+    }
+}
+}  // namespace
+
+int pool_get(size_t bytes, PoolBlock *b)
+{
+    const size_t unit = (size_t)2 << 20;
+    bytes = (bytes + unit - 1) / unit * unit;
+    int dev = 0;
+    FCOO_HIP(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    size_t best = g_pool.size();
+    for (size_t i = 0; i < g_pool.size(); ++i)
+        if (g_pool[i].dev == dev && g_pool[i].bytes >= bytes && g_pool[i].bytes <= bytes + bytes / 4 &&
+            (best == g_pool.size() || g_pool[i].bytes < g_pool[best].bytes))
+            best = i;
+    if (best < g_pool.size()) {
+        *b = g_pool[best];
+        g_pool_bytes -= b->bytes;
+        g_pool[best] = g_pool.back();
+        g_pool.pop_back();
+        return FCOO_OK;
+    }
+    b->bytes = bytes;
+    b->dev = dev;
+    if (hipMalloc(&b->p, bytes) == hipSuccess) return FCOO_OK;
+    (void)hipGetLastError();
+    pool_trim([&](const PoolBlock &x) { return x.dev == dev; });
+    if (hipMalloc(&b->p, bytes) == hipSuccess) return FCOO_OK;
+    (void)hipGetLastError();
+    b->p = nullptr;
+    return fail(FCOO_ENOMEM, "device build (%lld bytes)", (long long)bytes);
+}
+
+void pool_free(PoolBlock *b)
+{
+    if (b->p) (void)hipFree(b->p);
+    *b = PoolBlock();
+}
+
+void pool_put(PoolBlock *b)
+{
+    if (!b->p) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (g_handles > 0 && g_pool_bytes + b->bytes <= kPoolKeep) {
+        try {
+            g_pool.push_back(*b);
+            g_pool_bytes += b->bytes;
+            *b = PoolBlock();
+            return;
+        } catch (const std::bad_alloc &) {
+        }
+    }
+    pool_free(b);
+}
+
+void pool_handles(int delta)
+{
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    g_handles += delta;
+    if (g_handles == 0) pool_trim([](const PoolBlock &) { return true; });
+}
+
 void Built::free_device()
 {
-    if (d_bpart) (void)hipFree(d_bpart);
-    d_bpart = nullptr;
-    bpart_cap = 0;
+    if (arena.p) {
+        // work queued on any stream may still read the arrays, as before a
+        // hipFree, which waits; where the wait is refused (a stream is being
+        // captured) the block goes to the driver
+        if (hipDeviceSynchronize() == hipSuccess) {
+            pool_put(&arena);
+        } else {
+            (void)hipGetLastError();
+            pool_free(&arena);
+        }
+        for (auto &p : d_pidx) p = nullptr;
+        d_val = nullptr; d_hr = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr;
+        d_perm = nullptr; d_fix = nullptr; d_empty = nullptr;
+    }
     for (auto &p : d_pidx) { if (p) (void)hipFree(p); p = nullptr; }
-    void *ptrs[] = {d_val, d_hr, d_bf, d_sf, d_seg_row, d_perm, d_fix, d_empty, d_carry,
+    void *ptrs[] = {d_val, d_hr, d_bf, d_sf, d_seg_row, d_perm, d_fix, d_empty, d_carry, d_bpart,
                     d_gperm, d_partial, d_sp_from, d_sp_words, d_sp_ticket, d_sp_err};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     d_val = nullptr; d_hr = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr;
-    d_perm = nullptr; d_fix = nullptr; d_empty = nullptr; d_carry = nullptr; d_gperm = nullptr;
+    d_perm = nullptr; d_fix = nullptr; d_empty = nullptr; d_carry = nullptr; d_bpart = nullptr; d_gperm = nullptr;
     d_partial = nullptr; d_sp_from = nullptr; d_sp_words = nullptr; d_sp_ticket = nullptr; d_sp_err = nullptr;
-    carry_cap = 0; partial_cap = 0; device_bytes = 0; sp_words_cap = 0; sp_tickets = 0; sp_epoch = 0;
+    carry_cap = 0; bpart_cap = 0; partial_cap = 0; device_bytes = 0; sp_words_cap = 0; sp_tickets = 0; sp_epoch = 0;
     on_device = false;
 }
 
@@ -537,11 +628,17 @@ void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::v
     }
 }
 
-// the plans' fix-up lists, one after the other (the copy ends before it returns)
-int upload_plans(Built &b, hipStream_t s, int64_t *acct)
+std::vector<int32_t> all_fixes(const Built &b)
 {
     std::vector<int32_t> all;
     for (const Plan &pl : b.plan) all.insert(all.end(), pl.fix.begin(), pl.fix.end());
+    return all;
+}
+
+// the plans' fix-up lists, one after the other (the copy ends before it returns)
+static int upload_plans(Built &b, hipStream_t s, int64_t *acct)
+{
+    const std::vector<int32_t> all = all_fixes(b);
     int rc = upload(&b.d_fix, all.data(), (int64_t)all.size(), 3, s, acct);
     if (!rc) FCOO_HIP(hipStreamSynchronize(s));
     return rc;
@@ -554,6 +651,7 @@ static int first_carries(Built &b, hipStream_t s)
     int64_t need = 0;
     for (int R : {16, 32, 64})
         need = std::max(need, 2 * pick_plan(b, FCOO_F32, R, false, false).ntiles * R);
+    if (b.carry_cap >= need) return FCOO_OK;
     return need > 0 ? ensure_device_floats(&b.d_carry, &b.carry_cap, need, s) : FCOO_OK;
 }
 
@@ -669,6 +767,7 @@ int fcoo_create(int order, const int64_t *dims, int64_t nnz, const int32_t *cons
     double s = 0.0;
     for (int64_t e = 0; e < nnz; ++e) s += (double)t->vals[e] * (double)t->vals[e];
     t->normX2 = s;
+    pool_handles(1);
     *out = t;
     return FCOO_OK;
 }
@@ -810,6 +909,7 @@ void fcoo_destroy(fcoo_tensor *t)
     if (t->ev_solved) (void)hipEventDestroy(t->ev_solved);
     if (t->aux) (void)hipStreamDestroy(t->aux);
     delete t;
+    pool_handles(-1);
 }
 
 // ---------------------------------------------------------------------------

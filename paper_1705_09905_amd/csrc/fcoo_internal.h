@@ -29,6 +29,13 @@ void clear_error();
         if (e_ != hipSuccess) return ::fcoo::hip_fail(e_, #call); \
     } while (0)
 
+// A block of device memory from the library's pool (below).
+struct PoolBlock {
+    void *p = nullptr;
+    size_t bytes = 0;
+    int dev = 0;
+};
+
 // A split of a build's nonzeros into tiles of T as launched: which segments
 // are finished across tiles, and with XCD blocks each block's tiles.
 struct Plan {
@@ -78,7 +85,9 @@ struct Built {
 
     std::vector<int32_t> empty_rows;          // MTTKRP rows with no nonzero
 
-    // device copies
+    // device copies; a build made on the GPU holds those up to d_empty in one
+    // pool block (arena), the others each in an allocation of its own
+    PoolBlock arena;
     int32_t *d_pidx[kMaxOrder] = {};
     float *d_val = nullptr;
     uint32_t *d_hr = nullptr;                 // per 32 nonzeros: segment heads, heads before; +2 zero pairs
@@ -152,11 +161,23 @@ struct fcoo_tensor {
 
 namespace fcoo {
 
+// Device memory of the builds made on the GPU, kept from one build for the next:
+// allocating and freeing it (about 50 bytes a nonzero, most of it scratch) costs
+// more than the build, as the driver clears freed memory before it hands it out
+// again.  At most kPoolKeep bytes lie idle, and none once no handle is left; any
+// thread may call.  A block is given back only when no device work can still
+// use it (the caller has waited).
+constexpr size_t kPoolKeep = (size_t)4 << 30;
+int pool_get(size_t bytes, PoolBlock *b);    // FCOO_OK or FCOO_ENOMEM
+void pool_put(PoolBlock *b);                 // b->p may be null
+void pool_free(PoolBlock *b);                // to the driver, not to the pool
+void pool_handles(int delta);                // handles alive
+
 // helpers implemented in fcoo_host.cpp
 int ensure_device_floats(float **p, int64_t *cap, int64_t need, hipStream_t s);
 int ensure_device_doubles(double **p, int64_t *cap, int64_t need, hipStream_t s);
 int upload_coo(fcoo_tensor *t, hipStream_t s);
-int upload_plans(Built &b, hipStream_t s, int64_t *acct);
+std::vector<int32_t> all_fixes(const Built &b);   // the plans' fix-up lists, one after the other
 int upload_i32(int32_t **dst, const std::vector<int32_t> &v, int64_t pad, hipStream_t s, int64_t *acct);
 // the plans' carry fix-up chains and the empty output rows from the head counts
 // of the shortest tiles (heads_before[t] = heads before nonzero t * T, t = 0 ..
