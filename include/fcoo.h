@@ -335,11 +335,8 @@ int fcoo_resid_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, in
  *            `grams_valid` = 0 to have them computed from the factors first.
  *   fit      host double* (out); the call waits for it.
  *   used_pinv host int* or NULL (out): bit n set if mode n used the pseudo-inverse.
- * Requires fcoo_build(n, FCOO_OP_MTTKRP) for every mode n.  The R x R solve
- * of each mode runs on a second stream owned by the handle, beside that
- * mode's SpMTTKRP (it needs only the other modes' Grams); events order it
- * after the earlier work on `stream` and before the row solve, so for the
- * caller all the work is ordered on `stream`.
+ * Requires fcoo_build(n, FCOO_OP_MTTKRP) for every mode n.  All the work runs
+ * on `stream`.
  * Errors: FCOO_EINVAL, FCOO_ENOTBUILT, FCOO_EUNSUPPORTED, FCOO_EHIP, FCOO_ENOMEM.
  */
 int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, double *lambda,

@@ -16,41 +16,51 @@
 // Every reduction runs in a fixed order: results are bitwise repeatable.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fcoo_device.h"
 #include "fcoo_internal.h"
 
 namespace fcoo {
 namespace dev {
 
-constexpr int kGramRows = 1024;        // rows of A per Gram workgroup (256 per wave)
+// rows summed in float32 before they go to float64 (bfloat16: the order of sums
+// that CP-ALS with bfloat16 factors keeps, see TileProblem::keep_order)
+template <typename FT> constexpr int kGramFlush = sizeof(FT) == 4 ? 64 : 256;
+constexpr int kCpBlocks = 256;         // workgroups of the row solve passes at most
 constexpr int kMaxCpR = 64;            // R bound of the in-LDS solve
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
-// Partial Gram of rows [blk * kGramRows, ...) for the 32 x 32 tile pair
-// (tr, tc): each wave accumulates its quarter of the rows on the matrix
-// cores (float32 inputs: 32x32x2; bfloat16: 32x32x8), the four waves are
-// summed in float64 and written to partial[blk][R x R].  The operands of the
-// next GU matrix steps are loaded while the current ones run.
+// Partial Gram of `rows` rows (a multiple of 1024) for the 32 x 32 tile
+// pair (tr, tc): each wave accumulates its quarter of the rows on the matrix
+// cores (float32 inputs: 32x32x2; bfloat16: 32x32x8), in float64 past
+// kGramFlush rows of its own; the four waves are summed in float64 and written to
+// partial[blk][R x R].  The operands of the next GU matrix steps are loaded
+// while the current ones run.
 template <typename FT>
-__global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict__ A, int64_t I, int R,
+__global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict__ A, int64_t I, int R, int rows,
                                                            double *__restrict__ partial)
 {
-    __shared__ float red[4][32][33];
+    __shared__ double red[32][33];
     const int ntile = (R + 31) / 32;
     const int tr = blockIdx.y / ntile, tc = blockIdx.y % ntile;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t b0 = (int64_t)blockIdx.x * kGramRows;
-    const int64_t r0 = b0 + (int64_t)w * (kGramRows / 4);
-    int64_t r1 = r0 + kGramRows / 4;
+    const int64_t r0 = (int64_t)blockIdx.x * rows + (int64_t)w * (rows / 4);
+    int64_t r1 = r0 + rows / 4;
     if (r1 > I) r1 = I;
     const int ca = tr * 32 + (lane & 31), cb = tc * 32 + (lane & 31);
     const bool va = ca < R, vb = cb < R;
     const int kk = lane >> 5;
     floatx16 acc;
+    double sum[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int v = 0; v < 16; ++v) { acc[v] = 0.f; sum[v] = 0.0; }
+    auto flush = [&]() {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { sum[v] += (double)acc[v]; acc[v] = 0.f; }
+    };
     constexpr int GU = 8;                                    // matrix steps per operand batch
     if constexpr (sizeof(FT) == 4) {
         const float *Af = reinterpret_cast<const float *>(A);
@@ -72,6 +82,7 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict_
             for (int u = 0; u < GU; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0v[u], acc, 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < GU; ++u) { a0[u] = a1[u]; b0v[u] = b1[u]; }
+            if ((i - r0) % kGramFlush<FT> == kGramFlush<FT> - STEP) flush();
         }
     } else {
         const uint16_t *Ab = reinterpret_cast<const uint16_t *>(A);
@@ -97,42 +108,63 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict_
             for (int u = 0; u < GB; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a0[u], b0v[u], acc, 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < GB; ++u) { a0[u] = a1[u]; b0v[u] = b1[u]; }
+            if ((i - r0) % kGramFlush<FT> == kGramFlush<FT> - STEP) flush();
         }
     }
+    flush();
     // accumulator v of lane l holds tile element (8 (v/4) + 4 (l/32) + v%4, l%32)
+    for (int k = 0; k < 4; ++k) {
+        if (w == k) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[w][8 * (v >> 2) + 4 * kk + (v & 3)][lane & 31] = acc[v];
-    __syncthreads();
-    for (int e = threadIdx.x; e < 32 * 32; e += 256) {
-        const int i = e >> 5, jj = e & 31;
-        const int gi = tr * 32 + i, gj = tc * 32 + jj;
-        if (gi < R && gj < R) {
-            const double s = ((double)red[0][i][jj] + (double)red[1][i][jj]) + ((double)red[2][i][jj] + (double)red[3][i][jj]);
-            partial[(int64_t)blockIdx.x * R * R + (int64_t)gi * R + gj] = s;
+            for (int v = 0; v < 16; ++v) {
+                double &x = red[8 * (v >> 2) + 4 * kk + (v & 3)][lane & 31];
+                x = k ? x + sum[v] : sum[v];
+            }
         }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < 32 * 32; e += 256) {
+        const int gi = tr * 32 + (e >> 5), gj = tc * 32 + (e & 31);
+        if (gi < R && gj < R) partial[(int64_t)blockIdx.x * R * R + (int64_t)gi * R + gj] = red[e >> 5][e & 31];
     }
 }
 
-// out[e] = sum_b partial[b][e] (b < nblk): one wave per element, lane t sums
-// b = t, t + 64, ..., then a butterfly; fixed order, so repeatable.
-__global__ __launch_bounds__(64) void sum_blocks_kernel(const double *__restrict__ partial, int64_t nblk,
-                                                        int64_t n_per, double *__restrict__ out)
+// out[e] = sum_b partial[b][e] (b < nblk): 32 elements x 8 strided shares of the
+// blocks per workgroup (whole 256-byte pieces per load), the shares added in a
+// fixed order, so repeatable.
+__global__ __launch_bounds__(256) void sum_blocks_kernel(const double *__restrict__ partial, int64_t nblk,
+                                                         int64_t n_per, double *__restrict__ out)
 {
-    const int64_t e = blockIdx.x;
+    __shared__ double red[8][32];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int64_t e = (int64_t)blockIdx.x * 32 + x;
     double s = 0.0;
-    for (int64_t b = threadIdx.x; b < nblk; b += 64) s += partial[b * n_per + e];
+    if (e < n_per) {
+        for (int64_t b = y; b < nblk; b += 64) {
+            double v[8];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) out[e] = s;
+            for (int u = 0; u < 8; ++u) v[u] = b + 8 * u < nblk ? partial[(b + 8 * u) * n_per + e] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+    }
+    red[y][x] = s;
+    __syncthreads();
+    if (y == 0 && e < n_per) {
+        for (int k = 1; k < 8; ++k) s += red[k][x];
+        out[e] = s;
+    }
 }
 
 // One workgroup: V = Hadamard of the Grams but mode n; W = V^-1 by
-// Gauss-Jordan elimination without row exchanges (lane k of each wave owns
-// column k, the four waves share its rows; the pivots are the
-// Schur-complement diagonal, i.e. the squared Cholesky pivots of V = L L^T), or V^+ from a cyclic Jacobi eigendecomposition when
-// a pivot is <= 0 or below 1e-13 * max(diag V).  flags[n] = 1 when the
-// pseudo-inverse was used.  R <= kMaxCpR.  V is inverted in place in LDS;
-// the Jacobi fallback keeps its eigenvectors in tmp (global, R x R).
+// Gauss-Jordan elimination without row exchanges (the pivots are the
+// Schur-complement diagonal, i.e. the squared Cholesky pivots of V = L L^T), or
+// V^+ from a cyclic Jacobi eigendecomposition when a pivot is <= 0 or below
+// 1e-13 * max(diag V).  flags[n] = 1 when the pseudo-inverse was used.
+// R <= 4 RPL <= kMaxCpR.  Wave q holds rows q, q + 4, ... in registers, lane k
+// column k: a step passes the pivot row through LDS (one barrier; the buffers
+// alternate) and takes the pivot column by lane reads.  (With the matrix in LDS
+// and three barriers a step it took 61 us at R = 32; 21 now.)  The Jacobi fallback works in LDS, its eigenvectors in tmp (R x R).
 __device__ void form_hadamard(const double *__restrict__ grams, int N, int n, int R,
                               double (*V)[kMaxCpR + 1])
 {
@@ -144,56 +176,75 @@ __device__ void form_hadamard(const double *__restrict__ grams, int N, int n, in
     }
 }
 
+__device__ __forceinline__ double lane_value(double x, int lane)
+{
+    const uint64_t u = __double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+template <int RPL>
 __global__ __launch_bounds__(256) void als_solve_kernel(const double *__restrict__ grams, int N, int n,
                                                         int R, double *__restrict__ W,
                                                         double *__restrict__ tmp, int *__restrict__ flags)
 {
     __shared__ double V[kMaxCpR][kMaxCpR + 1];
-    __shared__ double rj[kMaxCpR], cj[kMaxCpR];
-    __shared__ double cs_s[2];
+    __shared__ double prow[2][kMaxCpR];
+    __shared__ double cs_s[4];
     const int tid = threadIdx.x;
     const int k = tid & 63;                         // column of this lane
     const int q = tid >> 6;                         // rows q, q + 4, q + 8, ... of that column
-    form_hadamard(grams, N, n, R, V);
-    __syncthreads();
+    double a[RPL];
     double dmax = 0.0;
-    for (int i = 0; i < R; ++i) dmax = V[i][i] > dmax ? V[i][i] : dmax;
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) {
+        const int i = q + 4 * u;
+        double h = 0.0;
+        if (i < R && k < R) {
+            h = 1.0;
+            for (int m = 0; m < N; ++m)
+                if (m != n) h *= grams[(int64_t)m * R * R + i * R + k];
+        }
+        a[u] = h;
+        if (i < R) {
+            const double d = lane_value(h, i);
+            dmax = d > dmax ? d : dmax;
+        }
+    }
+    if (k == 0) cs_s[q] = dmax;
+    __syncthreads();
+    for (int i = 0; i < 4; ++i) dmax = cs_s[i] > dmax ? cs_s[i] : dmax;
     bool fail = false;
-    constexpr int RPL = kMaxCpR / 4;                // rows per lane at most
-    for (int j = 0; j < R; ++j) {
-        const double p = V[j][j];                   // Schur-complement pivot (same on every lane)
-        if (!(p > 0.0) || p <= 1e-13 * dmax) { fail = true; break; }
-        if (tid < R) {
-            rj[tid] = V[j][tid];
-            cj[tid] = V[tid][j];
-        }
-        __syncthreads();
-        const double ip = 1.0 / p;
-        if (k < R) {
-            const double rjk = rj[k] * ip;
-            // rows i != j: a - c_i rjk (column j: -c_i / p); row j is set below
-            double a[RPL], c[RPL];
+#pragma unroll
+    for (int u0 = 0; u0 < RPL; ++u0) {
+        for (int qq = 0; qq < 4 && !fail; ++qq) {
+            const int j = 4 * u0 + qq;
+            if (j >= R) break;
+            double *pr = prow[j & 1];
+            if (q == qq) pr[k] = a[u0];
+            __syncthreads();
+            const double p = pr[j];                  // Schur-complement pivot (same on every lane)
+            if (!(p > 0.0) || p <= 1e-13 * dmax) { fail = true; break; }
+            const double ip = 1.0 / p;
+            const double rjk = pr[k] * ip;
+            // rows i != j: a - c_i rjk (column j: -c_i / p); row j: rjk (1 / p)
 #pragma unroll
             for (int u = 0; u < RPL; ++u) {
-                const int i = q + 4 * u;
-                const int ic = i < R ? i : 0;
-                a[u] = V[ic][k];
-                c[u] = cj[ic];
-            }
-#pragma unroll
-            for (int u = 0; u < RPL; ++u) {
-                const int i = q + 4 * u;
-                const double t = a[u] - c[u] * rjk;
-                const double tc = -c[u] * ip;
-                if (i < R) V[i][k] = k == j ? tc : t;
+                const double c = lane_value(a[u], j);
+                const double t = a[u] - c * rjk;
+                const double tc = -c * ip;
+                const bool own = u == u0 && q == qq;
+                a[u] = own ? (k == j ? ip : rjk) : (k == j ? tc : t);
             }
         }
-        __syncthreads();
-        if (tid < R) V[j][tid] = tid == j ? ip : rj[tid] * ip;
-        __syncthreads();
     }
     if (!fail) {
-        for (int e = tid; e < R * R; e += 256) W[e] = V[e / R][e % R];
+#pragma unroll
+        for (int u = 0; u < RPL; ++u) {
+            const int i = q + 4 * u;
+            if (i < R && k < R) W[i * R + k] = a[u];
+        }
         if (tid == 0) flags[n] = 0;
         return;
     }
@@ -272,11 +323,19 @@ __global__ __launch_bounds__(256) void als_solve_kernel(const double *__restrict
 
 
 // Row solve, Y = M W (I x R, float64 accumulation), in row tiles staged in
-// LDS with W.  Lane layout: 256 / RC row slots x RC columns (RC = R rounded
-// up to a power of two, R <= kMaxCpR); a tile has RPT rows per slot.
-//   STORE = false: per block, the column sums of Y^2 -> partial[blk][R];
-//   STORE = true:  A(i, c) = Y(i, c) / lambda_c (0 when lambda_c = 0), stored
-//                  as FT (bfloat16: round to nearest even).
+// LDS with W.  Lane layout: TH / RC row slots x RC columns (RC = R rounded
+// up to a power of two, R <= kMaxCpR); a tile has RPT rows per slot, and a
+// workgroup takes tiles_per_block tiles, so that what is summed over workgroups
+// is short enough for the next pass to sum in each of its own:
+//   rownorm_kernel:  per block, the column sums of Y^2 -> partial[blk][R];
+//   rowstore_kernel: lambda_c = sqrt(sum_b partial[b][c]); A(i, c) = Y(i, c) /
+//                    lambda_c (0 when lambda_c = 0) stored as FT (bfloat16: round
+//                    to nearest even); the block's share of A^T A from the
+//                    stored values on the matrix cores -> gpart[blk][R x R];
+//                    and (ipart) of the fit's sum_i sum_r lambda_r M(i, r) A(i, r).
+// (As five kernels -- norms, lambda, store, partial Gram, inner product -- they
+// took 11 + 5 + 10 + 13 us a mode, 14 the last, over the modes of 50k to 1k rows
+// at R = 32, now 12 + 16; for 200 rows at R = 8 21 us, now 8.)
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 {
     const uint32_t u = __float_as_uint(f);
@@ -284,117 +343,240 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 }
 
 template <int RC> struct RowTile {
-    static constexpr int SLOTS = 256 / RC;
-    static constexpr int RPT = RC >= 4 ? RC / 4 : 1;          // rows per slot per tile
+    // threads: the products read M's tile from LDS, and one wave a SIMD waited
+    // on each read (24 us a pass at R = 32 where 16 waves a CU take 12)
+    static constexpr int TH = RC >= 16 ? 1024 : 256;
+    static constexpr int SLOTS = TH / RC;
+    static constexpr int RPT = SLOTS < 64 ? 64 / SLOTS : 1;   // rows per slot per tile
     static constexpr int ROWS = SLOTS * RPT;                  // rows per tile (64 .. 256)
+    static constexpr int LD = RC >= 4 ? RC + 4 : RC;          // row stride of M's tile in LDS
 };
 
-template <typename FT, int RC, bool STORE>
-__global__ __launch_bounds__(256) void rowsolve_kernel(const float *__restrict__ M, const double *__restrict__ W,
-                                                       const double *__restrict__ lambda, int64_t I, int R,
-                                                       int tiles_per_block, double *__restrict__ partial,
-                                                       FT *__restrict__ A)
+template <int RC>
+__device__ __forceinline__ void load_w(const double *__restrict__ W, int R, double (&sW)[RC * RC])
 {
-    using RT = RowTile<RC>;
-    __shared__ double sW[RC * RC];
-    __shared__ float sM[RT::ROWS * (RC + 1)];
-    __shared__ double red[256];
-    const int tid = threadIdx.x;
-    const int slot = tid / RC, c = tid % RC;
-    for (int e = tid; e < RC * RC; e += 256) {
+    for (int e = threadIdx.x; e < RC * RC; e += RowTile<RC>::TH) {
         const int k = e / RC, cc = e % RC;
         sW[e] = (k < R && cc < R) ? W[k * R + cc] : 0.0;
     }
-    const double lam = (STORE && c < R) ? lambda[c] : 0.0;
+}
+
+// rows [i0, i0 + nrow) of M, zeros past them and past column R
+template <int RC>
+__device__ __forceinline__ void load_m(const float *__restrict__ M, int64_t i0, int nrow, int R, float *sM)
+{
+    using RT = RowTile<RC>;
+    for (int e = threadIdx.x; e < RT::ROWS * RC; e += RT::TH) {
+        const int r = e / RC, cc = e % RC;
+        sM[r * RT::LD + cc] = (r < nrow && cc < R) ? M[(i0 + r) * R + cc] : 0.f;
+    }
+}
+
+// y[u] = (row u SLOTS + slot of the tile) . (column c of W)
+template <int RC>
+__device__ __forceinline__ void row_products(const float *sM, const double (&sW)[RC * RC], int slot, int c,
+                                             double (&y)[RowTile<RC>::RPT])
+{
+    using RT = RowTile<RC>;
+#pragma unroll
+    for (int u = 0; u < RT::RPT; ++u) y[u] = 0.0;
+    if constexpr (RC >= 4) {
+#pragma unroll 2
+        for (int k = 0; k < RC; k += 4) {
+            const double w0 = sW[k * RC + c], w1 = sW[(k + 1) * RC + c];
+            const double w2 = sW[(k + 2) * RC + c], w3 = sW[(k + 3) * RC + c];
+#pragma unroll
+            for (int u = 0; u < RT::RPT; ++u) {
+                const float4 m = *reinterpret_cast<const float4 *>(sM + (u * RT::SLOTS + slot) * RT::LD + k);
+                y[u] += (double)m.x * w0;
+                y[u] += (double)m.y * w1;
+                y[u] += (double)m.z * w2;
+                y[u] += (double)m.w * w3;
+            }
+        }
+    } else {
+        for (int k = 0; k < RC; ++k) {
+            const double wk = sW[k * RC + c];
+#pragma unroll
+            for (int u = 0; u < RT::RPT; ++u) y[u] += (double)sM[(u * RT::SLOTS + slot) * RT::LD + k] * wk;
+        }
+    }
+}
+
+template <int RC>
+__global__ __launch_bounds__(RowTile<RC>::TH) void rownorm_kernel(const float *__restrict__ M, const double *__restrict__ W,
+                                                      int64_t I, int R, int tiles_per_block,
+                                                      double *__restrict__ partial)
+{
+    using RT = RowTile<RC>;
+    __shared__ double sW[RC * RC];
+    __shared__ __align__(16) float sM[RT::ROWS * RT::LD];
+    __shared__ double red[RT::TH];
+    const int tid = threadIdx.x;
+    const int slot = tid / RC, c = tid % RC;
+    load_w<RC>(W, R, sW);
     double ss = 0.0;
     const int64_t first = (int64_t)blockIdx.x * tiles_per_block * RT::ROWS;
     for (int tt = 0; tt < tiles_per_block; ++tt) {
         const int64_t i0 = first + (int64_t)tt * RT::ROWS;
         if (i0 >= I) break;
-        const int nrow = I - i0 < RT::ROWS ? (int)(I - i0) : RT::ROWS;
         __syncthreads();                                   // sW written / previous tile consumed
-        for (int e = tid; e < nrow * R; e += 256) sM[(e / R) * (RC + 1) + e % R] = M[i0 * R + e];
+        load_m<RC>(M, i0, I - i0 < RT::ROWS ? (int)(I - i0) : RT::ROWS, R, sM);
         __syncthreads();
         double y[RT::RPT];
+        row_products<RC>(sM, sW, slot, c, y);
 #pragma unroll
-        for (int u = 0; u < RT::RPT; ++u) y[u] = 0.0;
-        for (int k = 0; k < R; ++k) {
-            const double wk = sW[k * RC + c];
+        for (int u = 0; u < RT::RPT; ++u) ss += y[u] * y[u];   // rows and columns past the end are 0
+    }
+    red[tid] = ss;
+    __syncthreads();
+    if (tid < R) {
+        double s = 0.0;
+        for (int k = 0; k < RT::SLOTS; ++k) s += red[k * RC + tid];
+        partial[(int64_t)blockIdx.x * R + tid] = s;
+    }
+}
+
+template <typename FT, int RC>
+__global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *__restrict__ M, const double *__restrict__ W,
+                                                       const double *__restrict__ partial, int64_t I, int R,
+                                                       int tiles_per_block, double *__restrict__ lambda,
+                                                       FT *__restrict__ A, double *__restrict__ gpart,
+                                                       double *__restrict__ ipart)
+{
+    using RT = RowTile<RC>;
+    __shared__ double sW[RC * RC];
+    __shared__ __align__(16) float sM[RT::ROWS * RT::LD];      // M's tile, then the stored rows
+    __shared__ double red[RT::TH];
+    __shared__ double sLam[RC];
+    __shared__ double gbuf[RC <= 32 ? 32 * 32 : 1];            // (RC = 64: four tiles, in W's place)
+    const int tid = threadIdx.x;
+    const int slot = tid / RC, c = tid % RC;
+    load_w<RC>(W, R, sW);
+    {   // lambda, in the same order in every workgroup
+        double s = 0.0;
+        const int nblk = gridDim.x;
+        if (c < R)
+            for (int b = slot; b < nblk; b += 8 * RT::SLOTS) {
+                double v[8];
 #pragma unroll
-            for (int u = 0; u < RT::RPT; ++u) y[u] += (double)sM[(u * RT::SLOTS + slot) * (RC + 1) + k] * wk;
+                for (int u = 0; u < 8; ++u) v[u] = b + u * RT::SLOTS < nblk ? partial[(int64_t)(b + u * RT::SLOTS) * R + c] : 0.0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += v[u];
+            }
+        red[tid] = s;
+        __syncthreads();
+        if (tid < RC) {
+            double l = 0.0;
+            for (int k = 0; k < RT::SLOTS; ++k) l += red[k * RC + tid];
+            l = tid < R ? sqrt(l) : 0.0;
+            sLam[tid] = l;
+            if (blockIdx.x == 0 && tid < R) lambda[tid] = l;
         }
+        __syncthreads();
+    }
+    const double lam = sLam[c];
+    double inner = 0.0;
+    // this wave's part of the block's Gram: a share of the rows of the one 32 x 32
+    // tile, or with RC = 64 of tile (w / 2 % 2, w % 2).  bfloat16 keeps the order of
+    // sums of gram_partial_kernel (wave 0, or with RC = 64 waves 0 .. 3, 8 rows a step, in float32 over each 256 rows: a block's tiles are
+    // whole numbers of them)
+    const int lane = tid & 63, w = tid >> 6, kk = lane >> 5;
+    const int ca = (RC <= 32 ? 0 : (w >> 1 & 1) * 32) + (lane & 31), cb = (RC <= 32 ? 0 : (w & 1) * 32) + (lane & 31);
+    constexpr int NW = RT::TH / 64, GP = RC <= 32 ? NW : NW / 4;   // waves, waves per tile
+    constexpr int GR = RT::ROWS / GP;
+    const int g0 = (RC <= 32 ? w : w >> 2) * GR;
+    double gsum[16];
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { gsum[v] = 0.0; acc[v] = 0.f; }
+    auto flush = [&]() {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { gsum[v] += (double)acc[v]; acc[v] = 0.f; }
+    };
+    const int64_t first = (int64_t)blockIdx.x * tiles_per_block * RT::ROWS;
+    for (int tt = 0; tt < tiles_per_block; ++tt) {
+        const int64_t i0 = first + (int64_t)tt * RT::ROWS;
+        if (i0 >= I) break;
+        const int nrow = I - i0 < RT::ROWS ? (int)(I - i0) : RT::ROWS;
+        __syncthreads();                                   // previous tile consumed
+        load_m<RC>(M, i0, nrow, R, sM);
+        __syncthreads();
+        double y[RT::RPT];
+        row_products<RC>(sM, sW, slot, c, y);
+        __syncthreads();                                   // from here each element is its own thread's
 #pragma unroll
         for (int u = 0; u < RT::RPT; ++u) {
             const int r = u * RT::SLOTS + slot;
-            if (r < nrow && c < R) {
-                if constexpr (STORE) {
-                    const double a = lam > 0.0 ? y[u] / lam : 0.0;
-                    const int64_t o = (i0 + r) * R + c;
-                    if constexpr (sizeof(FT) == 4) reinterpret_cast<float *>(A)[o] = (float)a;
-                    else reinterpret_cast<uint16_t *>(A)[o] = f32_to_bf16_rne((float)a);
-                } else {
-                    ss += y[u] * y[u];
+            float f = lam > 0.0 ? (float)(y[u] / lam) : 0.f;
+            const int64_t o = (i0 + r) * R + c;
+            const bool in = r < nrow && c < R;
+            if constexpr (sizeof(FT) == 4) {
+                if (in) reinterpret_cast<float *>(A)[o] = f;
+            } else {
+                const uint16_t h = f32_to_bf16_rne(f);
+                if (in) reinterpret_cast<uint16_t *>(A)[o] = h;
+                f = bf16_to_f32(h);
+            }
+            if (ipart && in) inner += lam * (double)sM[r * RT::LD + c] * (double)f;
+            sM[r * RT::LD + c] = in ? f : 0.f;
+        }
+        __syncthreads();
+        if constexpr (sizeof(FT) == 2) {
+            if (w >= (RC <= 32 ? 1 : 4)) continue;
+#pragma unroll 4
+            for (int i = 0; i < RT::ROWS; i += 8) {
+                shortx4 av, bv;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float *row = sM + (i + 4 * kk + t) * RT::LD;
+                    av[t] = (short)(ca < RC ? __float_as_uint(row[ca]) >> 16 : 0u);
+                    bv[t] = (short)(cb < RC ? __float_as_uint(row[cb]) >> 16 : 0u);
                 }
+                acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
+            }
+            if ((i0 + RT::ROWS) % kGramFlush<FT> == 0 || i0 + RT::ROWS >= I) flush();
+            continue;
+        }
+#pragma unroll 8
+        for (int i = 0; i < GR; i += 2) {
+            const int row = (g0 + i + kk) * RT::LD;
+            const float av = ca < RC ? sM[row + ca] : 0.f, bv = cb < RC ? sM[row + cb] : 0.f;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
+        }
+        flush();
+    }
+    double *gp = gpart + (int64_t)blockIdx.x * R * R;
+    // the waves' shares of a tile added in turn
+    double *gred = RC <= 32 ? gbuf : sW;
+    __syncthreads();                                           // W has been read
+    constexpr bool ONE = sizeof(FT) == 2;
+    for (int k = 0; k < (ONE ? 1 : GP); ++k) {
+        if ((RC <= 32 ? w : w >> 2) == k) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                double &x = gred[(RC <= 32 ? 0 : w & 3) * 1024 + (8 * (v >> 2) + 4 * kk + (v & 3)) * 32 + (lane & 31)];
+                x = k ? x + gsum[v] : gsum[v];
             }
         }
-    }
-    if constexpr (!STORE) {
-        red[tid] = ss;
         __syncthreads();
-        if (tid < R) {
-            double s = 0.0;
-            for (int k = 0; k < RT::SLOTS; ++k) s += red[k * RC + tid];
-            partial[(int64_t)blockIdx.x * R + tid] = s;
+    }
+    for (int e = tid; e < R * R; e += RT::TH) {
+        const int gi = e / R, gj = e % R;
+        gp[e] = gred[(RC <= 32 ? 0 : (gi >> 5) * 2 + (gj >> 5)) * 1024 + (gi & 31) * 32 + (gj & 31)];
+    }
+    if (ipart) {
+        red[tid] = inner;
+        __syncthreads();
+        for (int o = RT::TH / 2; o >= 1; o >>= 1) {
+            if (tid < o) red[tid] += red[tid + o];
+            __syncthreads();
         }
+        if (tid == 0) ipart[blockIdx.x] = red[0];
     }
 }
 
-// lambda_c = sqrt(sum_b partial[b][c]): one workgroup per column, fixed order.
-__global__ __launch_bounds__(256) void lambda_kernel(const double *__restrict__ partial, int64_t nblk, int R,
-                                                     double *__restrict__ lambda)
-{
-    __shared__ double red[256];
-    const int c = blockIdx.x;
-    double s = 0.0;
-    for (int64_t b = threadIdx.x; b < nblk; b += 256) s += partial[b * R + c];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) lambda[c] = sqrt(red[0]);
-}
-
-
-// Fit, pass 1: per block, sum_i sum_r lambda_r M(i, r) A(i, r) in float64.
-template <typename FT>
-__global__ __launch_bounds__(256) void inner_kernel(const float *__restrict__ M, const FT *__restrict__ A,
-                                                    const double *__restrict__ lambda, int64_t I, int R,
-                                                    int rows_per_block, double *__restrict__ partial)
-{
-    __shared__ double red[256];
-    const int64_t b0 = (int64_t)blockIdx.x * rows_per_block;
-    int64_t b1 = b0 + rows_per_block;
-    if (b1 > I) b1 = I;
-    double s = 0.0;
-    for (int64_t e = b0 * R + threadIdx.x; e < b1 * R; e += 256) {
-        const int r = (int)(e % R);
-        float a;
-        if constexpr (sizeof(FT) == 4) a = reinterpret_cast<const float *>(A)[e];
-        else a = bf16_to_f32(reinterpret_cast<const uint16_t *>(A)[e]);
-        s += lambda[r] * (double)M[e] * (double)a;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-// Fit, pass 2 (one workgroup).
+// Fit (one workgroup), from the blocks' inner products.
 __global__ __launch_bounds__(256) void fit_kernel(const double *__restrict__ partial, int64_t nblk,
                                                   const double *__restrict__ grams, int N, int R,
                                                   const double *__restrict__ lambda, double normX2,
@@ -456,40 +638,53 @@ static int rowsolve_rows(int RC)
     }
 }
 
-template <typename FT, bool STORE>
-static hipError_t rowsolve_launch(int RC, int nblk, hipStream_t s, const float *M, const double *W,
-                                  const double *lambda, int64_t I, int R, double *partial, FT *A)
+template <int RC>
+static hipError_t rowsolve_rc(int nblk, int tpb, hipStream_t s, const float *M, const double *W, int64_t I, int R,
+                              double *norms, double *lambda, void *A, int dtype, double *gpart, double *ipart)
 {
-    const dim3 g((unsigned)nblk), b(256);
-    switch (RC) {
-        case 1: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 1, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-        case 2: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 2, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-        case 4: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 4, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-        case 8: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 8, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-        case 16: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 16, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-        case 32: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 32, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-        default: hipLaunchKernelGGL((dev::rowsolve_kernel<FT, 64, STORE>), g, b, 0, s, M, W, lambda, I, R, 1, partial, A); break;
-    }
+    const dim3 g((unsigned)nblk), b(dev::RowTile<RC>::TH);
+    hipLaunchKernelGGL(dev::rownorm_kernel<RC>, g, b, 0, s, M, W, I, R, tpb, norms);
+    if (dtype == FCOO_F32)
+        hipLaunchKernelGGL((dev::rowstore_kernel<float, RC>), g, b, 0, s, M, W, norms, I, R, tpb, lambda, (float *)A,
+                           gpart, ipart);
+    else
+        hipLaunchKernelGGL((dev::rowstore_kernel<dev::bf16raw, RC>), g, b, 0, s, M, W, norms, I, R, tpb, lambda,
+                           (dev::bf16raw *)A, gpart, ipart);
     return hipGetLastError();
+}
+
+// out = sum over nblk blocks of R x R partials
+static hipError_t sum_blocks(const double *partial, int nblk, int R, double *out, hipStream_t s)
+{
+    const int n = R * R;
+    hipLaunchKernelGGL(dev::sum_blocks_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, s, partial, (int64_t)nblk,
+                       (int64_t)n, out);
+    return hipGetLastError();
+}
+
+// rows per Gram workgroup: 256 (bfloat16 1024: whole chains of its order of sums),
+// more past 512 workgroups (bounded partials)
+static int gram_rows(int64_t I, int dtype)
+{
+    const int unit = dtype == FCOO_F32 ? 256 : 1024;
+    return unit * ceil_div(ceil_div(I, 512), unit);
 }
 
 // G = A^T A (float64) of an I x R factor; partials in ws->dbl.
 static int gram_launch(fcoo_tensor *t, const void *A, int dtype, int64_t I, int R, double *G, hipStream_t s)
 {
-    const int nblk = ceil_div(I, dev::kGramRows);
+    const int rows = gram_rows(I, dtype), nblk = ceil_div(I, rows);
     const int ntile = (R + 31) / 32;
     int rc = ensure_device_doubles(&t->ws.dbl, &t->ws.dbl_cap, (int64_t)nblk * R * R + 16, s);
     if (rc) return rc;
     if (dtype == FCOO_F32)
         hipLaunchKernelGGL(dev::gram_partial_kernel<float>, dim3(nblk, ntile * ntile), dim3(256), 0, s,
-                           (const float *)A, I, R, t->ws.dbl);
+                           (const float *)A, I, R, rows, t->ws.dbl);
     else
         hipLaunchKernelGGL(dev::gram_partial_kernel<dev::bf16raw>, dim3(nblk, ntile * ntile), dim3(256), 0, s,
-                           (const dev::bf16raw *)A, I, R, t->ws.dbl);
+                           (const dev::bf16raw *)A, I, R, rows, t->ws.dbl);
     FCOO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(dev::sum_blocks_kernel, dim3((unsigned)((int64_t)R * R)), dim3(64), 0, s,
-                       t->ws.dbl, (int64_t)nblk, (int64_t)R * R, G);
-    FCOO_HIP(hipGetLastError());
+    FCOO_HIP(sum_blocks(t->ws.dbl, nblk, R, G, s));
     return FCOO_OK;
 }
 
@@ -526,70 +721,62 @@ int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, dou
     int64_t maxI = 0;
     for (int n = 0; n < N; ++n) maxI = t->dims[n] > maxI ? t->dims[n] : maxI;
     if ((rc = ensure_device_floats(&t->ws.M, &t->ws.M_cap, maxI * R, s))) return rc;
-    // scratch doubles: gram partials | W | tmp | block partials | fit
+    // scratch doubles: gram partials | W | tmp | column norms | inner products | fit, flags
     const int RC = pow2_ceil(R);
     const int rows_tile = rowsolve_rows(RC);
-    const int inner_rows = R < 8192 ? 8192 / R : 1;              // rows per fit-partial block
-    const int64_t nblk_max = ceil_div(maxI, rows_tile < inner_rows ? rows_tile : inner_rows) + 1;
-    const int64_t gram_need = (int64_t)ceil_div(maxI, dev::kGramRows) * R * R + 16;
-    const int64_t need = 2 * (int64_t)R * R + nblk_max * R + 64 + gram_need;
+    const int64_t gram_blocks = std::max<int64_t>(dev::kCpBlocks, ceil_div(maxI, gram_rows(maxI, dtype)));
+    const int64_t gram_need = gram_blocks * R * R + 16;
+    const int64_t need = gram_need + 2 * (int64_t)R * R + dev::kCpBlocks * (int64_t)R + dev::kCpBlocks + 16;
     if ((rc = ensure_device_doubles(&t->ws.dbl, &t->ws.dbl_cap, need, s))) return rc;
-    if (!t->ws.flags) FCOO_HIP(hipMalloc((void **)&t->ws.flags, 16 * sizeof(int)));
     if (!t->ws.host_pinned) FCOO_HIP(hipHostMalloc((void **)&t->ws.host_pinned, 64, hipHostMallocDefault));
-    double *Wd = t->ws.dbl + gram_need;
+    double *gpart = t->ws.dbl;
+    double *Wd = gpart + gram_need;
     double *tmpd = Wd + (int64_t)R * R;
-    double *part = tmpd + (int64_t)R * R;
-    double *fitd = part + nblk_max * R;
+    double *norms = tmpd + (int64_t)R * R;
+    double *ipart = norms + dev::kCpBlocks * (int64_t)R;
+    double *fitd = ipart + dev::kCpBlocks;
+    int *flagd = reinterpret_cast<int *>(fitd + 1);
 
     if (!grams_valid)
         for (int m = 0; m < N; ++m)
             if ((rc = gram_launch(t, factors[m], dtype, t->dims[m], R, grams + (int64_t)m * R * R, s))) return rc;
 
-    // V_n needs only the Grams of the other modes, which are final before
-    // SpMTTKRP_n starts: the solve runs on a second stream beside it
-    if (!t->aux) {
-        FCOO_HIP(hipStreamCreateWithFlags(&t->aux, hipStreamNonBlocking));
-        FCOO_HIP(hipEventCreateWithFlags(&t->ev_dep, hipEventDisableTiming));
-        FCOO_HIP(hipEventCreateWithFlags(&t->ev_solved, hipEventDisableTiming));
-    }
+    int nblk = 0;
     for (int n = 0; n < N; ++n) {
         const int64_t I = t->dims[n];
-        FCOO_HIP(hipEventRecord(t->ev_dep, s));
-        FCOO_HIP(hipStreamWaitEvent(t->aux, t->ev_dep, 0));
-        hipLaunchKernelGGL(dev::als_solve_kernel, dim3(1), dim3(256), 0, t->aux, grams, N, n, R, Wd, tmpd,
-                           t->ws.flags);
+        if ((rc = spmttkrp(t, n, (const void *const *)factors, dtype, R, t->ws.M, dtype == FCOO_BF16, s))) return rc;
+        // (on the caller's stream: beside the SpMTTKRP, on a stream of its own, the
+        // two waits between the streams cost as much as the solve takes at R = 32
+        // and four times that at R = 8)
+        if (R <= 16) hipLaunchKernelGGL(dev::als_solve_kernel<4>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
+        else if (R <= 32) hipLaunchKernelGGL(dev::als_solve_kernel<8>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
+        else hipLaunchKernelGGL(dev::als_solve_kernel<16>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
         FCOO_HIP(hipGetLastError());
-        FCOO_HIP(hipEventRecord(t->ev_solved, t->aux));
-        if ((rc = fcoo_spmttkrp(t, n, (const void *const *)factors, dtype, R, t->ws.M, stream))) return rc;
-        FCOO_HIP(hipStreamWaitEvent(s, t->ev_solved, 0));
-        const int nblk = ceil_div(I, rows_tile);
-        hipError_t e = rowsolve_launch<float, false>(RC, nblk, s, t->ws.M, Wd, nullptr, I, R, part, nullptr);
-        if (e != hipSuccess) return hip_fail(e, "row solve (norms)");
-        hipLaunchKernelGGL(dev::lambda_kernel, dim3(R), dim3(256), 0, s, part, (int64_t)nblk, R, lambda);
-        FCOO_HIP(hipGetLastError());
-        if (dtype == FCOO_F32)
-            e = rowsolve_launch<float, true>(RC, nblk, s, t->ws.M, Wd, lambda, I, R, nullptr, (float *)factors[n]);
-        else
-            e = rowsolve_launch<dev::bf16raw, true>(RC, nblk, s, t->ws.M, Wd, lambda, I, R, nullptr,
-                                                    (dev::bf16raw *)factors[n]);
-        if (e != hipSuccess) return hip_fail(e, "row solve (store)");
-        if ((rc = gram_launch(t, factors[n], dtype, I, R, grams + (int64_t)n * R * R, s))) return rc;
+        const int ntiles = ceil_div(I, rows_tile);
+        // (bfloat16: whole chains of 256 rows a workgroup, see rowstore_kernel)
+        const int chain = dtype == FCOO_F32 ? 1 : 256 / rows_tile;
+        const int tpb = chain * ceil_div(ceil_div(ntiles, dev::kCpBlocks), chain);
+        nblk = ceil_div(ntiles, tpb);
+        double *ip = n == N - 1 ? ipart : nullptr;
+        hipError_t e;
+        switch (RC) {
+            case 1: e = rowsolve_rc<1>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+            case 2: e = rowsolve_rc<2>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+            case 4: e = rowsolve_rc<4>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+            case 8: e = rowsolve_rc<8>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+            case 16: e = rowsolve_rc<16>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+            case 32: e = rowsolve_rc<32>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+            default: e = rowsolve_rc<64>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+        }
+        if (e != hipSuccess) return hip_fail(e, "row solve");
+        FCOO_HIP(sum_blocks(gpart, nblk, R, grams + (int64_t)n * R * R, s));
     }
-    const int64_t IN = t->dims[N - 1];
-    const int nblk = ceil_div(IN, inner_rows);
-    if (dtype == FCOO_F32)
-        hipLaunchKernelGGL(dev::inner_kernel<float>, dim3(nblk), dim3(256), 0, s, t->ws.M,
-                           (const float *)factors[N - 1], lambda, IN, R, inner_rows, part);
-    else
-        hipLaunchKernelGGL(dev::inner_kernel<dev::bf16raw>, dim3(nblk), dim3(256), 0, s, t->ws.M,
-                           (const dev::bf16raw *)factors[N - 1], lambda, IN, R, inner_rows, part);
-    FCOO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(dev::fit_kernel, dim3(1), dim3(256), 0, s, part, (int64_t)nblk, grams, N, R, lambda,
+    hipLaunchKernelGGL(dev::fit_kernel, dim3(1), dim3(256), 0, s, ipart, (int64_t)nblk, grams, N, R, lambda,
                        t->normX2, fitd);
     FCOO_HIP(hipGetLastError());
-    FCOO_HIP(hipMemcpyAsync(t->ws.host_pinned, fitd, sizeof(double), hipMemcpyDeviceToHost, s));
+    // the fit and, next to it, the modes' flags
     int *hflags = reinterpret_cast<int *>(t->ws.host_pinned + 1);
-    FCOO_HIP(hipMemcpyAsync(hflags, t->ws.flags, (size_t)N * sizeof(int), hipMemcpyDeviceToHost, s));
+    FCOO_HIP(hipMemcpyAsync(t->ws.host_pinned, fitd, sizeof(double) + (size_t)N * sizeof(int), hipMemcpyDeviceToHost, s));
     FCOO_HIP(hipStreamSynchronize(s));
     *fit = t->ws.host_pinned[0];
     if (used_pinv) {

@@ -235,9 +235,8 @@ void Workspace::free_all()
 {
     if (M) (void)hipFree(M);
     if (dbl) (void)hipFree(dbl);
-    if (flags) (void)hipFree(flags);
     if (host_pinned) (void)hipHostFree(host_pinned);
-    M = nullptr; dbl = nullptr; flags = nullptr; host_pinned = nullptr;
+    M = nullptr; dbl = nullptr; host_pinned = nullptr;
     M_cap = dbl_cap = 0;
 }
 
@@ -905,9 +904,6 @@ void fcoo_destroy(fcoo_tensor *t)
     for (auto &p : t->d_coo) if (p) (void)hipFree(p);
     if (t->d_coo_val) (void)hipFree(t->d_coo_val);
     t->ws.free_all();
-    if (t->ev_dep) (void)hipEventDestroy(t->ev_dep);
-    if (t->ev_solved) (void)hipEventDestroy(t->ev_solved);
-    if (t->aux) (void)hipStreamDestroy(t->aux);
     delete t;
     pool_handles(-1);
 }
@@ -920,7 +916,7 @@ void fcoo_destroy(fcoo_tensor *t)
 // partial output (nblk x rows x width floats) of the build.
 static int prep_tiles(Built *b, TileProblem &p, bool resid, hipStream_t s)
 {
-    p.plan = &pick_plan(*b, p.dtype, p.R, resid, p.kron);
+    p.plan = p.keep_order ? &b->plan[0] : &pick_plan(*b, p.dtype, p.R, resid, p.kron);
     int rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * p.plan->ntiles * (int64_t)p.R, s);
     if (rc) return rc;
     p.carry = b->d_carry;
@@ -935,13 +931,20 @@ int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtyp
                   void *stream)
 {
     clear_error();
+    return spmttkrp(t, mode, factors, dtype, R, M, false, (hipStream_t)stream);
+}
+
+}  // extern "C"
+
+int fcoo::spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtype, int R, float *M, bool keep_order,
+                   hipStream_t s)
+{
     int rc;
     Built *b = get_built(t, mode, FCOO_OP_MTTKRP, true, &rc);
     if (!b) return rc;
     rc = check_factors(t, mode, factors, dtype, R);
     if (rc) return rc;
     if (!M) return fail(FCOO_EINVAL, "M is NULL");
-    hipStream_t s = (hipStream_t)stream;
     TileProblem p{};
     p.b = b;
     for (size_t q = 0; q < b->pmodes.size(); ++q) p.fac[q] = factors[b->pmodes[q]];
@@ -949,12 +952,15 @@ int fcoo_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtyp
     p.dtype = dtype;
     p.R = R;
     p.out = M;
+    p.keep_order = keep_order;
     if ((rc = prep_tiles(b, p, false, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     p.ev_before = t->ev_before;
     p.ev_after = t->ev_after;
     return launch_segmented(p, s, false);
 }
+
+extern "C" {
 
 int fcoo_spttmc(fcoo_tensor *t, int mode, const void *const *factors, int dtype, const int *ranks,
                 float *Y, void *stream)

@@ -129,8 +129,7 @@ struct Built {
 struct Workspace {
     float *M = nullptr;          int64_t M_cap = 0;      // floats
     double *dbl = nullptr;       int64_t dbl_cap = 0;    // doubles
-    int *flags = nullptr;                               // device ints (pinv flags)
-    double *host_pinned = nullptr;                      // fit readback
+    double *host_pinned = nullptr;                      // fit and flags readback
     void free_all();
 };
 
@@ -154,9 +153,6 @@ struct fcoo_tensor {
 
     // optional events recorded around each tile kernel (caller-owned)
     hipEvent_t ev_before = nullptr, ev_after = nullptr;
-    // CP-ALS: second stream for the R x R solve (default priority), created on first use
-    hipStream_t aux = nullptr;
-    hipEvent_t ev_dep = nullptr, ev_solved = nullptr;
 };
 
 namespace fcoo {
@@ -231,6 +227,12 @@ struct TileProblem {
     bool kron = false;
     int kr[kMaxOrder] = {};          // per product mode q: columns of its factor
     int64_t fac_rows[kMaxOrder] = {};   // and its rows
+    // sums in one order whatever tile and lane shapes are best: the format's tiles,
+    // runs and chains.  CP-ALS with bfloat16 factors asks for it: there a last-bit
+    // change of M moves a stored factor by a whole bfloat16 step, which the
+    // following modes amplify (to 1e-3 of lambda within two sweeps), and two
+    // versions of the library would no longer agree to float32 accuracy
+    bool keep_order = false;
     // single pass (set by prep_single_pass; sp_words null: carries + fix-up)
     uint64_t *sp_words = nullptr;
     uint32_t sp_epoch = 0;
@@ -238,11 +240,14 @@ struct TileProblem {
 // single-pass words of a build for a launch of width R (no-op for other builds)
 int prep_single_pass(Built *b, TileProblem &p, hipStream_t s);
 // how rows of R columns are spread over lanes: columns per lane, lanes per
-// nonzero (at most 16), bfloat16 in 4-column chunks
+// nonzero (at most 16; 64 of one column each), bfloat16 in 4-column chunks
 struct LaneShape { int vw, lpn; bool half; };
-LaneShape lane_shape(const Built &b, int dtype, int R, bool resid);
+LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_order = false);
 // the tiles a launch over rows of width R takes
 const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron);
+// fcoo_spmttkrp, with the sums' order kept (TileProblem)
+int spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtype, int R, float *M, bool keep_order,
+             hipStream_t s);
 int launch_ttmc(const TileProblem &p, float *out, hipStream_t s);
 int launch_segmented(const TileProblem &p, hipStream_t s, bool resid);
 int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s);

@@ -37,6 +37,7 @@ struct FinishArgs {
     double scale;
     double *loss;
     int nfix, nlong, fblk, zblk, R;
+    bool in_turn;                    // chains on 256 threads, 8 tiles' carries in turn (TileProblem::keep_order)
 };
 
 constexpr int kFinish = 1024;        // threads per workgroup
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
     if ((int)blockIdx.x < A.fblk) {
         __shared__ float red_s[kFinish];
         const bool is_long = (int)blockIdx.x < A.nlong;
-        const int n = is_long ? kFinish : 256;                       // threads of a chain
+        const int n = is_long && !A.in_turn ? kFinish : 256;         // threads of a chain (those past n add nothing)
         const int part = is_long ? 0 : (int)threadIdx.x / 256, tid = (int)threadIdx.x - part * 256;
         const int e = is_long ? (int)blockIdx.x : A.nlong + ((int)blockIdx.x - A.nlong) * 4 + part;
         float *red = red_s + part * 256;
@@ -68,6 +69,11 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
                     float x[kChain];
 #pragma unroll
                     for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? A.ca[(int64_t)(t + u * slots) * R + c] : 0.f;
+                    if (A.in_turn) {
+#pragma unroll
+                        for (int u = 0; u < kChain; ++u) s += x[u];
+                        continue;
+                    }
                     // (in pairs: a wide row has one slot, and a chain of a thousand
                     // tiles would be as many roundings in a row)
 #pragma unroll
@@ -214,7 +220,7 @@ static int grid_for(int64_t work, int64_t per_block, int cap = 65535 * 8)
     return (int)g;
 }
 
-LaneShape lane_shape(const Built &b, int dtype, int R, bool resid)
+LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_order)
 {
     // bfloat16 in 4-column (8-byte) lane chunks: twice the rows per gather
     // batch at 4 waves per SIMD, against 8-column chunks at 3 waves.  The
@@ -231,6 +237,11 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid)
     // per lane, 64 lanes a nonzero: SpMTTKRP of 4M nonzeros, order 4, R = 25
     // took 323 us and takes 100; SpTTM of 300k, bfloat16 R = 10, 321 and 16)
     sh.vw = (dtype == FCOO_F32 || sh.half) ? 4 : 8;
+    if (keep_order && R % sh.vw) {
+        // such ranks have their sums' order from a time of one column a lane
+        const bool half = half_ok && R % 4 == 0 && sh.half;
+        return half ? LaneShape{4, next_pow2(R / 4), true} : LaneShape{1, 64, false};
+    }
     while (sh.vw > R) sh.vw >>= 1;
     sh.lpn = next_pow2((R + sh.vw - 1) / sh.vw);
     if (sh.lpn > 16) sh.lpn = 16;
@@ -270,7 +281,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         a.tile_nnz = pl.T;
         a.nseg = (int)b.nseg;
         a.inv_nnz = p.inv_nnz;
-        const LaneShape sh = lane_shape(b, p.dtype, R, resid);
+        const LaneShape sh = lane_shape(b, p.dtype, R, resid, p.keep_order);
         L.vw = sh.vw;
         L.half = sh.half;
         L.lpn = sh.lpn;
@@ -330,6 +341,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         f.scale = p.loss_scale;
         f.loss = p.loss;
         f.R = R;
+        f.in_turn = p.keep_order;
         hipLaunchKernelGGL(dev::finish_kernel, dim3((unsigned)(f.fblk + f.zblk + (p.loss ? 1 : 0))), dim3(dev::kFinish), 0,
                            s, f);
         FCOO_HIP(hipGetLastError());

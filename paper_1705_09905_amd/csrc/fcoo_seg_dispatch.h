@@ -10,7 +10,7 @@ namespace fcoo {
 struct SegLaunch {
     dev::SegArgs args;
     int vw;          // columns per lane: 8 (bfloat16), 4, 2 or 1
-    int lpn;         // lanes per nonzero: 1, 2, 4, 8 or 16
+    int lpn;         // lanes per nonzero: 1, 2, 4, 8 or 16 (64: one column each)
     int npt;         // product modes as a template value: 1, 2, 3, or 0 (runtime count)
     bool rowmap;     // output row = seg_row[segment] (SpMTTKRP) or the segment ordinal (SpTTM)
     bool half;       // bfloat16 in 4-column (8-byte) lane chunks, R <= 64
@@ -58,6 +58,13 @@ static hipError_t seg_dispatch(const SegLaunch &L, hipStream_t s)
 template <typename FT, bool RESID>
 static hipError_t seg_dispatch_narrow(const SegLaunch &L, hipStream_t s)
 {
+    if constexpr (sizeof(FT) == 2 && !RESID) {
+        if (L.lpn == 64) {           // a wave per nonzero, one column a lane (SpMTTKRP, kept order of sums)
+            if (L.npt == 2) return seg_go<FT, 1, 64, 2, false, true>(L, s);
+            if (L.npt == 3) return seg_go<FT, 1, 64, 3, false, true>(L, s);
+            return seg_go<FT, 1, 64, 0, false, true>(L, s);
+        }
+    }
     if (L.vw == 1) {
         if constexpr (!RESID) {
             if (!L.rowmap) return seg_go<FT, 1, 1, 0, false, false>(L, s);
