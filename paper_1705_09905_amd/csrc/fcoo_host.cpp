@@ -596,11 +596,11 @@ void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::v
     int64_t at = 0;
     for (Plan &pl : b.plan) {
         const int64_t ntiles = pl.ntiles, k = pl.T / b.plan.back().T, nfine = b.plan.back().ntiles;
-        std::vector<int32_t> shorter;
+        std::vector<int32_t> middle, shortest;
         pl.fix.clear();
         int64_t last = -1;
         auto add = [&](int64_t tb, int64_t g) {
-            std::vector<int32_t> &to = tb - last > kLongChain ? pl.fix : shorter;
+            std::vector<int32_t> &to = tb - last > kLongChain ? pl.fix : tb - last > 2 ? middle : shortest;
             to.push_back((int32_t)tb);
             to.push_back((int32_t)last);
             to.push_back(out_row(g));
@@ -613,7 +613,9 @@ void finish_tiles(const fcoo_tensor *t, Built &b, int mode, int op, const std::v
         }
         if (b.nnz > 0) add(ntiles, cnt - 1);
         pl.nlong = pl.nfix();
-        pl.fix.insert(pl.fix.end(), shorter.begin(), shorter.end());
+        pl.nshort = (int64_t)shortest.size() / 3;
+        pl.fix.insert(pl.fix.end(), middle.begin(), middle.end());
+        pl.fix.insert(pl.fix.end(), shortest.begin(), shortest.end());
         pl.fix_at = at;
         at += pl.nfix();
     }

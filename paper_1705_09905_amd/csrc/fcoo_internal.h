@@ -42,9 +42,10 @@ struct Plan {
     int T = 0;
     int64_t ntiles = 0;
     // carry fix-up list: (closing tile b, chain start tile a, output row) per
-    // entry, the nlong chains of more than kLongChain tiles first
+    // entry, the nlong chains of more than kLongChain tiles first, the nshort
+    // chains with at most one tile between their ends last
     std::vector<int32_t> fix;
-    int64_t nlong = 0;
+    int64_t nlong = 0, nshort = 0;
     int64_t fix_at = 0;                       // its first entry in d_fix
     std::vector<int64_t> blk_ts;              // nblk + 1 tile starts: block b's tiles [blk_ts[b], blk_ts[b+1])
     int64_t nfix() const { return (int64_t)fix.size() / 3; }

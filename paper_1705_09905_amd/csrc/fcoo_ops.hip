@@ -18,10 +18,14 @@ namespace dev {
 //                    (its first partial; b = ntiles is the end of the tensor),
 //                    with tiles a+1 .. b-1 wholly inside it.  The nlong chains
 //                    of more than kLongChain tiles come first, a workgroup
-//                    each; of the others (most have no tile between) four
-//                    share one.  (With 256 threads for every chain a slice of
-//                    1.3M nonzeros over 1300 tiles took 40 us at R = 256: one
-//                    thread a column);
+//                    each; of the others four share one.  (With 256 threads for
+//                    every chain a slice of 1.3M nonzeros over 1300 tiles took
+//                    40 us at R = 256: one thread a column);
+//   the next sblk    the nshort chains with at most one tile between (nearly all
+//                    where segments are short): a thread a column, kFlat
+//                    elements a workgroup.  (Four such chains a workgroup of
+//                    1024: SpTTM, R = 16, 20M Zipf nonzeros, 19.5k chains, 26.5
+//                    us; now 7);
 //   the next zblk    rows of an MTTKRP result that no nonzero touches: 0;
 //   the last one     the residual form's loss: fixed-order strided sums of the
 //                    tiles' partials, then a tree; bitwise repeatable.
@@ -36,11 +40,12 @@ struct FinishArgs {
     int64_t npartial;
     double scale;
     double *loss;
-    int nfix, nlong, fblk, zblk, R;
+    int nfix, nlong, nshort, fblk, sblk, zblk, R;
     bool in_turn;                    // chains on 256 threads, 8 tiles' carries in turn (TileProblem::keep_order)
 };
 
 constexpr int kFinish = 1024;        // threads per workgroup
+constexpr int kFlat = 1024;          // elements per workgroup of the short chains
 constexpr int kZeroPer = 4096;       // elements per workgroup of the zero rows
 constexpr int kChain = 16;           // carries in flight per thread along a chain
 
@@ -54,7 +59,7 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
         const int part = is_long ? 0 : (int)threadIdx.x / 256, tid = (int)threadIdx.x - part * 256;
         const int e = is_long ? (int)blockIdx.x : A.nlong + ((int)blockIdx.x - A.nlong) * 4 + part;
         float *red = red_s + part * 256;
-        const bool on = e < A.nfix;
+        const bool on = e < A.nfix - A.nshort;
         int tb = 0, ta = 0, row = 0;
         if (on) { tb = A.fix[3 * e]; ta = A.fix[3 * e + 1]; row = A.fix[3 * e + 2]; }
         // columns cw at a time (SpTTMc's rows may be wider than the threads)
@@ -102,9 +107,24 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
         return;
     }
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x < A.fblk + A.zblk) {
+    if ((int)blockIdx.x < A.fblk + A.sblk) {
+        const int per = R < kFlat ? kFlat / R : 1;                       // chains of this workgroup
+        const int e0 = A.nfix - A.nshort + ((int)blockIdx.x - A.fblk) * per;
+        const int n = (A.nfix - e0 < per ? A.nfix - e0 : per) * R;
+#pragma unroll 4
+        for (int i = tid; i < n; i += kFinish) {
+            const int e = e0 + i / R, c = i % R;
+            const int tb = A.fix[3 * e], ta = A.fix[3 * e + 1], row = A.fix[3 * e + 2];
+            float v = A.cb[(int64_t)ta * R + c];
+            if (tb - ta > 1) v += A.ca[(int64_t)(ta + 1) * R + c];
+            if (tb < A.ntiles) v += A.ca[(int64_t)tb * R + c];
+            A.out[(int64_t)row * R + c] = v;
+        }
+        return;
+    }
+    if ((int)blockIdx.x < A.fblk + A.sblk + A.zblk) {
         const int64_t n = A.nempty * R;
-        for (int64_t i0 = ((int64_t)blockIdx.x - A.fblk) * kZeroPer; i0 < n; i0 += (int64_t)A.zblk * kZeroPer) {
+        for (int64_t i0 = ((int64_t)blockIdx.x - A.fblk - A.sblk) * kZeroPer; i0 < n; i0 += (int64_t)A.zblk * kZeroPer) {
 #pragma unroll
             for (int u = 0; u < kZeroPer / kFinish; ++u) {
                 const int64_t i = i0 + u * kFinish + tid;
@@ -327,7 +347,9 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
     f.nfix = b.nnz > 0 && !p.sp_words ? (int)pl.nfix() : 0;
     f.nempty = (int64_t)b.empty_rows.size();
     f.nlong = f.nfix > 0 ? (int)pl.nlong : 0;
-    f.fblk = f.nlong + (f.nfix - f.nlong + 3) / 4;
+    f.nshort = f.nfix > 0 ? (int)pl.nshort : 0;
+    f.fblk = f.nlong + (f.nfix - f.nlong - f.nshort + 3) / 4;
+    f.sblk = f.nshort > 0 ? grid_for(f.nshort, R < dev::kFlat ? dev::kFlat / R : 1, INT32_MAX) : 0;
     f.zblk = f.nempty > 0 ? grid_for(f.nempty * R, dev::kZeroPer, 1 << 20) : 0;
     if (f.nfix + f.zblk > 0 || p.loss) {
         f.fix = b.d_fix + 3 * pl.fix_at;
@@ -342,7 +364,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         f.loss = p.loss;
         f.R = R;
         f.in_turn = p.keep_order;
-        hipLaunchKernelGGL(dev::finish_kernel, dim3((unsigned)(f.fblk + f.zblk + (p.loss ? 1 : 0))), dim3(dev::kFinish), 0,
+        hipLaunchKernelGGL(dev::finish_kernel, dim3((unsigned)(f.fblk + f.sblk + f.zblk + (p.loss ? 1 : 0))), dim3(dev::kFinish), 0,
                            s, f);
         FCOO_HIP(hipGetLastError());
     }
