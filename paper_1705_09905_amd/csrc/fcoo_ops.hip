@@ -245,12 +245,17 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_ord
     // bfloat16 in 4-column (8-byte) lane chunks: twice the rows per gather
     // batch at 4 waves per SIMD, against 8-column chunks at 3 waves.  The
     // build's lane_cols picks (fcoo_autotune times both); by default 4
-    // columns with exactly two product modes (with three, the batch per mode
-    // gets short and 8-column chunks won on the order-4 Zipf tensor)
+    // columns for SpMTTKRP with exactly two product modes (with three, the
+    // batch per mode gets short and 8-column chunks won on the order-4 Zipf
+    // tensor), and for SpTTM, whose 32 bytes of output per 8 columns would
+    // leave in two halves (8 / 4 columns, 20M nonzeros, Zipf, us: R = 8 266 /
+    // 185, 24 411 / 368, 64 509 / 449, uniform 1848 / 1102), but for rows of 16
+    // (236 / 253, uniform 508 / 603) or 32 (301 / 320, uniform 730 / 681)
     const int np = (int)b.pmodes.size();
     const bool half_ok = dtype == FCOO_BF16 && !resid && np <= 3 && R >= 4 && R <= 64;
     LaneShape sh;
-    sh.half = half_ok && (b.lane_cols == 4 || R < 8 || (b.lane_cols == 0 && np == 2 && b.op == FCOO_OP_MTTKRP));
+    sh.half = half_ok && (b.lane_cols == 4 || R < 8 ||
+                          (b.lane_cols == 0 && (b.op == FCOO_OP_TTM ? R != 16 && R != 32 : np == 2)));
     // columns per lane: the type's vector, or the widest piece a shorter row
     // holds.  A row need not be a multiple of it: its last piece ends at
     // column R and overlaps the one before.  (Such rows once ran one column
@@ -311,7 +316,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         if (resid && R > most)
             return fail(FCOO_EUNSUPPORTED, "fused residual needs R <= %d for this dtype (R = %d)", most, R);
         L.npt = np <= 3 ? np : 0;
-        L.rowmap = b.op == FCOO_OP_MTTKRP;
+        L.out = b.op == FCOO_OP_MTTKRP ? dev::kOutMap : R % 16 == 0 ? dev::kOutStream : dev::kOutPlain;
         a.nblk = b.nblk;
         a.rows_own = (int)b.rows;
         if (p.sp_words) {

@@ -12,31 +12,38 @@ struct SegLaunch {
     int vw;          // columns per lane: 8 (bfloat16), 4, 2 or 1
     int lpn;         // lanes per nonzero: 1, 2, 4, 8 or 16 (64: one column each)
     int npt;         // product modes as a template value: 1, 2, 3, or 0 (runtime count)
-    bool rowmap;     // output row = seg_row[segment] (SpMTTKRP) or the segment ordinal (SpTTM)
+    int out;         // dev::kOutMap (SpMTTKRP), kOutStream or kOutPlain (SpTTM)
     bool half;       // bfloat16 in 4-column (8-byte) lane chunks, R <= 64
     dim3 grid;
 };
 
-template <typename FT, int VW, int LPN, int NP, bool RESID, bool ROWMAP>
+template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT>
 static hipError_t seg_go(const SegLaunch &L, hipStream_t s)
 {
-    hipLaunchKernelGGL((dev::seg_tile_kernel<FT, VW, LPN, NP, RESID, ROWMAP>), L.grid, dim3(256), 0, s,
+    hipLaunchKernelGGL((dev::seg_tile_kernel<FT, VW, LPN, NP, RESID, OUT>), L.grid, dim3(256), 0, s,
                        L.args);
     return hipGetLastError();
 }
 
 // SpTTM has one product mode and identity row map; SpMTTKRP maps rows.
+template <typename FT, int VW, int LPN, int NP>
+static hipError_t seg_ttm(const SegLaunch &L, hipStream_t s)
+{
+    if (L.out == dev::kOutStream) return seg_go<FT, VW, LPN, NP, false, dev::kOutStream>(L, s);
+    return seg_go<FT, VW, LPN, NP, false, dev::kOutPlain>(L, s);
+}
+
 template <typename FT, int VW, int LPN, bool RESID>
 static hipError_t seg_np(const SegLaunch &L, hipStream_t s)
 {
     if constexpr (!RESID) {
-        if (!L.rowmap) return seg_go<FT, VW, LPN, 1, false, false>(L, s);
+        if (L.out != dev::kOutMap) return seg_ttm<FT, VW, LPN, 1>(L, s);
     }
     switch (L.npt) {
-        case 1: return seg_go<FT, VW, LPN, 1, RESID, true>(L, s);
-        case 2: return seg_go<FT, VW, LPN, 2, RESID, true>(L, s);
-        case 3: return seg_go<FT, VW, LPN, 3, RESID, true>(L, s);
-        default: return seg_go<FT, VW, LPN, 0, RESID, true>(L, s);
+        case 1: return seg_go<FT, VW, LPN, 1, RESID, dev::kOutMap>(L, s);
+        case 2: return seg_go<FT, VW, LPN, 2, RESID, dev::kOutMap>(L, s);
+        case 3: return seg_go<FT, VW, LPN, 3, RESID, dev::kOutMap>(L, s);
+        default: return seg_go<FT, VW, LPN, 0, RESID, dev::kOutMap>(L, s);
     }
 }
 
@@ -60,16 +67,16 @@ static hipError_t seg_dispatch_narrow(const SegLaunch &L, hipStream_t s)
 {
     if constexpr (sizeof(FT) == 2 && !RESID) {
         if (L.lpn == 64) {           // a wave per nonzero, one column a lane (SpMTTKRP, kept order of sums)
-            if (L.npt == 2) return seg_go<FT, 1, 64, 2, false, true>(L, s);
-            if (L.npt == 3) return seg_go<FT, 1, 64, 3, false, true>(L, s);
-            return seg_go<FT, 1, 64, 0, false, true>(L, s);
+            if (L.npt == 2) return seg_go<FT, 1, 64, 2, false, dev::kOutMap>(L, s);
+            if (L.npt == 3) return seg_go<FT, 1, 64, 3, false, dev::kOutMap>(L, s);
+            return seg_go<FT, 1, 64, 0, false, dev::kOutMap>(L, s);
         }
     }
     if (L.vw == 1) {
         if constexpr (!RESID) {
-            if (!L.rowmap) return seg_go<FT, 1, 1, 0, false, false>(L, s);
+            if (L.out != dev::kOutMap) return seg_ttm<FT, 1, 1, 0>(L, s);
         }
-        return seg_go<FT, 1, 1, 0, RESID, true>(L, s);
+        return seg_go<FT, 1, 1, 0, RESID, dev::kOutMap>(L, s);
     }
     if (L.vw == 2) return L.lpn == 1 ? seg_np<FT, 2, 1, RESID>(L, s) : seg_np<FT, 2, 2, RESID>(L, s);
     if constexpr (sizeof(FT) == 2) return L.lpn == 1 ? seg_np<FT, 4, 1, RESID>(L, s) : seg_np<FT, 4, 2, RESID>(L, s);
@@ -81,11 +88,11 @@ static hipError_t seg_dispatch_narrow(const SegLaunch &L, hipStream_t s)
 template <typename FT, int LPN>
 static hipError_t seg_np_half(const SegLaunch &L, hipStream_t s)
 {
-    if (!L.rowmap) return seg_go<FT, 4, LPN, 1, false, false>(L, s);
+    if (L.out != dev::kOutMap) return seg_ttm<FT, 4, LPN, 1>(L, s);
     switch (L.npt) {
-        case 1: return seg_go<FT, 4, LPN, 1, false, true>(L, s);
-        case 2: return seg_go<FT, 4, LPN, 2, false, true>(L, s);
-        default: return seg_go<FT, 4, LPN, 3, false, true>(L, s);
+        case 1: return seg_go<FT, 4, LPN, 1, false, dev::kOutMap>(L, s);
+        case 2: return seg_go<FT, 4, LPN, 2, false, dev::kOutMap>(L, s);
+        default: return seg_go<FT, 4, LPN, 3, false, dev::kOutMap>(L, s);
     }
 }
 

@@ -294,10 +294,20 @@ struct TileShape {
                                     : (F32PLAIN || B16ONE || (sizeof(FT) == 2 && NP >= 2)) ? 32 : 64;
 };
 
-template <typename FT, int VW, int LPN, int NP, bool RESID, bool ROWMAP>
+// Output rows: of segment g at seg_row[g] (SpMTTKRP), or at g (SpTTM: one row per
+// fibre, written once and not read again), the latter by streaming stores where
+// rows are whole 64-byte pieces: those keep the gathers' lines cached (20M Zipf
+// nonzeros, float32, streaming / plain: R = 16 248 / 262 us, R = 32 318 / 333, R = 64
+// 482 / 612).  Shorter or ragged rows leave a line in parts, which a streaming
+// store sends out one by one (R = 8 250 / 186, R = 10 387 / 241; 20M uniform,
+// bfloat16, R = 10 1793 / 519).
+enum { kOutStream = 0, kOutMap = 1, kOutPlain = 2 };
+
+template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT>
 __global__ __launch_bounds__(256, (TileShape<FT, VW, LPN, NP, RESID>::waves))
 void seg_tile_kernel(SegArgs A)
 {
+    constexpr bool ROWMAP = OUT == kOutMap;
     constexpr int Q = 64 / LPN;                       // lane groups per wave
     constexpr int NPM = NP > 0 ? NP : kMaxNP;         // product modes held per step
     constexpr int RAWREGS = (int)(sizeof(Raw<FT, VW>) / 4);
@@ -384,7 +394,7 @@ void seg_tile_kernel(SegArgs A)
 
     // store the lane's VW columns of one output (or carry) row
     auto store_acc = [&](float *rowp, const float (&v)[VW]) {
-        if constexpr (!ROWMAP) store_row_stream<VW>(rowp + col, v);   // SpTTM: one row per fibre, never re-read
+        if constexpr (OUT == kOutStream) store_row_stream<VW>(rowp + col, v);
         else store_row<VW>(rowp + col, v);
     };
 
