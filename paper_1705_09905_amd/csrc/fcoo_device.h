@@ -44,12 +44,14 @@ __device__ __forceinline__ int dpp(int old, int x)
     return __builtin_amdgcn_update_dpp(old, x, CTRL, 0xF, BANKS, false);
 }
 
-// Broadcast with a compile-time source lane of the group.
-template <int LPN, int SRC>
+// Broadcast with a compile-time source lane of the group (LDSQ: by ds_swizzle).
+template <int LPN, int SRC, bool LDSQ = false>
 __device__ __forceinline__ int bcast_imm(int x)
 {
     if constexpr (LPN == 1) {
         return x;
+    } else if constexpr (LDSQ && LPN <= 32) {
+        return __builtin_amdgcn_ds_swizzle(x, (0x1F & ~(LPN - 1)) | (SRC << 5));
     } else if constexpr (LPN == 2) {
         return dpp<SRC | SRC << 2 | (2 + SRC) << 4 | (2 + SRC) << 6>(x, x);      // quad_perm
     } else if constexpr (LPN == 4) {
@@ -65,10 +67,10 @@ __device__ __forceinline__ int bcast_imm(int x)
     }
 }
 
-template <int LPN, int SRC>
+template <int LPN, int SRC, bool LDSQ = false>
 __device__ __forceinline__ float bcast_imm_f(float x)
 {
-    return __int_as_float(bcast_imm<LPN, SRC>(__float_as_int(x)));
+    return __int_as_float(bcast_imm<LPN, SRC, LDSQ>(__float_as_int(x)));
 }
 
 template <int CTRL>

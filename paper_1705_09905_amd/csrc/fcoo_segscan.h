@@ -248,16 +248,16 @@ __device__ __forceinline__ void load_schunk(const SegArgs &A, int j, int64_t bas
     }
 }
 
-template <int LPN, int ST, int K, int NPM>
+template <int LPN, int ST, bool LDSQ, int K, int NPM>
 __device__ __forceinline__ int sc_idx(const SChunk<K, NPM> &c, int qq)
 {
-    return bcast_imm<LPN, (ST / 4) % LPN>(c.idx[ST / (4 * LPN)][qq][ST % 4]);
+    return bcast_imm<LPN, (ST / 4) % LPN, LDSQ>(c.idx[ST / (4 * LPN)][qq][ST % 4]);
 }
 
-template <int LPN, int ST, int K, int NPM>
+template <int LPN, int ST, bool LDSQ, int K, int NPM>
 __device__ __forceinline__ float sc_val(const SChunk<K, NPM> &c)
 {
-    return bcast_imm_f<LPN, (ST / 4) % LPN>(c.v[ST / (4 * LPN)][ST % 4]);
+    return bcast_imm_f<LPN, (ST / 4) % LPN, LDSQ>(c.v[ST / (4 * LPN)][ST % 4]);
 }
 
 template <typename FT, int VW>
@@ -308,6 +308,10 @@ __global__ __launch_bounds__(256, (TileShape<FT, VW, LPN, NP, RESID>::waves))
 void seg_tile_kernel(SegArgs A)
 {
     constexpr bool ROWMAP = OUT == kOutMap;
+    // broadcasts: the residual's dot product waits on its moves; the other forms are
+    // bound by the vector units' issue, which ds_swizzle leaves alone (SpTTM, R = 16,
+    // 20M nonzeros: 244 us, by DPP 249)
+    constexpr bool LDSQ = !RESID;
     constexpr int Q = 64 / LPN;                       // lane groups per wave
     constexpr int NPM = NP > 0 ? NP : kMaxNP;         // product modes held per step
     constexpr int RAWREGS = (int)(sizeof(Raw<FT, VW>) / 4);
@@ -521,7 +525,7 @@ void seg_tile_kernel(SegArgs A)
                     constexpr int ST = decltype(sc)::value;
 #pragma unroll
                     for (int qq = 0; qq < NPM; ++qq) {
-                        const int idx = sc_idx<LPN, C0 + ST, K, NPM>(scur, qq);
+                        const int idx = sc_idx<LPN, C0 + ST, LDSQ, K, NPM>(scur, qq);
                         const char *p = fb[qq] + (uint64_t)(uint32_t)idx * (uint64_t)R4;
                         if (REUSE && qq == 0) {
                             const bool d = idx == lastidx;
@@ -549,7 +553,7 @@ void seg_tile_kernel(SegArgs A)
                 float vv[CLF];
                 static_for<CLF>([&](auto sc) {
                     constexpr int ST = decltype(sc)::value;
-                    vv[ST] = sc_val<LPN, C0 + ST, K, NPM>(scur);
+                    vv[ST] = sc_val<LPN, C0 + ST, LDSQ, K, NPM>(scur);
                 });
                 const uint64_t hm = (hms >> C0) & ((CLF >= 64) ? ~0ull : ((1ull << CLF) - 1ull));
                 const int n = nsc - C0;
