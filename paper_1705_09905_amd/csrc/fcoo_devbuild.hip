@@ -186,13 +186,17 @@ int grid_of(int64_t n, int cap = 65535 * 16)
 
 // Arrays laid out one after the other in a block: first every size is added
 // (add), then the block's address gives the pointers (set).
+// Arrays of 8 MiB or more start on a 2 MiB boundary, as an allocation of their own
+// would (SpTTM, R = 16, 20M Zipf nonzeros, streams of 80 MB: 208 us, packed 223).
 struct Layout {
     size_t bytes = 0;
     template <typename T>
     size_t add(int64_t n)
     {
+        const size_t len = ((size_t)(n > 0 ? n : 1) * sizeof(T) + 255) / 256 * 256;
+        if (len >= ((size_t)8 << 20)) bytes = (bytes + ((size_t)2 << 20) - 1) >> 21 << 21;
         const size_t at = bytes;
-        bytes += ((size_t)(n > 0 ? n : 1) * sizeof(T) + 255) / 256 * 256;
+        bytes += len;
         return at;
     }
 };
