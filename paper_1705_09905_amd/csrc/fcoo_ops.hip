@@ -73,7 +73,12 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
                 for (int t = ta + 1 + slot; t < tb; t += kChain * slots) {
                     float x[kChain];
 #pragma unroll
-                    for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? A.ca[(int64_t)(t + u * slots) * R + c] : 0.f;
+                    for (int u = 0; u < kChain; ++u) {               // (past the chain's end its last: no load behind a branch)
+                        const int tt = t + u * slots;
+                        x[u] = A.ca[(int64_t)(tt < tb ? tt : tb - 1) * R + c];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kChain; ++u) x[u] = t + u * slots < tb ? x[u] : 0.f;
                     if (A.in_turn) {
 #pragma unroll
                         for (int u = 0; u < kChain; ++u) s += x[u];
@@ -96,7 +101,16 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
                 float v = A.cb[(int64_t)ta * R + c];
                 const int used = tb - ta - 1 < slots ? tb - ta - 1 : slots;   // the other slots' sums are 0
                 if (slots > 1) {
-                    for (int k = 0; k < used; ++k) v += red[k * cw + tid];
+                    if (is_long && !A.in_turn) {
+                        // up to 1024 slots: eight sums (64 in a row, R = 16, had twice the error)
+                        float x[8] = {};
+                        for (int k = 0; k < used; k += 8)
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) x[u] += k + u < used ? red[(k + u) * cw + tid] : 0.f;
+                        v += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+                    } else {
+                        for (int k = 0; k < used; ++k) v += red[k * cw + tid];
+                    }
                 } else {
                     v += s;
                 }
