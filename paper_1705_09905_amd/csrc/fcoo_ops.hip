@@ -196,44 +196,81 @@ struct ModelArgs {
     int R;
 };
 
-// xhat[e] = sum_r prod_m A_m[i_m(e), r]: a lane group of LPN lanes per
-// nonzero, VW columns per lane, rank tiles looped inside (R <= 256).
-template <typename FT, int VW, int LPN>
+// xhat[e] = sum_r prod_m A_m[i_m(e), r]: a wave takes 64 consecutive nonzeros, one
+// index a lane and mode (the next 64 in flight meanwhile), and its lane groups of
+// LPN lanes their own LPN of them, each lane VW columns of a row (the last piece
+// moved down to end at column R, rank tiles looped inside), the gathers of a
+// batch of nonzeros back to back; lane j keeps the sum of the group's j-th.
+// (One nonzero a group at a time, and one column a lane at ranks that are no
+// multiple of the vector: 20M Zipf nonzeros, float32, R = 16 368 us, R = 10 3556.)
+template <typename FT, int VW, int LPN, int NM>
 __global__ __launch_bounds__(256) void model_kernel(ModelArgs A)
 {
-    constexpr int Q = 64 / LPN;
+    constexpr int NMM = NM > 0 ? NM : kMaxOrder;
+    constexpr int RAW = (int)(sizeof(Raw<FT, VW>) / 4);
+    constexpr int FIT = pow2_floor(48 / (NMM * RAW) > 0 ? 48 / (NMM * RAW) : 1);
+    constexpr int BS = FIT < LPN ? FIT : LPN;                  // nonzeros per batch
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int q = lane / LPN, j = lane % LPN;
-    const int64_t stride = (int64_t)gridDim.x * 4 * Q;
-    for (int64_t e = ((int64_t)blockIdx.x * 4 + w) * Q + q; e < A.nnz; e += stride) {
-        int ix[kMaxOrder];
+    const int j = lane % LPN;
+    const int nm = NM > 0 ? NM : A.order;
+    const uint32_t nnz = (uint32_t)A.nnz, stride = gridDim.x * 256u;
+    int cur[NMM], nxt[NMM];
+    auto load = [&](uint32_t e, int (&ix)[NMM]) {
+        const uint32_t ec = e < nnz ? e : nnz - 1;
 #pragma unroll
-        for (int m = 0; m < kMaxOrder; ++m) ix[m] = m < A.order ? __builtin_nontemporal_load(A.idx[m] + e) : 0;
-        float s = 0.f;
-        for (int c0 = 0; c0 < A.R; c0 += LPN * VW) {
-            const int col = c0 + j * VW;
-            if (col < A.R) {
-                Raw<FT, VW> raw[kMaxOrder];
+        for (int m = 0; m < NMM; ++m)
+            if (m < nm) ix[m] = __builtin_nontemporal_load(A.idx[m] + ec);
+    };
+    uint32_t e = blockIdx.x * 256u + (uint32_t)(w * 64 + lane);
+    load(e, cur);
+    for (; e - (uint32_t)lane < nnz; e += stride) {
+        load(e + stride, nxt);
+        float mine = 0.f;
+        static_for<LPN / BS>([&](auto bc) {
+            constexpr int B0 = decltype(bc)::value * BS;
+            float s[BS];
 #pragma unroll
-                for (int m = 0; m < kMaxOrder; ++m)
-                    if (m < A.order) load_raw<FT, VW>(reinterpret_cast<const FT *>(A.fac[m]) + (int64_t)ix[m] * A.R + col, raw[m]);
-                float p[VW];
-                to_float<FT, VW>(raw[0], p);
+            for (int b = 0; b < BS; ++b) s[b] = 0.f;
+            for (int t0 = 0; t0 < A.R; t0 += LPN * VW) {
+                const int c0 = t0 + j * VW;
+                const bool cval = c0 < A.R;
+                const int c1 = c0 + VW <= A.R ? c0 : A.R - VW;
+                const int col = cval ? c1 : 0, dup = cval ? c0 - c1 : VW;   // columns the lane before sums
+                Raw<FT, VW> raw[BS][NMM];
+                static_for<BS>([&](auto sc) {
+                    constexpr int S = decltype(sc)::value;
 #pragma unroll
-                for (int m = 1; m < kMaxOrder; ++m) {
-                    if (m < A.order) {
+                    for (int m = 0; m < NMM; ++m) {
+                        if (m >= nm) continue;
+                        const int ix = bcast_imm<LPN, B0 + S>(cur[m]);
+                        load_raw<FT, VW>(reinterpret_cast<const FT *>(A.fac[m]) + (int64_t)ix * A.R + col, raw[S][m]);
+                    }
+                });
+#pragma unroll
+                for (int b = 0; b < BS; ++b) {
+                    float p[VW];
+                    to_float<FT, VW>(raw[b][0], p);
+#pragma unroll
+                    for (int m = 1; m < NMM; ++m) {
+                        if (m >= nm) continue;
                         float x[VW];
-                        to_float<FT, VW>(raw[m], x);
+                        to_float<FT, VW>(raw[b][m], x);
 #pragma unroll
                         for (int k = 0; k < VW; ++k) p[k] *= x[k];
                     }
-                }
 #pragma unroll
-                for (int k = 0; k < VW; ++k) s += p[k];
+                    for (int k = 0; k < VW; ++k) s[b] += k >= dup ? p[k] : 0.f;
+                }
             }
-        }
-        s = group_sum<LPN>(s);
-        if (j == 0) A.xhat[e] = s;
+#pragma unroll
+            for (int b = 0; b < BS; ++b) {
+                const float x = group_sum<LPN>(s[b]);
+                mine = j == B0 + b ? x : mine;
+            }
+        });
+        if (e < nnz) A.xhat[e] = mine;
+#pragma unroll
+        for (int m = 0; m < NMM; ++m) cur[m] = nxt[m];
     }
 }
 
@@ -404,21 +441,32 @@ int launch_permute_values(const Built &b, const float *g, float *out, hipStream_
     return FCOO_OK;
 }
 
+template <typename FT, int VW, int LPN>
+static void model_nm(const dev::ModelArgs &a, hipStream_t s)
+{
+    // waves of 64 nonzeros, several each where there are enough to fill the chip
+    const dim3 g(grid_for(a.nnz, 256, 256 * 32)), b(256);
+    switch (a.order) {
+        case 2: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 2>), g, b, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 3>), g, b, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 4>), g, b, 0, s, a); break;
+        default: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 0>), g, b, 0, s, a); break;
+    }
+}
+
 template <typename FT>
-static hipError_t model_go(const dev::ModelArgs &a, bool vec, int lpn, hipStream_t s)
+static hipError_t model_go(const dev::ModelArgs &a, int vw, int lpn, hipStream_t s)
 {
     constexpr int V = dev::Elem<FT>::VEC;
-    auto grid = [&](int L) { return dim3(grid_for(a.nnz, 4 * (64 / L) * 4, 65535 * 4)); };
-    if (!vec) {
-        hipLaunchKernelGGL((dev::model_kernel<FT, 1, 64>), grid(64), dim3(256), 0, s, a);
-    } else {
-        switch (lpn) {
-            case 1: hipLaunchKernelGGL((dev::model_kernel<FT, V, 1>), grid(1), dim3(256), 0, s, a); break;
-            case 2: hipLaunchKernelGGL((dev::model_kernel<FT, V, 2>), grid(2), dim3(256), 0, s, a); break;
-            case 4: hipLaunchKernelGGL((dev::model_kernel<FT, V, 4>), grid(4), dim3(256), 0, s, a); break;
-            case 8: hipLaunchKernelGGL((dev::model_kernel<FT, V, 8>), grid(8), dim3(256), 0, s, a); break;
-            default: hipLaunchKernelGGL((dev::model_kernel<FT, V, 16>), grid(16), dim3(256), 0, s, a); break;
-        }
+    if (vw == 1) model_nm<FT, 1, 1>(a, s);
+    else if (vw == 2) lpn == 1 ? model_nm<FT, 2, 1>(a, s) : model_nm<FT, 2, 2>(a, s);
+    else if (vw < V) lpn == 1 ? model_nm<FT, 4, 1>(a, s) : model_nm<FT, 4, 2>(a, s);
+    else switch (lpn) {
+        case 1: model_nm<FT, V, 1>(a, s); break;
+        case 2: model_nm<FT, V, 2>(a, s); break;
+        case 4: model_nm<FT, V, 4>(a, s); break;
+        case 8: model_nm<FT, V, 8>(a, s); break;
+        default: model_nm<FT, V, 16>(a, s); break;
     }
     return hipGetLastError();
 }
@@ -436,11 +484,11 @@ int launch_model(const fcoo_tensor *t, const void *const *factors, int dtype, in
     a.nnz = t->nnz;
     a.order = t->order;
     a.R = R;
-    const int V = dtype == FCOO_F32 ? 4 : 8;
-    const bool vec = R % V == 0;
-    int lpn = next_pow2((R + V - 1) / V);
+    int vw = dtype == FCOO_F32 ? 4 : 8;
+    while (vw > R) vw >>= 1;
+    int lpn = next_pow2((R + vw - 1) / vw);
     if (lpn > 16) lpn = 16;
-    hipError_t e = dtype == FCOO_F32 ? model_go<float>(a, vec, lpn, s) : model_go<dev::bf16raw>(a, vec, lpn, s);
+    hipError_t e = dtype == FCOO_F32 ? model_go<float>(a, vw, lpn, s) : model_go<dev::bf16raw>(a, vw, lpn, s);
     if (e != hipSuccess) return hip_fail(e, "model kernel launch");
     return FCOO_OK;
 }
