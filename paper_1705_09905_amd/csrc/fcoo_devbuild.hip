@@ -289,7 +289,7 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bo
         size_t opx[kMaxOrder];
         const int np = (int)b.pmodes.size();
         for (int q = 0; q < np; ++q) opx[q] = l.add<int32_t>(Z + 4);
-        const size_t ov = l.add<float>(Z + 4), op_ = l.add<int32_t>(Z), oh = l.add<uint32_t>(2 * bfw + 4);
+        const size_t ov = l.add<float>(Z + 4), op_ = l.add<int32_t>(Z + 4), oh = l.add<uint32_t>(2 * bfw + 4);
         const size_t obf = l.add<uint32_t>(bfw + 2), osf = l.add<uint32_t>(sfw + 1);
         oseg = l.add<int32_t>(most_seg + 2);
         ofix = l.add<int32_t>(3 * nfix + 3);
@@ -304,8 +304,9 @@ int build_on_device(fcoo_tensor *t, Built &b, int mode, int op, int L, int T, bo
         // the streams' padding, which kernels read (and do not use): index 0, no head
         for (int q = 0; q < np; ++q) FCOO_HIP(hipMemsetAsync(b.d_pidx[q] + Z, 0, 4 * 4, s));
         FCOO_HIP(hipMemsetAsync(b.d_val + Z, 0, 4 * 4, s));
+        FCOO_HIP(hipMemsetAsync(b.d_perm + Z, 0, 4 * 4, s));
         FCOO_HIP(hipMemsetAsync(b.d_hr + 2 * bfw, 0, 4 * 4, s));
-        acct = (int64_t)np * (Z + 4) * 4 + (Z + 4) * 4 + Z * 4 + (2 * bfw + 4) * 4 + (bfw + 2) * 4 + (sfw + 1) * 4;
+        acct = (int64_t)np * (Z + 4) * 4 + (Z + 4) * 4 + (Z + 4) * 4 + (2 * bfw + 4) * 4 + (bfw + 2) * 4 + (sfw + 1) * 4;
     }
 
     if (blocked) {

@@ -222,10 +222,10 @@ void Built::free_device()
     }
     for (auto &p : d_pidx) { if (p) (void)hipFree(p); p = nullptr; }
     void *ptrs[] = {d_val, d_hr, d_bf, d_sf, d_seg_row, d_perm, d_fix, d_empty, d_carry, d_bpart,
-                    d_gperm, d_partial, d_sp_from, d_sp_words, d_sp_ticket, d_sp_err};
+                    d_partial, d_sp_from, d_sp_words, d_sp_ticket, d_sp_err};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     d_val = nullptr; d_hr = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr;
-    d_perm = nullptr; d_fix = nullptr; d_empty = nullptr; d_carry = nullptr; d_bpart = nullptr; d_gperm = nullptr;
+    d_perm = nullptr; d_fix = nullptr; d_empty = nullptr; d_carry = nullptr; d_bpart = nullptr;
     d_partial = nullptr; d_sp_from = nullptr; d_sp_words = nullptr; d_sp_ticket = nullptr; d_sp_err = nullptr;
     carry_cap = 0; bpart_cap = 0; partial_cap = 0; device_bytes = 0; sp_words_cap = 0; sp_tickets = 0; sp_epoch = 0;
     on_device = false;
@@ -686,7 +686,7 @@ static int build_device(Built &b, hipStream_t s)
     // bf itself and sf stay on the host (exported with the format)
     if (b.op == FCOO_OP_MTTKRP)
         if ((rc = upload(&b.d_seg_row, b.seg.data(), b.nseg, 2, s, &acct))) return rc;
-    if ((rc = upload(&b.d_perm, b.perm.data(), b.nnz, 0, s, &acct))) return rc;
+    if ((rc = upload(&b.d_perm, b.perm.data(), b.nnz, 4, s, &acct))) return rc;
     if ((rc = upload_plans(b, s, &acct))) return rc;
     if ((rc = upload(&b.d_empty, b.empty_rows.data(), (int64_t)b.empty_rows.size(), 1, s, &acct)))
         return rc;
@@ -1039,16 +1039,11 @@ int fcoo_spmttkrp_values(fcoo_tensor *t, int mode, const float *g, const void *c
     if (rc) return rc;
     if (!M || (!g && b->nnz)) return fail(FCOO_EINVAL, "M or g is NULL");
     hipStream_t s = (hipStream_t)stream;
-    // (4 entries past the values, read but not used, as the build's streams have)
-    int64_t cap = b->d_gperm ? b->nnz + 4 : 0;
-    if (!b->d_gperm && b->nnz) {
-        if ((rc = ensure_device_floats(&b->d_gperm, &cap, b->nnz + 4, s))) return rc;
-    }
-    if (b->nnz && (rc = launch_permute_values(*b, g, b->d_gperm, s))) return rc;
     TileProblem p{};
     p.b = b;
     for (size_t q = 0; q < b->pmodes.size(); ++q) p.fac[q] = factors[b->pmodes[q]];
-    p.vals = b->d_gperm;
+    p.vals = reinterpret_cast<const float *>(b->d_perm);
+    p.gvals = g;
     p.dtype = dtype;
     p.R = R;
     p.out = M;

@@ -95,7 +95,7 @@ struct Built {
     uint32_t *d_bf = nullptr;                 // device builds only (where they are made), for export
     uint32_t *d_sf = nullptr;
     int32_t *d_seg_row = nullptr;             // MTTKRP only
-    int32_t *d_perm = nullptr;
+    int32_t *d_perm = nullptr;                // Z, + 4 zeros
     int32_t *d_fix = nullptr;                 // the plans' fix-up lists, one after the other
     int32_t *d_empty = nullptr;
     int64_t device_bytes = 0;
@@ -103,7 +103,6 @@ struct Built {
     // scratch owned by this build, grown on demand
     float *d_carry = nullptr;                 // 2 x tiles x R floats
     int64_t carry_cap = 0;                    // floats
-    float *d_gperm = nullptr;                 // Z floats (values in stored order)
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
     int64_t bpart_cap = 0;                    // floats
     double *d_partial = nullptr;              // per-tile float64 partial sums
@@ -210,7 +209,8 @@ struct TileProblem {
     const Built *b;
     const Plan *plan;                // set by prep_tiles, with the scratch it needs
     const void *fac[kMaxOrder];      // per product mode q: factor base pointer
-    const float *vals;               // values in stored order (b->d_val or a permuted copy)
+    const float *vals;               // values in stored order; with gvals b->d_perm (positions)
+    const float *gvals = nullptr;    // replaced values in input order, or null
     int dtype;
     int R;
     float *out;                      // output rows, leading dimension R
@@ -251,7 +251,6 @@ int spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtype, in
              hipStream_t s);
 int launch_ttmc(const TileProblem &p, float *out, hipStream_t s);
 int launch_segmented(const TileProblem &p, hipStream_t s, bool resid);
-int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s);
 int launch_model(const fcoo_tensor *t, const void *const *factors, int dtype, int R, float *xhat,
                  hipStream_t s);
 

@@ -179,14 +179,6 @@ __global__ __launch_bounds__(256) void reduce_blocks_kernel(const float *__restr
     }
 }
 
-__global__ __launch_bounds__(256) void permute_kernel(const int32_t *__restrict__ perm,
-                                                      const float *__restrict__ g, int64_t n,
-                                                      float *__restrict__ out)
-{
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        out[i] = g[perm[i]];
-}
-
 struct ModelArgs {
     const int32_t *idx[kMaxOrder];
     const void *fac[kMaxOrder];
@@ -343,6 +335,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
             a.fac[q] = p.fac[q];
         }
         a.vals = p.vals;
+        a.gvals = p.gvals;
         a.hr = reinterpret_cast<const uint2 *>(b.d_hr);
         a.seg_row = b.op == FCOO_OP_MTTKRP ? b.d_seg_row : nullptr;
         a.out = b.nblk > 1 ? p.bpart : p.out;
@@ -430,14 +423,6 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
                            b.nblk, n, p.out);
         FCOO_HIP(hipGetLastError());
     }
-    return FCOO_OK;
-}
-
-int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(dev::permute_kernel, dim3(grid_for(b.nnz, 256 * 8)), dim3(256), 0, s, b.d_perm, g,
-                       b.nnz, out);
-    FCOO_HIP(hipGetLastError());
     return FCOO_OK;
 }
 

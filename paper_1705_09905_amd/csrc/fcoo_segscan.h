@@ -46,7 +46,8 @@ constexpr int kXcdBlocks = 8;        // XCDs of an MI355X: workgroup w runs on X
 struct SegArgs {
     const int32_t *pidx[kMaxNP];     // product-mode index streams (stored order)
     const void *fac[kMaxNP];         // factor matrix of each product mode
-    const float *vals;               // values in stored order
+    const float *vals;               // values in stored order; with gvals their positions (int32) there
+    const float *gvals;              // replaced values: value of nonzero s is gvals[position of s], or null
     const uint2 *hr;                 // per 32 nonzeros: (segment heads, heads before), padded
     const int32_t *seg_row;          // per segment output row (NULL: row = ordinal), 2 entries of padding
     float *out;                      // output rows, leading dimension R
@@ -516,6 +517,14 @@ void seg_tile_kernel(SegArgs A)
             const bool more = base + SC < re;
             const uint64_t hms = chunk_heads(scur);
             const int nsc = scur.n;
+            if (ROWMAP && !RESID && A.gvals) {
+                // replaced values: gathered with the rows, whose latency they share (a
+                // pass of their own over the positions took as long as the kernel)
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) scur.v[k][i] = A.gvals[__float_as_int(scur.v[k][i])];
+            }
             static_for<SC / CLF>([&](auto cc) {
                 constexpr int C0 = decltype(cc)::value * CLF;
                 // gathers of this chunk, back to back (repeated first-mode rows skipped)
@@ -614,6 +623,10 @@ void seg_tile_kernel(SegArgs A)
             if (more) load_chunk<LPN, CL, U, NPM>(A, np, j, base + CL, re, nxt);
             const uint64_t hm = chunk_heads(cur);
             const int n = cur.n;
+            if (ROWMAP && !RESID && A.gvals) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) cur.v[u] = A.gvals[__float_as_int(cur.v[u])];
+            }
             static_for<CL / CH>([&](auto sbc) {
                 constexpr int S0 = decltype(sbc)::value * CH;
                 Raw<FT, VW> rows[CH][NPM];
