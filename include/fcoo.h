@@ -89,10 +89,11 @@ typedef struct {
     int lane_cols;   /* bfloat16 factors, SpMTTKRP / SpTTM: columns of a row
                         that one lane reads per gather, 4 (8-byte pieces; the
                         kernel then runs 4 waves per SIMD) or 8 (16-byte
-                        pieces, 3 waves per SIMD; always so with R > 64, with
-                        the fused residual and with SpTTMc).  0: 4 with R <= 64
-                        and exactly two product modes (SpMTTKRP) or R other than
-                        16 and 32 (SpTTM), else 8; rows of fewer than 8 columns
+                        pieces, 3 waves per SIMD; always so with the fused
+                        residual, with SpTTMc and with R > 64, except SpTTM and
+                        R a multiple of 64).  0: 4 with R <= 64 and exactly two
+                        product modes (SpMTTKRP), or R other than 16, 32 or past
+                        64 no multiple of 64 (SpTTM), else 8; rows of fewer than 8 columns
                         take narrower pieces.  fcoo_autotune times both. */
     int single_pass; /* 1: finish the segments that cross tile boundaries inside
                         the tile kernel (the paper's adjacent synchronization,

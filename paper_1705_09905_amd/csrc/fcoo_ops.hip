@@ -293,9 +293,12 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_ord
     // tensor), and for SpTTM, whose 32 bytes of output per 8 columns would
     // leave in two halves (8 / 4 columns, 20M nonzeros, Zipf, us: R = 8 266 /
     // 185, 24 411 / 368, 64 509 / 449, uniform 1848 / 1102), but for rows of 16
-    // (236 / 253, uniform 508 / 603) or 32 (301 / 320, uniform 730 / 681)
+    // (236 / 253, uniform 508 / 603) or 32 (301 / 320, uniform 730 / 681), and past
+    // 64 columns only for whole rank tiles of 64 (128 1205 / 854, 256 2414 / 1704; 96
+    // 703 / 815)
     const int np = (int)b.pmodes.size();
-    const bool half_ok = dtype == FCOO_BF16 && !resid && np <= 3 && R >= 4 && R <= 64;
+    const bool half_ok = dtype == FCOO_BF16 && !resid && np <= 3 && R >= 4 &&
+                         (R <= 64 || (b.op == FCOO_OP_TTM && R % 64 == 0));
     LaneShape sh;
     sh.half = half_ok && (b.lane_cols == 4 || R < 8 ||
                           (b.lane_cols == 0 && (b.op == FCOO_OP_TTM ? R != 16 && R != 32 : np == 2)));
@@ -360,7 +363,8 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         if (resid && R > most)
             return fail(FCOO_EUNSUPPORTED, "fused residual needs R <= %d for this dtype (R = %d)", most, R);
         L.npt = np <= 3 ? np : 0;
-        L.out = b.op == FCOO_OP_MTTKRP ? dev::kOutMap : R % 16 == 0 ? dev::kOutStream : dev::kOutPlain;
+        L.out = b.op == FCOO_OP_MTTKRP ? dev::kOutMap
+              : R % 16 == 0 || R > sh.lpn * sh.vw ? dev::kOutStream : dev::kOutPlain;
         a.nblk = b.nblk;
         a.rows_own = (int)b.rows;
         if (p.sp_words) {

@@ -13,7 +13,7 @@ struct SegLaunch {
     int lpn;         // lanes per nonzero: 1, 2, 4, 8 or 16 (64: one column each)
     int npt;         // product modes as a template value: 1, 2, 3, or 0 (runtime count)
     int out;         // dev::kOutMap (SpMTTKRP), kOutStream or kOutPlain (SpTTM)
-    bool half;       // bfloat16 in 4-column (8-byte) lane chunks, R <= 64
+    bool half;       // bfloat16 in 4-column (8-byte) lane chunks
     dim3 grid;
 };
 

@@ -301,7 +301,9 @@ struct TileShape {
 // nonzeros, float32, streaming / plain: R = 16 248 / 262 us, R = 32 318 / 333, R = 64
 // 482 / 612).  Shorter or ragged rows leave a line in parts, which a streaming
 // store sends out one by one (R = 8 250 / 186, R = 10 387 / 241; 20M uniform,
-// bfloat16, R = 10 1793 / 519).
+// bfloat16, R = 10 1793 / 519).  Rows over more than one rank tile stream too: the
+// tiles' halves of a line would meet in the cache only by chance (R = 80 887 / 1259,
+// R = 200 2781 / 3499).
 enum { kOutStream = 0, kOutMap = 1, kOutPlain = 2 };
 
 template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT>
