@@ -408,8 +408,8 @@ def kernel_symbol(op, R, N):
     lpn = min(lpn, 16)
     np_ = (N - 1) if op == "mttkrp" else 1
     npt = np_ if np_ <= 3 else 0
-    return (f"void fcoo::dev::seg_tile_kernel<float, 4, {lpn}, {npt}, false, "
-            f"{'true' if op == 'mttkrp' else 'false'}, false, 1>(fcoo::dev::SegArgs)")
+    out = 1 if op == "mttkrp" else 0 if R % 16 == 0 or R > 4 * lpn else 2   # row map, streamed, plain rows
+    return f"void fcoo::dev::seg_tile_kernel<float, 4, {lpn}, {npt}, false, {out}>(fcoo::dev::SegArgs)"
 
 
 def rank_tile(R):
