@@ -194,7 +194,8 @@ struct ModelArgs {
 // moved down to end at column R, rank tiles looped inside), the gathers of a
 // batch of nonzeros back to back; lane j keeps the sum of the group's j-th.
 // (One nonzero a group at a time, and one column a lane at ranks that are no
-// multiple of the vector: 20M Zipf nonzeros, float32, R = 16 368 us, R = 10 3556.)
+// multiple of the vector: 20M Zipf nonzeros, float32, R = 16 368 us, R = 10 3556;
+// now 316 and 371.  The gathers of random rows bound it.)
 template <typename FT, int VW, int LPN, int NM>
 __global__ __launch_bounds__(256) void model_kernel(ModelArgs A)
 {
