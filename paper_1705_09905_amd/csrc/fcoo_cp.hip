@@ -670,21 +670,23 @@ static int gram_rows(int64_t I, int dtype)
     return unit * ceil_div(ceil_div(I, 512), unit);
 }
 
-// G = A^T A (float64) of an I x R factor; partials in ws->dbl.
-static int gram_launch(fcoo_tensor *t, const void *A, int dtype, int64_t I, int R, double *G, hipStream_t s)
+// ... and its workgroups: a step function of I, which a smaller I can have more of
+// (float32: 140,000 rows take 274, 120,000 take 469)
+static int gram_blocks(int64_t I, int dtype) { return ceil_div(I, gram_rows(I, dtype)); }
+
+// G = A^T A (float64) of an I x R factor; partials (gram_blocks x R x R) in gpart.
+static int gram_launch(const void *A, int dtype, int64_t I, int R, double *gpart, double *G, hipStream_t s)
 {
-    const int rows = gram_rows(I, dtype), nblk = ceil_div(I, rows);
+    const int rows = gram_rows(I, dtype), nblk = gram_blocks(I, dtype);
     const int ntile = (R + 31) / 32;
-    int rc = ensure_device_doubles(&t->ws.dbl, &t->ws.dbl_cap, (int64_t)nblk * R * R + 16, s);
-    if (rc) return rc;
     if (dtype == FCOO_F32)
         hipLaunchKernelGGL(dev::gram_partial_kernel<float>, dim3(nblk, ntile * ntile), dim3(256), 0, s,
-                           (const float *)A, I, R, rows, t->ws.dbl);
+                           (const float *)A, I, R, rows, gpart);
     else
         hipLaunchKernelGGL(dev::gram_partial_kernel<dev::bf16raw>, dim3(nblk, ntile * ntile), dim3(256), 0, s,
-                           (const dev::bf16raw *)A, I, R, rows, t->ws.dbl);
+                           (const dev::bf16raw *)A, I, R, rows, gpart);
     FCOO_HIP(hipGetLastError());
-    FCOO_HIP(sum_blocks(t->ws.dbl, nblk, R, G, s));
+    FCOO_HIP(sum_blocks(gpart, nblk, R, G, s));
     return FCOO_OK;
 }
 
@@ -701,7 +703,10 @@ int fcoo_gram(fcoo_tensor *t, int mode, const void *A, int dtype, int R, double 
     if (mode < 0 || mode >= t->order) return fail(FCOO_EINVAL, "mode %d out of range", mode);
     if (dtype != FCOO_F32 && dtype != FCOO_BF16) return fail(FCOO_EUNSUPPORTED, "unknown dtype %d", dtype);
     if (R < 1 || R > kMaxR) return fail(FCOO_EUNSUPPORTED, "R = %d outside [1, %d]", R, kMaxR);
-    return gram_launch(t, A, dtype, t->dims[mode], R, G, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t I = t->dims[mode];
+    const int rc = ensure_device_doubles(&t->ws.dbl, &t->ws.dbl_cap, (int64_t)gram_blocks(I, dtype) * R * R + 16, s);
+    return rc ? rc : gram_launch(A, dtype, I, R, t->ws.dbl, G, s);
 }
 
 int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, double *lambda,
@@ -724,8 +729,9 @@ int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, dou
     // scratch doubles: gram partials | W | tmp | column norms | inner products | fit, flags
     const int RC = pow2_ceil(R);
     const int rows_tile = rowsolve_rows(RC);
-    const int64_t gram_blocks = std::max<int64_t>(dev::kCpBlocks, ceil_div(maxI, gram_rows(maxI, dtype)));
-    const int64_t gram_need = gram_blocks * R * R + 16;
+    int most_blocks = dev::kCpBlocks;
+    for (int n = 0; n < N; ++n) most_blocks = std::max(most_blocks, gram_blocks(t->dims[n], dtype));
+    const int64_t gram_need = (int64_t)most_blocks * R * R + 16;
     const int64_t need = gram_need + 2 * (int64_t)R * R + dev::kCpBlocks * (int64_t)R + dev::kCpBlocks + 16;
     if ((rc = ensure_device_doubles(&t->ws.dbl, &t->ws.dbl_cap, need, s))) return rc;
     if (!t->ws.host_pinned) FCOO_HIP(hipHostMalloc((void **)&t->ws.host_pinned, 64, hipHostMallocDefault));
@@ -739,7 +745,7 @@ int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, dou
 
     if (!grams_valid)
         for (int m = 0; m < N; ++m)
-            if ((rc = gram_launch(t, factors[m], dtype, t->dims[m], R, grams + (int64_t)m * R * R, s))) return rc;
+            if ((rc = gram_launch(factors[m], dtype, t->dims[m], R, gpart, grams + (int64_t)m * R * R, s))) return rc;
 
     int nblk = 0;
     for (int n = 0; n < N; ++n) {

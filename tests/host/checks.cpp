@@ -1,0 +1,81 @@
+// Checks of the library's host code against the stand-in runtime, one per
+// command-line name; exit status 0 when the check holds.
+#include "fake_hip.h"
+
+#include <functional>
+#include <numeric>
+
+#include "fcoo.h"
+#include "fcoo_internal.h"
+
+#define CHECK(c)                                                                              \
+    do {                                                                                      \
+        if (!(c)) {                                                                           \
+            fprintf(stderr, "%s:%d: %s (%s) %s\n", __FILE__, __LINE__, #c, fcoo_last_error(), \
+                    fake::last_stale.c_str());                                                \
+            exit(1);                                                                          \
+        }                                                                                     \
+    } while (0)
+
+// Z nonzeros, one index of each mode after the other
+static fcoo_tensor *tensor(std::vector<int64_t> dims, int64_t Z)
+{
+    std::vector<std::vector<int32_t>> idx(dims.size());
+    std::vector<const int32_t *> p;
+    for (size_t m = 0; m < dims.size(); ++m) {
+        idx[m].resize(Z);
+        for (int64_t e = 0; e < Z; ++e) idx[m][e] = (int32_t)((e * (m ? 7 : 1)) % dims[m]);
+        p.push_back(idx[m].data());
+    }
+    std::vector<float> v(Z, 1.f);
+    fcoo_tensor *t = nullptr;
+    CHECK(fcoo_create((int)dims.size(), dims.data(), Z, p.data(), v.data(), &t) == FCOO_OK);
+    return t;
+}
+
+static void *dev(size_t bytes)
+{
+    void *p = nullptr;
+    CHECK(hipMalloc(&p, bytes) == hipSuccess);
+    return p;
+}
+
+// CP-ALS from fresh factors on a new handle: no kernel is given scratch that the
+// sweep has let go of, whichever mode's Gram takes the most of it.
+static void cp_workspace(std::vector<int64_t> dims, int R, int dtype)
+{
+    fcoo_tensor *t = tensor(dims, 64);
+    std::vector<void *> f;
+    for (size_t m = 0; m < dims.size(); ++m) {
+        CHECK(fcoo_build(t, (int)m, FCOO_OP_MTTKRP, nullptr, nullptr) == FCOO_OK);
+        f.push_back(dev((size_t)dims[m] * R * 4));
+    }
+    double *lambda = (double *)dev(R * 8), *grams = (double *)dev(dims.size() * R * R * 8), fit;
+    for (int sweep = 0; sweep < 2; ++sweep)
+        CHECK(fcoo_cp_als_iter(t, f.data(), dtype, R, lambda, grams, sweep, &fit, nullptr, nullptr) == FCOO_OK);
+    CHECK(fake::stale == 0);
+    fcoo_destroy(t);
+}
+
+int main(int argc, char **argv)
+{
+    const std::string name = argc > 1 ? argv[1] : "";
+    const std::map<std::string, std::function<void()>> checks = {
+        {"cp_workspace_f32", [] {
+             cp_workspace({140000, 120000, 50}, 8, FCOO_F32);
+             cp_workspace({131073, 131072, 5}, 16, FCOO_F32);
+             cp_workspace({50, 131072, 131073, 262145}, 33, FCOO_F32);
+         }},
+        {"cp_workspace_bf16", [] {
+             cp_workspace({524289, 524288, 50}, 16, FCOO_BF16);
+             cp_workspace({600000, 500000, 50}, 8, FCOO_BF16);
+         }},
+    };
+    const auto it = checks.find(name);
+    if (it == checks.end()) {
+        for (const auto &c : checks) printf("%s\n", c.first.c_str());
+        return 2;
+    }
+    it->second();
+    return 0;
+}
