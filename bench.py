@@ -409,7 +409,7 @@ def kernel_symbol(op, R, N):
     np_ = (N - 1) if op == "mttkrp" else 1
     npt = np_ if np_ <= 3 else 0
     out = 1 if op == "mttkrp" else 0 if R % 16 == 0 or R > 4 * lpn else 2   # row map, streamed, plain rows
-    return f"void fcoo::dev::seg_tile_kernel<float, 4, {lpn}, {npt}, false, {out}>(fcoo::dev::SegArgs)"
+    return f"void fcoo::dev::seg_tile_kernel<float, 4, {lpn}, {npt}, false, {out}, false>(fcoo::dev::SegArgs)"
 
 
 def rank_tile(R):

@@ -39,6 +39,8 @@ SOURCES = [
     "seg_bf16_half.hip",
     "seg_f32_resid.hip",
     "seg_bf16_resid.hip",
+    "seg_f32_resid_ragged.hip",
+    "seg_bf16_resid_ragged.hip",
     "seg_f32_narrow.hip",
     "seg_bf16_narrow.hip",
 ]

@@ -389,6 +389,7 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
         if (p.ev_before) FCOO_HIP(hipEventRecord(p.ev_before, s));
         const bool narrow = !L.half && sh.vw < (p.dtype == FCOO_F32 ? 4 : 8);
         if (narrow) e = p.dtype == FCOO_F32 ? seg_launch_f32_narrow(L, resid, s) : seg_launch_bf16_narrow(L, resid, s);
+        else if (resid && R % sh.vw) e = p.dtype == FCOO_F32 ? seg_launch_f32_resid_ragged(L, s) : seg_launch_bf16_resid_ragged(L, s);
         else if (p.dtype == FCOO_F32) e = resid ? seg_launch_f32_resid(L, s) : seg_launch_f32(L, s);
         else if (L.half) e = seg_launch_bf16_half(L, s);
         else e = resid ? seg_launch_bf16_resid(L, s) : seg_launch_bf16(L, s);

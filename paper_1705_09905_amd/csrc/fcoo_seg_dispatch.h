@@ -17,10 +17,10 @@ struct SegLaunch {
     dim3 grid;
 };
 
-template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT>
+template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT, bool RAGGED = false>
 static hipError_t seg_go(const SegLaunch &L, hipStream_t s)
 {
-    hipLaunchKernelGGL((dev::seg_tile_kernel<FT, VW, LPN, NP, RESID, OUT>), L.grid, dim3(256), 0, s,
+    hipLaunchKernelGGL((dev::seg_tile_kernel<FT, VW, LPN, NP, RESID, OUT, RAGGED>), L.grid, dim3(256), 0, s,
                        L.args);
     return hipGetLastError();
 }
@@ -33,30 +33,32 @@ static hipError_t seg_ttm(const SegLaunch &L, hipStream_t s)
     return seg_go<FT, VW, LPN, NP, false, dev::kOutPlain>(L, s);
 }
 
-template <typename FT, int VW, int LPN, bool RESID>
+template <typename FT, int VW, int LPN, bool RESID, bool RAGGED = false>
 static hipError_t seg_np(const SegLaunch &L, hipStream_t s)
 {
     if constexpr (!RESID) {
         if (L.out != dev::kOutMap) return seg_ttm<FT, VW, LPN, 1>(L, s);
     }
     switch (L.npt) {
-        case 1: return seg_go<FT, VW, LPN, 1, RESID, dev::kOutMap>(L, s);
-        case 2: return seg_go<FT, VW, LPN, 2, RESID, dev::kOutMap>(L, s);
-        case 3: return seg_go<FT, VW, LPN, 3, RESID, dev::kOutMap>(L, s);
-        default: return seg_go<FT, VW, LPN, 0, RESID, dev::kOutMap>(L, s);
+        case 1: return seg_go<FT, VW, LPN, 1, RESID, dev::kOutMap, RAGGED>(L, s);
+        case 2: return seg_go<FT, VW, LPN, 2, RESID, dev::kOutMap, RAGGED>(L, s);
+        case 3: return seg_go<FT, VW, LPN, 3, RESID, dev::kOutMap, RAGGED>(L, s);
+        default: return seg_go<FT, VW, LPN, 0, RESID, dev::kOutMap, RAGGED>(L, s);
     }
 }
 
-template <typename FT, bool RESID>
+template <typename FT, bool RESID, bool RAGGED = false>
 static hipError_t seg_dispatch(const SegLaunch &L, hipStream_t s)
 {
     constexpr int V = dev::Elem<FT>::VEC;
     switch (L.lpn) {
-        case 1: return seg_np<FT, V, 1, RESID>(L, s);
-        case 2: return seg_np<FT, V, 2, RESID>(L, s);
-        case 4: return seg_np<FT, V, 4, RESID>(L, s);
-        case 8: return seg_np<FT, V, 8, RESID>(L, s);
-        default: return seg_np<FT, V, 16, RESID>(L, s);
+        case 1:
+            if constexpr (!RAGGED) return seg_np<FT, V, 1, RESID>(L, s);   // (one lane a row: R is its vector)
+            else return hipErrorInvalidValue;
+        case 2: return seg_np<FT, V, 2, RESID, RAGGED>(L, s);
+        case 4: return seg_np<FT, V, 4, RESID, RAGGED>(L, s);
+        case 8: return seg_np<FT, V, 8, RESID, RAGGED>(L, s);
+        default: return seg_np<FT, V, 16, RESID, RAGGED>(L, s);
     }
 }
 
@@ -78,8 +80,8 @@ static hipError_t seg_dispatch_narrow(const SegLaunch &L, hipStream_t s)
         }
         return seg_go<FT, 1, 1, 0, RESID, dev::kOutMap>(L, s);
     }
-    if (L.vw == 2) return L.lpn == 1 ? seg_np<FT, 2, 1, RESID>(L, s) : seg_np<FT, 2, 2, RESID>(L, s);
-    if constexpr (sizeof(FT) == 2) return L.lpn == 1 ? seg_np<FT, 4, 1, RESID>(L, s) : seg_np<FT, 4, 2, RESID>(L, s);
+    if (L.vw == 2) return L.lpn == 1 ? seg_np<FT, 2, 1, RESID>(L, s) : seg_np<FT, 2, 2, RESID, RESID>(L, s);
+    if constexpr (sizeof(FT) == 2) return L.lpn == 1 ? seg_np<FT, 4, 1, RESID>(L, s) : seg_np<FT, 4, 2, RESID, RESID>(L, s);
     return hipErrorInvalidValue;
 }
 
@@ -113,6 +115,8 @@ hipError_t seg_launch_bf16(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_half(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_f32_resid(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_bf16_resid(const SegLaunch &L, hipStream_t s);
+hipError_t seg_launch_f32_resid_ragged(const SegLaunch &L, hipStream_t s);
+hipError_t seg_launch_bf16_resid_ragged(const SegLaunch &L, hipStream_t s);
 hipError_t seg_launch_f32_narrow(const SegLaunch &L, bool resid, hipStream_t s);
 hipError_t seg_launch_bf16_narrow(const SegLaunch &L, bool resid, hipStream_t s);
 

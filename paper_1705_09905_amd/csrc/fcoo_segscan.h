@@ -306,7 +306,9 @@ struct TileShape {
 // R = 200 2781 / 3499).
 enum { kOutStream = 0, kOutMap = 1, kOutPlain = 2 };
 
-template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT>
+// RAGGED (RESID): R is no multiple of VW, which costs the dot product of every step
+// a choice per column (2% of the kernel at R = 64, where nothing needs it)
+template <typename FT, int VW, int LPN, int NP, bool RESID, int OUT, bool RAGGED = false>
 __global__ __launch_bounds__(256, (TileShape<FT, VW, LPN, NP, RESID>::waves))
 void seg_tile_kernel(SegArgs A)
 {
@@ -386,14 +388,8 @@ void seg_tile_kernel(SegArgs A)
     const uint32_t R4 = (uint32_t)R * (uint32_t)sizeof(FT);
     // RESID: factor row of the index mode for an output row (blocks add block * rows)
     auto own_row = [&](int r) -> int64_t { return A.nblk > 1 ? (int64_t)(r % A.rows_own) : (int64_t)r; };
-    // (a column two lanes hold counts once in the dot product: zero in the second)
     auto load_own = [&](int r, Raw<FT, VW> &o) {
         load_raw<FT, VW>(reinterpret_cast<const FT *>(A.own) + own_row(r) * R + colc, o);
-    };
-    auto take_own = [&](const Raw<FT, VW> &x, float (&o)[VW]) {
-        to_float<FT, VW>(x, o);
-#pragma unroll
-        for (int k = 0; k < VW - 1; ++k) o[k] = k < dup ? 0.f : o[k];
     };
     const char *fb[NPM];
 #pragma unroll
@@ -458,7 +454,7 @@ void seg_tile_kernel(SegArgs A)
                 Raw<FT, VW> own0;
                 load_own(row0, own0);
                 load_own(row1, own1);
-                take_own(own0, own);
+                to_float<FT, VW>(own0, own);
             }
         }
     }
@@ -480,7 +476,7 @@ void seg_tile_kernel(SegArgs A)
             if constexpr (RESID) {
                 currow = row1;
                 row1 = row2;
-                take_own(own1, own);
+                to_float<FT, VW>(own1, own);
                 load_own(row1, own1);
                 row2 = A.seg_row[g + 2];
             } else if constexpr (ROWMAP) {
@@ -493,10 +489,15 @@ void seg_tile_kernel(SegArgs A)
         on_head(hm, st);
         if (st < n) {
             if constexpr (RESID) {
-                // lanes past R hold column 0 (clamped reads): kept out of the dot product
+                // lanes past R hold column 0 (clamped reads): kept out of the dot product;
+                // a column that two lanes hold counts in the first (by a choice
+                // between sums, as a factor of 0 would turn an infinity into NaN)
                 float d = 0.f;
 #pragma unroll
-                for (int k = 0; k < VW; ++k) d += own[k] * h[k];
+                for (int k = 0; k < VW; ++k) {
+                    if constexpr (RAGGED) d = k < dup ? d : d + own[k] * h[k];
+                    else d += own[k] * h[k];
+                }
                 d = group_sum<LPN>(cval ? d : 0.f);
                 const float r = d - v;
                 const float sc = r * A.inv_nnz;
