@@ -207,15 +207,18 @@ void pool_handles(int delta)
 void Built::free_device()
 {
     if (arena.p) {
-        // work queued on any stream may still read the arrays, as before a
-        // hipFree, which waits; where the wait is refused (a stream is being
-        // captured) the block goes to the driver
-        if (hipDeviceSynchronize() == hipSuccess) {
-            pool_put(&arena);
-        } else {
-            (void)hipGetLastError();
-            pool_free(&arena);
-        }
+        // work queued on any stream of the block's device (the current one may be
+        // another) may still read the arrays, as before a hipFree, which waits;
+        // where the wait is refused (a stream is being captured) the block goes to
+        // the driver
+        int cur = arena.dev;
+        (void)hipGetDevice(&cur);
+        bool idle = cur == arena.dev || hipSetDevice(arena.dev) == hipSuccess;
+        idle = idle && hipDeviceSynchronize() == hipSuccess;
+        if (!idle) (void)hipGetLastError();
+        if (cur != arena.dev) (void)hipSetDevice(cur);
+        if (idle) pool_put(&arena);
+        else pool_free(&arena);
         for (auto &p : d_pidx) p = nullptr;
         d_val = nullptr; d_hr = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr;
         d_perm = nullptr; d_fix = nullptr; d_empty = nullptr;

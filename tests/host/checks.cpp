@@ -57,6 +57,23 @@ static void cp_workspace(std::vector<int64_t> dims, int R, int dtype)
     fcoo_destroy(t);
 }
 
+// A block goes back to the pool once nothing queued on its own device can still use
+// it, whichever device is current when its build is released.
+static void pool_device()
+{
+    using namespace fcoo;
+    fcoo_tensor *t = tensor({4, 4}, 8);                  // (the pool keeps blocks while a handle lives)
+    Built b;
+    CHECK(pool_get((size_t)8 << 20, &b.arena) == FCOO_OK);
+    CHECK(b.arena.dev == 0);
+    fake::pending[0] = true;
+    CHECK(hipSetDevice(1) == hipSuccess);
+    b.free_device();
+    CHECK(!fake::pending[0]);
+    CHECK(fake::device == 1);
+    fcoo_destroy(t);
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -70,6 +87,7 @@ int main(int argc, char **argv)
              cp_workspace({524289, 524288, 50}, 16, FCOO_BF16);
              cp_workspace({600000, 500000, 50}, 8, FCOO_BF16);
          }},
+        {"pool_device", [] { pool_device(); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
