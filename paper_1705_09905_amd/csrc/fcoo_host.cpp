@@ -145,31 +145,44 @@ void pool_trim(F which)
 }
 }  // namespace
 
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        pool_trim([&](const PoolBlock &x) { return x.dev == dev; });
+    }
+    return hipMalloc(p, bytes);
+}
+
 int pool_get(size_t bytes, PoolBlock *b)
 {
     const size_t unit = (size_t)2 << 20;
     bytes = (bytes + unit - 1) / unit * unit;
     int dev = 0;
     FCOO_HIP(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    size_t best = g_pool.size();
-    for (size_t i = 0; i < g_pool.size(); ++i)
-        if (g_pool[i].dev == dev && g_pool[i].bytes >= bytes && g_pool[i].bytes <= bytes + bytes / 4 &&
-            (best == g_pool.size() || g_pool[i].bytes < g_pool[best].bytes))
-            best = i;
-    if (best < g_pool.size()) {
-        *b = g_pool[best];
-        g_pool_bytes -= b->bytes;
-        g_pool[best] = g_pool.back();
-        g_pool.pop_back();
-        return FCOO_OK;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        size_t best = g_pool.size();
+        for (size_t i = 0; i < g_pool.size(); ++i)
+            if (g_pool[i].dev == dev && g_pool[i].bytes >= bytes && g_pool[i].bytes <= bytes + bytes / 4 &&
+                (best == g_pool.size() || g_pool[i].bytes < g_pool[best].bytes))
+                best = i;
+        if (best < g_pool.size()) {
+            *b = g_pool[best];
+            g_pool_bytes -= b->bytes;
+            g_pool[best] = g_pool.back();
+            g_pool.pop_back();
+            return FCOO_OK;
+        }
     }
     b->bytes = bytes;
     b->dev = dev;
-    if (hipMalloc(&b->p, bytes) == hipSuccess) return FCOO_OK;
-    (void)hipGetLastError();
-    pool_trim([&](const PoolBlock &x) { return x.dev == dev; });
-    if (hipMalloc(&b->p, bytes) == hipSuccess) return FCOO_OK;
+    if (device_malloc(&b->p, bytes) == hipSuccess) return FCOO_OK;
     (void)hipGetLastError();
     b->p = nullptr;
     return fail(FCOO_ENOMEM, "device build (%lld bytes)", (long long)bytes);
@@ -254,7 +267,7 @@ int ensure_device_floats(float **p, int64_t *cap, int64_t need, hipStream_t s)
         *p = nullptr;
         *cap = 0;
     }
-    FCOO_HIP(hipMalloc((void **)p, (size_t)need * sizeof(float)));
+    FCOO_HIP(device_malloc((void **)p, (size_t)need * sizeof(float)));
     *cap = need;
     return FCOO_OK;
 }
@@ -268,7 +281,7 @@ int ensure_device_doubles(double **p, int64_t *cap, int64_t need, hipStream_t s)
         *p = nullptr;
         *cap = 0;
     }
-    FCOO_HIP(hipMalloc((void **)p, (size_t)need * sizeof(double)));
+    FCOO_HIP(device_malloc((void **)p, (size_t)need * sizeof(double)));
     *cap = need;
     return FCOO_OK;
 }
@@ -277,7 +290,7 @@ template <class T>
 static int upload(T **dst, const T *src, int64_t n, int64_t pad_elems, hipStream_t s, int64_t *acct)
 {
     const size_t bytes = (size_t)(n + pad_elems) * sizeof(T);
-    FCOO_HIP(hipMalloc((void **)dst, bytes ? bytes : sizeof(T)));
+    FCOO_HIP(device_malloc((void **)dst, bytes ? bytes : sizeof(T)));
     if (pad_elems) FCOO_HIP(hipMemsetAsync(*dst, 0, bytes, s));
     if (n) FCOO_HIP(hipMemcpyAsync(*dst, src, (size_t)n * sizeof(T), hipMemcpyHostToDevice, s));
     *acct += (int64_t)bytes;
@@ -378,8 +391,8 @@ int setup_single_pass(Built &b, hipStream_t s)
     int64_t acct = 0;
     int rc = upload_i32(&b.d_sp_from, from, 0, s, &acct);
     if (rc) return rc;
-    FCOO_HIP(hipMalloc((void **)&b.d_sp_ticket, sizeof(unsigned long long)));
-    FCOO_HIP(hipMalloc((void **)&b.d_sp_err, sizeof(int)));
+    FCOO_HIP(device_malloc((void **)&b.d_sp_ticket, sizeof(unsigned long long)));
+    FCOO_HIP(device_malloc((void **)&b.d_sp_err, sizeof(int)));
     FCOO_HIP(hipMemsetAsync(b.d_sp_ticket, 0, sizeof(unsigned long long), s));
     FCOO_HIP(hipMemsetAsync(b.d_sp_err, 0, sizeof(int), s));
     FCOO_HIP(hipStreamSynchronize(s));
@@ -402,7 +415,7 @@ int prep_single_pass(Built *b, TileProblem &p, hipStream_t s)
             b->d_sp_words = nullptr;
             b->sp_words_cap = 0;
         }
-        FCOO_HIP(hipMalloc((void **)&b->d_sp_words, (size_t)need * sizeof(uint64_t)));
+        FCOO_HIP(device_malloc((void **)&b->d_sp_words, (size_t)need * sizeof(uint64_t)));
         FCOO_HIP(hipMemsetAsync(b->d_sp_words, 0, (size_t)need * sizeof(uint64_t), s));
         b->sp_words_cap = need;
     }

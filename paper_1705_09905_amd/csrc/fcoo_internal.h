@@ -168,6 +168,9 @@ int pool_get(size_t bytes, PoolBlock *b);    // FCOO_OK or FCOO_ENOMEM
 void pool_put(PoolBlock *b);                 // b->p may be null
 void pool_free(PoolBlock *b);                // to the driver, not to the pool
 void pool_handles(int delta);                // handles alive
+// hipMalloc for everything else that the library allocates: where the device has no
+// room left, the pool's idle blocks on it are given back first
+hipError_t device_malloc(void **p, size_t bytes);
 
 // helpers implemented in fcoo_host.cpp
 int ensure_device_floats(float **p, int64_t *cap, int64_t need, hipStream_t s);

@@ -73,7 +73,7 @@ extern "C" int fcoo_autotune(fcoo_tensor *t, int mode, int op, const void *const
     if ((rc = fcoo_info(t, mode, op, &inf))) return rc;
     const int64_t rows = op == FCOO_OP_MTTKRP ? t->dims[mode] : inf.nseg;
     float *out = nullptr;
-    if (rows > 0 && hipMalloc((void **)&out, (size_t)rows * R * sizeof(float)) != hipSuccess)
+    if (rows > 0 && device_malloc((void **)&out, (size_t)rows * R * sizeof(float)) != hipSuccess)
         return fail(FCOO_ENOMEM, "autotune output (%lld x %d floats)", (long long)rows, R);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {

@@ -74,6 +74,51 @@ static void pool_device()
     fcoo_destroy(t);
 }
 
+// With no room left but what lies idle in the pool, whatever the library allocates
+// gets it: nothing is refused for the sake of idle blocks.
+static void pool_gives_way()
+{
+    using namespace fcoo;
+    const size_t big = (size_t)64 << 20;
+    fcoo_tensor *t = tensor({300, 200, 100}, 100000);
+    PoolBlock b;
+    auto fill = [&] {
+        fake::limit = (size_t)1 << 40;
+        CHECK(pool_get(big, &b) == FCOO_OK);
+        pool_put(&b);
+        fake::limit = fake::live_bytes + 64;
+    };
+    const int R = 256;
+    void *f[3] = {dev(300 * R * 4), dev(200 * R * 4), dev(100 * R * 4)};
+    float *out = (float *)dev(300 * R * 4), *g = (float *)dev(100000 * 4), best_ms;
+    double *d = (double *)dev(3 * 64 * 64 * 8), fit;
+    for (int m = 0; m < 3; ++m) {
+        fill();
+        CHECK(fcoo_build(t, m, FCOO_OP_MTTKRP, nullptr, nullptr) == FCOO_OK);
+    }
+    fill();
+    CHECK(fcoo_spmttkrp(t, 0, f, FCOO_F32, R, out, nullptr) == FCOO_OK);             // carries
+    fill();
+    CHECK(fcoo_resid_spmttkrp(t, 0, f, FCOO_F32, 64, out, d, nullptr) == FCOO_OK);   // partial losses
+    fill();
+    CHECK(fcoo_gram(t, 0, f[0], FCOO_F32, R, d + 64, nullptr) == FCOO_OK);           // partial Grams
+    fill();
+    CHECK(fcoo_cp_als_iter(t, f, FCOO_F32, 64, d, d, 0, &fit, nullptr, nullptr) == FCOO_OK);
+    fill();
+    CHECK(fcoo_model_at_nnz(t, f, FCOO_F32, 8, g, nullptr) == FCOO_OK);              // coordinates
+    fcoo_opts one{};
+    one.single_pass = 1;
+    fill();
+    CHECK(fcoo_build(t, 1, FCOO_OP_MTTKRP, &one, nullptr) == FCOO_OK);
+    fill();
+    CHECK(fcoo_spmttkrp(t, 1, f, FCOO_F32, R, out, nullptr) == FCOO_OK);             // published partials
+    const int tile = 4096;
+    fcoo_opts best;
+    fill();
+    CHECK(fcoo_autotune(t, 2, FCOO_OP_MTTKRP, f, FCOO_F32, R, &tile, 1, 1, &best, &best_ms, nullptr) == FCOO_OK);
+    fcoo_destroy(t);
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -88,6 +133,7 @@ int main(int argc, char **argv)
              cp_workspace({600000, 500000, 50}, 8, FCOO_BF16);
          }},
         {"pool_device", [] { pool_device(); }},
+        {"pool_gives_way", [] { pool_gives_way(); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
