@@ -662,14 +662,17 @@ static int upload_plans(Built &b, hipStream_t s, int64_t *acct)
 }
 
 // Carries for rows of up to 64 columns (4 bytes for every 16 nonzeros), so that
-// the first operation need not allocate them; wider rows grow them.
-static int first_carries(Built &b, hipStream_t s)
+// the first operation need not allocate them; wider rows grow them.  A build whose
+// arrays leave no room for them is none the worse: that operation asks again.
+static void first_carries(Built &b, hipStream_t s)
 {
     int64_t need = 0;
     for (int R : {16, 32, 64})
         need = std::max(need, 2 * pick_plan(b, FCOO_F32, R, false, false).ntiles * R);
-    if (b.carry_cap >= need) return FCOO_OK;
-    return need > 0 ? ensure_device_floats(&b.d_carry, &b.carry_cap, need, s) : FCOO_OK;
+    if (need > 0 && ensure_device_floats(&b.d_carry, &b.carry_cap, need, s)) {
+        (void)hipGetLastError();
+        clear_error();
+    }
 }
 
 static int build_device(Built &b, hipStream_t s)
@@ -824,7 +827,7 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
             rc = fail(FCOO_ENOMEM, "device build (host side)");
         }
         if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
-        if (!rc) rc = first_carries(b, (hipStream_t)stream);
+        if (!rc) first_carries(b, (hipStream_t)stream);
         if (rc) {
             b.free_device();
             b = Built();
@@ -843,8 +846,8 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
     if (host_only) return FCOO_OK;
     rc = build_device(b, (hipStream_t)stream);
     if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
-    if (!rc) rc = first_carries(b, (hipStream_t)stream);
     if (rc) { b.free_device(); return rc; }
+    first_carries(b, (hipStream_t)stream);
     return FCOO_OK;
 }
 

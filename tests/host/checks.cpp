@@ -119,6 +119,29 @@ static void pool_gives_way()
     fcoo_destroy(t);
 }
 
+// A build succeeds where the arrays it is made of fit, also with no room for the
+// carries that the first operation will want.
+static void build_without_carries(int single_pass)
+{
+    fcoo_opts o{};
+    o.single_pass = single_pass;
+    const size_t before = fake::live_bytes;
+    fcoo_tensor *t = tensor({300, 200, 100}, 100000);
+    CHECK(fcoo_build(t, 0, FCOO_OP_TTM, &o, nullptr) == FCOO_OK);
+    const size_t all = fake::live_bytes - before;
+    fcoo_destroy(t);
+    t = tensor({300, 200, 100}, 100000);
+    fake::limit = fake::live_bytes + all - 1;
+    CHECK(fcoo_build(t, 0, FCOO_OP_TTM, &o, nullptr) == FCOO_OK);
+    CHECK(std::string(fcoo_last_error()).empty());
+    void *U = nullptr;
+    fake::limit += (size_t)64 << 20;
+    U = dev(300 * 16 * 4);
+    CHECK(fcoo_spttm(t, 0, U, FCOO_F32, 16, (float *)dev((size_t)100000 * 16 * 4), nullptr) == FCOO_OK);
+    fcoo_destroy(t);
+    fake::limit = (size_t)1 << 40;
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -134,6 +157,7 @@ int main(int argc, char **argv)
          }},
         {"pool_device", [] { pool_device(); }},
         {"pool_gives_way", [] { pool_gives_way(); }},
+        {"build_without_carries", [] { build_without_carries(0), build_without_carries(1); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
