@@ -243,7 +243,7 @@ void Built::free_device()
     d_val = nullptr; d_hr = nullptr; d_bf = nullptr; d_sf = nullptr; d_seg_row = nullptr;
     d_perm = nullptr; d_fix = nullptr; d_empty = nullptr; d_carry = nullptr; d_bpart = nullptr;
     d_partial = nullptr; d_sp_from = nullptr; d_sp_words = nullptr; d_sp_ticket = nullptr; d_sp_err = nullptr;
-    carry_cap = 0; bpart_cap = 0; partial_cap = 0; device_bytes = 0; sp_words_cap = 0; sp_tickets = 0; sp_epoch = 0;
+    carry_cap = 0; carry_width = 0; bpart_cap = 0; partial_cap = 0; device_bytes = 0; sp_words_cap = 0; sp_tickets = 0; sp_epoch = 0;
     on_device = false;
 }
 
@@ -457,14 +457,16 @@ void Built::set_plans(int fmt_tile, bool own)
 //   SpTTM R = 32: 400k 15.4 / 13.1 / 15.6 / 24.8, 5M 114 / 75 / 78 / 102, 20M 419 /
 //   262 / 272 / 320; R = 8: 248 / 236 / 284 / 381.
 // SpTTMc: a wave takes a tile, so short ones (512 / 1024 / 2048 / 4096 at R = 16: 1M
-// 46 / 59 / 96 / 168, 10M 175 / 175 / 181 / 221), unless the carries of wide rows
-// would outweigh the work.  Past 64M nonzeros short tiles gain nothing that their
-// carries' scratch would be worth.
+// 46 / 59 / 96 / 168, 10M 175 / 175 / 181 / 221), whatever tile a workgroup of the
+// other operations was asked to take, unless the carries of wide rows would outweigh
+// the work.  Past 64M nonzeros short tiles gain nothing that their carries' scratch
+// would be worth.
 const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron)
 {
+    const bool large = b.nnz > (int64_t)64000000;
     int want = b.plan[0].T;
-    if (kron) want = R > 1024 ? want : b.nnz < 400000 ? 256 : b.nnz < 4000000 ? 512 : 1024;
-    else if (b.own_tile || b.nnz > (int64_t)64000000) return b.plan[0];
+    if (kron) want = R > 1024 ? want : large ? 2048 : b.nnz < 400000 ? 256 : b.nnz < 4000000 ? 512 : 1024;
+    else if (b.own_tile || large) return b.plan[0];
     else if (b.op == FCOO_OP_TTM || lane_shape(b, dtype, R, resid).lpn <= 4) want = 1024;
     else want = resid && b.nnz >= 10000000 ? 4096 : 2048;
     if (!kron) {
@@ -661,15 +663,32 @@ static int upload_plans(Built &b, hipStream_t s, int64_t *acct)
     return rc;
 }
 
-// Carries for rows of up to 64 columns (4 bytes for every 16 nonzeros), so that
+// Most tiles that an operation on rows of 1024 columns at most takes.
+static int64_t most_tiles(const Built &b)
+{
+    const int64_t n = pick_plan(b, FCOO_F32, 16, false, false).ntiles;
+    return b.pmodes.size() > 1 ? std::max(n, pick_plan(b, FCOO_F32, 16, false, true).ntiles) : n;
+}
+
+// Carries that no operation on rows of `width` columns or fewer outgrows, whatever
+// tiles it takes.  Scratch that is let go of may be in a captured graph, and none
+// can be had while a stream is being captured: what a caller's widest rows have
+// been through holds for all narrower ones.
+static int64_t carry_need(const Built &b, int64_t width)
+{
+    const int64_t n = 2 * most_tiles(b) * std::min<int64_t>(width, 1024);
+    return width <= 1024 ? n : std::max(n, 2 * pick_plan(b, FCOO_F32, (int)width, false, true).ntiles * width);
+}
+
+// Carries for rows of up to 64 columns (4 bytes for every 8 nonzeros), so that
 // the first operation need not allocate them; wider rows grow them.  A build whose
 // arrays leave no room for them is none the worse: that operation asks again.
 static void first_carries(Built &b, hipStream_t s)
 {
-    int64_t need = 0;
-    for (int R : {16, 32, 64})
-        need = std::max(need, 2 * pick_plan(b, FCOO_F32, R, false, false).ntiles * R);
-    if (need > 0 && ensure_device_floats(&b.d_carry, &b.carry_cap, need, s)) {
+    if (b.nnz == 0) return;
+    if (ensure_device_floats(&b.d_carry, &b.carry_cap, carry_need(b, 64), s) == FCOO_OK) {
+        b.carry_width = 64;
+    } else {
         (void)hipGetLastError();
         clear_error();
     }
@@ -933,12 +952,34 @@ void fcoo_destroy(fcoo_tensor *t)
 // sparse operations: argument checks, then the HIP launchers
 // ---------------------------------------------------------------------------
 
+// Carries for the launch's tiles, p.plan.  They are those of the widest rows so far
+// (carry_need), which no narrower launch replaces.
+static int prep_carries(Built *b, TileProblem &p, hipStream_t s)
+{
+    const bool fits = 2 * p.plan->ntiles * (int64_t)p.R <= b->carry_cap;
+    if (fits && p.R <= b->carry_width) return FCOO_OK;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (fits && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        return FCOO_OK;
+    }
+    int rc = ensure_device_floats(&b->d_carry, &b->carry_cap, carry_need(*b, p.R), s);
+    if (rc == FCOO_ENOMEM) {       // the format's tiles, which have the fewest carries
+        (void)hipGetLastError();
+        clear_error();
+        p.plan = &b->plan[0];
+        rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * p.plan->ntiles * (int64_t)p.R, s);
+    }
+    if (!rc) b->carry_width = std::max(b->carry_width, p.R);
+    return rc;
+}
+
 // The tiles of a launch and its scratch: the carries, and with XCD blocks the
 // partial output (nblk x rows x width floats) of the build.
 static int prep_tiles(Built *b, TileProblem &p, bool resid, hipStream_t s)
 {
     p.plan = p.keep_order ? &b->plan[0] : &pick_plan(*b, p.dtype, p.R, resid, p.kron);
-    int rc = ensure_device_floats(&b->d_carry, &b->carry_cap, 2 * p.plan->ntiles * (int64_t)p.R, s);
+    int rc = prep_carries(b, p, s);
     if (rc) return rc;
     p.carry = b->d_carry;
     if (b->nblk <= 1) return FCOO_OK;
@@ -1096,7 +1137,8 @@ int fcoo_resid_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, in
     if ((rc = prep_tiles(b, p, true, s))) return rc;
     if ((rc = prep_single_pass(b, p, s))) return rc;
     if (loss) {
-        if ((rc = ensure_device_doubles(&b->d_partial, &b->partial_cap, p.plan->ntiles + 1, s))) return rc;
+        // (for every rank's tiles, as the carries)
+        if ((rc = ensure_device_doubles(&b->d_partial, &b->partial_cap, most_tiles(*b) + 1, s))) return rc;
         p.partial = b->d_partial;
         p.loss = loss;
         p.loss_scale = b->nnz ? 0.5 / (double)b->nnz : 0.0;

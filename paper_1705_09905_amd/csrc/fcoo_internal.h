@@ -103,6 +103,7 @@ struct Built {
     // scratch owned by this build, grown on demand
     float *d_carry = nullptr;                 // 2 x tiles x R floats
     int64_t carry_cap = 0;                    // floats
+    int carry_width = 0;                      // widest rows they were made for
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
     int64_t bpart_cap = 0;                    // floats
     double *d_partial = nullptr;              // per-tile float64 partial sums

@@ -142,6 +142,88 @@ static void build_without_carries(int single_pass)
     fake::limit = (size_t)1 << 40;
 }
 
+// Scratch goes by the widest rows that a build has worked on: once those have been
+// through, no operation on rows as wide or narrower lets go of scratch (a captured
+// graph may hold it) or asks for more (a stream may be being captured).
+static void scratch_stays(int64_t Z, std::vector<int64_t> dims)
+{
+    fcoo_tensor *t = tensor(dims, Z);
+    CHECK(fcoo_build(t, 0, FCOO_OP_MTTKRP, nullptr, nullptr) == FCOO_OK);
+    const size_t W = 256;
+    std::vector<void *> f;
+    for (int64_t d : dims) f.push_back(dev((size_t)d * W * 4));
+    float *out = (float *)dev((size_t)dims[0] * 2048 * 4), *g = (float *)dev((size_t)Z * 4);
+    double *loss = (double *)dev(8);
+    auto chain = [&](int a, int b) {
+        std::vector<int> k(dims.size(), 1);
+        k[1] = a;
+        k[2] = b;
+        CHECK(fcoo_spttmc(t, 0, f.data(), FCOO_F32, k.data(), out, nullptr) == FCOO_OK);
+    };
+    CHECK(fcoo_resid_spmttkrp(t, 0, f.data(), FCOO_F32, 64, out, loss, nullptr) == FCOO_OK);
+    for (int widest : {64, 256, 2048}) {
+        if (widest <= 256) CHECK(fcoo_spmttkrp(t, 0, f.data(), FCOO_F32, widest, out, nullptr) == FCOO_OK);
+        else chain(64, 32);
+        fake::capturing = true;
+        const int frees = fake::frees, mallocs = fake::mallocs;
+        for (int dtype : {FCOO_F32, FCOO_BF16})
+            for (int R : {1, 3, 8, 16, 17, 31, 32, 33, 64, 128, 256}) {
+                if (R > widest) break;
+                CHECK(fcoo_spmttkrp(t, 0, f.data(), dtype, R, out, nullptr) == FCOO_OK);
+                CHECK(fcoo_spmttkrp_values(t, 0, g, f.data(), dtype, R, out, nullptr) == FCOO_OK);
+                if (R <= 64) CHECK(fcoo_resid_spmttkrp(t, 0, f.data(), dtype, R, out, loss, nullptr) == FCOO_OK);
+            }
+        for (int a = 1; a * 8 <= widest; a *= 2) chain(a, 8);
+        CHECK(fake::frees == frees && fake::mallocs == mallocs);
+        fake::capturing = false;
+    }
+    fcoo_destroy(t);
+}
+
+// ... and they hold the carries of each launch's tiles.
+static void carries_hold(std::vector<int64_t> dims, int64_t Z, int tile)
+{
+    using namespace fcoo;
+    fcoo_tensor *t = tensor(dims, Z);
+    fcoo_opts o{};
+    o.tile_nnz = tile;
+    CHECK(fcoo_build(t, 0, FCOO_OP_MTTKRP, &o, nullptr) == FCOO_OK);
+    const Built &b = t->b[FCOO_OP_MTTKRP][0];
+    std::vector<void *> f;
+    for (int64_t d : dims) f.push_back(dev((size_t)d * 4096 * 4));
+    float *out = (float *)dev((size_t)dims[0] * 8192 * 4);
+    const bool kron = dims.size() > 2;
+    for (int w = 1; w <= (kron ? 4096 : 256); w += w < 70 ? 1 : w / 2) {
+        std::vector<int> k(dims.size(), 1);
+        k[1] = std::min(w, 256);
+        if (kron) k[2] = w / k[1];
+        const int W = k[1] * (kron ? k[2] : 1);
+        if (w <= 256) CHECK(fcoo_spmttkrp(t, 0, f.data(), FCOO_BF16, w, out, nullptr) == FCOO_OK);
+        CHECK(fcoo_spttmc(t, 0, f.data(), FCOO_F32, k.data(), out, nullptr) == FCOO_OK);
+        for (int dtype : {FCOO_F32, FCOO_BF16})
+            for (bool resid : {false, true})
+                CHECK(w > 256 || 2 * pick_plan(b, dtype, w, resid, false).ntiles * w <= b.carry_cap);
+        CHECK(2 * pick_plan(b, FCOO_F32, W, false, kron).ntiles * W <= b.carry_cap);
+    }
+    fcoo_destroy(t);
+}
+
+// With no room for the carries of the tiles that suit a call, it runs on the build's
+// own tiles, whose carries fit.
+static void carries_that_fit()
+{
+    fcoo_tensor *t = tensor({300, 200, 100}, 2000000);
+    fcoo_opts o{};
+    o.tile_nnz = 1 << 20;
+    CHECK(fcoo_build(t, 0, FCOO_OP_MTTKRP, &o, nullptr) == FCOO_OK);
+    void *f[3] = {nullptr, dev(200 * 32 * 4), dev(100 * 32 * 4)};
+    const int k[3] = {1, 32, 32};
+    float *out = (float *)dev(300 * 1024 * 4);
+    fake::limit = fake::live_bytes + (size_t)4 * 1024 * 4;          // two tiles' carries
+    CHECK(fcoo_spttmc(t, 0, f, FCOO_F32, k, out, nullptr) == FCOO_OK);
+    fcoo_destroy(t);
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -158,6 +240,13 @@ int main(int argc, char **argv)
         {"pool_device", [] { pool_device(); }},
         {"pool_gives_way", [] { pool_gives_way(); }},
         {"build_without_carries", [] { build_without_carries(0), build_without_carries(1); }},
+        {"scratch_stays_small", [] { scratch_stays(5000, {30, 20, 10}), scratch_stays(300000, {300, 200, 10}); }},
+        {"scratch_stays_large", [] { scratch_stays(1500000, {3000, 200, 10}); }},
+        {"carries_hold", [] {
+             for (int64_t Z : {1, 300, 5000, 250000, 450000, 1100000})
+                 for (int tile : {0, 256, 1024, 65536}) carries_hold({30, 20}, Z, tile), carries_hold({30, 20, 10}, Z, tile);
+         }},
+        {"carries_that_fit", [] { carries_that_fit(); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
