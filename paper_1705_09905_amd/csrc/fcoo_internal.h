@@ -104,6 +104,8 @@ struct Built {
     float *d_carry = nullptr;                 // 2 x tiles x R floats
     int64_t carry_cap = 0;                    // floats
     int carry_width = 0;                      // widest rows they were made for
+    float *d_gcopy = nullptr;                 // replaced values that lie where the result goes
+    int64_t gcopy_cap = 0;                    // floats
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
     int64_t bpart_cap = 0;                    // floats
     double *d_partial = nullptr;              // per-tile float64 partial sums
