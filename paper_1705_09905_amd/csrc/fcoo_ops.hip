@@ -11,7 +11,7 @@ namespace fcoo {
 namespace dev {
 
 // What is left after the tile kernel, in one launch whose workgroups take one
-// of three parts (each was a kernel of its own; one launch costs 3-5 us on the
+// of four parts (each was a kernel of its own; one launch costs 3-5 us on the
 // stream whatever it does, as much as a small tensor's tile kernel):
 //   the first fblk   carry fix-up: entry (b, a, row) finishes the segment that
 //                    tile a starts (its last open partial) and tile b closes
@@ -22,7 +22,7 @@ namespace dev {
 //                    every chain a slice of 1.3M nonzeros over 1300 tiles took
 //                    40 us at R = 256: one thread a column);
 //   the next sblk    the nshort chains with at most one tile between (nearly all
-//                    where segments are short): a thread a column, kFlat
+//                    where segments are short): a thread a column, about kFlat
 //                    elements a workgroup.  (Four such chains a workgroup of
 //                    1024: SpTTM, R = 16, 20M Zipf nonzeros, 19.5k chains, 26.5
 //                    us; now 7);
@@ -41,6 +41,7 @@ struct FinishArgs {
     double scale;
     double *loss;
     int nfix, nlong, nshort, fblk, sblk, zblk, R;
+    int per;                         // short chains per workgroup
     bool in_turn;                    // chains on 256 threads, 8 tiles' carries in turn (TileProblem::keep_order)
 };
 
@@ -122,9 +123,8 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
     }
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < A.fblk + A.sblk) {
-        const int per = R < kFlat ? kFlat / R : 1;                       // chains of this workgroup
-        const int e0 = A.nfix - A.nshort + ((int)blockIdx.x - A.fblk) * per;
-        const int n = (A.nfix - e0 < per ? A.nfix - e0 : per) * R;
+        const int e0 = A.nfix - A.nshort + ((int)blockIdx.x - A.fblk) * A.per;
+        const int n = (A.nfix - e0 < A.per ? A.nfix - e0 : A.per) * R;
 #pragma unroll 4
         for (int i = tid; i < n; i += kFinish) {
             const int e = e0 + i / R, c = i % R;
@@ -404,7 +404,9 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
     f.nlong = f.nfix > 0 ? (int)pl.nlong : 0;
     f.nshort = f.nfix > 0 ? (int)pl.nshort : 0;
     f.fblk = f.nlong + (f.nfix - f.nlong - f.nshort + 3) / 4;
-    f.sblk = f.nshort > 0 ? grid_for(f.nshort, R < dev::kFlat ? dev::kFlat / R : 1, INT32_MAX) : 0;
+    // (2^20 workgroups at most, as of the zero rows: a grid has less than 2^32 threads)
+    f.per = std::max(R < dev::kFlat ? dev::kFlat / R : 1, (f.nshort >> 20) + 1);
+    f.sblk = f.nshort > 0 ? grid_for(f.nshort, f.per, INT32_MAX) : 0;
     f.zblk = f.nempty > 0 ? grid_for(f.nempty * R, dev::kZeroPer, 1 << 20) : 0;
     if (f.nfix + f.zblk > 0 || p.loss) {
         f.fix = b.d_fix + 3 * pl.fix_at;

@@ -224,6 +224,32 @@ static void carries_that_fit()
     fcoo_destroy(t);
 }
 
+// The launch after the tile kernel stays below 2^32 threads with the most and
+// shortest tiles that a tensor can have, wide rows included.
+static void finish_grid()
+{
+    using namespace fcoo;
+    for (int R : {1, 64, 256, 1024, 16384}) {
+        Built b;
+        b.op = FCOO_OP_MTTKRP;
+        b.nnz = INT32_MAX;
+        b.pmodes = {1, 2};
+        b.set_plans(256, true);
+        Plan &pl = b.plan[0];
+        pl.fix.resize((size_t)3 * pl.ntiles);
+        pl.nshort = pl.ntiles;
+        TileProblem p{};
+        p.b = &b;
+        p.plan = &pl;
+        p.R = R;
+        p.kron = R > 256;
+        p.kr[0] = R / 64, p.kr[1] = 64;
+        p.fac_rows[0] = p.fac_rows[1] = 10;
+        CHECK(launch_segmented(p, nullptr, false) == FCOO_OK);
+        CHECK((uint64_t)fake::grid.x * fake::block.x < (1ull << 32));
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -247,6 +273,7 @@ int main(int argc, char **argv)
                  for (int tile : {0, 256, 1024, 65536}) carries_hold({30, 20}, Z, tile), carries_hold({30, 20, 10}, Z, tile);
          }},
         {"carries_that_fit", [] { carries_that_fit(); }},
+        {"finish_grid", [] { finish_grid(); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
