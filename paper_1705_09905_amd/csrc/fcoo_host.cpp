@@ -843,10 +843,10 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
     if (on_gpu) {
         try {
             rc = build_on_device(t, b, mode, op, threadlen, tile_nnz, own_tile, nblk, xmode, (hipStream_t)stream);
+            if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
         } catch (const std::bad_alloc &) {
             rc = fail(FCOO_ENOMEM, "device build (host side)");
         }
-        if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
         if (!rc) first_carries(b, (hipStream_t)stream);
         if (rc) {
             b.free_device();
@@ -864,8 +864,12 @@ int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *st
     if (rc) return rc;
     b.lane_cols = lane_cols;
     if (host_only) return FCOO_OK;
-    rc = build_device(b, (hipStream_t)stream);
-    if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
+    try {
+        rc = build_device(b, (hipStream_t)stream);
+        if (!rc && single_pass) rc = setup_single_pass(b, (hipStream_t)stream);
+    } catch (const std::bad_alloc &) {
+        rc = fail(FCOO_ENOMEM, "device copies (host side)");
+    }
     if (rc) { b.free_device(); return rc; }
     first_carries(b, (hipStream_t)stream);
     return FCOO_OK;

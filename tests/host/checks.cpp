@@ -3,10 +3,22 @@
 #include "fake_hip.h"
 
 #include <functional>
-#include <numeric>
+#include <new>
 
 #include "fcoo.h"
 #include "fcoo_internal.h"
+
+// host allocations of 256 bytes and more until one is refused (-1: none is)
+static int refuse_in = -1;
+void *operator new(size_t n)
+{
+    if (n >= 256 && refuse_in >= 0 && refuse_in-- == 0) throw std::bad_alloc();
+    void *p = malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 #define CHECK(c)                                                                              \
     do {                                                                                      \
@@ -250,6 +262,26 @@ static void finish_grid()
     }
 }
 
+// No host allocation that a build is refused leaves it by an exception: the C entry
+// returns FCOO_ENOMEM, and the next build succeeds.
+static void host_memory(int device, int single_pass)
+{
+    fcoo_tensor *t = tensor({300, 200, 100}, 5000);
+    fcoo_opts o{};
+    o.device = device;
+    o.single_pass = single_pass;
+    int rc = FCOO_ENOMEM;
+    for (int k = 0; rc != FCOO_OK; ++k) {
+        CHECK(k < 1000);
+        refuse_in = k;
+        rc = fcoo_build(t, 0, FCOO_OP_MTTKRP, &o, nullptr);
+        const bool refused = refuse_in < 0;
+        refuse_in = -1;
+        CHECK(rc == (refused ? FCOO_ENOMEM : FCOO_OK));
+    }
+    fcoo_destroy(t);
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -274,6 +306,7 @@ int main(int argc, char **argv)
          }},
         {"carries_that_fit", [] { carries_that_fit(); }},
         {"finish_grid", [] { finish_grid(); }},
+        {"host_memory", [] { host_memory(0, 0), host_memory(0, 1), host_memory(1, 0), host_memory(1, 1); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
