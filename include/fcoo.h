@@ -67,10 +67,10 @@ typedef struct {
                         threadlen (default 4096; with the default, fcoo_info
                         and fcoo_export go by 4096 while the kernels take
                         512 .. 4096 nonzeros per workgroup, by Z).  SpTTMc,
-                        where a wave takes a tile, has 256 .. 2048 of them
-                        there whatever this says, for rows of up to 1024
-                        columns and if its scratch has room (2 x tiles x
-                        columns floats); else this many. */
+                        where a wave takes a tile, has 64 .. 2048 of them there
+                        whatever this says, if their scratch (2 x tiles x
+                        columns floats) stays within 256 MB and there is
+                        room for it; else as many as this. */
     int host_only;   /* 1: build the host arrays only (no device upload), e.g. to
                         fcoo_export them on a machine without a GPU. */
     int device;      /* 1: sort and encode on the GPU (same arrays, bit for bit);

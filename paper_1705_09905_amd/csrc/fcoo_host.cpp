@@ -434,8 +434,8 @@ void Built::set_plans(int fmt_tile, bool own)
     plan.clear();
     plan.resize(1);
     plan[0].T = fmt_tile;
-    for (int t : {2048, 1024, 512, 256}) {
-        if (t >= plan.back().T || fmt_tile % t) continue;
+    for (int t : {2048, 1024, 512, 256, 128, 64}) {
+        if (t >= plan.back().T || fmt_tile % t || (t < 256 && nnz >= 4000000)) continue;
         plan.emplace_back();
         plan.back().T = t;
     }
@@ -457,23 +457,36 @@ void Built::set_plans(int fmt_tile, bool own)
 //   residual R = 64: 5M 209 / 133 / 139 / 168, 20M 792 / 470 / 444 / 438;
 //   SpTTM R = 32: 400k 15.4 / 13.1 / 15.6 / 24.8, 5M 114 / 75 / 78 / 102, 20M 419 /
 //   262 / 272 / 320; R = 8: 248 / 236 / 284 / 381.
-// SpTTMc: a wave takes a tile, so short ones (512 / 1024 / 2048 / 4096 at R = 16: 1M
-// 46 / 59 / 96 / 168, 10M 175 / 175 / 181 / 221), whatever tile a workgroup of the
-// other operations was asked to take, unless the carries of wide rows would outweigh
-// the work.  Past 64M nonzeros short tiles gain nothing that their carries' scratch
-// would be worth.
+// SpTTMc: a wave takes a tile, whatever tile a workgroup of the other operations was
+// asked to take, and where segments are short it stores row after row, so tiles are
+// as short as leaves each SIMD several waves (64 / 128 / 256 / 512 / 1024 / 4096
+// nonzeros: 20k, ranks 8 x 8, rows of one nonzero 44 / 66 / 112 / 202 / 379 / 1428;
+// 100k, 16 x 16, rows of 50 13 / 14 / 14 / 20 / 34 / 108; 600k, 8 x 8, rows of 3 38 / 36
+// / 45 / 63 / 103 / 371; 1.6M Zipf, 16 x 16 100 / 77 / 80 / 103 / 167 / 587; 8M, 16 x 16,
+// rows of 4000 (256) 102 / 97 / 97 / 106; 10M Zipf, rows in no order (512) 183 / 180), a
+// size longer where wide, long rows make little work between carries (1.5M, 16 x 16,
+// rows of 750 (256) 31 / 26) or a size shorter where they are few nonzeros long
+// (1.4M Zipf over 129k rows, 1 x 8 (256) 52 / 39; 3M over 100k, 16 x 16 78 / 88), and unless their carries would pass kTtmcCarries.  Past
+// 64M nonzeros short tiles gain nothing that their carries' scratch would be worth.
+constexpr int64_t kTtmcCarries = (int64_t)64 << 20;      // floats
+
 const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron)
 {
     const bool large = b.nnz > (int64_t)64000000;
     int want = b.plan[0].T;
-    if (kron) want = R > 1024 ? want : large ? 2048 : b.nnz < 400000 ? 256 : b.nnz < 4000000 ? 512 : 1024;
-    else if (b.own_tile || large) return b.plan[0];
+    if (kron) {
+        const bool short_rows = b.nnz < (R < 128 ? 40 : 8) * b.nseg, long_rows = R >= 128 && b.nnz > 300 * b.nseg;
+        want = b.nnz < 150000 ? 64 : b.nnz < (short_rows ? 4000000 : 700000) ? 128
+             : b.nnz < (long_rows ? 1200000 : 4000000) ? 256 : b.nnz < 8000000 ? 512 : large ? 2048 : 1024;
+        for (size_t i = b.plan.size() - 1; i > 0; --i)
+            if (b.plan[i].T >= want && 2 * b.plan[i].ntiles * (int64_t)R <= kTtmcCarries) return b.plan[i];
+        return b.plan[0];
+    }
+    if (b.own_tile || large) return b.plan[0];
     else if (b.op == FCOO_OP_TTM || lane_shape(b, dtype, R, resid).lpn <= 4) want = 1024;
     else want = resid && b.nnz >= 10000000 ? 4096 : 2048;
-    if (!kron) {
-        if (b.nnz < 1000000 && want > 1024) want = 1024;
-        if (b.nnz < 200000 && want > 512) want = 512;
-    }
+    if (b.nnz < 1000000 && want > 1024) want = 1024;
+    if (b.nnz < 200000 && want > 512) want = 512;
     for (const Plan &pl : b.plan)
         if (pl.T <= want) return pl;
     return b.plan.back();
@@ -664,7 +677,7 @@ static int upload_plans(Built &b, hipStream_t s, int64_t *acct)
     return rc;
 }
 
-// Most tiles that an operation on rows of 1024 columns at most takes.
+// Most tiles that an operation takes.
 static int64_t most_tiles(const Built &b)
 {
     const int64_t n = pick_plan(b, FCOO_F32, 16, false, false).ntiles;
@@ -677,8 +690,7 @@ static int64_t most_tiles(const Built &b)
 // been through holds for all narrower ones.
 static int64_t carry_need(const Built &b, int64_t width)
 {
-    const int64_t n = 2 * most_tiles(b) * std::min<int64_t>(width, 1024);
-    return width <= 1024 ? n : std::max(n, 2 * pick_plan(b, FCOO_F32, (int)width, false, true).ntiles * width);
+    return std::min(2 * most_tiles(b) * width, std::max(kTtmcCarries, 2 * b.plan[0].ntiles * width));
 }
 
 // Carries for rows of up to 64 columns (4 bytes for every 8 nonzeros), so that

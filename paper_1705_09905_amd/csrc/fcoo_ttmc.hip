@@ -13,10 +13,9 @@
 // the bytes through the texture path, which bounded it: 10M nonzeros, Zipf(1.1),
 // R = 16 a mode took 255 us.)
 //
-// Stream: 64 nonzeros a load, lane (g, m) taking nonzero 4 NS (m / NS) + NS g +
-// m % NS, so step s of the h-th sub-chunk of 4 NS finds its nonzero in lane
-// h NS + s of each row of 16: a row broadcast (DPP), folded into the address
-// add.  The rows of the next sub-chunk are in flight while one is contracted.
+// Stream: 64 nonzeros a load, lane (g, m) taking nonzero 4 m + g, so step s of the
+// 16 has nonzeros 4 s .. 4 s + 3, each in lane s of its row of 16: a row broadcast
+// (DPP), folded into the address add.  The rows of the next sub-chunk are in flight while one is contracted.
 // Nonzeros outside the segment at hand are zeroed in both operands (so that an
 // infinity in one segment's row leaves the others alone).
 //
@@ -82,16 +81,19 @@ __device__ __forceinline__ void unroll(F &&f)
     }
 }
 
-template <typename FT>
-__device__ __forceinline__ float load_elem(const char *p)
-{
-    if constexpr (sizeof(FT) == 4) return *reinterpret_cast<const float *>(p);
-    else return bf16_to_f32(*reinterpret_cast<const uint16_t *>(p));
-}
+// the register is loaded from here on: a use further down waits for nothing
+__device__ __forceinline__ void loaded(float &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void loaded(uint32_t &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void loaded(float2 &x) { loaded(x.x), loaded(x.y); }
+__device__ __forceinline__ void loaded(uint2 &x) { loaded(x.x), loaded(x.y); }
+__device__ __forceinline__ void loaded(float4 &x) { loaded(x.x), loaded(x.y), loaded(x.z), loaded(x.w); }
 
-// NA: product modes of the A side (1, 2 or 0: runtime, np - 1).  WIDE: a factor
-// of 4 GiB or more (64-bit row offsets instead of a 32-bit one on the base)
-template <typename FT, int BA, int BB, int NA, bool WIDE = false>
+// NA: product modes of the A side (1, 2 or 0: runtime, np - 1).  VB: columns of the B
+// side that a lane holds next to each other, one of each of VB blocks (BB where it
+// divides RB, else 1): its element of a row is one load and of a result row one
+// store (RA = 5, RB = 40, bfloat16, 3.9M nonzeros, 194 us with four loads of one, now 165).
+// WIDE: a factor of 4 GiB or more (64-bit row offsets instead of a 32-bit one on the base)
+template <typename FT, int BA, int BB, int NA, int VB = 1, bool WIDE = false>
 __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcArgs A)
 {
     constexpr int NAM = NA > 0 ? NA : kMaxOrder - 1;
@@ -115,7 +117,8 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
     // this lane's element of each A-side mode's row and of the last mode's row;
     // elements past the ranks read element 0 and are never stored
     int pa0[BA][NAM];
-    int pb0[BB];
+    constexpr int NVB = BB / VB;                               // column b of lane m: (b / VB, VB m + b % VB)
+    int pb0[NVB];
 #pragma unroll
     for (int a = 0; a < BA; ++a) {
         const int p = (ya * BA + a) * 16 + m;
@@ -128,8 +131,8 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
         }
     }
 #pragma unroll
-    for (int b = 0; b < BB; ++b) {
-        const int p = (yb * BB + b) * 16 + m;
+    for (int b = 0; b < NVB; ++b) {
+        const int p = (yb * BB + b) * 16 + m * VB;
         pb0[b] = (p < A.RB ? p : 0) * (int)sizeof(FT);
     }
 
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
     };
     clear(acc);
     clear(tot);
-    // register v of lane (g, m) holds column (16 a + 4 g + v, 16 b + m) of the block
+    // register v of lane (g, m) holds column (16 a + 4 g + v, 16 b + m) of the block (VB = 1)
     auto store = [&](float *rowp) {
 #pragma unroll
         for (int a = 0; a < BA; ++a)
@@ -164,9 +167,12 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
                 const int pa = (ya * BA + a) * 16 + 4 * g + v;
                 if (pa >= A.RA) continue;
 #pragma unroll
-                for (int b = 0; b < BB; ++b) {
-                    const int pb = (yb * BB + b) * 16 + m;
-                    if (pb < A.RB) rowp[pa * A.RB + pb] = tot[a][b][v];
+                for (int b = 0; b < NVB; ++b) {
+                    const int pb = (yb * BB + b) * 16 + m * VB;
+                    float x[VB];
+#pragma unroll
+                    for (int k = 0; k < VB; ++k) x[k] = tot[a][b * VB + k][v];
+                    if (pb < A.RB) store_row<VB>(rowp + (pa * A.RB + pb), x);
                 }
             }
     };
@@ -174,13 +180,16 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
     // segment open at the tile's start; tiles start at multiples of 64
     int seg = (int)load_uniform(&A.hr[s0 >> 5].y) - 1;
     bool have = false;
+    // the output row of the first segment that is closed here, then of the next one,
+    // read a segment ahead
+    int next_row = load_uniform(A.seg_row + (seg + 1));
 
     // 64 nonzeros of the stream: row indices (or byte offsets), values
     struct Stream {
         int ix[NAM + 1];
         float v;
     };
-    const int lpos = SUB * (m / NS) + NS * g + m % NS;
+    const int lpos = 4 * m + g;
     auto load_stream = [&](uint32_t base, Stream &st) {
         const uint32_t e0 = base + (uint32_t)lpos;
         const uint32_t e = e0 < A.nnz ? e0 : A.nnz;            // the streams' padding past Z
@@ -199,15 +208,16 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
         st.ix[NAM] = (int)((uint32_t)st.ix[NAM] * (uint32_t)(A.RB * (int)sizeof(FT)));
     };
     struct Rows {
-        float a[NS][BA][NAM];
-        float b[NS][BB];
+        Raw<FT, 1> a[NS][BA][NAM];
+        Raw<FT, VB> b[NS][NVB];
     };
     auto gather = [&](const Stream &st, auto hc, Rows &r) {
         constexpr int H = decltype(hc)::value;
-        auto row = [&](int q, int x, int col) -> const char * {
+        auto row = [&](int q, int x, int col) -> const FT * {
             const char *f = reinterpret_cast<const char *>(A.fac[q]);
-            if constexpr (WIDE) return f + (uint64_t)(uint32_t)x * (uint64_t)(uint32_t)(A.kr[q] * (int)sizeof(FT)) + (uint32_t)col;
-            else return f + ((uint32_t)x + (uint32_t)col);
+            if constexpr (WIDE) f += (uint64_t)(uint32_t)x * (uint64_t)(uint32_t)(A.kr[q] * (int)sizeof(FT)) + (uint32_t)col;
+            else f += (uint32_t)x + (uint32_t)col;
+            return reinterpret_cast<const FT *>(f);
         };
         unroll<NS>([&](auto sc) {
             constexpr int S = decltype(sc)::value;
@@ -216,11 +226,11 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
                 if (q >= na) continue;
                 const int x = row_bcast<H * NS + S>(st.ix[q]);
 #pragma unroll
-                for (int a = 0; a < BA; ++a) r.a[S][a][q] = load_elem<FT>(row(q, x, pa0[a][q]));
+                for (int a = 0; a < BA; ++a) load_raw<FT, 1>(row(q, x, pa0[a][q]), r.a[S][a][q]);
             }
             const int x = row_bcast<H * NS + S>(st.ix[NAM]);
 #pragma unroll
-            for (int b = 0; b < BB; ++b) r.b[S][b] = load_elem<FT>(row(na, x, pb0[b]));
+            for (int b = 0; b < NVB; ++b) load_raw<FT, VB>(row(na, x, pb0[b]), r.b[S][b]);
         });
     };
     auto contract = [&](const Rows &r, int S, float v, bool act) {
@@ -230,11 +240,20 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
             float x = v;
 #pragma unroll
             for (int q = 0; q < NAM; ++q)
-                if (q < na) x *= r.a[S][a][q];
+                if (q < na) {
+                    float f[1];
+                    to_float<FT, 1>(r.a[S][a][q], f);
+                    x *= f[0];
+                }
             av[a] = act ? x : 0.f;
         }
 #pragma unroll
-        for (int b = 0; b < BB; ++b) bv[b] = act ? r.b[S][b] : 0.f;
+        for (int b = 0; b < NVB; ++b) {
+            float f[VB];
+            to_float<FT, VB>(r.b[S][b], f);
+#pragma unroll
+            for (int k = 0; k < VB; ++k) bv[b * VB + k] = act ? f[k] : 0.f;
+        }
 #pragma unroll
         for (int a = 0; a < BA; ++a)
 #pragma unroll
@@ -242,7 +261,7 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
                 acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc[a][b], 0, 0, 0);
     };
     // one sub-chunk: heads `hm` among its first n nonzeros
-    auto consume = [&](const Rows &r, auto hc, float vreg, uint32_t hm, int n) {
+    auto consume = [&](Rows &r, auto hc, float vreg, uint32_t hm, int n) {
         constexpr int H = decltype(hc)::value;
         if (hm == 0u && n >= SUB) {
             unroll<NS>([&](auto sc) {
@@ -251,29 +270,44 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
             });
             return;
         }
-        const int nn = n < SUB ? n : SUB;
-        for (int lo = 0; lo < nn;) {
-            if ((hm >> lo) & 1u) {
+        if constexpr (NA > 0) {
+            // the sub-chunk's rows are waited for here: inside the loop that wait would
+            // be for the stores of the segments before, too (a counter has both in order)
+#pragma unroll
+            for (int S = 0; S < NS; ++S) {
+#pragma unroll
+                for (int a = 0; a < BA; ++a)
+#pragma unroll
+                    for (int q = 0; q < NAM; ++q) loaded(r.a[S][a][q].v);
+#pragma unroll
+                for (int b = 0; b < NVB; ++b) loaded(r.b[S][b].v);
+            }
+        }
+        // step by step, and in a step segment by segment: rows of a few nonzeros meet a
+        // head every other step, and looking for the steps of each segment among the
+        // sub-chunk's cost more than its products
+        unroll<NS>([&](auto sc) {
+            constexpr int S = decltype(sc)::value;
+            if (n <= 4 * S) return;
+            const uint32_t live = n - 4 * S >= 4 ? 15u : (1u << (n - 4 * S)) - 1u;
+            const float v = row_bcast<H * NS + S>(vreg);
+            uint32_t heads = (hm >> (4 * S)) & live;
+            uint32_t mask = live & ((heads & (0u - heads)) - 1u);     // up to the first head (all, with none)
+            if (mask) contract(r, S, v, (mask >> g) & 1u);
+            while (heads) {
                 // a segment starts: the one before it is complete, or is the tile's first partial
                 add_up();
-                store(have ? A.out + (int64_t)load_uniform(A.seg_row + seg) * W : A.carry_a + tile * W);
+                store(have ? A.out + (int64_t)next_row * W : A.carry_a + tile * W);
+                if (have) next_row = load_uniform(A.seg_row + seg + 1);
                 have = true;
                 ++seg;
                 clear(tot);
+                const uint32_t rest = heads & (heads - 1u);
+                mask = live & ((rest & (0u - rest)) - 1u) & ~((heads & (0u - heads)) - 1u);
+                contract(r, S, v, (mask >> g) & 1u);
+                heads = rest;
             }
-            const uint32_t rest = hm & ~((2u << lo) - 1u);
-            const int next = rest ? __builtin_ctz(rest) : nn;
-            const int hi = next < nn ? next : nn;
-            const uint32_t mask = (hi >= 32 ? ~0u : ((1u << hi) - 1u)) & ~((1u << lo) - 1u);
-            const uint32_t mine = mask >> (NS * g);
-            unroll<NS>([&](auto sc) {
-                constexpr int S = decltype(sc)::value;
-                constexpr uint32_t slots = NS == 8 ? 0x01010101u : 0x1111u;
-                const float v = row_bcast<H * NS + S>(vreg);
-                if ((mask >> S) & slots) contract(r, S, v, (mine >> S) & 1u);
-            });
-            lo = hi;
-        }
+        });
     };
 
     Stream cur, nxt;
@@ -312,23 +346,30 @@ __global__ __launch_bounds__(256, (BA * BB > 1 ? 2 : 4)) void ttmc_kernel(TtmcAr
 
 namespace {
 
-template <typename FT, int BA, int BB>
+template <typename FT, int BA, int BB, int VB>
 void ttmc_na(const dev::TtmcArgs &a, dim3 grid, hipStream_t s)
 {
-    if (a.np == 2) hipLaunchKernelGGL((dev::ttmc_kernel<FT, BA, BB, 1>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((dev::ttmc_kernel<FT, BA, BB, 2>), grid, dim3(256), 0, s, a);
+    if (a.np == 2) hipLaunchKernelGGL((dev::ttmc_kernel<FT, BA, BB, 1, VB>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((dev::ttmc_kernel<FT, BA, BB, 2, VB>), grid, dim3(256), 0, s, a);
+}
+
+template <typename FT, int BA, int BB>
+void ttmc_vb(const dev::TtmcArgs &a, dim3 grid, hipStream_t s)
+{
+    if (a.RB % BB == 0) ttmc_na<FT, BA, BB, BB>(a, grid, s);
+    else ttmc_na<FT, BA, BB, 1>(a, grid, s);
 }
 
 template <typename FT>
 void ttmc_shape(const dev::TtmcArgs &a, bool wide, int ba, int bb, dim3 grid, hipStream_t s)
 {
-    if (wide) hipLaunchKernelGGL((dev::ttmc_kernel<FT, 1, 1, 0, true>), grid, dim3(256), 0, s, a);
+    if (wide) hipLaunchKernelGGL((dev::ttmc_kernel<FT, 1, 1, 0, 1, true>), grid, dim3(256), 0, s, a);
     else if (a.np > 3) hipLaunchKernelGGL((dev::ttmc_kernel<FT, 1, 1, 0>), grid, dim3(256), 0, s, a);
-    else if (ba == 1 && bb == 1) ttmc_na<FT, 1, 1>(a, grid, s);
-    else if (ba == 1 && bb == 2) ttmc_na<FT, 1, 2>(a, grid, s);
-    else if (ba == 2 && bb == 1) ttmc_na<FT, 2, 1>(a, grid, s);
-    else if (ba == 2 && bb == 2) ttmc_na<FT, 2, 2>(a, grid, s);
-    else ttmc_na<FT, 1, 4>(a, grid, s);
+    else if (ba == 1 && bb == 1) ttmc_na<FT, 1, 1, 1>(a, grid, s);
+    else if (ba == 1 && bb == 2) ttmc_vb<FT, 1, 2>(a, grid, s);
+    else if (ba == 2 && bb == 1) ttmc_na<FT, 2, 1, 1>(a, grid, s);
+    else if (ba == 2 && bb == 2) ttmc_vb<FT, 2, 2>(a, grid, s);
+    else ttmc_vb<FT, 1, 4>(a, grid, s);
 }
 
 }  // namespace
