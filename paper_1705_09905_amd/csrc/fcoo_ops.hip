@@ -186,27 +186,39 @@ struct ModelArgs {
     int64_t nnz;
     int order;
     int R;
+    int per;                         // nonzeros a lane group takes in turn
 };
 
-// xhat[e] = sum_r prod_m A_m[i_m(e), r]: a wave takes 64 consecutive nonzeros, one
-// index a lane and mode (the next 64 in flight meanwhile), and its lane groups of
-// LPN lanes their own LPN of them, each lane VW columns of a row (the last piece
-// moved down to end at column R, rank tiles looped inside), the gathers of a
-// batch of nonzeros back to back; lane j keeps the sum of the group's j-th.
+// gathered nonzeros in flight per lane group, by the registers their rows take; half
+// as many over more than one rank tile, whose gathers wait on each other (more waves
+// then: 0.9M nonzeros, order 3, bfloat16, R = 200 149 us, now 143)
+template <typename FT, int VW, int LPN, int NM, bool TILES>
+constexpr int model_batch()
+{
+    constexpr int regs = (NM > 0 ? NM : kMaxOrder) * (int)(sizeof(Raw<FT, VW>) / 4), all = TILES ? 24 : 48;
+    constexpr int fit = pow2_floor(all / regs > 0 ? all / regs : 1);
+    return fit < LPN ? fit : LPN;
+}
+
+// xhat[e] = sum_r prod_m A_m[i_m(e), r]: a lane group of LPN lanes takes `per`
+// consecutive nonzeros (LPN at most), one index a lane and mode (the next ones in
+// flight meanwhile), each lane VW columns of a row (the last piece moved down to
+// end at column R, rank tiles looped inside), the gathers of a batch of nonzeros
+// back to back; lane j keeps the sum of the group's j-th.
 // (One nonzero a group at a time, and one column a lane at ranks that are no
 // multiple of the vector: 20M Zipf nonzeros, float32, R = 16 368 us, R = 10 3556;
 // now 316 and 371.  The gathers of random rows bound it.)
-template <typename FT, int VW, int LPN, int NM>
+template <typename FT, int VW, int LPN, int NM, bool TILES>
 __global__ __launch_bounds__(256) void model_kernel(ModelArgs A)
 {
     constexpr int NMM = NM > 0 ? NM : kMaxOrder;
-    constexpr int RAW = (int)(sizeof(Raw<FT, VW>) / 4);
-    constexpr int FIT = pow2_floor(48 / (NMM * RAW) > 0 ? 48 / (NMM * RAW) : 1);
-    constexpr int BS = FIT < LPN ? FIT : LPN;                  // nonzeros per batch
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int BS = model_batch<FT, VW, LPN, NM, TILES>();         // nonzeros per batch
+    constexpr uint32_t G = 256 / LPN;                          // lane groups of the workgroup
+    const int lane = threadIdx.x & 63;
     const int j = lane % LPN;
-    const int nm = NM > 0 ? NM : A.order;
-    const uint32_t nnz = (uint32_t)A.nnz, stride = gridDim.x * 256u;
+    const int nm = NM > 0 ? NM : A.order, per = LPN == BS ? BS : A.per;
+    const uint32_t nnz = (uint32_t)A.nnz, stride = gridDim.x * G * (uint32_t)per;
+    const uint32_t wave0 = (blockIdx.x * G + (threadIdx.x & ~63u) / LPN) * (uint32_t)per;   // this wave's first nonzero
     int cur[NMM], nxt[NMM];
     auto load = [&](uint32_t e, int (&ix)[NMM]) {
         const uint32_t ec = e < nnz ? e : nnz - 1;
@@ -214,13 +226,15 @@ __global__ __launch_bounds__(256) void model_kernel(ModelArgs A)
         for (int m = 0; m < NMM; ++m)
             if (m < nm) ix[m] = __builtin_nontemporal_load(A.idx[m] + ec);
     };
-    uint32_t e = blockIdx.x * 256u + (uint32_t)(w * 64 + lane);
-    load(e, cur);
-    for (; e - (uint32_t)lane < nnz; e += stride) {
+    const uint32_t off = (uint32_t)(lane / LPN * per + j);     // (lanes past `per` hold the next group's)
+    load(wave0 + off, cur);
+    for (uint32_t e0 = wave0; e0 < nnz; e0 += stride) {
+        const uint32_t e = e0 + off;
         load(e + stride, nxt);
         float mine = 0.f;
         static_for<LPN / BS>([&](auto bc) {
             constexpr int B0 = decltype(bc)::value * BS;
+            if (B0 >= per) return;
             float s[BS];
 #pragma unroll
             for (int b = 0; b < BS; ++b) s[b] = 0.f;
@@ -228,17 +242,23 @@ __global__ __launch_bounds__(256) void model_kernel(ModelArgs A)
                 const int c0 = t0 + j * VW;
                 const bool cval = c0 < A.R;
                 const int c1 = c0 + VW <= A.R ? c0 : A.R - VW;
-                const int col = cval ? c1 : 0, dup = cval ? c0 - c1 : VW;   // columns the lane before sums
+                const int col = c1, dup = cval ? c0 - c1 : VW;          // columns the lane before sums
                 Raw<FT, VW> raw[BS][NMM];
+                int ix[BS][NMM];
                 static_for<BS>([&](auto sc) {
                     constexpr int S = decltype(sc)::value;
 #pragma unroll
-                    for (int m = 0; m < NMM; ++m) {
-                        if (m >= nm) continue;
-                        const int ix = bcast_imm<LPN, B0 + S>(cur[m]);
-                        load_raw<FT, VW>(reinterpret_cast<const FT *>(A.fac[m]) + (int64_t)ix * A.R + col, raw[S][m]);
-                    }
+                    for (int m = 0; m < NMM; ++m)
+                        if (m < nm) ix[S][m] = bcast_imm<LPN, B0 + S>(cur[m]);
                 });
+                if (cval) {                                             // (lanes past R read nothing and sum nothing)
+#pragma unroll
+                    for (int b = 0; b < BS; ++b)
+#pragma unroll
+                        for (int m = 0; m < NMM; ++m)
+                            if (m < nm)
+                                load_raw<FT, VW>(reinterpret_cast<const FT *>(A.fac[m]) + (int64_t)ix[b][m] * A.R + col, raw[b][m]);
+                }
 #pragma unroll
                 for (int b = 0; b < BS; ++b) {
                     float p[VW];
@@ -261,7 +281,7 @@ __global__ __launch_bounds__(256) void model_kernel(ModelArgs A)
                 mine = j == B0 + b ? x : mine;
             }
         });
-        if (e < nnz) A.xhat[e] = mine;
+        if (j < per && e < nnz) A.xhat[e] = mine;
 #pragma unroll
         for (int m = 0; m < NMM; ++m) cur[m] = nxt[m];
     }
@@ -434,16 +454,26 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
     return FCOO_OK;
 }
 
-template <typename FT, int VW, int LPN>
+template <typename FT, int VW, int LPN, bool TILES = false>
 static void model_nm(const dev::ModelArgs &a, hipStream_t s)
 {
-    // waves of 64 nonzeros, several each where there are enough to fill the chip
-    const dim3 g(grid_for(a.nnz, 256, 256 * 32)), b(256);
+    // a lane group takes a batch of nonzeros, or several up to its lanes where that
+    // leaves the chip 32k waves and more: with LPN each, few nonzeros or wide rows had
+    // few waves in flight (13k nonzeros, order 5, R = 256 46 us, now 13)
+    auto go = [&](auto nm) {
+        constexpr int NM = decltype(nm)::value;
+        dev::ModelArgs x = a;
+        x.per = dev::model_batch<FT, VW, LPN, NM, TILES>();
+        while (x.per < LPN && a.nnz / (x.per * (64 / LPN)) > 32768) x.per *= 2;
+        hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, NM, TILES>), dim3(grid_for(a.nnz, x.per * (256 / LPN), 256 * 32)),
+                           dim3(256), 0, s, x);
+    };
     switch (a.order) {
-        case 2: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 2>), g, b, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 3>), g, b, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 4>), g, b, 0, s, a); break;
-        default: hipLaunchKernelGGL((dev::model_kernel<FT, VW, LPN, 0>), g, b, 0, s, a); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case 5: go(std::integral_constant<int, 5>{}); break;
+        default: go(std::integral_constant<int, 0>{}); break;
     }
 }
 
@@ -459,7 +489,7 @@ static hipError_t model_go(const dev::ModelArgs &a, int vw, int lpn, hipStream_t
         case 2: model_nm<FT, V, 2>(a, s); break;
         case 4: model_nm<FT, V, 4>(a, s); break;
         case 8: model_nm<FT, V, 8>(a, s); break;
-        default: model_nm<FT, V, 16>(a, s); break;
+        default: a.R > 16 * V ? model_nm<FT, V, 16, true>(a, s) : model_nm<FT, V, 16>(a, s); break;
     }
     return hipGetLastError();
 }
