@@ -24,26 +24,26 @@
 namespace fcoo {
 namespace dev {
 
-// rows summed in float32 before they go to float64 (bfloat16: the order of sums
-// that CP-ALS with bfloat16 factors keeps, see TileProblem::keep_order)
-template <typename FT> constexpr int kGramFlush = sizeof(FT) == 4 ? 64 : 256;
+// rows that the row solve sums in float32 before they go to float64 with bfloat16
+// factors: the order of sums that CP-ALS keeps there, see TileProblem::keep_order
+constexpr int kGramChain = 256;
 constexpr int kCpBlocks = 256;         // workgroups of the row solve passes at most
 constexpr int kMaxCpR = 64;            // R bound of the in-LDS solve
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
-// Partial Gram of `rows` rows (a multiple of 1024) for the 32 x 32 tile
-// pair (tr, tc): each wave accumulates its quarter of the rows on the matrix
-// cores (float32 inputs: 32x32x2; bfloat16: 32x32x8), in float64 past
-// kGramFlush rows of its own; the four waves are summed in float64 and written to
-// partial[blk][R x R].  The operands of the next GU matrix steps are loaded
-// while the current ones run.
+// Partial Gram of `rows` rows (float32: 256 or 1024; bfloat16: 1024) for the 32 x 32
+// tile pair (tr, tc): each wave accumulates its quarter of the rows on the matrix
+// cores (float32 inputs: 32x32x2; bfloat16: 32x32x8), the four waves are summed in
+// float64 and written to partial[blk][R x R].  The operands of the next GU matrix
+// steps are loaded while the current ones run.  (Shorter chains in float32, added
+// up every 64 rows, cost 10-20%: 1.1M rows, R = 12, 58 us.)
 template <typename FT>
 __global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict__ A, int64_t I, int R, int rows,
                                                            double *__restrict__ partial)
 {
-    __shared__ double red[32][33];
+    __shared__ float red[4][32][33];
     const int ntile = (R + 31) / 32;
     const int tr = blockIdx.y / ntile, tc = blockIdx.y % ntile;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -54,13 +54,8 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict_
     const bool va = ca < R, vb = cb < R;
     const int kk = lane >> 5;
     floatx16 acc;
-    double sum[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { acc[v] = 0.f; sum[v] = 0.0; }
-    auto flush = [&]() {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { sum[v] += (double)acc[v]; acc[v] = 0.f; }
-    };
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     constexpr int GU = 8;                                    // matrix steps per operand batch
     if constexpr (sizeof(FT) == 4) {
         const float *Af = reinterpret_cast<const float *>(A);
@@ -82,7 +77,6 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict_
             for (int u = 0; u < GU; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0v[u], acc, 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < GU; ++u) { a0[u] = a1[u]; b0v[u] = b1[u]; }
-            if ((i - r0) % kGramFlush<FT> == kGramFlush<FT> - STEP) flush();
         }
     } else {
         const uint16_t *Ab = reinterpret_cast<const uint16_t *>(A);
@@ -108,49 +102,49 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const FT *__restrict_
             for (int u = 0; u < GB; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a0[u], b0v[u], acc, 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < GB; ++u) { a0[u] = a1[u]; b0v[u] = b1[u]; }
-            if ((i - r0) % kGramFlush<FT> == kGramFlush<FT> - STEP) flush();
         }
     }
-    flush();
     // accumulator v of lane l holds tile element (8 (v/4) + 4 (l/32) + v%4, l%32)
-    for (int k = 0; k < 4; ++k) {
-        if (w == k) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                double &x = red[8 * (v >> 2) + 4 * kk + (v & 3)][lane & 31];
-                x = k ? x + sum[v] : sum[v];
-            }
-        }
-        __syncthreads();
-    }
+    for (int v = 0; v < 16; ++v) red[w][8 * (v >> 2) + 4 * kk + (v & 3)][lane & 31] = acc[v];
+    __syncthreads();
     for (int e = threadIdx.x; e < 32 * 32; e += 256) {
-        const int gi = tr * 32 + (e >> 5), gj = tc * 32 + (e & 31);
-        if (gi < R && gj < R) partial[(int64_t)blockIdx.x * R * R + (int64_t)gi * R + gj] = red[e >> 5][e & 31];
+        const int i = e >> 5, jj = e & 31;
+        const int gi = tr * 32 + i, gj = tc * 32 + jj;
+        if (gi < R && gj < R) {
+            const double s = ((double)red[0][i][jj] + (double)red[1][i][jj]) + ((double)red[2][i][jj] + (double)red[3][i][jj]);
+            partial[(int64_t)blockIdx.x * R * R + (int64_t)gi * R + gj] = s;
+        }
     }
 }
 
-// out[e] = sum_b partial[b][e] (b < nblk): 32 elements x 8 strided shares of the
-// blocks per workgroup (whole 256-byte pieces per load), the shares added in a
-// fixed order, so repeatable.
-__global__ __launch_bounds__(256) void sum_blocks_kernel(const double *__restrict__ partial, int64_t nblk,
-                                                         int64_t n_per, double *__restrict__ out)
+// out[e] = sum_b partial[b][e] (b < nblk): X elements x Y strided shares of the
+// blocks per workgroup, the shares added in a fixed order, so repeatable.
+template <int X, int Y>
+__global__ __launch_bounds__(X * Y) void sum_blocks_kernel(const double *__restrict__ partial, int64_t nblk,
+                                                           int64_t n_per, double *__restrict__ out)
 {
-    __shared__ double red[8][32];
-    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
-    const int64_t e = (int64_t)blockIdx.x * 32 + x;
+    __shared__ double red[Y][X];
+    const int x = threadIdx.x % X, y = threadIdx.x / X;
+    const int64_t e = (int64_t)blockIdx.x * X + x;
     double s = 0.0;
     if (e < n_per) {
-        for (int64_t b = y; b < nblk; b += 64) {
+        for (int64_t b = y; b < nblk; b += 8 * Y) {
             double v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = b + 8 * u < nblk ? partial[(b + 8 * u) * n_per + e] : 0.0;
+            for (int u = 0; u < 8; ++u) v[u] = b + Y * u < nblk ? partial[(b + Y * u) * n_per + e] : 0.0;
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += v[u];
         }
     }
     red[y][x] = s;
     __syncthreads();
+    for (int o = Y / 2; o >= 8; o >>= 1) {
+        if (y < o) red[y][x] += red[y + o][x];
+        __syncthreads();
+    }
     if (y == 0 && e < n_per) {
+        s = red[0][x];
         for (int k = 1; k < 8; ++k) s += red[k][x];
         out[e] = s;
     }
@@ -535,7 +529,7 @@ __global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *
                 }
                 acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
             }
-            if ((i0 + RT::ROWS) % kGramFlush<FT> == 0 || i0 + RT::ROWS >= I) flush();
+            if ((i0 + RT::ROWS) % kGramChain == 0 || i0 + RT::ROWS >= I) flush();
             continue;
         }
 #pragma unroll 8
@@ -653,25 +647,26 @@ static hipError_t rowsolve_rc(int nblk, int tpb, hipStream_t s, const float *M, 
     return hipGetLastError();
 }
 
-// out = sum over nblk blocks of R x R partials
+// out = sum over nblk blocks of R x R partials: 32 elements a workgroup (whole
+// 256-byte pieces per load), with few elements and many blocks 8
 static hipError_t sum_blocks(const double *partial, int nblk, int R, double *out, hipStream_t s)
 {
     const int n = R * R;
-    hipLaunchKernelGGL(dev::sum_blocks_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, s, partial, (int64_t)nblk,
-                       (int64_t)n, out);
+    const dim3 g((unsigned)((n + 31) / 32)), g8((unsigned)((n + 7) / 8));
+    if (nblk <= 256)
+        hipLaunchKernelGGL((dev::sum_blocks_kernel<32, 8>), g, dim3(256), 0, s, partial, (int64_t)nblk, (int64_t)n, out);
+    else if (n > 1024)
+        hipLaunchKernelGGL((dev::sum_blocks_kernel<32, 32>), g, dim3(1024), 0, s, partial, (int64_t)nblk, (int64_t)n, out);
+    else
+        hipLaunchKernelGGL((dev::sum_blocks_kernel<8, 128>), g8, dim3(1024), 0, s, partial, (int64_t)nblk, (int64_t)n, out);
     return hipGetLastError();
 }
 
-// rows per Gram workgroup: 256 (bfloat16 1024: whole chains of its order of sums),
-// more past 512 workgroups (bounded partials)
-static int gram_rows(int64_t I, int dtype)
-{
-    const int unit = dtype == FCOO_F32 ? 256 : 1024;
-    return unit * ceil_div(ceil_div(I, 512), unit);
-}
+// Rows per Gram workgroup: 1024, or 256 where there are few (float32; bfloat16 has
+// whole chains of its order of sums).
+static int gram_rows(int64_t I, int dtype) { return dtype == FCOO_F32 && I <= 16384 ? 256 : 1024; }
 
-// ... and its workgroups: a step function of I, which a smaller I can have more of
-// (float32: 140,000 rows take 274, 120,000 take 469)
+// ... and its workgroups, of which a smaller I can have more
 static int gram_blocks(int64_t I, int dtype) { return ceil_div(I, gram_rows(I, dtype)); }
 
 // G = A^T A (float64) of an I x R factor; partials (gram_blocks x R x R) in gpart.
