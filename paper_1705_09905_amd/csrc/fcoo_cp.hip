@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "fcoo_device.h"
 #include "fcoo_internal.h"
@@ -27,7 +28,6 @@ namespace dev {
 // rows that the row solve sums in float32 before they go to float64 with bfloat16
 // factors: the order of sums that CP-ALS keeps there, see TileProblem::keep_order
 constexpr int kGramChain = 256;
-constexpr int kCpBlocks = 256;         // workgroups of the row solve passes at most
 constexpr int kMaxCpR = 64;            // R bound of the in-LDS solve
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -316,149 +316,197 @@ __global__ __launch_bounds__(256) void als_solve_kernel(const double *__restrict
 }
 
 
-// Row solve, Y = M W (I x R, float64 accumulation), in row tiles staged in
-// LDS with W.  Lane layout: TH / RC row slots x RC columns (RC = R rounded
-// up to a power of two, R <= kMaxCpR); a tile has RPT rows per slot, and a
-// workgroup takes tiles_per_block tiles, so that what is summed over workgroups
-// is short enough for the next pass to sum in each of its own:
+// Row solve, Y = M W (I x R, float64 accumulation), in row tiles of M staged in
+// LDS, RC = R rounded up to a power of two (R <= kMaxCpR).  A thread has NY
+// elements of a tile's Y, all of one column.  From RC = 16 on they come from the
+// matrix cores (16x16x4 float64; a wave has one 16 x 16 block of the tile, and its
+// columns of W in registers), below from a loop over W in LDS.  A workgroup takes
+// tiles_per_block tiles, the next one's rows of M in flight meanwhile, so that what
+// is summed over workgroups is short enough for the next pass to sum in each of
+// its own:
 //   rownorm_kernel:  per block, the column sums of Y^2 -> partial[blk][R];
 //   rowstore_kernel: lambda_c = sqrt(sum_b partial[b][c]); A(i, c) = Y(i, c) /
 //                    lambda_c (0 when lambda_c = 0) stored as FT (bfloat16: round
 //                    to nearest even); the block's share of A^T A from the
-//                    stored values on the matrix cores -> gpart[blk][R x R];
-//                    and (ipart) of the fit's sum_i sum_r lambda_r M(i, r) A(i, r).
+//                    stored values on the matrix cores -> gpart[blk][R x R], if
+//                    given; and (ipart) of the fit's sum_i sum_r lambda_r M(i, r)
+//                    A(i, r).
 // (As five kernels -- norms, lambda, store, partial Gram, inner product -- they
 // took 11 + 5 + 10 + 13 us a mode, 14 the last, over the modes of 50k to 1k rows
-// at R = 32, now 12 + 16; for 200 rows at R = 8 21 us, now 8.)
+// at R = 32, now 6 + 14; for 200 rows at R = 8 21 us, now 8.  Products by a loop
+// over W and M in LDS, 4 rows a thread, waited on those reads: R = 48, modes of
+// 108k, 41k, 24k and 4k rows, 37 + 45 us a mode, now 18 + 26.)
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 {
     const uint32_t u = __float_as_uint(f);
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
-template <int RC> struct RowTile {
-    // threads: the products read M's tile from LDS, and one wave a SIMD waited
-    // on each read (24 us a pass at R = 32 where 16 waves a CU take 12)
-    static constexpr int TH = RC >= 16 ? 1024 : 256;
-    static constexpr int SLOTS = TH / RC;
-    static constexpr int RPT = SLOTS < 64 ? 64 / SLOTS : 1;   // rows per slot per tile
-    static constexpr int ROWS = SLOTS * RPT;                  // rows per tile (64 .. 256)
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// TH threads: 1024; 256 for few short rows, whose tiles would be few (RC <= 8)
+template <int RC, int TH> struct RowTile {
+    static constexpr bool MAT = RC >= 16;
+    static constexpr int SLOTS = TH / RC;                     // threads of a column
+    static constexpr int NY = MAT ? 4 : SLOTS < 64 ? 64 / SLOTS : 1;
+    static constexpr int ROWS = SLOTS * NY;                   // rows per tile (64 .. 1024)
     static constexpr int LD = RC >= 4 ? RC + 4 : RC;          // row stride of M's tile in LDS
+    int slot, c;                                              // this thread's
+    int lane, rt;
+    __device__ RowTile()
+    {
+        lane = threadIdx.x & 63;
+        const int w = threadIdx.x >> 6;
+        if constexpr (MAT) {
+            // block (rt, ct) of the wave: register v of lane (g, m) is element (4 v + g, m)
+            rt = w / (RC / 16);
+            c = w % (RC / 16) * 16 + (lane & 15);
+            slot = rt * 4 + (lane >> 4);
+        } else {
+            rt = 0;
+            slot = threadIdx.x / RC;
+            c = threadIdx.x % RC;
+        }
+    }
+    // tile row of element u
+    __device__ int row(int u) const { return MAT ? rt * 16 + 4 * u + (lane >> 4) : u * SLOTS + slot; }
 };
 
-template <int RC>
-__device__ __forceinline__ void load_w(const double *__restrict__ W, int R, double (&sW)[RC * RC])
-{
-    for (int e = threadIdx.x; e < RC * RC; e += RowTile<RC>::TH) {
-        const int k = e / RC, cc = e % RC;
-        sW[e] = (k < R && cc < R) ? W[k * R + cc] : 0.0;
-    }
-}
-
-// rows [i0, i0 + nrow) of M, zeros past them and past column R
-template <int RC>
-__device__ __forceinline__ void load_m(const float *__restrict__ M, int64_t i0, int nrow, int R, float *sM)
-{
-    using RT = RowTile<RC>;
-    for (int e = threadIdx.x; e < RT::ROWS * RC; e += RT::TH) {
-        const int r = e / RC, cc = e % RC;
-        sM[r * RT::LD + cc] = (r < nrow && cc < R) ? M[(i0 + r) * R + cc] : 0.f;
-    }
-}
-
-// y[u] = (row u SLOTS + slot of the tile) . (column c of W)
-template <int RC>
-__device__ __forceinline__ void row_products(const float *sM, const double (&sW)[RC * RC], int slot, int c,
-                                             double (&y)[RowTile<RC>::RPT])
-{
-    using RT = RowTile<RC>;
+// W for a thread's products: its column's elements (MAT), or all of it in LDS
+template <int RC, int TH> struct RowW {
+    static constexpr bool MAT = RC >= 16;
+    double w[MAT ? RC / 4 : 1];
+    const double *sW;
+    __device__ RowW(const RowTile<RC, TH> &t, const double *__restrict__ W, int R, double *lds) : sW(lds)
+    {
+        if constexpr (MAT) {
 #pragma unroll
-    for (int u = 0; u < RT::RPT; ++u) y[u] = 0.0;
-    if constexpr (RC >= 4) {
-#pragma unroll 2
-        for (int k = 0; k < RC; k += 4) {
-            const double w0 = sW[k * RC + c], w1 = sW[(k + 1) * RC + c];
-            const double w2 = sW[(k + 2) * RC + c], w3 = sW[(k + 3) * RC + c];
-#pragma unroll
-            for (int u = 0; u < RT::RPT; ++u) {
-                const float4 m = *reinterpret_cast<const float4 *>(sM + (u * RT::SLOTS + slot) * RT::LD + k);
-                y[u] += (double)m.x * w0;
-                y[u] += (double)m.y * w1;
-                y[u] += (double)m.z * w2;
-                y[u] += (double)m.w * w3;
+            for (int q = 0; q < RC / 4; ++q) {
+                const int k = 4 * q + (t.lane >> 4);
+                w[q] = (k < R && t.c < R) ? W[k * R + t.c] : 0.0;
+            }
+        } else {
+            for (int e = threadIdx.x; e < RC * RC; e += TH) {
+                const int k = e / RC, cc = e % RC;
+                lds[e] = (k < R && cc < R) ? W[k * R + cc] : 0.0;
             }
         }
-    } else {
-        for (int k = 0; k < RC; ++k) {
-            const double wk = sW[k * RC + c];
+    }
+    // y[u] = (row t.row(u) of the tile) . (column t.c of W)
+    __device__ void products(const RowTile<RC, TH> &t, const float *sM, double (&y)[RowTile<RC, TH>::NY]) const
+    {
+        using RT = RowTile<RC, TH>;
+        if constexpr (MAT) {
+            doublex4 d = {0.0, 0.0, 0.0, 0.0};
+            const float *m = sM + (t.rt * 16 + (t.lane & 15)) * RT::LD + (t.lane >> 4);
 #pragma unroll
-            for (int u = 0; u < RT::RPT; ++u) y[u] += (double)sM[(u * RT::SLOTS + slot) * RT::LD + k] * wk;
+            for (int q = 0; q < RC / 4; ++q)
+                d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)m[4 * q], w[q], d, 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) y[u] = d[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < RT::NY; ++u) y[u] = 0.0;
+#pragma unroll
+            for (int k = 0; k < RC; ++k) {
+                const double wk = sW[k * RC + t.c];
+#pragma unroll
+                for (int u = 0; u < RT::NY; ++u) y[u] += (double)sM[t.row(u) * RT::LD + k] * wk;
+            }
         }
     }
-}
+};
 
-template <int RC>
-__global__ __launch_bounds__(RowTile<RC>::TH) void rownorm_kernel(const float *__restrict__ M, const double *__restrict__ W,
-                                                      int64_t I, int R, int tiles_per_block,
-                                                      double *__restrict__ partial)
+// rows [i0, i0 + ROWS) of M into registers, zeros past row I and column R, and from
+// there to LDS
+template <int RC, int TH>
+__device__ __forceinline__ void fetch_m(const float *__restrict__ M, int64_t i0, int64_t I, int R,
+                                        float (&m)[RowTile<RC, TH>::NY])
 {
-    using RT = RowTile<RC>;
-    __shared__ double sW[RC * RC];
-    __shared__ __align__(16) float sM[RT::ROWS * RT::LD];
-    __shared__ double red[RT::TH];
-    const int tid = threadIdx.x;
-    const int slot = tid / RC, c = tid % RC;
-    load_w<RC>(W, R, sW);
-    double ss = 0.0;
-    const int64_t first = (int64_t)blockIdx.x * tiles_per_block * RT::ROWS;
-    for (int tt = 0; tt < tiles_per_block; ++tt) {
-        const int64_t i0 = first + (int64_t)tt * RT::ROWS;
-        if (i0 >= I) break;
-        __syncthreads();                                   // sW written / previous tile consumed
-        load_m<RC>(M, i0, I - i0 < RT::ROWS ? (int)(I - i0) : RT::ROWS, R, sM);
-        __syncthreads();
-        double y[RT::RPT];
-        row_products<RC>(sM, sW, slot, c, y);
 #pragma unroll
-        for (int u = 0; u < RT::RPT; ++u) ss += y[u] * y[u];   // rows and columns past the end are 0
-    }
-    red[tid] = ss;
-    __syncthreads();
-    if (tid < R) {
-        double s = 0.0;
-        for (int k = 0; k < RT::SLOTS; ++k) s += red[k * RC + tid];
-        partial[(int64_t)blockIdx.x * R + tid] = s;
+    for (int u = 0; u < RowTile<RC, TH>::NY; ++u) {
+        const int e = threadIdx.x + u * TH, r = e / RC, cc = e % RC;
+        m[u] = (i0 + r < I && cc < R) ? M[(i0 + r) * R + cc] : 0.f;
     }
 }
 
-template <typename FT, int RC>
-__global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *__restrict__ M, const double *__restrict__ W,
-                                                       const double *__restrict__ partial, int64_t I, int R,
-                                                       int tiles_per_block, double *__restrict__ lambda,
-                                                       FT *__restrict__ A, double *__restrict__ gpart,
-                                                       double *__restrict__ ipart)
+template <int RC, int TH>
+__device__ __forceinline__ void stage_m(const float (&m)[RowTile<RC, TH>::NY], float *sM)
 {
-    using RT = RowTile<RC>;
-    __shared__ double sW[RC * RC];
-    __shared__ __align__(16) float sM[RT::ROWS * RT::LD];      // M's tile, then the stored rows
-    __shared__ double red[RT::TH];
+#pragma unroll
+    for (int u = 0; u < RowTile<RC, TH>::NY; ++u) {
+        const int e = threadIdx.x + u * TH;
+        sM[e / RC * RowTile<RC, TH>::LD + e % RC] = m[u];
+    }
+}
+
+template <int RC, int TH>
+__global__ __launch_bounds__(TH) void rownorm_kernel(const float *__restrict__ M, const double *__restrict__ W,
+                                                     int64_t I, int R, int tiles_per_block,
+                                                     double *__restrict__ partial)
+{
+    using RT = RowTile<RC, TH>;
+    __shared__ double sW[RT::MAT ? 1 : RC * RC];
+    __shared__ float sM[RT::ROWS * RT::LD];
+    __shared__ double red[TH];
+    const RT t;
+    const int64_t first = (int64_t)blockIdx.x * tiles_per_block * RT::ROWS;
+    const int64_t last = first + (int64_t)tiles_per_block * RT::ROWS < I ? first + (int64_t)tiles_per_block * RT::ROWS : I;
+    float m[RT::NY];
+    fetch_m<RC, TH>(M, first, I, R, m);
+    const RowW<RC, TH> w(t, W, R, sW);
+    double ss = 0.0;
+    for (int64_t i0 = first; i0 < last; i0 += RT::ROWS) {
+        __syncthreads();                                   // sW written / previous tile consumed
+        stage_m<RC, TH>(m, sM);
+        __syncthreads();
+        if (i0 + RT::ROWS < last) fetch_m<RC, TH>(M, i0 + RT::ROWS, I, R, m);
+        double y[RT::NY];
+        w.products(t, sM, y);
+#pragma unroll
+        for (int u = 0; u < RT::NY; ++u) ss += y[u] * y[u];   // rows and columns past the end are 0
+    }
+    red[t.slot * RC + t.c] = ss;
+    __syncthreads();
+    if ((int)threadIdx.x < R) {
+        double s = 0.0;
+        for (int k = 0; k < RT::SLOTS; ++k) s += red[k * RC + threadIdx.x];
+        partial[(int64_t)blockIdx.x * R + threadIdx.x] = s;
+    }
+}
+
+template <typename FT, int RC, int TH>
+__global__ __launch_bounds__(TH) void rowstore_kernel(const float *__restrict__ M, const double *__restrict__ W,
+                                                      const double *__restrict__ partial, int64_t I, int R,
+                                                      int tiles_per_block, double *__restrict__ lambda,
+                                                      FT *__restrict__ A, double *__restrict__ gpart,
+                                                      double *__restrict__ ipart)
+{
+    using RT = RowTile<RC, TH>;
+    __shared__ double sW[RT::MAT ? 1 : RC * RC];
+    __shared__ float sM[RT::ROWS * RT::LD];                    // M's tile, then the stored rows
+    __shared__ double red[TH];
     __shared__ double sLam[RC];
-    __shared__ double gbuf[RC <= 32 ? 32 * 32 : 1];            // (RC = 64: four tiles, in W's place)
+    __shared__ double gbuf[RC <= 32 ? 1024 : 4096];
+    const RT t;
     const int tid = threadIdx.x;
-    const int slot = tid / RC, c = tid % RC;
-    load_w<RC>(W, R, sW);
+    const int64_t first = (int64_t)blockIdx.x * tiles_per_block * RT::ROWS;
+    const int64_t last = first + (int64_t)tiles_per_block * RT::ROWS < I ? first + (int64_t)tiles_per_block * RT::ROWS : I;
+    float m[RT::NY];
+    fetch_m<RC, TH>(M, first, I, R, m);
+    const RowW<RC, TH> wgt(t, W, R, sW);
     {   // lambda, in the same order in every workgroup
         double s = 0.0;
         const int nblk = gridDim.x;
-        if (c < R)
-            for (int b = slot; b < nblk; b += 8 * RT::SLOTS) {
+        if (t.c < R)
+            for (int b = t.slot; b < nblk; b += 8 * RT::SLOTS) {
                 double v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = b + u * RT::SLOTS < nblk ? partial[(int64_t)(b + u * RT::SLOTS) * R + c] : 0.0;
+                for (int u = 0; u < 8; ++u) v[u] = b + u * RT::SLOTS < nblk ? partial[(int64_t)(b + u * RT::SLOTS) * R + t.c] : 0.0;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) s += v[u];
             }
-        red[tid] = s;
+        red[t.slot * RC + t.c] = s;
         __syncthreads();
         if (tid < RC) {
             double l = 0.0;
@@ -469,15 +517,15 @@ __global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *
         }
         __syncthreads();
     }
-    const double lam = sLam[c];
+    const double lam = sLam[t.c];
     double inner = 0.0;
     // this wave's part of the block's Gram: a share of the rows of the one 32 x 32
     // tile, or with RC = 64 of tile (w / 2 % 2, w % 2).  bfloat16 keeps the order of
-    // sums of gram_partial_kernel (wave 0, or with RC = 64 waves 0 .. 3, 8 rows a step, in float32 over each 256 rows: a block's tiles are
-    // whole numbers of them)
+    // sums of gram_partial_kernel (wave 0, or with RC = 64 waves 0 .. 3, 8 rows a step,
+    // in float32 over each 256 rows: a block's rows are whole numbers of them)
     const int lane = tid & 63, w = tid >> 6, kk = lane >> 5;
     const int ca = (RC <= 32 ? 0 : (w >> 1 & 1) * 32) + (lane & 31), cb = (RC <= 32 ? 0 : (w & 1) * 32) + (lane & 31);
-    constexpr int NW = RT::TH / 64, GP = RC <= 32 ? NW : NW / 4;   // waves, waves per tile
+    constexpr int NW = TH / 64, GP = RC <= 32 ? NW : NW / 4;   // waves, waves per tile
     constexpr int GR = RT::ROWS / GP;
     const int g0 = (RC <= 32 ? w : w >> 2) * GR;
     double gsum[16];
@@ -488,23 +536,21 @@ __global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *
 #pragma unroll
         for (int v = 0; v < 16; ++v) { gsum[v] += (double)acc[v]; acc[v] = 0.f; }
     };
-    const int64_t first = (int64_t)blockIdx.x * tiles_per_block * RT::ROWS;
-    for (int tt = 0; tt < tiles_per_block; ++tt) {
-        const int64_t i0 = first + (int64_t)tt * RT::ROWS;
-        if (i0 >= I) break;
+    for (int64_t i0 = first; i0 < last; i0 += RT::ROWS) {
         const int nrow = I - i0 < RT::ROWS ? (int)(I - i0) : RT::ROWS;
         __syncthreads();                                   // previous tile consumed
-        load_m<RC>(M, i0, nrow, R, sM);
+        stage_m<RC, TH>(m, sM);
         __syncthreads();
-        double y[RT::RPT];
-        row_products<RC>(sM, sW, slot, c, y);
+        if (i0 + RT::ROWS < last) fetch_m<RC, TH>(M, i0 + RT::ROWS, I, R, m);
+        double y[RT::NY];
+        wgt.products(t, sM, y);
         __syncthreads();                                   // from here each element is its own thread's
 #pragma unroll
-        for (int u = 0; u < RT::RPT; ++u) {
-            const int r = u * RT::SLOTS + slot;
+        for (int u = 0; u < RT::NY; ++u) {
+            const int r = t.row(u);
             float f = lam > 0.0 ? (float)(y[u] / lam) : 0.f;
-            const int64_t o = (i0 + r) * R + c;
-            const bool in = r < nrow && c < R;
+            const int64_t o = (i0 + r) * R + t.c;
+            const bool in = r < nrow && t.c < R;
             if constexpr (sizeof(FT) == 4) {
                 if (in) reinterpret_cast<float *>(A)[o] = f;
             } else {
@@ -512,9 +558,10 @@ __global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *
                 if (in) reinterpret_cast<uint16_t *>(A)[o] = h;
                 f = bf16_to_f32(h);
             }
-            if (ipart && in) inner += lam * (double)sM[r * RT::LD + c] * (double)f;
-            sM[r * RT::LD + c] = in ? f : 0.f;
+            if (ipart && in) inner += lam * (double)sM[r * RT::LD + t.c] * (double)f;
+            sM[r * RT::LD + t.c] = in ? f : 0.f;
         }
+        if (!gpart) continue;
         __syncthreads();
         if constexpr (sizeof(FT) == 2) {
             if (w >= (RC <= 32 ? 1 : 4)) continue;
@@ -522,14 +569,15 @@ __global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *
             for (int i = 0; i < RT::ROWS; i += 8) {
                 shortx4 av, bv;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float *row = sM + (i + 4 * kk + t) * RT::LD;
-                    av[t] = (short)(ca < RC ? __float_as_uint(row[ca]) >> 16 : 0u);
-                    bv[t] = (short)(cb < RC ? __float_as_uint(row[cb]) >> 16 : 0u);
+                for (int k = 0; k < 4; ++k) {
+                    const float *row = sM + (i + 4 * kk + k) * RT::LD;
+                    av[k] = (short)(ca < RC ? __float_as_uint(row[ca]) >> 16 : 0u);
+                    bv[k] = (short)(cb < RC ? __float_as_uint(row[cb]) >> 16 : 0u);
                 }
                 acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
+                if ((i0 + i + 8) % kGramChain == 0) flush();
             }
-            if ((i0 + RT::ROWS) % kGramChain == 0 || i0 + RT::ROWS >= I) flush();
+            if (i0 + RT::ROWS >= I) flush();
             continue;
         }
 #pragma unroll 8
@@ -540,29 +588,30 @@ __global__ __launch_bounds__(RowTile<RC>::TH) void rowstore_kernel(const float *
         }
         flush();
     }
-    double *gp = gpart + (int64_t)blockIdx.x * R * R;
-    // the waves' shares of a tile added in turn
-    double *gred = RC <= 32 ? gbuf : sW;
-    __syncthreads();                                           // W has been read
-    constexpr bool ONE = sizeof(FT) == 2;
-    for (int k = 0; k < (ONE ? 1 : GP); ++k) {
-        if ((RC <= 32 ? w : w >> 2) == k) {
+    if (gpart) {
+        double *gp = gpart + (int64_t)blockIdx.x * R * R;
+        // the waves' shares of a tile added in turn
+        constexpr bool ONE = sizeof(FT) == 2;
+        for (int k = 0; k < (ONE ? 1 : GP); ++k) {
+            if ((RC <= 32 ? w : w >> 2) == k) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                double &x = gred[(RC <= 32 ? 0 : w & 3) * 1024 + (8 * (v >> 2) + 4 * kk + (v & 3)) * 32 + (lane & 31)];
-                x = k ? x + gsum[v] : gsum[v];
+                for (int v = 0; v < 16; ++v) {
+                    double &x = gbuf[(RC <= 32 ? 0 : w & 3) * 1024 + (8 * (v >> 2) + 4 * kk + (v & 3)) * 32 + (lane & 31)];
+                    x = k ? x + gsum[v] : gsum[v];
+                }
             }
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    for (int e = tid; e < R * R; e += RT::TH) {
-        const int gi = e / R, gj = e % R;
-        gp[e] = gred[(RC <= 32 ? 0 : (gi >> 5) * 2 + (gj >> 5)) * 1024 + (gi & 31) * 32 + (gj & 31)];
+        for (int e = tid; e < R * R; e += TH) {
+            const int gi = e / R, gj = e % R;
+            gp[e] = gbuf[(RC <= 32 ? 0 : (gi >> 5) * 2 + (gj >> 5)) * 1024 + (gi & 31) * 32 + (gj & 31)];
+        }
     }
     if (ipart) {
+        __syncthreads();                                       // red has been read
         red[tid] = inner;
         __syncthreads();
-        for (int o = RT::TH / 2; o >= 1; o >>= 1) {
+        for (int o = TH / 2; o >= 1; o >>= 1) {
             if (tid < o) red[tid] += red[tid + o];
             __syncthreads();
         }
@@ -618,33 +667,56 @@ static int pow2_ceil(int x)
     return p;
 }
 
-// Rows per row-solve tile for RC = R rounded up to a power of two.
-static int rowsolve_rows(int RC)
+// The row solve of an I x R mode: its threads, rows per tile, tiles per workgroup and
+// workgroups.  bfloat16 past 262,144 rows leaves the Gram to gram_partial_kernel:
+// one wave's chains of 256 rows, one after the other in each workgroup, take
+// longer there (R = 7, modes of 1.7M, 93k and few rows: rowstore_kernel 430 us a sweep,
+// without 107 and gram_partial_kernel 40).
+struct RowPlan {
+    int RC, TH, rows, tpb, nblk;
+    bool gram;
+};
+
+static int cp_blocks(int RC) { return RC <= 16 ? 512 : 256; }   // (each sums the others' norms: R doubles each)
+
+static RowPlan row_plan(int64_t I, int R, int dtype)
 {
-    switch (RC) {
-        case 1: return dev::RowTile<1>::ROWS;
-        case 2: return dev::RowTile<2>::ROWS;
-        case 4: return dev::RowTile<4>::ROWS;
-        case 8: return dev::RowTile<8>::ROWS;
-        case 16: return dev::RowTile<16>::ROWS;
-        case 32: return dev::RowTile<32>::ROWS;
-        default: return dev::RowTile<64>::ROWS;
-    }
+    RowPlan p;
+    p.RC = pow2_ceil(R);
+    p.TH = p.RC >= 16 || I > 65536 ? 1024 : 256;
+    const int slots = p.TH / p.RC;
+    p.rows = p.RC >= 16 ? 4 * slots : std::max(slots, 64);
+    p.gram = dtype == FCOO_F32 || I <= 262144;
+    const int ntiles = ceil_div(I, p.rows);
+    // (bfloat16: whole chains of 256 rows a workgroup, see rowstore_kernel)
+    const int chain = dtype == FCOO_F32 || !p.gram ? 1 : std::max(1, 256 / p.rows);
+    p.tpb = chain * ceil_div(ceil_div(ntiles, cp_blocks(p.RC)), chain);
+    p.nblk = ceil_div(ntiles, p.tpb);
+    return p;
+}
+
+template <int RC, int TH>
+static hipError_t rowsolve_th(const RowPlan &p, hipStream_t s, const float *M, const double *W, int64_t I, int R,
+                              double *norms, double *lambda, void *A, int dtype, double *gpart, double *ipart)
+{
+    const dim3 g((unsigned)p.nblk), b(TH);
+    hipLaunchKernelGGL((dev::rownorm_kernel<RC, TH>), g, b, 0, s, M, W, I, R, p.tpb, norms);
+    if (dtype == FCOO_F32)
+        hipLaunchKernelGGL((dev::rowstore_kernel<float, RC, TH>), g, b, 0, s, M, W, norms, I, R, p.tpb, lambda,
+                           (float *)A, gpart, ipart);
+    else
+        hipLaunchKernelGGL((dev::rowstore_kernel<dev::bf16raw, RC, TH>), g, b, 0, s, M, W, norms, I, R, p.tpb, lambda,
+                           (dev::bf16raw *)A, gpart, ipart);
+    return hipGetLastError();
 }
 
 template <int RC>
-static hipError_t rowsolve_rc(int nblk, int tpb, hipStream_t s, const float *M, const double *W, int64_t I, int R,
+static hipError_t rowsolve_rc(const RowPlan &p, hipStream_t s, const float *M, const double *W, int64_t I, int R,
                               double *norms, double *lambda, void *A, int dtype, double *gpart, double *ipart)
 {
-    const dim3 g((unsigned)nblk), b(dev::RowTile<RC>::TH);
-    hipLaunchKernelGGL(dev::rownorm_kernel<RC>, g, b, 0, s, M, W, I, R, tpb, norms);
-    if (dtype == FCOO_F32)
-        hipLaunchKernelGGL((dev::rowstore_kernel<float, RC>), g, b, 0, s, M, W, norms, I, R, tpb, lambda, (float *)A,
-                           gpart, ipart);
-    else
-        hipLaunchKernelGGL((dev::rowstore_kernel<dev::bf16raw, RC>), g, b, 0, s, M, W, norms, I, R, tpb, lambda,
-                           (dev::bf16raw *)A, gpart, ipart);
-    return hipGetLastError();
+    if constexpr (RC < 16)
+        if (p.TH == 256) return rowsolve_th<RC, 256>(p, s, M, W, I, R, norms, lambda, A, dtype, gpart, ipart);
+    return rowsolve_th<RC, 1024>(p, s, M, W, I, R, norms, lambda, A, dtype, gpart, ipart);
 }
 
 // out = sum over nblk blocks of R x R partials: 32 elements a workgroup (whole
@@ -722,20 +794,19 @@ int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, dou
     for (int n = 0; n < N; ++n) maxI = t->dims[n] > maxI ? t->dims[n] : maxI;
     if ((rc = ensure_device_floats(&t->ws.M, &t->ws.M_cap, maxI * R, s))) return rc;
     // scratch doubles: gram partials | W | tmp | column norms | inner products | fit, flags
-    const int RC = pow2_ceil(R);
-    const int rows_tile = rowsolve_rows(RC);
-    int most_blocks = dev::kCpBlocks;
+    int most_blocks = cp_blocks(pow2_ceil(R));
+    const int64_t norm_blocks = most_blocks;
     for (int n = 0; n < N; ++n) most_blocks = std::max(most_blocks, gram_blocks(t->dims[n], dtype));
     const int64_t gram_need = (int64_t)most_blocks * R * R + 16;
-    const int64_t need = gram_need + 2 * (int64_t)R * R + dev::kCpBlocks * (int64_t)R + dev::kCpBlocks + 16;
+    const int64_t need = gram_need + 2 * (int64_t)R * R + norm_blocks * (R + 1) + 16;
     if ((rc = ensure_device_doubles(&t->ws.dbl, &t->ws.dbl_cap, need, s))) return rc;
     if (!t->ws.host_pinned) FCOO_HIP(hipHostMalloc((void **)&t->ws.host_pinned, 64, hipHostMallocDefault));
     double *gpart = t->ws.dbl;
     double *Wd = gpart + gram_need;
     double *tmpd = Wd + (int64_t)R * R;
     double *norms = tmpd + (int64_t)R * R;
-    double *ipart = norms + dev::kCpBlocks * (int64_t)R;
-    double *fitd = ipart + dev::kCpBlocks;
+    double *ipart = norms + norm_blocks * R;
+    double *fitd = ipart + norm_blocks;
     int *flagd = reinterpret_cast<int *>(fitd + 1);
 
     if (!grams_valid)
@@ -753,24 +824,22 @@ int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, dou
         else if (R <= 32) hipLaunchKernelGGL(dev::als_solve_kernel<8>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
         else hipLaunchKernelGGL(dev::als_solve_kernel<16>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
         FCOO_HIP(hipGetLastError());
-        const int ntiles = ceil_div(I, rows_tile);
-        // (bfloat16: whole chains of 256 rows a workgroup, see rowstore_kernel)
-        const int chain = dtype == FCOO_F32 ? 1 : 256 / rows_tile;
-        const int tpb = chain * ceil_div(ceil_div(ntiles, dev::kCpBlocks), chain);
-        nblk = ceil_div(ntiles, tpb);
-        double *ip = n == N - 1 ? ipart : nullptr;
+        const RowPlan p = row_plan(I, R, dtype);
+        nblk = p.nblk;
+        double *ip = n == N - 1 ? ipart : nullptr, *gp = p.gram ? gpart : nullptr, *G = grams + (int64_t)n * R * R;
         hipError_t e;
-        switch (RC) {
-            case 1: e = rowsolve_rc<1>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
-            case 2: e = rowsolve_rc<2>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
-            case 4: e = rowsolve_rc<4>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
-            case 8: e = rowsolve_rc<8>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
-            case 16: e = rowsolve_rc<16>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
-            case 32: e = rowsolve_rc<32>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
-            default: e = rowsolve_rc<64>(nblk, tpb, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gpart, ip); break;
+        switch (p.RC) {
+            case 1: e = rowsolve_rc<1>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
+            case 2: e = rowsolve_rc<2>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
+            case 4: e = rowsolve_rc<4>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
+            case 8: e = rowsolve_rc<8>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
+            case 16: e = rowsolve_rc<16>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
+            case 32: e = rowsolve_rc<32>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
+            default: e = rowsolve_rc<64>(p, s, t->ws.M, Wd, I, R, norms, lambda, factors[n], dtype, gp, ip); break;
         }
         if (e != hipSuccess) return hip_fail(e, "row solve");
-        FCOO_HIP(sum_blocks(gpart, nblk, R, grams + (int64_t)n * R * R, s));
+        if (p.gram) FCOO_HIP(sum_blocks(gpart, nblk, R, G, s));
+        else if ((rc = gram_launch(factors[n], dtype, I, R, gpart, G, s))) return rc;
     }
     hipLaunchKernelGGL(dev::fit_kernel, dim3(1), dim3(256), 0, s, ipart, (int64_t)nblk, grams, N, R, lambda,
                        t->normX2, fitd);

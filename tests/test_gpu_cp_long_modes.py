@@ -16,7 +16,12 @@ pytestmark = [pytest.mark.gpu,
 
 
 @pytest.mark.parametrize("dtype,R,dims", [("f32", 8, [140000, 120000, 50]), ("f32", 33, [131073, 131072, 50]),
-                                          ("bf16", 8, [600000, 500000, 50]), ("bf16", 33, [524289, 524288, 50])])
+                                          ("bf16", 8, [600000, 500000, 50]), ("bf16", 33, [524289, 524288, 50]),
+                                          # (rows past one workgroup's first tiles, for every row length)
+                                          ("f32", 1, [70000, 65537, 9]), ("f32", 2, [140001, 300, 9]),
+                                          ("f32", 4, [66000, 300, 50]), ("f32", 16, [132000, 300, 50]),
+                                          ("bf16", 1, [262144, 300, 9]), ("bf16", 3, [262145, 70000, 50]),
+                                          ("bf16", 7, [200000, 300, 50]), ("bf16", 20, [262145, 66000, 50])])
 def test_fresh_sweep(dtype, R, dims):
     import torch
     import paper_1705_09905_amd as P
