@@ -757,6 +757,29 @@ static int gram_launch(const void *A, int dtype, int64_t I, int R, double *gpart
     return FCOO_OK;
 }
 
+// Whether mode n's solve runs beside its SpMTTKRP (it needs only the other modes'
+// Grams), on a stream of its own.  The two waits between the streams cost as much
+// as the solve takes at R = 32 (20 us) and four times that at R = 8, so only where it
+// is longer and the SpMTTKRP is too: R > 32 with bfloat16 (R = 48, five modes, 2.3M
+// nonzeros, a sweep: 1256 us in turn, beside it 1112), and where V is singular for sure,
+// having at most as many dimensions as the other modes' extents have products, so
+// that the solve is the eigendecomposition (R = 17, 253 x 5: 1426, 1313).
+static bool solve_aside(const fcoo_tensor *t, int n, int R, int dtype)
+{
+    int64_t dim = 1;
+    for (int m = 0; m < t->order && dim < R; ++m)
+        if (m != n) dim *= t->dims[m];
+    return dim < R || (dtype == FCOO_BF16 && R > 32);
+}
+
+static int aux_stream(fcoo_tensor *t)
+{
+    if (!t->aux) FCOO_HIP(hipStreamCreateWithFlags(&t->aux, hipStreamNonBlocking));
+    if (!t->ev_dep) FCOO_HIP(hipEventCreateWithFlags(&t->ev_dep, hipEventDisableTiming));
+    if (!t->ev_solved) FCOO_HIP(hipEventCreateWithFlags(&t->ev_solved, hipEventDisableTiming));
+    return FCOO_OK;
+}
+
 }  // namespace fcoo
 
 using namespace fcoo;
@@ -816,14 +839,26 @@ int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, dou
     int nblk = 0;
     for (int n = 0; n < N; ++n) {
         const int64_t I = t->dims[n];
-        if ((rc = spmttkrp(t, n, (const void *const *)factors, dtype, R, t->ws.M, dtype == FCOO_BF16, s))) return rc;
-        // (on the caller's stream: beside the SpMTTKRP, on a stream of its own, the
-        // two waits between the streams cost as much as the solve takes at R = 32
-        // and four times that at R = 8)
-        if (R <= 16) hipLaunchKernelGGL(dev::als_solve_kernel<4>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
-        else if (R <= 32) hipLaunchKernelGGL(dev::als_solve_kernel<8>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
-        else hipLaunchKernelGGL(dev::als_solve_kernel<16>, dim3(1), dim3(256), 0, s, grams, N, n, R, Wd, tmpd, flagd);
+        const bool aside = solve_aside(t, n, R, dtype);
+        hipStream_t ss = s;
+        if (aside) {
+            if ((rc = aux_stream(t))) return rc;
+            ss = t->aux;
+            FCOO_HIP(hipEventRecord(t->ev_dep, s));
+            FCOO_HIP(hipStreamWaitEvent(ss, t->ev_dep, 0));
+        } else if ((rc = spmttkrp(t, n, (const void *const *)factors, dtype, R, t->ws.M, dtype == FCOO_BF16, s))) {
+            return rc;
+        }
+        if (R <= 16) hipLaunchKernelGGL(dev::als_solve_kernel<4>, dim3(1), dim3(256), 0, ss, grams, N, n, R, Wd, tmpd, flagd);
+        else if (R <= 32) hipLaunchKernelGGL(dev::als_solve_kernel<8>, dim3(1), dim3(256), 0, ss, grams, N, n, R, Wd, tmpd, flagd);
+        else hipLaunchKernelGGL(dev::als_solve_kernel<16>, dim3(1), dim3(256), 0, ss, grams, N, n, R, Wd, tmpd, flagd);
         FCOO_HIP(hipGetLastError());
+        if (aside) {
+            FCOO_HIP(hipEventRecord(t->ev_solved, ss));
+            rc = spmttkrp(t, n, (const void *const *)factors, dtype, R, t->ws.M, dtype == FCOO_BF16, s);
+            FCOO_HIP(hipStreamWaitEvent(s, t->ev_solved, 0));
+            if (rc) return rc;
+        }
         const RowPlan p = row_plan(I, R, dtype);
         nblk = p.nblk;
         double *ip = n == N - 1 ? ipart : nullptr, *gp = p.gram ? gpart : nullptr, *G = grams + (int64_t)n * R * R;

@@ -961,6 +961,9 @@ void fcoo_destroy(fcoo_tensor *t)
     for (auto &p : t->d_coo) if (p) (void)hipFree(p);
     if (t->d_coo_val) (void)hipFree(t->d_coo_val);
     t->ws.free_all();
+    if (t->ev_dep) (void)hipEventDestroy(t->ev_dep);
+    if (t->ev_solved) (void)hipEventDestroy(t->ev_solved);
+    if (t->aux) (void)hipStreamDestroy(t->aux);
     delete t;
     pool_handles(-1);
 }
