@@ -321,6 +321,12 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_ord
     const bool half_ok = dtype == FCOO_BF16 && !resid && np <= 3 && R >= 4 &&
                          (R <= 64 || (b.op == FCOO_OP_TTM && R % 64 == 0));
     LaneShape sh;
+    if (keep_order) {
+        // ranks no multiple of the vector (8, or 4 by what lane_cols and the modes say)
+        // have their sums' order from a time of one column a lane
+        const bool half = half_ok && R % 4 == 0 && (b.lane_cols == 4 || (b.lane_cols == 0 && np == 2));
+        if (R % (half ? 4 : 8)) return LaneShape{1, 64, false};
+    }
     sh.half = half_ok && (b.lane_cols == 4 || R < 8 ||
                           (b.lane_cols == 0 && (b.op == FCOO_OP_TTM ? R != 16 && R != 32 : np == 2)));
     // columns per lane: the type's vector, or the widest piece a shorter row
@@ -329,11 +335,6 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_ord
     // per lane, 64 lanes a nonzero: SpMTTKRP of 4M nonzeros, order 4, R = 25
     // took 323 us and takes 100; SpTTM of 300k, bfloat16 R = 10, 321 and 16)
     sh.vw = (dtype == FCOO_F32 || sh.half) ? 4 : 8;
-    if (keep_order && R % sh.vw) {
-        // such ranks have their sums' order from a time of one column a lane
-        const bool half = half_ok && R % 4 == 0 && sh.half;
-        return half ? LaneShape{4, next_pow2(R / 4), true} : LaneShape{1, 64, false};
-    }
     while (sh.vw > R) sh.vw >>= 1;
     sh.lpn = next_pow2((R + sh.vw - 1) / sh.vw);
     if (sh.lpn > 16) sh.lpn = 16;

@@ -282,6 +282,25 @@ static void host_memory(int device, int single_pass)
     fcoo_destroy(t);
 }
 
+// bfloat16 CP-ALS keeps one order of sums at every rank: a lane a column wherever the
+// vector of 8 (of 4 with two product modes) does not divide it.
+static void kept_order()
+{
+    using namespace fcoo;
+    for (int np : {1, 2, 3, 4})
+        for (int lane_cols : {0, 4, 8})
+            for (int R = 1; R <= 64; ++R) {
+                Built b;
+                b.op = FCOO_OP_MTTKRP;
+                b.pmodes.resize(np);
+                b.lane_cols = lane_cols;
+                const bool four = np <= 3 && (lane_cols == 4 || (lane_cols == 0 && np == 2));
+                const int V = four && R % 4 == 0 ? 4 : 8;
+                const LaneShape sh = lane_shape(b, FCOO_BF16, R, false, true);
+                CHECK(R % V ? sh.vw == 1 && sh.lpn == 64 : sh.vw == V && sh.half == (V == 4));
+            }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -307,6 +326,7 @@ int main(int argc, char **argv)
         {"carries_that_fit", [] { carries_that_fit(); }},
         {"finish_grid", [] { finish_grid(); }},
         {"host_memory", [] { host_memory(0, 0), host_memory(0, 1), host_memory(1, 0), host_memory(1, 1); }},
+        {"kept_order", [] { kept_order(); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
