@@ -457,6 +457,15 @@ void Built::set_plans(int fmt_tile, bool own)
 //   residual R = 64: 5M 209 / 133 / 139 / 168, 20M 792 / 470 / 444 / 438;
 //   SpTTM R = 32: 400k 15.4 / 13.1 / 15.6 / 24.8, 5M 114 / 75 / 78 / 102, 20M 419 /
 //   262 / 272 / 320; R = 8: 248 / 236 / 284 / 381.
+// One lane a row or pieces of two columns take 2048: a lane's run is 4 nonzeros at
+// 1024 (1024 / 2048 / 4096: SpMTTKRP of 8M, R = 4 62 / 43 / 69; 7M, order 2, bfloat16 R =
+// 8 56 / 39 / 49; 1.6M, R = 3 24 / 18 / 22; but five modes, whose path has no vectors,
+// 2.7M, R = 4 45 / 65 / 110).  Rows over several rank tiles have several workgroups a
+// tile, so 1024 from 60k nonzeros on (512 / 1024: 100k, R = 200 31 / 19; 190k 44 / 26;
+// 34k, R = 100 19 / 21).  Fibres of hardly more than one nonzero under 8-column
+// bfloat16 lanes: 512 (512 / 1024 / 4096: 2.4M, R = 16 68 / 94 / 103, R = 80 237 / 319 /
+// 316), but for wide rows in a few hundred tiles of 4096, each lane group of which
+// writes its own long stretch (750k, R = 80 90 / 103 / 66; 150k 24 / 21 / 56).
 // SpTTMc: a wave takes a tile, whatever tile a workgroup of the other operations was
 // asked to take, and where segments are short it stores row after row, so tiles are
 // as short as leaves each SIMD several waves (64 / 128 / 256 / 512 / 1024 / 4096
@@ -466,8 +475,9 @@ void Built::set_plans(int fmt_tile, bool own)
 // rows of 4000 (256) 102 / 97 / 97 / 106; 10M Zipf, rows in no order (512) 183 / 180), a
 // size longer where wide, long rows make little work between carries (1.5M, 16 x 16,
 // rows of 750 (256) 31 / 26) or a size shorter where they are few nonzeros long
-// (1.4M Zipf over 129k rows, 1 x 8 (256) 52 / 39; 3M over 100k, 16 x 16 78 / 88), and unless their carries would pass kTtmcCarries.  Past
-// 64M nonzeros short tiles gain nothing that their carries' scratch would be worth.
+// (1.4M Zipf over 129k rows, 1 x 8 (256) 52 / 39; 3M over 100k, 16 x 16 78 / 88), and
+// unless their carries would pass kTtmcCarries.  Past 64M nonzeros short tiles gain
+// nothing that their carries' scratch would be worth.
 constexpr int64_t kTtmcCarries = (int64_t)64 << 20;      // floats
 
 const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron)
@@ -483,10 +493,22 @@ const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron)
         return b.plan[0];
     }
     if (b.own_tile || large) return b.plan[0];
-    else if (b.op == FCOO_OP_TTM || lane_shape(b, dtype, R, resid).lpn <= 4) want = 1024;
-    else want = resid && b.nnz >= 10000000 ? 4096 : 2048;
-    if (b.nnz < 1000000 && want > 1024) want = 1024;
-    if (b.nnz < 200000 && want > 512) want = 512;
+    const LaneShape sh = lane_shape(b, dtype, R, resid);
+    const bool vectors = sh.vw > 1 && b.pmodes.size() <= 3;
+    if (vectors && (sh.lpn == 1 || sh.vw == 2)) {
+        want = 2048;
+    } else {
+        if (b.op == FCOO_OP_TTM && sh.vw == 8 && b.nnz < 2 * b.nseg) {
+            if (R > 64 && b.nnz >= 500000 && b.nnz < 1600000) return b.plan[0];
+            want = 512;
+        } else if (b.op == FCOO_OP_TTM || sh.lpn <= 4) {
+            want = 1024;
+        } else {
+            want = resid && b.nnz >= 10000000 ? 4096 : 2048;
+        }
+        if (b.nnz < 1000000) want = std::min(want, 1024);
+    }
+    if (b.nnz < (R > sh.lpn * sh.vw ? 60000 : 200000)) want = std::min(want, 512);
     for (const Plan &pl : b.plan)
         if (pl.T <= want) return pl;
     return b.plan.back();
@@ -680,7 +702,7 @@ static int upload_plans(Built &b, hipStream_t s, int64_t *acct)
 // Most tiles that an operation takes.
 static int64_t most_tiles(const Built &b)
 {
-    const int64_t n = pick_plan(b, FCOO_F32, 16, false, false).ntiles;
+    const int64_t n = std::max(pick_plan(b, FCOO_F32, 16, false, false).ntiles, pick_plan(b, FCOO_BF16, 16, false, false).ntiles);
     return b.pmodes.size() > 1 ? std::max(n, pick_plan(b, FCOO_F32, 16, false, true).ntiles) : n;
 }
 

@@ -316,10 +316,12 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_ord
     // 185, 24 411 / 368, 64 509 / 449, uniform 1848 / 1102), but for rows of 16
     // (236 / 253, uniform 508 / 603) or 32 (301 / 320, uniform 730 / 681), and past
     // 64 columns only for whole rank tiles of 64 (128 1205 / 854, 256 2414 / 1704; 96
-    // 703 / 815)
+    // 703 / 815), and but for few tiles of the caller's size, whose waves are too few
+    // to have half the nonzeros at a time (237k in tiles of 16384, R = 64 110 / 139)
     const int np = (int)b.pmodes.size();
     const bool half_ok = dtype == FCOO_BF16 && !resid && np <= 3 && R >= 4 &&
                          (R <= 64 || (b.op == FCOO_OP_TTM && R % 64 == 0));
+    const bool few = b.own_tile && b.plan[0].ntiles < 128;
     LaneShape sh;
     if (keep_order) {
         // ranks no multiple of the vector (8, or 4 by what lane_cols and the modes say)
@@ -328,7 +330,7 @@ LaneShape lane_shape(const Built &b, int dtype, int R, bool resid, bool keep_ord
         if (R % (half ? 4 : 8)) return LaneShape{1, 64, false};
     }
     sh.half = half_ok && (b.lane_cols == 4 || R < 8 ||
-                          (b.lane_cols == 0 && (b.op == FCOO_OP_TTM ? R != 16 && R != 32 : np == 2)));
+                          (b.lane_cols == 0 && (b.op == FCOO_OP_TTM ? R != 16 && R != 32 && !few : np == 2)));
     // columns per lane: the type's vector, or the widest piece a shorter row
     // holds.  A row need not be a multiple of it: its last piece ends at
     // column R and overlaps the one before.  (Such rows once ran one column
