@@ -104,8 +104,8 @@ struct Built {
     float *d_carry = nullptr;                 // 2 x tiles x R floats
     int64_t carry_cap = 0;                    // floats
     int carry_width = 0;                      // widest rows they were made for
-    float *d_gcopy = nullptr;                 // replaced values that lie where the result goes
-    int64_t gcopy_cap = 0;                    // floats
+    float *d_gperm = nullptr;                 // replaced values in stored order, where a launch wants that
+    int64_t gperm_cap = 0;                    // floats
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
     int64_t bpart_cap = 0;                    // floats
     double *d_partial = nullptr;              // per-tile float64 partial sums
@@ -259,6 +259,7 @@ const Plan &pick_plan(const Built &b, int dtype, int R, bool resid, bool kron);
 int spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, int dtype, int R, float *M, bool keep_order,
              hipStream_t s);
 int launch_ttmc(const TileProblem &p, float *out, hipStream_t s);
+int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s);   // to stored order
 int launch_segmented(const TileProblem &p, hipStream_t s, bool resid);
 int launch_model(const fcoo_tensor *t, const void *const *factors, int dtype, int R, float *xhat,
                  hipStream_t s);

@@ -168,6 +168,12 @@ __global__ __launch_bounds__(kFinish) void finish_kernel(FinishArgs A)
     if (tid == 0) A.loss[0] = sh[0] * A.scale;
 }
 
+__global__ __launch_bounds__(256) void permute_kernel(const int32_t *__restrict__ perm, const float *__restrict__ g,
+                                                      int64_t n, float *__restrict__ out)
+{
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = g[perm[i]];
+}
+
 // XCD blocks: out[i][c] = sum over blocks b of part[b][i][c], in block order.
 __global__ __launch_bounds__(256) void reduce_blocks_kernel(const float *__restrict__ part, int nblk,
                                                             int64_t n, float *__restrict__ out)
@@ -454,6 +460,13 @@ int launch_segmented(const TileProblem &p, hipStream_t s, bool resid)
                            b.nblk, n, p.out);
         FCOO_HIP(hipGetLastError());
     }
+    return FCOO_OK;
+}
+
+int launch_permute_values(const Built &b, const float *g, float *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(dev::permute_kernel, dim3(grid_for(b.nnz, 256 * 8)), dim3(256), 0, s, b.d_perm, g, b.nnz, out);
+    FCOO_HIP(hipGetLastError());
     return FCOO_OK;
 }
 
