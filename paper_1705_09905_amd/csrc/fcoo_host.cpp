@@ -161,7 +161,8 @@ hipError_t device_malloc(void **p, size_t bytes)
 
 int pool_get(size_t bytes, PoolBlock *b)
 {
-    const size_t unit = (size_t)2 << 20;
+    // (whole 2 MiB pages, but for blocks smaller than one)
+    const size_t unit = bytes < ((size_t)2 << 20) ? 4096 : (size_t)2 << 20;
     bytes = (bytes + unit - 1) / unit * unit;
     int dev = 0;
     FCOO_HIP(hipGetDevice(&dev));
@@ -198,7 +199,7 @@ void pool_put(PoolBlock *b)
 {
     if (!b->p) return;
     std::lock_guard<std::mutex> lk(g_pool_mu);
-    if (g_handles > 0 && g_pool_bytes + b->bytes <= kPoolKeep) {
+    if (g_handles > 0 && g_pool_bytes + b->bytes <= kPoolKeep && g_pool.size() < kPoolBlocks) {
         try {
             g_pool.push_back(*b);
             g_pool_bytes += b->bytes;

@@ -166,10 +166,10 @@ namespace fcoo {
 // Device memory of the builds made on the GPU, kept from one build for the next:
 // allocating and freeing it (about 50 bytes a nonzero, most of it scratch) costs
 // more than the build, as the driver clears freed memory before it hands it out
-// again.  At most kPoolKeep bytes lie idle, and none once no handle is left; any
-// thread may call.  A block is given back only when no device work can still
+// again.  At most kPoolKeep bytes in kPoolBlocks blocks lie idle, and none once no
+// handle is left; any thread may call.  A block is given back only when no device work can still
 // use it (the caller has waited).
-constexpr size_t kPoolKeep = (size_t)4 << 30;
+constexpr size_t kPoolKeep = (size_t)4 << 30, kPoolBlocks = 256;
 int pool_get(size_t bytes, PoolBlock *b);    // FCOO_OK or FCOO_ENOMEM
 void pool_put(PoolBlock *b);                 // b->p may be null
 void pool_free(PoolBlock *b);                // to the driver, not to the pool

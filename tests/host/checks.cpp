@@ -301,6 +301,23 @@ static void kept_order()
             }
 }
 
+// The GPU builds of small tensors take little more memory than their arrays.
+static void small_builds()
+{
+    fcoo_opts o{};
+    o.device = 1;
+    std::vector<fcoo_tensor *> ts(101);
+    size_t before = 0;
+    for (auto &t : ts) {
+        t = tensor({200, 150, 100}, 1000);
+        CHECK(fcoo_build(t, 0, FCOO_OP_MTTKRP, &o, nullptr) == FCOO_OK);
+        if (t == ts[0]) before = fake::live_bytes;
+    }
+    CHECK(fake::live_bytes - before < (size_t)100 * 128 * 1024);
+    for (auto t : ts) fcoo_destroy(t);
+    CHECK(fake::live_bytes == 0);
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -327,6 +344,7 @@ int main(int argc, char **argv)
         {"finish_grid", [] { finish_grid(); }},
         {"host_memory", [] { host_memory(0, 0), host_memory(0, 1), host_memory(1, 0), host_memory(1, 1); }},
         {"kept_order", [] { kept_order(); }},
+        {"small_builds", [] { small_builds(); }},
     };
     const auto it = checks.find(name);
     if (it == checks.end()) {
