@@ -414,11 +414,11 @@ def kernel_symbol(op, R, N):
 
 def rank_tile(R):
     """Columns one tile-kernel workgroup covers for float32 factors: 4 per
-    lane, lanes per nonzero the next power of two of R / 4 (at most 16); 64
-    one-column lanes when R is not a multiple of 4."""
-    if R % 4:
+    lane, lanes per nonzero the next power of two of R / 4 (at most 16).  (Rows
+    shorter than a lane's 4 columns, which the benchmark has none of: 64.)"""
+    if R < 4:
         return 64
-    lanes = R // 4
+    lanes = (R + 3) // 4
     lpn = 1
     while lpn < lanes:
         lpn *= 2

@@ -120,7 +120,9 @@ typedef struct {
     int64_t nfix;         /* segments finished by the carry fix-up pass           */
     int64_t nempty;       /* MTTKRP: output rows with no nonzero (written as 0)   */
     int64_t bytes_format; /* bytes of the F-COO arrays (pidx, val, bf, sf)        */
-    int64_t bytes_device; /* all device bytes held for this (op, mode)            */
+    int64_t bytes_device; /* device bytes of this (op, mode)'s arrays; with the
+                             option device they lie in one block of the library's
+                             pool, up to a quarter larger                       */
     int32_t threadlen;
     int32_t tile_nnz;
     int32_t order;
@@ -163,6 +165,10 @@ int fcoo_create(int order, const int64_t *dims, int64_t nnz, const int32_t *cons
  *   its first nonzero.
  *   opts may be NULL (defaults).  Rebuilding an (op, mode) replaces it.
  *   Waits for the upload to finish before returning.
+ *   With the option device, scratch and arrays come from a pool of the process:
+ *   up to 4 GiB of it lie idle while any handle is alive (for the next build, or
+ *   for whatever the library allocates when the device is full), none after the
+ *   last handle is destroyed.
  * Errors: FCOO_EINVAL, FCOO_ENOMEM, FCOO_EHIP.
  */
 int fcoo_build(fcoo_tensor *t, int mode, int op, const fcoo_opts *opts, void *stream);
@@ -293,6 +299,8 @@ int fcoo_spttmc(fcoo_tensor *t, int mode, const void *const *factors, int dtype,
  *   M[i, r] = sum_{e : i_mode(e) = i} g[e] prod_{m != mode} A_m[i_m(e), r].
  * This is the adjoint of the CP model at the nonzeros (its gradient with
  * respect to A_mode when g = dL/dxhat).
+ *   g may lie in M's memory.  Then, and for R > 64, the values are first copied
+ *   in stored order to scratch that the build keeps (4 Z bytes).
  * Requires fcoo_build(mode, FCOO_OP_MTTKRP).  Errors: as fcoo_spmttkrp.
  */
 int fcoo_spmttkrp_values(fcoo_tensor *t, int mode, const float *g, const void *const *factors,
@@ -341,8 +349,9 @@ int fcoo_resid_spmttkrp(fcoo_tensor *t, int mode, const void *const *factors, in
  *            `grams_valid` = 0 to have them computed from the factors first.
  *   fit      host double* (out); the call waits for it.
  *   used_pinv host int* or NULL (out): bit n set if mode n used the pseudo-inverse.
- * Requires fcoo_build(n, FCOO_OP_MTTKRP) for every mode n.  All the work runs
- * on `stream`.
+ * Requires fcoo_build(n, FCOO_OP_MTTKRP) for every mode n.  For the caller all
+ * the work is ordered on `stream`; a long R x R solve runs beside its SpMTTKRP on a
+ * second stream owned by the handle, between events on `stream`.
  * Errors: FCOO_EINVAL, FCOO_ENOTBUILT, FCOO_EUNSUPPORTED, FCOO_EHIP, FCOO_ENOMEM.
  */
 int fcoo_cp_als_iter(fcoo_tensor *t, void *const *factors, int dtype, int R, double *lambda,

@@ -50,7 +50,7 @@ __device__ __forceinline__ int bcast_imm(int x)
 {
     if constexpr (LPN == 1) {
         return x;
-    } else if constexpr (LDSQ && LPN <= 32) {
+    } else if constexpr (LDSQ && LPN <= 16) {
         return __builtin_amdgcn_ds_swizzle(x, (0x1F & ~(LPN - 1)) | (SRC << 5));
     } else if constexpr (LPN == 2) {
         return dpp<SRC | SRC << 2 | (2 + SRC) << 4 | (2 + SRC) << 6>(x, x);      // quad_perm
@@ -60,9 +60,8 @@ __device__ __forceinline__ int bcast_imm(int x)
         return dpp<0x158 + SRC, 0xC>(dpp<0x150 + SRC>(x, x), x);                 // row_newbcast, upper half its own
     } else if constexpr (LPN == 16) {
         return dpp<0x150 + SRC>(x, x);                                           // row_newbcast
-    } else if constexpr (LPN == 32) {
-        return __builtin_amdgcn_ds_swizzle(x, SRC << 5);
     } else {
+        static_assert(LPN == 64, "lanes of a group");
         return __builtin_amdgcn_readlane(x, SRC);
     }
 }
@@ -79,7 +78,7 @@ __device__ __forceinline__ float add_dpp(float v)
     return v + __int_as_float(dpp<CTRL>(__float_as_int(v), __float_as_int(v)));
 }
 
-// Butterfly sum over the LPN lanes of a group.
+// Butterfly sum over the LPN lanes of a group (16 at most).
 template <int LPN>
 __device__ __forceinline__ float group_sum(float v)
 {
@@ -87,8 +86,7 @@ __device__ __forceinline__ float group_sum(float v)
     if constexpr (LPN >= 4) v = add_dpp<0x4E>(v);                                // quad_perm: lane ^ 2
     if constexpr (LPN >= 8) v = add_dpp<0x141>(v);                               // row_half_mirror: the other quad
     if constexpr (LPN >= 16) v = add_dpp<0x140>(v);                              // row_mirror: the other half
-    if constexpr (LPN >= 32) v += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x1F | (16 << 10)));
-    if constexpr (LPN >= 64) v += __shfl_xor(v, 32, 64);
+    static_assert(LPN <= 16, "a row of lanes");
     return v;
 }
 

@@ -611,14 +611,15 @@ static int build_host(fcoo_tensor *t, Built &b, int mode, int op, int threadlen,
     std::vector<int64_t> heads_before_tile(fine.ntiles + 1, 0);
     int64_t cnt = 0;
     for (int64_t s = 0; s < Z; ++s) {
-        if (s % wtile == 0) heads_before_tile[s / wtile] = cnt;
+        const bool starts = s % wtile == 0;      // (a tile as launched; every format tile starts one)
+        if (starts) heads_before_tile[s / wtile] = cnt;
         if (head[s]) {
             ++cnt;
             seg_start.push_back(s);
             b.sf[(s / threadlen) >> 5] |= 1u << ((s / threadlen) & 31);
         }
         if (cnt & 1) b.bf[s >> 3] |= (uint8_t)(1u << (s & 7));
-        if (s % tile_nnz == 0) b.tile_seg0[s / tile_nnz] = (int32_t)(cnt - 1);
+        if (starts && s % tile_nnz == 0) b.tile_seg0[s / tile_nnz] = (int32_t)(cnt - 1);
     }
     heads_before_tile[fine.ntiles] = cnt;
     b.nseg = cnt;

@@ -14,7 +14,6 @@ namespace fcoo {
 constexpr int kMaxOrder = 8;
 constexpr int kMaxR = 256;
 constexpr int kMaxKronWidth = 16384;   // SpTTMc output columns (prod of the product-mode ranks)
-constexpr int kBlock = 256;        // threads per workgroup of the tile kernels (4 waves)
 constexpr int kLongChain = 64;     // tiles between the ends of a long carry chain
 constexpr int kXcds = 8;           // XCDs of an MI355X: workgroup w runs on XCD w % 8
 

@@ -1,6 +1,6 @@
-// Launch plans of the segmented F-COO operations, the carry fix-up, empty
-// rows, value permutation, deterministic float64 reductions and the CP
-// model at the nonzeros.
+// Launch plans of the segmented F-COO operations; what follows their tile
+// kernel (carry fix-up, empty rows, the residual's loss); the order of replaced
+// values; the CP model at the nonzeros.
 #include <algorithm>
 
 #include "fcoo_internal.h"

@@ -81,7 +81,10 @@ static hipError_t seg_dispatch_narrow(const SegLaunch &L, hipStream_t s)
         return seg_go<FT, 1, 1, 0, RESID, dev::kOutMap>(L, s);
     }
     if (L.vw == 2) return L.lpn == 1 ? seg_np<FT, 2, 1, RESID>(L, s) : seg_np<FT, 2, 2, RESID, RESID>(L, s);
-    if constexpr (sizeof(FT) == 2) return L.lpn == 1 ? seg_np<FT, 4, 1, RESID>(L, s) : seg_np<FT, 4, 2, RESID, RESID>(L, s);
+    if constexpr (sizeof(FT) == 2 && RESID) return L.lpn == 1 ? seg_np<FT, 4, 1, true>(L, s) : seg_np<FT, 4, 2, true, true>(L, s);
+    // (with up to three product modes, and in SpTTM, such rows are seg_launch_bf16_half's)
+    if constexpr (sizeof(FT) == 2 && !RESID)
+        return L.lpn == 1 ? seg_go<FT, 4, 1, 0, false, dev::kOutMap>(L, s) : seg_go<FT, 4, 2, 0, false, dev::kOutMap>(L, s);
     return hipErrorInvalidValue;
 }
 

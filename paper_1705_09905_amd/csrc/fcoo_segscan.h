@@ -18,8 +18,8 @@
 //     it in order; each lane holds VW columns, so one gather instruction
 //     fetches 64 / LPN whole rows (16 bytes per lane);
 //   * the stream (product indices, values) is read coalesced, one element
-//     per lane, non-temporally, and broadcast inside the group by DPP; the
-//     segment heads of 32 nonzeros and their rank come as one pair of words;
+//     per lane, non-temporally, and broadcast inside the group (ds_swizzle;
+//     by DPP in the residual's form); the segment heads of 32 nonzeros and their rank come as one pair of words;
 //   * a segment that starts and ends inside a run is written directly;
 //     the partial sums at run boundaries go through a wave-level segmented
 //     scan (cross-lane moves), then through LDS across the 4 waves; a
