@@ -1,6 +1,6 @@
 """Builds the C oracle (cpu_oracle.c -> liborc.so) with gcc and OpenMP.
 
-Test infrastructure: compiling the checker is part of the build; running it
+Test infrastructure: compiling the oracle is part of the build; running it
 is reserved for the tests, the smoke check and the CPU-baseline leg.
 """
 import os
