@@ -1156,9 +1156,10 @@ int fcoo_spmttkrp_values(fcoo_tensor *t, int mode, const float *g, const void *c
     const bool inside = g < M + t->dims[mode] * (int64_t)R && M < g + b->nnz;
     if (b->nnz && (inside || R > sh.lpn * sh.vw)) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        const bool grows = b->gperm_cap < b->nnz;
+        // (4 entries past the values, read but not used, as the build's streams have)
+        const bool grows = b->gperm_cap < b->nnz + 4;
         if (grows && !inside && hipStreamIsCapturing(s, &st) != hipSuccess) st = hipStreamCaptureStatusActive;
-        if (st == hipStreamCaptureStatusNone) rc = ensure_device_floats(&b->d_gperm, &b->gperm_cap, b->nnz, s);
+        if (st == hipStreamCaptureStatusNone) rc = ensure_device_floats(&b->d_gperm, &b->gperm_cap, b->nnz + 4, s);
         if (st != hipStreamCaptureStatusNone || (rc == FCOO_ENOMEM && !inside)) {
             (void)hipGetLastError();
             clear_error();

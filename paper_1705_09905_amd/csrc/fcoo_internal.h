@@ -103,7 +103,7 @@ struct Built {
     float *d_carry = nullptr;                 // 2 x tiles x R floats
     int64_t carry_cap = 0;                    // floats
     int carry_width = 0;                      // widest rows they were made for
-    float *d_gperm = nullptr;                 // replaced values in stored order, where a launch wants that
+    float *d_gperm = nullptr;                 // Z, + 4: replaced values in stored order, where a launch wants that
     int64_t gperm_cap = 0;                    // floats
     float *d_bpart = nullptr;                 // XCD blocks: nblk x I x width partial outputs
     int64_t bpart_cap = 0;                    // floats

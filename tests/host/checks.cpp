@@ -220,6 +220,24 @@ static void carries_hold(std::vector<int64_t> dims, int64_t Z, int tile)
     fcoo_destroy(t);
 }
 
+// Replaced values in stored order are as padded as the build's streams: a lane past
+// the last nonzero reads 4 entries there.  They are copied where rows have several
+// rank tiles, and where the values lie in the result's memory.
+static void values_padded(int64_t Z, int R, bool inside)
+{
+    fcoo_tensor *t = tensor({3000, 200, 10}, Z);
+    CHECK(fcoo_build(t, 0, FCOO_OP_MTTKRP, nullptr, nullptr) == FCOO_OK);
+    std::vector<void *> f;
+    for (int64_t d : {3000, 200, 10}) f.push_back(dev((size_t)d * R * 4));
+    float *out = (float *)dev(((size_t)3000 * R + Z) * 4), *g = inside ? out : (float *)dev((size_t)Z * 4);
+    const fcoo::Built &b = t->b[FCOO_OP_MTTKRP][0];
+    for (int dtype : {FCOO_F32, FCOO_BF16}) {
+        CHECK(fcoo_spmttkrp_values(t, 0, g, f.data(), dtype, R, out, nullptr) == FCOO_OK);
+        CHECK(b.d_gperm && fake::find(b.d_gperm)->bytes >= (size_t)(Z + 4) * 4);
+    }
+    fcoo_destroy(t);
+}
+
 // With no room for the carries of the tiles that suit a call, it runs on the build's
 // own tiles, whose carries fit.
 static void carries_that_fit()
@@ -341,6 +359,9 @@ int main(int argc, char **argv)
                  for (int tile : {0, 256, 1024, 65536}) carries_hold({30, 20}, Z, tile), carries_hold({30, 20, 10}, Z, tile);
          }},
         {"carries_that_fit", [] { carries_that_fit(); }},
+        {"values_padded", [] {
+             for (int64_t Z : {1, 4, 1024, 3072, 5001}) values_padded(Z, 200, false), values_padded(Z, 8, true);
+         }},
         {"finish_grid", [] { finish_grid(); }},
         {"host_memory", [] { host_memory(0, 0), host_memory(0, 1), host_memory(1, 0), host_memory(1, 1); }},
         {"kept_order", [] { kept_order(); }},
